@@ -913,7 +913,7 @@ __global__ __launch_bounds__(256) void vmm_finish_col2im_kernel(FinishCol2imArgs
 
 struct WriteArgs {
   float* W;
-  float* Gp;        // per-polarity device state (update_pair_write_kernel): positive device, in [0, 1]
+  float* Gp;        // per-polarity device state (PAIR): positive device, in [0, 1]
   float* Gn;        //   negative device
   const float* part;
   long long n;      // K * N
@@ -924,22 +924,9 @@ struct WriteArgs {
   const unsigned long long* step_add;   // optional device counter added to step
 };
 
-// 32 consecutive weights per block; the 8 thread groups of a block add up interleaved subsets of the
-// batch partials (fixed order, so the result does not depend on scheduling), group 0 then writes.
-__global__ __launch_bounds__(256) void update_write_kernel(WriteArgs a) {
-  __shared__ double red[8][32];
-  const int e = threadIdx.x & 31, grp = threadIdx.x >> 5;
-  const long long i = (long long)blockIdx.x * 32 + e;
-  double partial = 0.0;
-  if (i < a.n)
-    for (int c = grp; c < a.mchunks; c += 8) partial += (double)a.part[(size_t)c * a.n + i];
-  red[grp][e] = partial;
-  __syncthreads();
-  if (grp != 0 || i >= a.n) return;
-  double grad = 0.0;
-#pragma unroll
-  for (int g = 0; g < 8; ++g) grad += red[g][e];
-  const double g = (double)a.W[i] / a.w_max;
+// New state of one weight from its gradient: ideal change, non-linearity, noise (normal number z), clamp.
+__device__ __forceinline__ float written_weight(const WriteArgs& a, float w, double grad, double z) {
+  const double g = (double)w / a.w_max;
   const double delta = a.grad_scale * grad;
   double written = delta;
   if (a.flags & XBAR_NI_UPD_NL) {
@@ -948,37 +935,18 @@ __global__ __launch_bounds__(256) void update_write_kernel(WriteArgs a) {
     if (change > 0.0) written = delta * ::exp(-a.v * x);
     else if (change < 0.0) written = delta * ::exp(-a.v * (1.0 - x));
   }
-  if (a.flags & XBAR_NI_UPD_NOISE) {
-    NormalStream rng(a.seed, kStreamWrite, effective_step(a.step, a.step_add));
-    written += a.gamma * ::sqrt(::fabs(delta)) * rng.get((uint64_t)i);
-  }
-  const double g_new = clampd(g - a.lr * written, -1.0, 1.0);
-  a.W[i] = (float)(a.w_max * g_new);
+  if (a.flags & XBAR_NI_UPD_NOISE) written += a.gamma * ::sqrt(::fabs(delta)) * z;
+  return (float)(a.w_max * clampd(g - a.lr * written, -1.0, 1.0));
 }
-
-
 
 // The same write with the two devices of a weight as states of their own (a variant of Sec. IV-C's one
 // conductance per weight; Sec. IV-A keeps positive and negative conductances in two arrays): half the ideal
 // change to each, in opposite directions, each with the non-linearity at its own state and direction, a noise
 // draw of its own (sigma = gamma sqrt(|delta| / 2), numbers 2 i and 2 i + 1 of the pair stream) and its own
 // clamp to [0, 1]; W = w_max (gp - gn).
-__global__ __launch_bounds__(256) void update_pair_write_kernel(WriteArgs a) {
-  __shared__ double red[8][32];
-  const int e = threadIdx.x & 31, grp = threadIdx.x >> 5;
-  const long long i = (long long)blockIdx.x * 32 + e;
-  double partial = 0.0;
-  if (i < a.n)
-    for (int c = grp; c < a.mchunks; c += 8) partial += (double)a.part[(size_t)c * a.n + i];
-  red[grp][e] = partial;
-  __syncthreads();
-  if (grp != 0 || i >= a.n) return;
-  double grad = 0.0;
-#pragma unroll
-  for (int g = 0; g < 8; ++g) grad += red[g][e];
+__device__ __forceinline__ float written_pair(const WriteArgs& a, float& gp, float& gn, double grad, const double (&z)[2]) {
   const double half = 0.5 * (a.grad_scale * grad);
-  double state[2] = {(double)a.Gp[i], (double)a.Gn[i]};
-  NormalStream rng(a.seed, kStreamWritePair, effective_step(a.step, a.step_add));
+  double state[2] = {(double)gp, (double)gn};
 #pragma unroll
   for (int pol = 0; pol < 2; ++pol) {
     const double dir = pol == 0 ? -1.0 : 1.0;        // the positive device falls when the weight falls
@@ -989,13 +957,125 @@ __global__ __launch_bounds__(256) void update_pair_write_kernel(WriteArgs a) {
       if (change > 0.0) written = half * ::exp(-a.v * x);
       else if (change < 0.0) written = half * ::exp(-a.v * (1.0 - x));
     }
-    if (a.flags & XBAR_NI_UPD_NOISE) written += a.gamma * ::sqrt(::fabs(half)) * rng.get(2 * (uint64_t)i + (uint64_t)pol);
+    if (a.flags & XBAR_NI_UPD_NOISE) written += a.gamma * ::sqrt(::fabs(half)) * z[pol];
     state[pol] = clampd(state[pol] + dir * a.lr * written, 0.0, 1.0);
   }
-  const float gp = (float)state[0], gn = (float)state[1];
-  a.Gp[i] = gp;
-  a.Gn[i] = gn;
-  a.W[i] = (float)(a.w_max * ((double)gp - (double)gn));
+  gp = (float)state[0];
+  gn = (float)state[1];
+  return (float)(a.w_max * ((double)gp - (double)gn));
+}
+
+// Four consecutive weights per thread: 16-byte loads and stores where the layer's size allows them (VEC), and the
+// four normal numbers of one Philox block, which is half the logarithms, roots and angles of drawing them one by
+// one.  G thread groups of a block share its 1024 / G weights: group g adds up the batch partials g, g + G, ... and
+// the first group adds the groups' sums and writes (fixed order: the result does not depend on scheduling).  Few
+// partials or many weights: G = 1, every thread busy to the end -- the write is then bound by its double-precision
+// arithmetic.  Many partials of few weights: G = 8 or 32 keeps enough loads in flight.
+template <int G, bool VEC, bool PAIR>
+__global__ __launch_bounds__(256) void update_write_kernel(WriteArgs a) {
+  constexpr int Q = 256 / G;                         // quads of weights per block
+  __shared__ double red[G > 1 ? G : 1][G > 1 ? 4 * Q : 1];
+  const int quad = threadIdx.x % Q, grp = threadIdx.x / Q;
+  const long long i = ((long long)blockIdx.x * Q + quad) * 4;
+  const int live = (int)min(4ll, a.n - i);           // weights of this thread (may be negative)
+  double grad[4] = {0.0, 0.0, 0.0, 0.0};
+  if (live > 0) {
+#pragma unroll 4
+    for (int c = grp; c < a.mchunks; c += G) {
+      const float* src = a.part + (size_t)c * a.n + i;
+      float4 v;
+      if (VEC) {
+        v = *reinterpret_cast<const float4*>(src);
+      } else {                                       // clamped, not skipped: no branch between the loads
+        v.x = src[0];
+        v.y = src[min(1, live - 1)];
+        v.z = src[min(2, live - 1)];
+        v.w = src[min(3, live - 1)];
+      }
+      grad[0] += (double)v.x;
+      grad[1] += (double)v.y;
+      grad[2] += (double)v.z;
+      grad[3] += (double)v.w;
+    }
+  }
+  if constexpr (G > 1) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[grp][4 * quad + e] = grad[e];
+    __syncthreads();
+    constexpr int W = 4 * Q;                         // weights of the block; 256 / W shares of the groups each
+    if constexpr (G > 8) {
+      const int w = threadIdx.x % W, share = threadIdx.x / W;
+      double s = 0.0;
+#pragma unroll
+      for (int g = 0; g < G * W / 256; ++g) s += red[share * (G * W / 256) + g][w];
+      __syncthreads();
+      red[share][w] = s;
+      __syncthreads();
+    }
+    if (grp != 0) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      double s = 0.0;
+#pragma unroll
+      for (int g = 0; g < (G > 8 ? 256 / W : G); ++g) s += red[g][4 * quad + e];
+      grad[e] = s;
+    }
+  }
+  if (live <= 0) return;
+  const bool noisy = (a.flags & XBAR_NI_UPD_NOISE) != 0;
+  NormalStream rng(a.seed, PAIR ? kStreamWritePair : kStreamWrite, effective_step(a.step, a.step_add));
+  if constexpr (!PAIR) {
+    double z[4] = {0.0, 0.0, 0.0, 0.0};
+    if (noisy) rng.get4((uint64_t)i >> 2, z);
+    float w[4];
+    if (VEC) {
+      const float4 v = *reinterpret_cast<const float4*>(a.W + i);
+      w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = a.W[i + min(e, live - 1)];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = written_weight(a, w[e], grad[e], z[e]);
+    if (VEC) {
+      *reinterpret_cast<float4*>(a.W + i) = make_float4(w[0], w[1], w[2], w[3]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < live) a.W[i + e] = w[e];
+    }
+  } else {
+    double z[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};   // numbers 2 i .. 2 i + 7
+    if (noisy) {
+      rng.get4((uint64_t)i >> 1, z[0]);
+      rng.get4(((uint64_t)i >> 1) + 1, z[1]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (e >= live) break;
+      const double zz[2] = {z[e >> 1][2 * (e & 1)], z[e >> 1][2 * (e & 1) + 1]};
+      float gp = a.Gp[i + e], gn = a.Gn[i + e];
+      a.W[i + e] = written_pair(a, gp, gn, grad[e], zz);
+      a.Gp[i + e] = gp;
+      a.Gn[i + e] = gn;
+    }
+  }
+}
+
+// Weights whose batch partials one block's groups share: enough loads in flight for a layer with few weights
+// and many partials (an early convolution: 2304 weights, 512 partials), every lane busy for one with many weights.
+template <bool PAIR>
+hipError_t launch_update_write(const WriteArgs& a, hipStream_t st) {
+  const bool vec = a.n % 4 == 0;
+  const long long quads = (a.n + 3) / 4;
+  const int G = (a.mchunks <= 4 || quads >= 131072) ? 1 : (a.mchunks >= 64 && quads <= 8192) ? 32 : 8;
+  const int Q = 256 / G;
+  const dim3 grid((unsigned)((quads + Q - 1) / Q));
+  void (*k)(WriteArgs);
+  if (vec) k = G == 1 ? update_write_kernel<1, true, PAIR> : G == 8 ? update_write_kernel<8, true, PAIR> : update_write_kernel<32, true, PAIR>;
+  else k = G == 1 ? update_write_kernel<1, false, PAIR> : G == 8 ? update_write_kernel<8, false, PAIR> : update_write_kernel<32, false, PAIR>;
+  hipLaunchKernelGGL(k, grid, dim3(256), 0, st, a);
+  return hipGetLastError();
 }
 
 struct PairInitArgs {
@@ -1464,9 +1544,7 @@ int run_update(const xbar_config* cfg, float* W, const float* X, const float* dY
   w.w_max = (double)w_max; w.grad_scale = (double)grad_scale; w.lr = (double)lr;
   w.v = (double)cfg->upd_nl_v; w.gamma = (double)cfg->upd_noise_gamma;
   w.seed = cfg->seed; w.step = step; w.step_add = current_step_source();
-  if (Gp) hipLaunchKernelGGL(update_pair_write_kernel, dim3((unsigned)((w.n + 31) / 32)), dim3(256), 0, st, w);
-  else hipLaunchKernelGGL(update_write_kernel, dim3((unsigned)((w.n + 31) / 32)), dim3(256), 0, st, w);
-  if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
+  if ((Gp ? launch_update_write<true>(w, st) : launch_update_write<false>(w, st)) != hipSuccess) return XBAR_EHIP;
   return XBAR_OK;
 }
 

@@ -242,13 +242,26 @@ struct NormalStream {
       cached_blk = blk;
     }
     const bool second = (i & 2u) != 0;
-    const double u1 = ((double)(second ? w[2] : w[0]) + 0.5) * (1.0 / 4294967296.0);
-    const double u2 = ((double)(second ? w[3] : w[1]) + 0.5) * (1.0 / 4294967296.0);
+    double even, odd;
+    box_muller(second ? w[2] : w[0], second ? w[3] : w[1], even, odd);
+    return (i & 1u) ? odd : even;
+  }
+  // The four numbers 4 blk .. 4 blk + 3 of a block: one Philox evaluation, two logarithms, roots and angles.
+  __device__ void get4(uint64_t blk, double (&z)[4]) const {
+    uint32_t v[4];
+    philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), s0, s1, k0, k1, v);
+    box_muller(v[0], v[1], z[0], z[1]);
+    box_muller(v[2], v[3], z[2], z[3]);
+  }
+  static __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, double& even, double& odd) {
+    const double u1 = ((double)a + 0.5) * (1.0 / 4294967296.0);
+    const double u2 = ((double)b + 0.5) * (1.0 / 4294967296.0);
     const double r = ::sqrt(-2.0 * ::log(u1));
     // angle 2 pi u2: the half-turn form reduces the argument exactly and costs a fraction of sin / cos
     double sn, cs;
     ::sincospi(2.0 * u2, &sn, &cs);
-    return (i & 1u) ? r * sn : r * cs;
+    even = r * cs;
+    odd = r * sn;
   }
 };
 
