@@ -42,12 +42,12 @@ struct TileArgs {
   const uint32_t* codes; // term codes of every plane value (single-path wire model alone), this copy's orientation
   const double* wire_u;  // all-paths wire model: plane values [S_w][2][K][N], array index 0 (else unused)
   uint16_t* planes;  // start of this copy
-  int K, N, R, C, S_w, slice_bits, weight_bits, terms;
+  int K, N, R, C, S_w, slice_bits, terms;
   int tile, ks, T, OP;
   int spt;           // table-driven generator: slices per thread
-  int pol_out;       // -1: difference of the pair (array 0 minus array 1); 0 / 1: that array alone
   uint32_t flags;
-  double g_min, dg, var_sigma, r_row, r_col, r_source, r_sense, hi_scale, hi_inv_scale;
+  double g_min, dg, inv_dg, var_sigma, r_row, r_col, r_source, r_sense, hi_scale, hi_inv_scale;
+  double qw, q_per_w;    // 2^weight_bits - 1, and that over w_max
   float w_max;
   uint64_t seed, step;
   const unsigned long long* step_add;   // optional device counter added to step
@@ -55,124 +55,152 @@ struct TileArgs {
   int term_exp[kMaxTermsF6];            // kFmtF6: power of two of every term
 };
 
-// Plane value of slice s of weight (k, n), in units of one device level: the signed difference of the
-// device pair, or the conductance of one of the two devices.
-// pol_out: -1: difference of the pair (array 0 minus array 1); 0 / 1: that array alone.
-__device__ __forceinline__ double plane_value(const TileArgs& a, NormalStream& rng, int sign, int digit, int s, int k,
-                                              int n, int pol_out) {
-  if (a.flags & XBAR_NI_WIRE_AAM2) return a.wire_u[((size_t)(2 * s + (pol_out > 0 ? 1 : 0)) * a.K + k) * a.N + n];
-  if (pol_out < 0 && !(a.flags & (XBAR_NI_VARIATION | XBAR_NI_WIRE_AAM | XBAR_NI_WIRE_PROFILE)))
-    return (double)(sign * digit);
+// Plane value of slice s of weight (k, n), which sits at place (i, j) of its array, in units of one device level: the
+// signed difference of the device pair, or the conductance of one of the two devices.
+//   NPOL 1: u[0] = array 0 minus array 1;  2: u[0], u[1] = the arrays alone.
+template <int NPOL>
+__device__ __forceinline__ void plane_values(const TileArgs& a, NormalStream& rng, int sign, int digit, int s, int k, int n, int i,
+                                             int j, double (&u)[NPOL]) {
+  if (a.flags & XBAR_NI_WIRE_AAM2) {
+#pragma unroll
+    for (int pol = 0; pol < NPOL; ++pol) u[pol] = a.wire_u[((size_t)(2 * s + pol) * a.K + k) * a.N + n];
+    return;
+  }
+  if (NPOL == 1 && !(a.flags & (XBAR_NI_VARIATION | XBAR_NI_WIRE_AAM | XBAR_NI_WIRE_PROFILE))) {
+    u[0] = (double)(sign * digit);
+    return;
+  }
   double g[2];
   g[0] = a.g_min + (sign > 0 ? digit * a.dg : 0.0);
   g[1] = a.g_min + (sign < 0 ? digit * a.dg : 0.0);
-#pragma unroll
-  for (int pol = 0; pol < 2; ++pol) {
-    if (a.flags & XBAR_NI_VARIATION) {
-      const uint64_t dev = (((uint64_t)k * (uint64_t)a.N + (uint64_t)n) * (uint64_t)a.S_w + (uint64_t)s) * 2 + pol;
-      g[pol] *= 1.0 + a.var_sigma * rng.get(dev);
-    }
-    if (a.flags & XBAR_NI_WIRE_AAM) {
-      const int i = k % a.R, j = n % a.C;
-      const double rho = a.r_source + (double)(j + 1) * a.r_row + (double)(a.R - i) * a.r_col + a.r_sense;
-      g[pol] = g[pol] / (1.0 + rho * g[pol]);
-    } else if (a.flags & XBAR_NI_WIRE_PROFILE) {
-      const double dist = (double)a.profile[(((size_t)s * 2 + pol) * a.K + k) * a.N + n];
-      g[pol] = g[pol] * (1.0 - dist);
-    }
+  if (a.flags & XBAR_NI_VARIATION) {
+    double z[2];                                     // the two devices of a pair: consecutive numbers, one draw
+    rng.pair((((uint64_t)k * (uint64_t)a.N + (uint64_t)n) * (uint64_t)a.S_w + (uint64_t)s) * 2, z[0], z[1]);
+    g[0] *= 1.0 + a.var_sigma * z[0];
+    g[1] *= 1.0 + a.var_sigma * z[1];
   }
-  return (pol_out < 0 ? g[0] - g[1] : g[pol_out]) / a.dg;
-}
-
-__device__ __forceinline__ double plane_value(const TileArgs& a, NormalStream& rng, int sign, int digit, int s, int k,
-                                              int n) {
-  return plane_value(a, rng, sign, digit, s, k, n, a.pol_out);
-}
-
-// One thread produces the 8 consecutive contraction-index entries of one output column that make up
-// one 16-byte operand chunk of one slice (blockIdx.y), for every term.
-//   TRANSPOSED = false: contraction index k (rows), output index n;  = true: contraction n, output k.
-template <bool TRANSPOSED>
-__global__ __launch_bounds__(256) void tile_planes_kernel(TileArgs a) {
-  const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= a.n_threads) return;
-  // thread -> (chunk of 8 along the contraction, output index); output index fastest within 32
-  const int out_len_pad = a.OP * 32;
-  const int o = (int)(tid % out_len_pad);
-  const int cg = (int)(tid / out_len_pad);        // global 8-chunk along the contraction
-  const int c0 = cg * 8;
-  const int t = c0 / a.tile;
-  const int within = c0 - t * a.tile;
-  const int j = within / 16, half = (within % 16) / 8;
-  const int lane = (o % 32) + 32 * half;
-  const int op = o / 32;
-  const int Lc = TRANSPOSED ? a.N : a.K;          // contraction length
-  const int Lo = TRANSPOSED ? a.K : a.N;
-
-  NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
-  const double qw = (double)((1u << a.weight_bits) - 1);
-  const uint32_t dmask = (1u << a.slice_bits) - 1;
-
-  int sign[8];
-  uint32_t mag[8];
+  if (a.flags & XBAR_NI_WIRE_AAM) {
+    const double rho = a.r_source + (double)(j + 1) * a.r_row + (double)(a.R - i) * a.r_col + a.r_sense;
+    g[0] = g[0] / (1.0 + rho * g[0]);
+    g[1] = g[1] / (1.0 + rho * g[1]);
+  } else if (a.flags & XBAR_NI_WIRE_PROFILE) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int c = c0 + e;
-    sign[e] = 0;
-    mag[e] = 0;
-    if (c < Lc && o < Lo) {
-      const int k = TRANSPOSED ? o : c, n = TRANSPOSED ? c : o;
-      const double q = ::rint(clampd((double)a.W[(size_t)k * a.N + n] / (double)a.w_max, -1.0, 1.0) * qw);
-      sign[e] = (q > 0.0) - (q < 0.0);
-      mag[e] = (uint32_t)::fabs(q);
-    }
+    for (int pol = 0; pol < 2; ++pol)
+      g[pol] = g[pol] * (1.0 - (double)a.profile[(((size_t)s * 2 + pol) * a.K + k) * a.N + n]);
   }
-  const size_t blk0 = ((size_t)t * a.OP + op) * a.S_w;
-  const int s = blockIdx.y;                         // one slice per grid row: short serial chains
-  union { u32x4 v; _Float16 h[8]; } hi, lo;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int c = c0 + e;
-    double u = 0.0;
-    if (c < Lc && o < Lo) {
-      const int k = TRANSPOSED ? o : c, n = TRANSPOSED ? c : o;
-      u = plane_value(a, rng, sign[e], (int)((mag[e] >> (a.slice_bits * s)) & dmask), s, k, n);
-    }
-    // leading term on the grid 2^-hi_frac (coarser where fp16 cannot hold it), residual in fp16
-    const _Float16 h = a.terms == 2 ? (_Float16)(::rint(u * a.hi_scale) * a.hi_inv_scale) : (_Float16)u;
-    hi.h[e] = h;
-    lo.h[e] = (_Float16)(u - (double)h);
-  }
-  const size_t chunk = ((blk0 + s) * a.terms * a.ks + j) * 64 + lane;   // in 16-byte units
-  reinterpret_cast<u32x4*>(a.planes)[chunk] = hi.v;
-  if (a.terms == 2) reinterpret_cast<u32x4*>(a.planes)[chunk + (size_t)a.ks * 64] = lo.v;
-}
-
-// E2M3 number (1 sign, 2 exponent, 3 mantissa bits, bias 1: multiples of 1/8 up to 2, of 1/4 up to 4, of
-// 1/2 up to 7.5) nearest to x; returns its 6-bit code and the number itself.
-__device__ __forceinline__ uint32_t e2m3_nearest(double x, double& value) {
-  const double a = ::fabs(x);
-  uint32_t code;
-  double v;
-  if (a < 2.0) {
-    const double k = ::rint(a * 8.0);                 // 0 .. 16; codes continue linearly into the next binade
-    code = (uint32_t)k;
-    v = k * 0.125;
-  } else if (a < 4.0) {
-    const double k = ::rint(a * 4.0);                 // 8 .. 16
-    code = 8u + (uint32_t)k;
-    v = k * 0.25;
+  if (NPOL == 1) {
+    u[0] = (g[0] - g[1]) * a.inv_dg;
   } else {
-    const double k = ::fmin(::rint(a * 2.0), 15.0);   // 8 .. 15: 7.5 is the largest number
-    code = 16u + (uint32_t)k;
-    v = k * 0.5;
+#pragma unroll
+    for (int pol = 0; pol < NPOL; ++pol) u[pol] = g[pol] * a.inv_dg;
   }
-  if (x < 0.0 && code) {
-    code |= 32u;
-    v = -v;
+}
+
+// Weight as its signed integer: rne(clamp(W / w_max) * Qw).  The product with the rounded factor Qw / w_max is within
+// 2 ulp (2^-36 of a step) of that quotient times Qw, so it rounds to the same integer unless it lies within 1e-9 of half
+// a step; those few are decided by the division itself, as the oracle decides all of them.
+__device__ __forceinline__ int quantized_weight(float w, double w_max, double qw, double q_per_w) {
+  double y = clampd((double)w * q_per_w, -qw, qw);
+  double q = ::rint(y);
+  if (!(::fabs(y - q) < 0.5 - 1e-9)) q = ::rint(clampd((double)w / w_max, -1.0, 1.0) * qw);
+  return (int)q;
+}
+
+// Both copies of one layer's planes.
+struct BothCopies {
+  TileArgs a;                // K, N, physics; the per-copy members are unused
+  uint8_t* base[2];          // forward copy, backward copy
+  int OP[2], ks[2], tile[2]; // output patches, k-steps per tile, tile length of either copy
+  size_t pol_bytes[2];
+  int nb;                    // blocks along n
+};
+
+// fp16 planes, both copies at once: a block owns 32 x 32 weights and two slices at a time (blockIdx.y counts slice
+// pairs), computes every device of them once -- in double precision, which is what bounds this kernel -- turns the
+// values through LDS as (leading term, residual) pairs of halves and writes the operand chunks of both directions,
+// 16 bytes per thread and copy.  One kernel computing each copy on its own, 8 devices of a column per thread in one
+// serial chain, took 14 + 11 us on a 256 x 256 layer of 4 slices.
+template <int NPOL>
+__global__ __launch_bounds__(256) void tile_f16_kernel(BothCopies b) {
+  __shared__ uint32_t uv[NPOL][2][32][33];           // [array][slice of the pair][k][n]: leading half | residual << 16
+  const TileArgs& a = b.a;
+  const int k0 = (int)(blockIdx.x / b.nb) * 32, n0 = (int)(blockIdx.x % b.nb) * 32;
+  const int s0 = 2 * (int)blockIdx.y, ns = min(2, a.S_w - s0);
+  const int nl = threadIdx.x & 31, kl = threadIdx.x >> 5;
+  NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
+  const uint32_t dmask = (1u << a.slice_bits) - 1;
+  const int n = n0 + nl, j = n % a.C;
+#pragma unroll 2
+  for (int r = 0; r < 4; ++r) {
+    const int k = k0 + kl + 8 * r;
+    const bool real = k < a.K && n < a.N;
+    const int q = real ? quantized_weight(a.W[(size_t)k * a.N + n], (double)a.w_max, a.qw, a.q_per_w) : 0;
+    const int sign = (q > 0) - (q < 0);
+    const uint32_t mag = (uint32_t)::abs(q);
+#pragma unroll
+    for (int sl = 0; sl < 2; ++sl) {
+      double u[NPOL];
+#pragma unroll
+      for (int pol = 0; pol < NPOL; ++pol) u[pol] = 0.0;
+      if (real && sl < ns)
+        plane_values<NPOL>(a, rng, sign, (int)((mag >> (a.slice_bits * (s0 + sl))) & dmask), s0 + sl, k, n, k % a.R, j, u);
+#pragma unroll
+      for (int pol = 0; pol < NPOL; ++pol) {
+        // leading term on the grid 2^-hi_frac (coarser where fp16 cannot hold it), residual in fp16
+        const _Float16 h = a.terms == 2 ? (_Float16)(::rint(u[pol] * a.hi_scale) * a.hi_inv_scale) : (_Float16)u[pol];
+        const _Float16 l = (_Float16)(u[pol] - (double)h);
+        uv[pol][sl][kl + 8 * r][nl] = (uint32_t)__builtin_bit_cast(uint16_t, h) | ((uint32_t)__builtin_bit_cast(uint16_t, l) << 16);
+      }
+    }
   }
-  value = v;
-  return code;
+  __syncthreads();
+  // thread = (term, 16-row step, lane) of either copy; entries c0 .. c0 + 7 of one output
+  const int lane = threadIdx.x & 63, js = (threadIdx.x >> 6) & 1, term = threadIdx.x >> 7;
+  if (term >= a.terms) return;
+  const int ol = lane & 31, c0 = 16 * js + 8 * (lane >> 5);
+#pragma unroll
+  for (int dir = 0; dir < 2; ++dir) {
+    const int c = (dir == 0 ? k0 : n0) + 16 * js, op = (dir == 0 ? n0 : k0) >> 5;
+    if (c >= (dir == 0 ? a.K : a.N)) continue;       // the contraction never reads this k-step
+    const int t = c / b.tile[dir], step = (c - t * b.tile[dir]) >> 4;
+#pragma unroll
+    for (int pol = 0; pol < NPOL; ++pol)
+      for (int sl = 0; sl < ns; ++sl) {
+        u32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t w0 = dir == 0 ? uv[pol][sl][c0 + 2 * e][ol] : uv[pol][sl][ol][c0 + 2 * e];
+          const uint32_t w1 = dir == 0 ? uv[pol][sl][c0 + 2 * e + 1][ol] : uv[pol][sl][ol][c0 + 2 * e + 1];
+          v[e] = term == 0 ? (w0 & 0xFFFFu) | (w1 << 16) : (w0 >> 16) | (w1 & 0xFFFF0000u);
+        }
+        const size_t chunk = (((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms + term) * b.ks[dir] + step) * 64 + lane;
+        reinterpret_cast<u32x4*>(b.base[dir] + (size_t)pol * b.pol_bytes[dir])[chunk] = v;
+      }
+  }
+}
+
+// Codes of a plane value in the 6-bit format: E2M3 numbers (1 sign, 2 exponent, 3 mantissa bits, bias 1: multiples of
+// 1/8 up to 2, of 1/4 up to 4, of 1/2 up to 7.5) times 2^term_exp[j], each the nearest to what the terms before it
+// left; term j's code at bit 6 j.  Adding 1.5 x 2^52 steps rounds to a multiple of the step (half to even) and leaves
+// the multiple in the low bits, so a term costs two additions and integer work (rndne and ldexp are quarter-rate).
+__device__ __forceinline__ uint32_t term_codes(double left, int terms, const int (&term_exp)[kMaxTermsF6]) {
+  uint32_t word = 0;
+#pragma unroll
+  for (int j = 0; j < kMaxTermsF6; ++j) {
+    if (j >= terms) break;
+    const uint32_t bias = (uint32_t)(1023 + term_exp[j]) << 20;
+    const uint32_t sign = (uint32_t)__double2hiint(left) & 0x80000000u;
+    const double a = ::fmin(::fabs(left), __hiloint2double((int)(bias + (2u << 20) + 0xE0000u), 0));   // 7.5 units at most
+    const uint32_t high = (uint32_t)__double2hiint(a);
+    const uint32_t binade = (high >= bias + (1u << 20) ? 1u : 0u) + (high >= bias + (2u << 20) ? 1u : 0u);
+    const double magic = __hiloint2double((int)(bias + ((49u + binade) << 20) + 0x80000u), 0);
+    const double sum = a + magic;
+    const uint32_t code = (uint32_t)__double2loint(sum) + 8u * binade;
+    const double v = sum - magic;
+    left -= __hiloint2double((int)((uint32_t)__double2hiint(v) | sign), __double2loint(v));
+    word |= (code | (code ? sign >> 26 : 0u)) << (6 * j);
+  }
+  return word;
 }
 
 // Planes in the 6-bit format: one thread produces the 8 contraction entries (48 bits per term) that one
@@ -201,7 +229,6 @@ __global__ __launch_bounds__(256) void tile_planes_f6_kernel(TileArgs a) {
   const int s = blockIdx.y;
 
   NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
-  const double qw = (double)((1u << a.weight_bits) - 1);
   const uint32_t dmask = (1u << a.slice_bits) - 1;
   unsigned long long bits[kMaxTermsF6];
 #pragma unroll
@@ -211,18 +238,17 @@ __global__ __launch_bounds__(256) void tile_planes_f6_kernel(TileArgs a) {
     const int c = c0 + e;
     if (within + e >= rows || o >= Lo) continue;
     const int k = TRANSPOSED ? o : c, n = TRANSPOSED ? c : o;
-    const double q = ::rint(clampd((double)a.W[(size_t)k * a.N + n] / (double)a.w_max, -1.0, 1.0) * qw);
-    const int sign = (q > 0.0) - (q < 0.0);
-    const uint32_t mag = (uint32_t)::fabs(q);
-    double left = plane_value(a, rng, sign, (int)((mag >> (a.slice_bits * s)) & dmask), s, k, n);
+    const int q = quantized_weight(a.W[(size_t)k * a.N + n], (double)a.w_max, a.qw, a.q_per_w);
+    const int sign = (q > 0) - (q < 0);
+    const uint32_t mag = (uint32_t)::abs(q);
+    double u[1];
+    plane_values<1>(a, rng, sign, (int)((mag >> (a.slice_bits * s)) & dmask), s, k, n, k % a.R, n % a.C, u);
+    const uint32_t word = term_codes(u[0], a.terms, a.term_exp);
     const int nibble = 2 * (e & 3) + (e >> 2);       // where the input stage's byte e lands in the digit word
 #pragma unroll
     for (int j = 0; j < kMaxTermsF6; ++j) {
       if (j >= a.terms) break;
-      double v;
-      const uint32_t code = e2m3_nearest(::ldexp(left, -a.term_exp[j]), v);
-      left -= ::ldexp(v, a.term_exp[j]);
-      bits[j] |= (unsigned long long)code << (6 * nibble);
+      bits[j] |= (unsigned long long)((word >> (6 * j)) & 63u) << (6 * nibble);
     }
   }
   // 24-byte record of the lane: bytes 0..15 in the fragment's first KiB, 16..23 in its last half KiB
@@ -245,30 +271,22 @@ __global__ __launch_bounds__(256) void tile_planes_f6_kernel(TileArgs a) {
 // General 6-bit generator, first pass: one thread per device pair (k, n) and slice (blockIdx.y) computes the plane
 // value -- quantisation, variation draw, wire model: the arithmetic of tile_planes_f6_kernel -- once, splits it
 // into the terms of the schedule and stores the codes as one word per array: words[array][slice][k][n].
-__global__ __launch_bounds__(256) void device_words_kernel(TileArgs a, uint32_t* words, int npol) {
+template <int NPOL>
+__global__ __launch_bounds__(256) void device_words_kernel(TileArgs a, uint32_t* words) {
   const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (tid >= (long long)a.K * a.N) return;
   const int n = (int)(tid % a.N), k = (int)(tid / a.N);
   const int s = blockIdx.y;
   NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
-  const double qw = (double)((1u << a.weight_bits) - 1);
   const uint32_t dmask = (1u << a.slice_bits) - 1;
-  const double q = ::rint(clampd((double)a.W[(size_t)k * a.N + n] / (double)a.w_max, -1.0, 1.0) * qw);
-  const int sign = (q > 0.0) - (q < 0.0);
-  const int digit = (int)(((uint32_t)::fabs(q) >> (a.slice_bits * s)) & dmask);
-  for (int pol = 0; pol < npol; ++pol) {
-    double left = plane_value(a, rng, sign, digit, s, k, n, npol == 2 ? pol : -1);
-    uint32_t word = 0;
+  const int q = quantized_weight(a.W[(size_t)k * a.N + n], (double)a.w_max, a.qw, a.q_per_w);
+  const int sign = (q > 0) - (q < 0);
+  const uint32_t mag = (uint32_t)::abs(q);
+  double u[NPOL];
+  plane_values<NPOL>(a, rng, sign, (int)((mag >> (a.slice_bits * s)) & dmask), s, k, n, k % a.R, n % a.C, u);
 #pragma unroll
-    for (int j = 0; j < kMaxTermsF6; ++j) {
-      if (j >= a.terms) break;
-      double v;
-      const uint32_t code = e2m3_nearest(::ldexp(left, -a.term_exp[j]), v);
-      left -= ::ldexp(v, a.term_exp[j]);
-      word |= code << (6 * j);
-    }
-    words[(((size_t)pol * a.S_w + s) * a.K + k) * a.N + n] = word;
-  }
+  for (int pol = 0; pol < NPOL; ++pol)
+    words[(((size_t)pol * a.S_w + s) * a.K + k) * a.N + n] = term_codes(u[pol], a.terms, a.term_exp);
 }
 
 // Second pass: one plane copy from the words of its array (a.codes: [slice][k][n]), integer work only.  One wave
@@ -339,8 +357,123 @@ __global__ __launch_bounds__(256) void tile_planes_f6_words_kernel(TileArgs a) {
   }
 }
 
+// Where tile_f6_kernel gets its term codes from.
+constexpr int kFromDigits = 0;    // ideal arrays: the plane value is the digit
+constexpr int kFromTable = 1;     // single-path wire model alone: looked up by (sign, digit, place in the array)
+constexpr int kFromDevices = 2;   // anything else: every device of the patch computed
+
+// Planes in the 6-bit format, both copies at once, for arrays of whole 64-row and 64-column steps: a block owns 64 x 64
+// weights and two slices at a time, gets the term codes of every one of them once, as one word per array and slice in
+// LDS, and its waves pack the records of the 2 x 2 fragments per slice that either direction reads, each lane one
+// 24-byte record per term.  Devices: bound by the double-precision arithmetic of the normal numbers and the wire model
+// (one Philox block for the four devices of a slice pair); the words never reach memory, and each weight is quantised
+// once per slice pair instead of once per slice and copy.  On 4096 x 4096 weights with variation, 8 slices, 5 terms, the
+// three kernels this replaces (a word per device to memory, then one packing pass per copy) took 2.71 + 0.41 + 0.39 ms.
+template <int SRC, int NPOL, int NTH>
+__global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns) {
+  constexpr int SL = NPOL == 2 ? 1 : 2;              // slices per turn: as many words in LDS either way
+  __shared__ uint32_t words[NPOL][SL][64][65];       // [array][slice of the turn][k][n]
+  const TileArgs& a = b.a;
+  constexpr int NW = NTH / 64, PER = 64 / NW;        // waves; weights per thread
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int k0 = (int)(blockIdx.x / b.nb) * 64, n0 = (int)(blockIdx.x % b.nb) * 64;
+  const int n = n0 + lane;
+  const uint32_t dmask = (1u << a.slice_bits) - 1;
+  const int i0 = k0 % a.R, j = n0 % a.C + lane;      // place in the array: whole steps of 64 do not straddle arrays
+  NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
+  int q[PER];
+  if constexpr (SRC != kFromDevices) {
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      const int k = k0 + wave + NW * r;
+      q[r] = k < a.K && n < a.N ? quantized_weight(a.W[(size_t)k * a.N + n], (double)a.w_max, a.qw, a.q_per_w) : 0;
+    }
+  }
+  for (int turn = (int)blockIdx.y * turns; turn < ((int)blockIdx.y + 1) * turns; ++turn) {
+    const int s0 = SL * turn, ns = min(SL, a.S_w - s0);
+    if (ns <= 0) return;
+    if (turn != (int)blockIdx.y * turns) __syncthreads();   // everyone has packed the previous turn
+    if constexpr (SRC == kFromDevices) {
+#pragma unroll 1
+      for (int r = 0; r < PER; ++r) {
+        const int kl = wave + NW * r, k = k0 + kl;
+        const bool real = k < a.K && n < a.N;
+        const int w = real ? quantized_weight(a.W[(size_t)k * a.N + n], (double)a.w_max, a.qw, a.q_per_w) : 0;
+        const int sign = (w > 0) - (w < 0);
+        const uint32_t mag = (uint32_t)::abs(w);
+#pragma unroll
+        for (int sl = 0; sl < SL; ++sl) {
+          uint32_t word[NPOL];
+#pragma unroll
+          for (int pol = 0; pol < NPOL; ++pol) word[pol] = 0;
+          if (real && sl < ns) {
+            double u[NPOL];
+            plane_values<NPOL>(a, rng, sign, (int)((mag >> (a.slice_bits * (s0 + sl))) & dmask), s0 + sl, k, n, i0 + kl, j, u);
+#pragma unroll
+            for (int pol = 0; pol < NPOL; ++pol) word[pol] = term_codes(u[pol], a.terms, a.term_exp);
+          }
+#pragma unroll
+          for (int pol = 0; pol < NPOL; ++pol) words[pol][sl][kl][lane] = word[pol];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int sl = 0; sl < SL; ++sl)
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+          const int kl = wave + NW * r;
+          const uint32_t digit = ((uint32_t)::abs(q[r]) >> (a.slice_bits * (s0 + sl))) & dmask;   // zero beyond K, N and S_w
+          uint32_t word = 0;                         // both devices of the pair in the same state: exactly zero
+          if constexpr (SRC == kFromTable) {
+            if (digit) word = a.codes[((size_t)((q[r] < 0 ? dmask : 0u) + digit - 1) * a.R + i0 + kl) * a.C + j];
+          } else {
+            word = term_codes(q[r] < 0 ? -(double)digit : (double)digit, 1, a.term_exp);
+          }
+          words[0][sl][kl][lane] = word;
+        }
+    }
+    __syncthreads();
+    // fragment groups: (array, slice, direction, half of 32 outputs), one wave each
+    const int ol = lane & 31, half = lane >> 5;
+    for (int grp = wave; grp < 8; grp += NW) {
+      const int hh = grp & 1, dir = (grp >> 1) & 1, sl = NPOL == 2 ? 0 : grp >> 2, pol = NPOL == 2 ? grp >> 2 : 0;
+      const int op = ((dir ? k0 : n0) >> 5) + hh, c = dir ? n0 : k0;
+      if (sl >= ns || op >= b.OP[dir]) continue;
+      const int t = c / b.tile[dir], J = (c - t * b.tile[dir]) >> 6;
+      const uint32_t* from = &words[pol][sl][0][0] + (dir ? (32 * hh + ol) * 65 : 32 * hh + ol);
+      const int stride = dir ? 1 : 65;
+      uint32_t rec[kMaxTermsF6][6];
+#pragma unroll
+      for (int x = 0; x < kMaxTermsF6 * 6; ++x) rec[x / 6][x % 6] = 0u;
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const uint32_t word = from[(w * 16 + half * 8 + e) * stride];
+          const int bit = 6 * (8 * w + 2 * (e & 3) + (e >> 2)), x = bit >> 5, sh = bit & 31;   // place among the lane's 32 codes
+#pragma unroll
+          for (int term = 0; term < kMaxTermsF6; ++term) {
+            if (term >= a.terms) break;
+            const uint32_t code = (word >> (6 * term)) & 63u;
+            rec[term][x] |= code << sh;
+            if (sh > 26) rec[term][x + 1] |= code >> (32 - sh);
+          }
+        }
+      uint8_t* frag = b.base[dir] + (size_t)pol * b.pol_bytes[dir] +
+                      ((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms * b.ks[dir] + J) * 1536;
+#pragma unroll
+      for (int term = 0; term < kMaxTermsF6; ++term) {
+        if (term >= a.terms) break;
+        uint8_t* at = frag + (size_t)term * b.ks[dir] * 1536;
+        *reinterpret_cast<u32x4*>(at + lane * 16) = u32x4{rec[term][0], rec[term][1], rec[term][2], rec[term][3]};
+        *reinterpret_cast<u32x2*>(at + 1024 + lane * 8) = u32x2{rec[term][4], rec[term][5]};
+      }
+    }
+  }
+}
+
 // Term codes of the plane value of every (sign, digit, row, column): one thread per (digit, row, column)
-// computes the value with the arithmetic of plane_value, splits it into the terms of the schedule and
+// computes the value with the arithmetic of plane_values, splits it into the terms of the schedule and
 // writes both signs in both orientations.
 __global__ __launch_bounds__(256) void code_table_kernel(TileArgs a, uint32_t* table) {
   const int nd = (1 << a.slice_bits) - 1;
@@ -351,14 +484,9 @@ __global__ __launch_bounds__(256) void code_table_kernel(TileArgs a, uint32_t* t
   const size_t words = (size_t)2 * nd * a.R * a.C;
 #pragma unroll
   for (int neg = 0; neg < 2; ++neg) {
-    double left = plane_value(a, rng, neg ? -1 : 1, digit, 0, i, j);
-    uint32_t word = 0;
-    for (int t = 0; t < a.terms; ++t) {
-      double v;
-      const uint32_t code = e2m3_nearest(::ldexp(left, -a.term_exp[t]), v);
-      left -= ::ldexp(v, a.term_exp[t]);
-      word |= code << (6 * t);
-    }
+    double u[1];
+    plane_values<1>(a, rng, neg ? -1 : 1, digit, 0, i, j, i, j, u);
+    const uint32_t word = term_codes(u[0], a.terms, a.term_exp);
     const size_t plane = (size_t)(neg * nd + digit - 1) * a.R * a.C;
     table[plane + (size_t)i * a.C + j] = word;
     table[words + plane + (size_t)j * a.R + i] = word;
@@ -386,7 +514,6 @@ __global__ __launch_bounds__(256) void tile_planes_f6_table_kernel(TileArgs a) {
   const int lane = (o & 31) + 32 * half;
   const int op = o >> 5;
   const int c0 = t * a.tile + within;
-  const double qw = (double)((1u << a.weight_bits) - 1);
   const uint32_t dmask = (1u << a.slice_bits) - 1;
   const int nd = (int)dmask;
   // table of this orientation: [sign][digit - 1][contraction place][output place]
@@ -402,9 +529,9 @@ __global__ __launch_bounds__(256) void tile_planes_f6_table_kernel(TileArgs a) {
     if (within + e >= rows || o >= Lo) continue;
     const int c = c0 + e;
     const int k = TRANSPOSED ? o : c, n = TRANSPOSED ? c : o;
-    const double q = ::rint(clampd((double)a.W[(size_t)k * a.N + n] / (double)a.w_max, -1.0, 1.0) * qw);
-    mag[e] = (uint32_t)::fabs(q);
-    first[e] = q < 0.0 ? nd : 0;
+    const int q = quantized_weight(a.W[(size_t)k * a.N + n], (double)a.w_max, a.qw, a.q_per_w);
+    mag[e] = (uint32_t)::abs(q);
+    first[e] = q < 0 ? nd : 0;
   }
   uint8_t* base = reinterpret_cast<uint8_t*>(a.planes);
   const int s_end = min(a.S_w, ((int)blockIdx.y + 1) * a.spt);
@@ -1744,51 +1871,90 @@ int xbar_tile(const xbar_config* cfg, const float* W, int K, int N, float w_max,
     hipLaunchKernelGGL(weight_sums_kernel, dim3((unsigned)(cdiv(K, 64) * cdiv(N, 64))), dim3(256), 0, st, sa);
     if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
   }
-  size_t offset = 0;
-  for (int dir = 0; dir < 2; ++dir)
-  for (int pol = 0; pol < d.npol; ++pol) {
-    const PlaneGeom g = plane_geom(cfg, d, K, N, dir == 1);
-    TileArgs a;
-    a.W = W;
-    a.profile = profile;
-    a.wire_u = wire_u;
-    a.pol_out = d.npol == 2 ? pol : -1;
-    a.planes = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(planes) + offset + (size_t)pol * g.pol_bytes);
-    a.K = K; a.N = N; a.R = cfg->xbar_rows; a.C = cfg->xbar_cols; a.S_w = d.S_w;
-    a.slice_bits = cfg->slice_bits; a.weight_bits = cfg->weight_bits; a.terms = d.terms;
-    a.tile = g.tile; a.ks = g.ks; a.T = g.T; a.OP = g.OP;
-    a.flags = cfg->flags;
-    a.g_min = 1.0 / (double)cfg->r_max;
-    a.dg = (1.0 / (double)cfg->r_min - a.g_min) / (double)((1 << cfg->slice_bits) - 1);
-    a.var_sigma = (double)cfg->var_sigma;
-    a.r_row = (double)cfg->r_row;
-    a.r_col = (double)cfg->r_col;
-    a.r_source = (double)cfg->r_source;
-    a.r_sense = (double)cfg->r_sense;
-    {  // |U| < 2^slice_bits: fp16 holds multiples of 2^-(11 - slice_bits) below that bound exactly; one
-       // array alone adds the off-state conductance (below the full range for on/off ratios from 2): one bit less
-      const int hi_frac = (d.npol == 2 ? 10 : 11) - cfg->slice_bits;
-      a.hi_scale = std::ldexp(1.0, hi_frac);
-      a.hi_inv_scale = std::ldexp(1.0, -hi_frac);
+  TileArgs a;
+  a.W = W;
+  a.profile = profile;
+  a.codes = nullptr;
+  a.wire_u = wire_u;
+  a.K = K; a.N = N; a.R = cfg->xbar_rows; a.C = cfg->xbar_cols; a.S_w = d.S_w;
+  a.slice_bits = cfg->slice_bits; a.terms = d.terms;
+  a.flags = cfg->flags;
+  a.g_min = 1.0 / (double)cfg->r_max;
+  a.dg = (1.0 / (double)cfg->r_min - a.g_min) / (double)((1 << cfg->slice_bits) - 1);
+  a.inv_dg = 1.0 / a.dg;
+  a.var_sigma = (double)cfg->var_sigma;
+  a.r_row = (double)cfg->r_row;
+  a.r_col = (double)cfg->r_col;
+  a.r_source = (double)cfg->r_source;
+  a.r_sense = (double)cfg->r_sense;
+  {  // |U| < 2^slice_bits: fp16 holds multiples of 2^-(11 - slice_bits) below that bound exactly; one
+     // array alone adds the off-state conductance (below the full range for on/off ratios from 2): one bit less
+    const int hi_frac = (d.npol == 2 ? 10 : 11) - cfg->slice_bits;
+    a.hi_scale = std::ldexp(1.0, hi_frac);
+    a.hi_inv_scale = std::ldexp(1.0, -hi_frac);
+  }
+  a.w_max = w_max;
+  a.qw = (double)((1u << cfg->weight_bits) - 1);
+  a.q_per_w = a.qw / (double)w_max;
+  a.seed = cfg->seed;
+  a.step = step;
+  a.step_add = current_step_source();
+  for (int j = 0; j < kMaxTermsF6; ++j) a.term_exp[j] = d.term_exp[j];
+
+  uint8_t* at = reinterpret_cast<uint8_t*>(planes);
+  PlaneGeom g[2] = {plane_geom(cfg, d, K, N, false), plane_geom(cfg, d, K, N, true)};
+  BothCopies b;
+  for (int dir = 0; dir < 2; ++dir) {
+    b.base[dir] = at + (dir ? align256(g[0].bytes) : 0);
+    b.OP[dir] = g[dir].OP; b.ks[dir] = g[dir].ks; b.tile[dir] = g[dir].tile; b.pol_bytes[dir] = g[dir].pol_bytes;
+  }
+  const int pairs = cdiv(d.S_w, 2);
+  if (d.fmt == kFmtF16) {
+    b.a = a;
+    b.nb = cdiv(N, 32);
+    const dim3 grid((unsigned)(cdiv(K, 32) * b.nb), (unsigned)pairs);
+    if (d.npol == 2) hipLaunchKernelGGL(tile_f16_kernel<2>, grid, dim3(256), 0, st, b);
+    else hipLaunchKernelGGL(tile_f16_kernel<1>, grid, dim3(256), 0, st, b);
+    return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
+  }
+  uint32_t* table = nullptr;
+  if (uses_code_table(d)) {
+    table = reinterpret_cast<uint32_t*>(at + code_table_offset(cfg, d, K, N));
+    const int entries = ((1 << cfg->slice_bits) - 1) * cfg->xbar_rows * cfg->xbar_cols;
+    hipLaunchKernelGGL(code_table_kernel, dim3((unsigned)cdiv(entries, 256)), dim3(256), 0, st, a, table);
+    if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
+    a.codes = table;
+  }
+  if (a.R % 64 == 0 && a.C % 64 == 0) {
+    b.a = a;
+    b.nb = cdiv(N, 64);
+    const unsigned patches = (unsigned)(cdiv(K, 64) * b.nb);
+    // one slice pair per block, in 16 waves where the layer has few patches (a wave then has four weights to work
+    // through); the cheap sources take all the slices of a patch in one block once that leaves 4 blocks per compute unit
+    if (uses_device_words(d)) {
+      const dim3 grid(patches, (unsigned)pairs);
+      const bool few = patches * (unsigned)pairs < 1024;
+      if (d.npol == 2) hipLaunchKernelGGL((tile_f6_kernel<kFromDevices, 2, 512>), dim3(patches, (unsigned)d.S_w), dim3(512), 0, st, b, 1);
+      else if (few) hipLaunchKernelGGL((tile_f6_kernel<kFromDevices, 1, 1024>), grid, dim3(1024), 0, st, b, 1);
+      else hipLaunchKernelGGL((tile_f6_kernel<kFromDevices, 1, 512>), grid, dim3(512), 0, st, b, 1);
+    } else {
+      const int per = (int)std::min<unsigned>((unsigned)pairs, std::max(1u, patches * (unsigned)pairs / 1024u));
+      const dim3 grid(patches, (unsigned)cdiv(pairs, per));
+      if (table) hipLaunchKernelGGL((tile_f6_kernel<kFromTable, 1, 512>), grid, dim3(512), 0, st, b, per);
+      else hipLaunchKernelGGL((tile_f6_kernel<kFromDigits, 1, 512>), grid, dim3(512), 0, st, b, per);
     }
-    a.w_max = w_max;
-    a.seed = cfg->seed;
-    a.step = step;
-    a.step_add = current_step_source();
-    for (int j = 0; j < kMaxTermsF6; ++j) a.term_exp[j] = d.term_exp[j];
-    // every k-step that the contraction reads is written whole, padding included
-    const int Lc = dir == 1 ? N : K;
-    if (d.fmt == kFmtF6) {
-      a.n_threads = (long long)g.T * g.ks * 8 * g.OP * 32;
+    return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
+  }
+  // arrays whose rows or columns are no whole steps of 64: the two copies group the devices differently, each is
+  // written on its own
+  for (int dir = 0; dir < 2; ++dir)
+    for (int pol = 0; pol < d.npol; ++pol) {
+      a.planes = reinterpret_cast<uint16_t*>(b.base[dir] + (size_t)pol * g[dir].pol_bytes);
+      a.tile = g[dir].tile; a.ks = g[dir].ks; a.T = g[dir].T; a.OP = g[dir].OP;
+      // every k-step that the contraction reads is written whole, padding included
+      a.n_threads = (long long)a.T * a.ks * 8 * a.OP * 32;
       const unsigned blocks = (unsigned)((a.n_threads + 255) / 256);
-      a.codes = nullptr;
-      if (uses_code_table(d)) {
-        uint32_t* table = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(planes) + code_table_offset(cfg, d, K, N));
-        if (dir == 0) {
-          const int entries = ((1 << cfg->slice_bits) - 1) * cfg->xbar_rows * cfg->xbar_cols;
-          hipLaunchKernelGGL(code_table_kernel, dim3((unsigned)cdiv(entries, 256)), dim3(256), 0, st, a, table);
-          if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
-        }
+      if (table) {
         a.codes = table + (dir == 1 ? code_table_words(cfg) : 0);
         // a thread quantises its weights once for all the slices it covers: as many slices per thread as
         // still leave about four waves for every SIMD of the chip
@@ -1797,31 +1963,22 @@ int xbar_tile(const xbar_config* cfg, const float* W, int K, int N, float w_max,
         if (dir == 0) hipLaunchKernelGGL(tile_planes_f6_table_kernel<false>, grid, dim3(256), 0, st, a);
         else hipLaunchKernelGGL(tile_planes_f6_table_kernel<true>, grid, dim3(256), 0, st, a);
       } else if (uses_device_words(d)) {
-        uint32_t* words = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(planes) + device_words_offset(cfg, d, K, N));
+        uint32_t* words = reinterpret_cast<uint32_t*>(at + device_words_offset(cfg, d, K, N));
         if (dir == 0 && pol == 0) {                  // every device once, for both copies and both arrays
-          const unsigned wblocks = (unsigned)(((long long)K * N + 255) / 256);
-          hipLaunchKernelGGL(device_words_kernel, dim3(wblocks, (unsigned)d.S_w), dim3(256), 0, st, a, words, d.npol);
+          const dim3 wgrid((unsigned)(((long long)K * N + 255) / 256), (unsigned)d.S_w);
+          if (d.npol == 2) hipLaunchKernelGGL(device_words_kernel<2>, wgrid, dim3(256), 0, st, a, words);
+          else hipLaunchKernelGGL(device_words_kernel<1>, wgrid, dim3(256), 0, st, a, words);
           if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
         }
         a.codes = words + (size_t)pol * d.S_w * K * N;
-        a.n_threads = (long long)g.T * g.OP * g.ks * 64;   // one wave per fragment group
+        a.n_threads = (long long)a.T * a.OP * a.ks * 64;   // one wave per fragment group
         const dim3 pgrid((unsigned)((a.n_threads + 255) / 256), (unsigned)d.S_w);
         if (dir == 0) hipLaunchKernelGGL(tile_planes_f6_words_kernel<false>, pgrid, dim3(256), 0, st, a);
         else hipLaunchKernelGGL(tile_planes_f6_words_kernel<true>, pgrid, dim3(256), 0, st, a);
       } else if (dir == 0) hipLaunchKernelGGL(tile_planes_f6_kernel<false>, dim3(blocks, (unsigned)d.S_w), dim3(256), 0, st, a);
       else hipLaunchKernelGGL(tile_planes_f6_kernel<true>, dim3(blocks, (unsigned)d.S_w), dim3(256), 0, st, a);
       if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
-      if (pol == d.npol - 1) offset += align256(g.bytes);
-      continue;
     }
-    const long long chunks = (long long)cdiv(Lc, 16) * 2;
-    a.n_threads = chunks * g.OP * 32;
-    const unsigned blocks = (unsigned)((a.n_threads + 255) / 256);
-    if (dir == 0) hipLaunchKernelGGL(tile_planes_kernel<false>, dim3(blocks, (unsigned)d.S_w), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(tile_planes_kernel<true>, dim3(blocks, (unsigned)d.S_w), dim3(256), 0, st, a);
-    if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
-    if (pol == d.npol - 1) offset += align256(g.bytes);
-  }
   return XBAR_OK;
 }
 

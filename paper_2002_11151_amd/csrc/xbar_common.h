@@ -246,6 +246,16 @@ struct NormalStream {
     box_muller(second ? w[2] : w[0], second ? w[3] : w[1], even, odd);
     return (i & 1u) ? odd : even;
   }
+  // Numbers i and i + 1, i even: they share a logarithm, a root and an angle.
+  __device__ void pair(uint64_t i, double& even, double& odd) {
+    const uint64_t blk = i >> 2;
+    if (blk != cached_blk) {
+      philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), s0, s1, k0, k1, w);
+      cached_blk = blk;
+    }
+    const bool second = (i & 2u) != 0;
+    box_muller(second ? w[2] : w[0], second ? w[3] : w[1], even, odd);
+  }
   // The four numbers 4 blk .. 4 blk + 3 of a block: one Philox evaluation, two logarithms, roots and angles.
   __device__ void get4(uint64_t blk, double (&z)[4]) const {
     uint32_t v[4];

@@ -4,11 +4,17 @@ import numpy as np
 import pytest
 
 import workloads
-from test_gpu_parity import both_configs, dev, rel_l2, xb  # noqa: F401 (fixture)
+from test_gpu_parity import both_configs, dev, gpu_bwd, gpu_fwd, rel_l2, xb  # noqa: F401 (fixture)
 
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
+
+
+def close_codes(got, want):
+    """The code bar (one LSB on at most 1e-4 of the conversions) for few conversions: two may differ."""
+    diff = np.abs(got.astype(np.int64) - want.astype(np.int64))
+    return diff.max() <= 1 and (diff > 0).sum() <= max(2, 1e-4 * diff.size)
 
 
 # M, K, N: odd weight counts (no 16-byte rows), one batch partial, the 8- and 32-group reductions, many weights
@@ -30,3 +36,19 @@ def test_update_write(xo, xb, M, K, N, pair):
     torch.cuda.synchronize()
     assert rel_l2(Wg.cpu().numpy() - W, want - W) <= 1e-3
 
+
+# patches of 64 x 64 (32 x 32 with 4-bit cycles) weights, slices in pairs: one less, exact, one more; odd slice counts;
+# arrays of whole 64-row steps and others (48: each copy on its own)
+@pytest.mark.parametrize("R,sb,wb,slb", [(64, 1, 8, 2), (128, 1, 6, 2), (64, 4, 6, 2), (48, 1, 4, 2), (48, 4, 3, 1), (192, 2, 4, 4)])
+@pytest.mark.parametrize("ni", ["aam", "var", "var+pa", "ideal"])
+@pytest.mark.parametrize("K,N", [(1, 1), (63, 33), (64, 64), (65, 31), (193, 129)])
+def test_generator(xo, xb, R, sb, wb, slb, ni, K, N):
+    M = 4
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=K + 3 * N)
+    flags = {"aam": xo.WIRE_AAM, "var": xo.VARIATION | xo.WIRE_AAM, "var+pa": xo.VARIATION | xo.ADC_PER_ARRAY, "ideal": 0}[ni]
+    fs = 1.037 * workloads.adc_full_scale(R, sb, slb)             # off the binary grid: no ties
+    co, cg = both_configs(xo, xb, xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=slb, stream_bits=sb,
+                          flags=flags | xo.INPUT_SIGNED, var_sigma=0.1, seed=9, adc_fs_fwd=fs, adc_fs_bwd=fs)
+    w_max, xs, gs = float(np.abs(W).max()), float(np.abs(X).max()), float(np.abs(dY).max())
+    assert close_codes(gpu_fwd(xb, cg, W, X, w_max, xs, step=2)[1], xo.fwd(co, W, X, w_max, xs, step=2, want_codes=True)[1])
+    assert close_codes(gpu_bwd(xb, cg, W, dY, w_max, gs, step=2)[1], xo.bwd(co, W, dY, w_max, gs, step=2, want_codes=True)[1])
