@@ -42,9 +42,11 @@ struct PulseArgs {
   ConvGeom conv;                        // convolution layer: X is the NHWC image and row m of the layer's
                                         //   input matrix is gathered from it (CONV variant of the train kernel)
   int coded, tx, td;                    // 1: deterministic time coding, tx frames of td sub-slots; 2: magnitude coding
-  unsigned long long* marks;            // two-phase walk: [n_words][K N] one bit per sample and device
+  unsigned long long* marks;            // two-phase walk: [K N][n_words] one bit per sample and device
   unsigned long long* summary;          //   [ceil(n_words / 64)][K N] one bit per word that is not empty
   int n_words;                          //   64-sample words of the current chunk
+  int seg_words;                        //   words per block of the marking pass (a multiple of 4)
+  double series[8];                     // streamed walk: exp(-v y) = sum of series[i] y^i for v up to 1 / 32
 };
 
 __device__ __forceinline__ uint32_t pulse_train(uint32_t k0, uint32_t k1, uint64_t step, uint64_t index, double p, int bl) {
@@ -208,8 +210,7 @@ __global__ __launch_bounds__(256) void pulse_apply_kernel(PulseArgs a) {
           live[w] = 0;
           if constexpr (MARKED) {
             const int word = s0 / 64 + w;
-            if (word < a.n_words && k0 + i < a.K && n0 + j < a.N)
-              live[w] = a.marks[(size_t)word * ((size_t)a.K * a.N) + dev];
+            if (word < a.n_words && k0 + i < a.K && n0 + j < a.N) live[w] = a.marks[(size_t)dev * a.n_words + word];
             continue;
           }
 #pragma unroll
@@ -279,17 +280,18 @@ __global__ __launch_bounds__(256) void pulse_apply_kernel(PulseArgs a) {
 }
 
 // Two-phase walk for layers with few devices and many samples (convolution layers: a 144 x 16 layer has
-// 9 blocks of devices and 131072 samples).  Phase 1, one block per (16 x 16 devices, stage of 256
-// samples at a time, 4096 per block), fills the chip: it marks the samples in which a device's row and
-// column share a slot, one bit per sample and device, plus one summary bit per 64-sample word that is
-// not empty.  Phase 2, one thread per device, walks only the marked samples, in order (summary ->
-// word -> sample), fetching their two trains from memory: the sequential part shrinks to the pulses.
+// 9 blocks of devices and 131072 samples).  Phase 1, one block per 16 x 16 devices and segment of samples
+// (256 at a time), fills the chip: it marks the samples in which a device's row and column share a slot,
+// one bit per sample and device, plus, for the plain walk, one summary bit per 64-sample word that is not
+// empty.  Phase 2 walks only the marked samples, in order: pulse_stream_kernel where the layer has few
+// devices, else one thread per device (summary -> word -> sample), fetching their two trains from memory:
+// the sequential part shrinks to the pulses.
 __global__ __launch_bounds__(256) void pulse_mark_kernel(PulseArgs a) {
-  constexpr int TE = 16, ST = 256, LD = ST + 4, PER = ST * TE / 256, NW = ST / 64, SEG = 64 * 64;
+  constexpr int TE = 16, ST = 256, LD = ST + 4, PER = ST * TE / 256, NW = ST / 64;
   __shared__ __align__(16) uint32_t rt[TE * LD];
   __shared__ __align__(16) uint32_t ct[TE * LD];
   const int nb = (a.N + TE - 1) / TE, tiles = ((a.K + TE - 1) / TE) * nb;
-  const int tile = blockIdx.x % tiles, seg = blockIdx.x / tiles;     // segment = 64 words = 4096 samples
+  const int tile = blockIdx.x % tiles, seg = blockIdx.x / tiles, seg_samples = 64 * a.seg_words;
   const int kt = (tile / nb) * TE, nt = (tile % nb) * TE;
   const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
   const int k = kt + ty, n = nt + tx;
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(256) void pulse_mark_kernel(PulseArgs a) {
   const uint32_t* cp = &ct[tx * LD];
   const size_t kn = (size_t)a.K * a.N, dev = (size_t)k * a.N + n;
   unsigned long long summary = 0;                  // bit = word of the segment that has a marked sample
-  for (int s0 = seg * SEG; s0 < min(a.mc, (seg + 1) * SEG); s0 += ST) {
+  for (int s0 = seg * seg_samples; s0 < min(a.mc, (seg + 1) * seg_samples); s0 += ST) {
     const int ns = min(ST, a.mc - s0);
     __syncthreads();                               // everyone is done with the previous stage
 #pragma unroll
@@ -323,12 +325,12 @@ __global__ __launch_bounds__(256) void pulse_mark_kernel(PulseArgs a) {
         bits |= (unsigned long long)four << (4 * v);
       }
       if (valid && word < a.n_words) {
-        a.marks[(size_t)word * kn + dev] = bits;
-        if (bits) summary |= 1ull << (word - 64 * seg);
+        a.marks[dev * a.n_words + word] = bits;
+        if (bits) summary |= 1ull << ((word - a.seg_words * seg) & 63);
       }
     }
   }
-  if (valid) a.summary[(size_t)seg * kn + dev] = summary;
+  if (valid && a.seg_words == 64) a.summary[(size_t)seg * kn + dev] = summary;   // one word of it per segment (the plain walk's)
 }
 
 template <bool NL, bool NOISE>
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(256) void pulse_walk_kernel(PulseArgs a) {
         if (summary == 0) break;                     // no marked sample left
         const int wi = seg_base + __builtin_ctzll(summary);
         summary &= summary - 1;
-        word = a.marks[(size_t)wi * kn + dev];       // not empty: its summary bit is set
+        word = a.marks[dev * a.n_words + wi];        // not empty: its summary bit is set
         word_base = 64 * wi;
       }
       const int at = word_base + __builtin_ctzll(word);
@@ -375,6 +377,175 @@ __global__ __launch_bounds__(256) void pulse_walk_kernel(PulseArgs a) {
   if (a.last) a.W[dev] = (float)(a.w_max * gs);
   else a.state[dev] = gs;
   if (a.pulses) a.pulses[dev] = (a.first ? 0 : a.pulses[dev]) + moved;
+}
+
+// The streamed walk: L lanes share a device, so that a layer with few devices spreads over the chip.  Only the moves of
+// a device are sequential; which samples it is pulsed in, the trains and the normal numbers of its pulses are not.  A
+// group of L lanes reads L mark words of its device at a time, lists the marked samples in LDS, fetches the trains of L
+// of them side by side, lists their pulses, evaluates L normal numbers side by side, and then all its lanes walk through
+// those L moves in step, each move a handful of dependent double-precision operations.  Samples and pulses that do not
+// fill a batch of L wait for the next one.  What bounds it: the walk's dependent chain (about 60 cycles per pulse) plus
+// a normal number (about 1000 instructions) per L pulses.
+// NL: 0 linear device; 1 write non-linearity by its power series (v <= 1/32: seven powers leave less than 3e-17 of
+// exp(-v y) on 0 <= y <= 1); 2 by exp().
+template <int L, int NL, bool NOISE>
+__global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
+#pragma clang fp contract(off)
+  constexpr int D = 64 / L;                          // devices per wave
+  constexpr int SQ = 33 * L, PQ = 32 * L;            // queues: up to L - 1 waiting, plus 32 words' halves / 31 pulses per sample
+  __shared__ uint32_t samples[D][SQ];
+  __shared__ uint32_t pulses[D][PQ];                 // sample << 6 | ordinal << 1 | upwards
+  __shared__ double2 moves[64];                      // noise of a pulse; half its direction (+-0.5, 0: no pulse)
+  const int lane = threadIdx.x, gl = lane & (L - 1), grp = lane / L;
+  const size_t kn = (size_t)a.K * a.N, want = (size_t)blockIdx.x * D + grp;
+  const bool valid = want < kn;
+  const size_t dev = valid ? want : kn - 1;
+  const int k = (int)(dev / a.N), n = (int)(dev % a.N);
+  NormalStream rng(a.seed, kStreamPulseNoise, (effective_step(a.step, a.step_add) << 31) | dev);
+  const unsigned long long* marks = a.marks + dev * a.n_words;
+  uint32_t* sq = samples[grp];
+  uint32_t* pq = pulses[grp];
+  const double2* mv = &moves[grp * L];
+  double g = a.first ? (double)a.W[dev] / a.w_max : a.state[dev];
+  double gx = clampd(g, -1.0, 1.0);                  // where the non-linearity finds the state
+  const double up_down = 2.0 * a.dw_min;
+  int n_s = 0, n_p = 0, moved = 0;
+
+  auto scan = [&](int v) __attribute__((always_inline)) {   // inclusive, over the lanes of the group
+#pragma unroll
+    for (int d = 1; d < L; d <<= 1) {
+      const int o = __shfl_up(v, d, L);
+      if (gl >= d) v += o;
+    }
+    return v;
+  };
+  // All loops below run as long as any device of the wave has work (their conditions are the same for all lanes).  The
+  // last turn (`flush`) lists nothing and takes what is left in the queues.
+  unsigned long long next_word = (valid && gl < a.n_words) ? marks[gl] : 0ull;
+  bool flush = false;
+  for (int w0 = 0; !flush; w0 += L) {
+    flush = w0 >= a.n_words;
+    const unsigned long long word = next_word;
+    next_word = (valid && w0 + L + gl < a.n_words) ? marks[w0 + L + gl] : 0ull;
+    // the words of one half of the lanes at a time: the queue holds that many samples
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+      {
+        unsigned long long bits = (gl >= L / 2) == (half == 1) ? word : 0ull;
+        const int c = __popcll(bits), inc = scan(c);
+        int pos = n_s + inc - c;
+        const uint32_t base = (uint32_t)(w0 + gl) * 64u;
+        while (__any(bits != 0))
+          if (bits) {
+            sq[pos++] = base + (uint32_t)__builtin_ctzll(bits);
+            bits &= bits - 1;
+          }
+        n_s += __shfl(inc, L - 1, L);
+      }
+      __syncthreads();
+      int taken = 0;
+      while (__any(n_s - taken >= (flush ? 1 : L) || (flush && n_p > 0))) {
+        // a batch of samples: their trains, and their pulses
+        const int take = n_s - taken >= L ? L : (flush ? n_s - taken : 0);
+        uint32_t at = 0, q = 0, up = 0;
+        if (gl < take) {
+          at = sq[taken + gl];
+          const uint32_t rw = a.rows[(size_t)at * a.K + k], cw = a.cols[(size_t)at * a.N + n];
+          q = rw & cw & 0x7FFFFFFFu;
+          up = (rw ^ cw) >> 31;                      // against the sign of x d
+        }
+        taken += take;
+        {
+          const int c = __popc(q), inc = scan(c);
+          int pos = n_p + inc - c;
+          for (uint32_t ord = 0; __any(q != 0); ++ord)
+            if (q) {
+              pq[pos++] = (at << 6) | (ord << 1) | up;
+              q &= q - 1;
+            }
+          n_p += __shfl(inc, L - 1, L);
+        }
+        __syncthreads();
+        const int full = flush && taken >= n_s ? 1 : L;   // the device's very last pulses need not fill a batch
+        int done = 0;
+        while (__any(n_p - done >= full)) {
+          // a batch of pulses: their normal numbers side by side, then the moves one after the other
+          const int run = n_p - done >= full ? min(L, n_p - done) : 0;
+          double2 e = {0.0, 0.0};
+          if (gl < run) {
+            const uint32_t p = pq[done + gl];
+            const bool upwards = (p & 1u) != 0;
+            e.y = upwards ? 0.5 : -0.5;
+            moved += upwards ? 1 : -1;
+            if constexpr (NOISE) e.x = a.sigma * rng.get((uint64_t)(a.m0 + (int)(p >> 6)) * 32 + ((p >> 1) & 31u));
+          }
+          moves[lane] = e;
+          __syncthreads();
+          // a device without a pulse in this batch keeps its state, also one beyond the range
+          const double lo = run > 0 ? -1.0 : -INFINITY, hi = run > 0 ? 1.0 : INFINITY;
+#pragma unroll 1
+          for (int t0 = 0; t0 < L; t0 += 8) {
+            if (!__any(t0 < run)) break;
+            double2 b[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) b[t] = mv[t0 + t];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+              const double step = b[t].y * up_down;
+              double next;
+              if constexpr (NL == 0) {
+                next = g + step;
+              } else {
+                const double y = __builtin_fma(b[t].y, gx, 0.5);   // x upwards, 1 - x downwards
+                double f;
+                if constexpr (NL == 1) {
+                  const double y2 = y * y, y4 = y2 * y2;
+                  const double p0 = __builtin_fma(a.series[1], y, a.series[0]), p1 = __builtin_fma(a.series[3], y, a.series[2]);
+                  const double p2 = __builtin_fma(a.series[5], y, a.series[4]), p3 = __builtin_fma(a.series[7], y, a.series[6]);
+                  f = __builtin_fma(y4, __builtin_fma(y2, p3, p2), __builtin_fma(y2, p1, p0));
+                } else {
+                  f = ::exp(-a.v * y);
+                }
+                next = g + step * f;
+              }
+              if constexpr (NOISE) next += b[t].x;
+              g = ::fmin(::fmax(next, lo), hi);
+              if constexpr (NL != 0) gx = run > 0 ? g : gx;
+            }
+          }
+          done += run;
+          __syncthreads();
+        }
+        const uint32_t rest = gl < n_p - done ? pq[done + gl] : 0u;
+        __syncthreads();
+        pq[gl] = rest;
+        n_p -= done;
+        __syncthreads();
+      }
+      const uint32_t rest = gl < n_s - taken ? sq[taken + gl] : 0u;
+      __syncthreads();
+      sq[gl] = rest;
+      n_s -= taken;
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int d = 1; d < L; d <<= 1) moved += __shfl_xor(moved, d, L);
+  if (valid && gl == 0) {
+    if (a.last) a.W[dev] = (float)(a.w_max * g);
+    else a.state[dev] = g;
+    if (a.pulses) a.pulses[dev] = (a.first ? 0 : a.pulses[dev]) + moved;
+  }
+}
+
+template <int L>
+void launch_pulse_stream(const PulseArgs& a, bool nl, bool noise, hipStream_t st) {
+  const int mode = !nl ? 0 : a.v <= 1.0 / 32.0 ? 1 : 2;
+  void (*k)(PulseArgs);
+  if (noise) k = mode == 0 ? pulse_stream_kernel<L, 0, true> : mode == 1 ? pulse_stream_kernel<L, 1, true> : pulse_stream_kernel<L, 2, true>;
+  else k = mode == 0 ? pulse_stream_kernel<L, 0, false> : mode == 1 ? pulse_stream_kernel<L, 1, false> : pulse_stream_kernel<L, 2, false>;
+  const long long kn = (long long)a.K * a.N;
+  hipLaunchKernelGGL(k, dim3((unsigned)((kn * L + 63) / 64)), dim3(64), 0, st, a);
 }
 
 constexpr int kTwoPhaseBlocks = 4096;
@@ -451,6 +622,8 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
   a.sigma = (double)cfg->upd_noise_gamma * std::sqrt(lr_eq * (double)dw_min);
   a.seed = cfg->seed; a.step = step; a.step_add = current_step_source();
   a.conv = conv ? *conv : ConvGeom{};
+  a.series[0] = 1.0;
+  for (int i = 1; i < 8; ++i) a.series[i] = a.series[i - 1] * -a.v / (double)i;
   // 4 x 4 devices per thread when that still fills the chip, else one device per thread
   const bool patch4 = (long long)cdiv(K, 64) * cdiv(N, 64) >= 512;
   const int edge = patch4 ? 64 : 16;
@@ -481,10 +654,20 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
     }
     if (p.two_phase) {
       a.n_words = cdiv(a.mc, 64);
+      const long long devices = (long long)K * N;
+      const bool stream = devices < (noise ? 49152 : 32768);
       const unsigned tiles16 = (unsigned)(cdiv(K, 16) * cdiv(N, 16));
-      hipLaunchKernelGGL(pulse_mark_kernel, dim3(tiles16 * (unsigned)cdiv(a.mc, 4096)), dim3(256), 0, st, a);
+      // the plain walk needs whole summary words (64-word segments); else short ones, for some thousand blocks
+      a.seg_words = !stream || tiles16 >= 256 ? 64 : tiles16 >= 64 ? 16 : 4;
+      hipLaunchKernelGGL(pulse_mark_kernel, dim3(tiles16 * (unsigned)cdiv(a.n_words, a.seg_words)), dim3(256), 0, st, a);
       if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
-      if (noise) {
+      // few devices: several lanes per device, so that about a thousand waves or more share the walk (measured with
+      // noise, ms per update, lanes per device 64 / 32 / 16 / none: 432 devices x 131072 samples 0.77 / 1.01 / 1.58 / 7.85,
+      // 2304 x 131072 2.66 / 2.55 / 2.94 / 14.2, 18432 x 8192 1.10 / 0.87 / 0.82 / 1.31, 65536 x 12544 4.6 / 3.5 / 3.0 / 2.7)
+      if (stream && devices < 1024) launch_pulse_stream<64>(a, nl, noise, st);
+      else if (stream && devices < 12288) launch_pulse_stream<32>(a, nl, noise, st);
+      else if (stream) launch_pulse_stream<16>(a, nl, noise, st);
+      else if (noise) {
         // lanes decoupled over the whole chunk: with a normal number per pulse every turn counts
         void (*walk)(PulseArgs) = nl ? pulse_walk_kernel<true, true> : pulse_walk_kernel<false, true>;
         hipLaunchKernelGGL(walk, dim3((unsigned)cdiv(K * N, 64)), dim3(64), 0, st, a);     // one wave per block: spread over the chip

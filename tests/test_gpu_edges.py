@@ -52,3 +52,25 @@ def test_generator(xo, xb, R, sb, wb, slb, ni, K, N):
     w_max, xs, gs = float(np.abs(W).max()), float(np.abs(X).max()), float(np.abs(dY).max())
     assert close_codes(gpu_fwd(xb, cg, W, X, w_max, xs, step=2)[1], xo.fwd(co, W, X, w_max, xs, step=2, want_codes=True)[1])
     assert close_codes(gpu_bwd(xb, cg, W, dY, w_max, gs, step=2)[1], xo.bwd(co, W, dY, w_max, gs, step=2, want_codes=True)[1])
+
+
+# Streamed walk: 64 / 32 / 16 lanes per device and none, one device, queues that never fill and ones that always do,
+# the power series of the non-linearity (v up to 1 / 32) and exp(), states that start beyond the range
+@pytest.mark.parametrize("M,K,N,density,v,ni", [
+    (2048, 1, 1, 4.0, 0.01, "nl+noise"), (2100, 31, 33, 4.0, 1.0 / 32, "nl"), (4200, 31, 33, 0.02, 0.01, "nl+noise"),
+    (2049, 23, 45, 0.3, 0.0, ""), (4200, 96, 37, 0.5, 0.04, "nl+noise"), (2100, 96, 37, 0.05, 0.0, ""),
+    (2049, 160, 80, 0.05, 0.01, "nl+noise"), (2048, 160, 80, 0.05, 0.04, "nl"), (2048, 300, 170, 0.02, 0.01, "nl+noise")])
+def test_pulsed_walk(xo, xb, M, K, N, density, v, ni):
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=M + K + N)
+    w_max = 0.5 * float(np.abs(W).max())
+    flags = (xo.UPD_NL if "nl" in ni else 0) | (xo.UPD_NOISE if "noise" in ni else 0)
+    co, cg = both_configs(xo, xb, flags=flags, upd_nl_v=v, upd_noise_gamma=0.4, seed=3)
+    xr, dr, dw = 1.0 / density ** 0.5, 0.01 / density ** 0.5, 2.0 ** -10
+    Wo, pulses_o = xo.update_pulsed(co, W, X, dY, w_max, xr, dr, 31, dw, step=6, want_pulses=True)
+    Wg, pulses_g = xb.update_pulsed(cg, dev(W.copy()), dev(X), dev(dY), w_max, xr, dr, 31, dw, step=6, want_pulses=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(pulses_g.cpu().numpy(), pulses_o)
+    if ni:
+        assert np.abs(Wg.cpu().numpy() - Wo).max() <= 2e-7 * np.abs(W).max()
+    else:
+        assert np.array_equal(Wg.cpu().numpy(), Wo)
