@@ -222,19 +222,24 @@ __global__ __launch_bounds__(256) void fcm_kernel(FcmArgs a) {
   }
 }
 
-// Same solve for 64 x 64 and 128 x 128 crossbars with the whole state on chip.  NT threads form a
-// (NT / 16) x 16 grid; thread (ty, tx) owns the SR x SC devices at rows SR ty.., columns SC tx..;
-// residual and search direction live in its registers, sqrt(G) in LDS.  Prefix sums along a row run
-// over the 16 consecutive lanes that share ty (DPP row shifts), along a column over the 4 lane groups
-// of a wave (shuffles) and over the waves (LDS).  A p is computed twice per iteration (for p.Ap, then
-// for the residual update) instead of being stored: registers and LDS together hold three vectors of
-// crossbar size plus sqrt(G), not four.
+// Same solve for 64 x 64 and 128 x 128 crossbars with the whole state on chip.  NT threads form a (NT / 16) x 16 grid;
+// thread (ty, tx) owns the SR x SC devices at rows SR ty.., columns SC tx..; residual and search direction live in its
+// registers (two waves per SIMD: one alone leaves the double-precision pipe waiting for its own results), sqrt(G) in
+// LDS.  With u = s p, S_k the sum of a row's u from column k on and P_k that of a column's u down to row k,
+//   (Lr u)_j = r_source S_0 + r_row sum_{k <= j} S_k,     u.Lr u = r_source S_0^2 + r_row sum_k S_k^2,
+//   (Lc u)_i = r_sense P_last + r_col sum_{k >= i} P_k,   u.Lc u = r_sense P_last^2 + r_col sum_k P_k^2,
+// so p.Ap comes out of the pass that forms p and its sums (9 operations per device: squares of the sums inside the
+// thread's patch, completed with what lies outside it after the scans), and the residual pass rebuilds A p from
+// running sums (9 more); A p is never stored.  Sums along a row run over the 16 consecutive lanes that share ty (DPP row
+// shifts), along a column over the 4 lane groups of a wave (shuffles) and over the waves (LDS, one thread per column).
+// Measured on the 784 x 500 layer of the 784-500-10 perceptron (128 x 128 arrays, 4 slices): 12.4 -> 5.0 ms against
+// 8 x 8 devices per thread, one wave per SIMD and A p evaluated twice (40 operations per device and iteration).
 template <int CTRL>
 __device__ __forceinline__ double dpp_row_f64(double x) {   // lanes whose source lies outside the row of 16 get 0
   union { double d; int i[2]; } v, o;
   v.d = x;
-  o.i[0] = __builtin_amdgcn_update_dpp(0, v.i[0], CTRL, 0xF, 0xF, false);
-  o.i[1] = __builtin_amdgcn_update_dpp(0, v.i[1], CTRL, 0xF, 0xF, false);
+  o.i[0] = __builtin_amdgcn_update_dpp(0, v.i[0], CTRL, 0xF, 0xF, true);
+  o.i[1] = __builtin_amdgcn_update_dpp(0, v.i[1], CTRL, 0xF, 0xF, true);
   return o.d;
 }
 
@@ -246,12 +251,34 @@ __device__ __forceinline__ double row16_inclusive_scan(double x) {
   return x;
 }
 
+// Inclusive sum over the four groups of 16 lanes of a wave (lane by lane), by row swaps: even and odd rows, then halves.
+__device__ __forceinline__ double group16_inclusive_scan(double x, int lane) {
+  union { double d; uint32_t i[2]; } v, even, odd, t, low;
+  v.d = x;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const auto s = __builtin_amdgcn_permlane16_swap(v.i[h], v.i[h], false, false);
+    even.i[h] = s[0];                               // rows 0, 0, 2, 2
+    odd.i[h] = s[1];                                // rows 1, 1, 3, 3
+  }
+  t.d = even.d + odd.d;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) low.i[h] = __builtin_amdgcn_permlane32_swap(t.i[h], t.i[h], false, false)[0];   // rows 0 + 1
+  return ((lane & 16) ? t.d : x) + (lane >= 32 ? low.d : 0.0);
+}
+
+// Sum over the block, returned to every thread, in a fixed order: rows of 16 lanes by DPP, the four rows of a wave by
+// lane reads, the waves through LDS.  `red`: one of two sets of slots used in turn, so that one barrier is enough.
 template <int NW>
 __device__ __forceinline__ double block_sum_n(double v, double* red) {
+  v = row16_inclusive_scan(v);
+  union { double d; int i[2]; } x;
+  x.d = v;
+  double row[4];
 #pragma unroll
-  for (int d = 32; d; d >>= 1) v += __shfl_xor(v, d, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  for (int g = 0; g < 4; ++g)
+    row[g] = __hiloint2double(__builtin_amdgcn_readlane(x.i[1], 16 * g + 15), __builtin_amdgcn_readlane(x.i[0], 16 * g + 15));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = (row[0] + row[1]) + (row[2] + row[3]);
   __syncthreads();
   double t = 0.0;
 #pragma unroll
@@ -260,19 +287,22 @@ __device__ __forceinline__ double block_sum_n(double v, double* red) {
 }
 
 template <int SR, int SC, int NT>
-__global__ __launch_bounds__(NT) void fcm_onchip_kernel(FcmArgs a) {
+__global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
   extern __shared__ double fcm_lds[];
   constexpr int NW = NT / 64;                        // waves; 4 thread rows (ty) per wave
   constexpr int R = (NT / 16) * SR, C = 16 * SC;     // == a.R, a.C
   double* s_lds = fcm_lds;                           // [SR * SC][NT]: element (ar, bc) of thread tid
-  double* xch = fcm_lds + SR * SC * NT;              // [2][NW][16 tx][SC]
-  double* red = xch + 2 * NW * 16 * SC;              // [NW]
+  double* xch = s_lds + SR * SC * NT;                // [2][NW][C]: a wave's column sums, then what the waves before / behind it
+                                                     //   hold; column SC tx + bc at 16 bc + tx (no bank conflicts)
+  double* tot = xch + 2 * NW * C;                    // [C] column totals
+  double* red = tot + C;                             // [2][NW]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int tx = tid & 15, ty = tid >> 4;
   const int i0 = ty * SR, j0 = tx * SC;
   NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
 
-  for (int item = blockIdx.x; item < a.n_items; item += gridDim.x) {
+  {
+    const int item = blockIdx.x;
     const int group = item % a.groups;
     const int t1 = item / a.groups;
     const int pol = t1 & 1;
@@ -281,8 +311,9 @@ __global__ __launch_bounds__(NT) void fcm_onchip_kernel(FcmArgs a) {
     const int k0 = (tile / a.tiles_c) * R, n0 = (tile % a.tiles_c) * C;
     const int rows = min(R, a.K - k0), cols = min(C, a.N - n0);
 
-    __syncthreads();
+#pragma unroll 1
     for (int ar = 0; ar < SR; ++ar)
+#pragma unroll 1
       for (int bc = 0; bc < SC; ++bc) {
         const int i = i0 + ar, j = j0 + bc;
         double g = 0.0;
@@ -305,7 +336,7 @@ __global__ __launch_bounds__(NT) void fcm_onchip_kernel(FcmArgs a) {
 
     const int rhs_end = min(rows, (group + 1) * a.rhs_per_group);
     for (int rhs = group * a.rhs_per_group; rhs < rhs_end; ++rhs) {
-      double r[SR][SC], p[SR][SC], e_acc[SC];
+      double r[SR][SC], p[SR][SC], e = 0.0;          // e: solution summed over column tid
       double part = 0.0;
 #pragma unroll
       for (int ar = 0; ar < SR; ++ar)
@@ -315,116 +346,131 @@ __global__ __launch_bounds__(NT) void fcm_onchip_kernel(FcmArgs a) {
           p[ar][bc] = 0.0;
           part += r[ar][bc] * r[ar][bc];
         }
-#pragma unroll
-      for (int bc = 0; bc < SC; ++bc) e_acc[bc] = 0.0;
       double rr = block_sum_n<NW>(part, red);
       const double stop = a.tol2 * rr;
       double beta = 0.0;
       for (int it = 0; it < a.max_iter && rr > stop; ++it) {
-        // p <- r + beta p, and the sums of u = s p over this thread's part of every row and column
-        double row0[SR], row1[SR], rtot[SR], col0[SC], col1[SC], ctot[SC];
-#pragma unroll
-        for (int x = 0; x < SR; ++x) row0[x] = row1[x] = 0.0;
+        // p <- r + beta p; u = s p: sums, sums of the sums and their squares inside this thread's patch, rows from the
+        // right, columns from above
+        double row0[SR], row1[SR], col0[SC], col1[SC];
+        double pq = 0.0, row_sq = 0.0, col_sq = 0.0;
 #pragma unroll
         for (int x = 0; x < SC; ++x) col0[x] = col1[x] = 0.0;
 #pragma unroll
-        for (int ar = 0; ar < SR; ++ar)
+        for (int ar = 0; ar < SR; ++ar) {
+          double run = 0.0, runs = 0.0;
 #pragma unroll
-          for (int bc = 0; bc < SC; ++bc) {
-            p[ar][bc] = r[ar][bc] + beta * p[ar][bc];
+          for (int bc = SC - 1; bc >= 0; --bc) {
+            p[ar][bc] = __builtin_fma(beta, p[ar][bc], r[ar][bc]);
             const double u = s_lds[(ar * SC + bc) * NT + tid] * p[ar][bc];
-            row0[ar] += u;
-            row1[ar] += (double)(j0 + bc + 1) * u;
+            pq = __builtin_fma(p[ar][bc], p[ar][bc], pq);
+            run += u;
+            runs += run;
+            row_sq = __builtin_fma(run, run, row_sq);
             col0[bc] += u;
-            col1[bc] += (double)(R - (i0 + ar)) * u;
+            col1[bc] += col0[bc];
+            col_sq = __builtin_fma(col0[bc], col0[bc], col_sq);
           }
-        // rows: sums over the threads to the left (same ty = one DPP row of 16 lanes), and the row totals
+          row0[ar] = run;                            // sum of u
+          row1[ar] = runs;                           // sum of (j - j0 + 1) u
+          // a row at a time: left alone, the compiler sets the chains of squares aside and spills what they wait for
+          asm volatile("" : "+v"(pq), "+v"(row_sq), "+v"(col_sq));
+        }
+        // rows: what lies outside the patch, and p.Ap's row part
+        double suffix[SR], left1[SR], energy = a.r_row * row_sq;
 #pragma unroll
         for (int ar = 0; ar < SR; ++ar) {
-          const double inc0 = row16_inclusive_scan(row0[ar]), inc1 = row16_inclusive_scan(row1[ar]);
-          rtot[ar] = dpp_row_f64<0x15F>(inc0);         // row_newbcast:15
-          row0[ar] = inc0 - row0[ar];                  // sum_{j' < j0} u
-          row1[ar] = inc1 - row1[ar];                  // sum_{j' < j0} (j' + 1) u
+          const double full1 = __builtin_fma((double)j0, row0[ar], row1[ar]);   // sum of (j + 1) u
+          const double inc0 = row16_inclusive_scan(row0[ar]), inc1 = row16_inclusive_scan(full1);
+          const double total = dpp_row_f64<0x15F>(inc0);   // row_newbcast:15
+          const double right = total - inc0;         // sum of u to the right of the patch
+          suffix[ar] = a.r_row * (right + row0[ar]); // S at the patch's first column; then the sum over k < j0 of S_k with
+          left1[ar] = __builtin_fma(a.r_row, __builtin_fma((double)j0, total - (inc0 - row0[ar]), inc1 - full1), a.r_source * total);
+          energy = __builtin_fma(a.r_row * right, __builtin_fma((double)SC, right, 2.0 * row1[ar]), energy);   // the driver's share
+          if (tx == 0) energy = __builtin_fma(a.r_source * total, total, energy);
+          if (ar & 1) asm volatile("" : "+v"(suffix[ar]), "+v"(left1[ar]), "+v"(energy));
         }
-        // columns: sums over the lane groups above inside the wave, then over the waves
+        // columns: sums over the lane groups above inside the wave.  Kept per column: the sum and the sum of (R - i) u down
+        // to and with this thread inside the wave, and what multiplies the sum above the wave in the squares of P
+        double cross[SC];
 #pragma unroll
         for (int bc = 0; bc < SC; ++bc) {
-          double inc0 = col0[bc], inc1 = col1[bc];
-          double y0 = __shfl_up(inc0, 16, 64), y1 = __shfl_up(inc1, 16, 64);
-          if (lane >= 16) { inc0 += y0; inc1 += y1; }
-          y0 = __shfl_up(inc0, 32, 64); y1 = __shfl_up(inc1, 32, 64);
-          if (lane >= 32) { inc0 += y0; inc1 += y1; }
-          if (lane >= 48) {                            // last group of the wave holds the wave's sums
-            xch[(0 * NW + wave) * 16 * SC + tx * SC + bc] = inc0;
-            xch[(1 * NW + wave) * 16 * SC + tx * SC + bc] = inc1;
+          double inc0 = col0[bc], inc1 = __builtin_fma((double)(R - SR - i0), col0[bc], col1[bc]);
+          inc0 = group16_inclusive_scan(inc0, lane);
+          inc1 = group16_inclusive_scan(inc1, lane);
+          const double in0 = inc0 - col0[bc];        // above this thread, inside the wave
+          col_sq = __builtin_fma(in0, __builtin_fma((double)SR, in0, 2.0 * col1[bc]), col_sq);
+          cross[bc] = 2.0 * __builtin_fma((double)SR, in0, col1[bc]);
+          col0[bc] = inc0;
+          col1[bc] = inc1;
+          if (bc & 1) asm volatile("" : "+v"(col0[bc]), "+v"(col1[bc]), "+v"(cross[bc]), "+v"(col_sq));
+        }
+        if (lane >= 48) {                            // last group of the wave holds the wave's sums
+#pragma unroll
+          for (int bc = 0; bc < SC; ++bc) {
+            xch[(0 * NW + wave) * C + 16 * bc + tx] = col0[bc];
+            xch[(1 * NW + wave) * C + 16 * bc + tx] = col1[bc];
           }
-          col0[bc] = inc0 - col0[bc];                  // groups above, inside the wave
-          col1[bc] = inc1 - col1[bc];
         }
         __syncthreads();
+        if (tid < 2 * C) {                           // one thread per column and kind of sum: prefix / suffix over the waves
+          const int kind = tid / C, j = tid % C;
+          double* line = xch + kind * NW * C + j;
+          double v[NW], run = 0.0;
+#pragma unroll
+          for (int w = 0; w < NW; ++w) v[w] = line[w * C];
+          if (kind == 0) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) { line[w * C] = run; run += v[w]; }   // above this wave
+            tot[j] = run;
+          } else {
+#pragma unroll
+            for (int w = NW - 1; w >= 0; --w) { run += v[w]; line[w * C] = run; }   // this wave and below
+          }
+        }
+        __syncthreads();
+        double lc[SC], pre[SC];                      // from the row below the patch up; P at the patch's last row (both in Ohm units)
 #pragma unroll
         for (int bc = 0; bc < SC; ++bc) {
-          double all0 = 0.0, all1 = 0.0, before0 = 0.0, before1 = 0.0;
-#pragma unroll
-          for (int w = 0; w < NW; ++w) {
-            const double w0 = xch[(0 * NW + w) * 16 * SC + tx * SC + bc], w1 = xch[(1 * NW + w) * 16 * SC + tx * SC + bc];
-            all0 += w0;
-            all1 += w1;
-            if (w < wave) { before0 += w0; before1 += w1; }
-          }
-          ctot[bc] = all0;
-          col0[bc] += before0;                         // sum_{i' < i0} u
-          col1[bc] = all1 - (before1 + col1[bc]);      // sum_{i' >= i0} (R - i') u
+          const double total = tot[16 * bc + tx], above = xch[(0 * NW + wave) * C + 16 * bc + tx];
+          const double below1 = xch[(1 * NW + wave) * C + 16 * bc + tx] - col1[bc];
+          col_sq = __builtin_fma(above, __builtin_fma((double)SR, above, cross[bc]), col_sq);
+          if (ty == 0) energy = __builtin_fma(a.r_sense * total, total, energy);
+          const double last = above + col0[bc];
+          pre[bc] = a.r_col * last;
+          lc[bc] = __builtin_fma(a.r_col, __builtin_fma((double)(R - SR - i0), last, below1), a.r_sense * total);
+          if (bc & 1) asm volatile("" : "+v"(pre[bc]), "+v"(lc[bc]), "+v"(col_sq), "+v"(energy));
         }
-        // A p = p + s (Lr + Lc)(u): first for p.Ap, walking down the rows (the column sums end one
-        // block further down) ...
-        double pq = 0.0;
-#pragma unroll
-        for (int ar = 0; ar < SR; ++ar) {
-          double run0 = row0[ar], run1 = row1[ar];
-#pragma unroll
-          for (int bc = 0; bc < SC; ++bc) {
-            const double sv = s_lds[(ar * SC + bc) * NT + tid];
-            const double u = sv * p[ar][bc];
-            const double jj = (double)(j0 + bc + 1), ii = (double)(R - (i0 + ar));
-            run0 += u;
-            run1 += jj * u;
-            col0[bc] += u;
-            col1[bc] -= ii * u;
-            const double lr = a.r_source * rtot[ar] + a.r_row * (run1 + jj * (rtot[ar] - run0));
-            const double lc = a.r_col * (ii * col0[bc] + col1[bc]) + a.r_sense * ctot[bc];
-            pq += p[ar][bc] * (p[ar][bc] + sv * (lr + lc));
-          }
-        }
-        pq = block_sum_n<NW>(pq, red);
+        pq += __builtin_fma(a.r_col, col_sq, energy);
+        pq = block_sum_n<NW>(pq, red + NW);
         const double alpha = rr / pq;
-        // ... then again for r <- r - alpha A p, walking back up and undoing the column sums
+        // r <- r - alpha A p, walking up the rows
         part = 0.0;
 #pragma unroll
         for (int ar = SR - 1; ar >= 0; --ar) {
-          double run0 = row0[ar], run1 = row1[ar];
+          double suf = suffix[ar], lr = left1[ar];
 #pragma unroll
           for (int bc = 0; bc < SC; ++bc) {
             const double sv = s_lds[(ar * SC + bc) * NT + tid];
             const double u = sv * p[ar][bc];
-            const double jj = (double)(j0 + bc + 1), ii = (double)(R - (i0 + ar));
-            run0 += u;
-            run1 += jj * u;
-            const double lr = a.r_source * rtot[ar] + a.r_row * (run1 + jj * (rtot[ar] - run0));
-            const double lc = a.r_col * (ii * col0[bc] + col1[bc]) + a.r_sense * ctot[bc];
-            col0[bc] -= u;
-            col1[bc] += ii * u;
-            const double rn = r[ar][bc] - alpha * (p[ar][bc] + sv * (lr + lc));
+            lr += suf;
+            suf = __builtin_fma(-a.r_row, u, suf);
+            lc[bc] += pre[bc];
+            pre[bc] = __builtin_fma(-a.r_col, u, pre[bc]);
+            const double q = __builtin_fma(sv, lr + lc[bc], p[ar][bc]);
+            const double rn = __builtin_fma(-alpha, q, r[ar][bc]);
             r[ar][bc] = rn;
-            part += rn * rn;
+            part = __builtin_fma(rn, rn, part);
           }
+          asm volatile("" : "+v"(part));
         }
-#pragma unroll
-        for (int bc = 0; bc < SC; ++bc) e_acc[bc] += alpha * ctot[bc];   // column sums of x = s y, y = sum alpha p
+        if (tid < C) e = __builtin_fma(alpha, tot[tid], e);   // column sum of x = s y, y = sum alpha p
         const double rr_new = block_sum_n<NW>(part, red);
         beta = rr_new / rr;
         rr = rr_new;
       }
+      if (tid < C) tot[tid] = e;                     // everyone has read the totals: the reduction of rr came after
+      __syncthreads();
       if (rhs >= i0 && rhs < i0 + SR) {
 #pragma unroll
         for (int bc = 0; bc < SC; ++bc) {
@@ -433,13 +479,16 @@ __global__ __launch_bounds__(NT) void fcm_onchip_kernel(FcmArgs a) {
             const double sv = s_lds[((rhs - i0) * SC + bc) * NT + tid];
             const double g = sv * sv;
             a.profile[((size_t)(2 * s + pol) * a.K + k0 + rhs) * a.N + n0 + j] =
-                g > 0.0 ? (float)((g - e_acc[bc]) / g) : 0.0f;
+                g > 0.0 ? (float)((g - tot[16 * bc + tx]) / g) : 0.0f;
           }
         }
       }
+      // the next solve writes the totals only behind the barriers of its first reduction
     }
   }
 }
+
+constexpr int kFcmThreads128 = 512, kFcmThreads64 = 256;   // fcm_onchip_kernel: 4 x 8 and 4 x 4 devices per thread
 
 struct FcmPlan {
   int n_items, groups, rhs_per_group, blocks;
@@ -456,9 +505,9 @@ FcmPlan plan_fcm(const xbar_config* c, const Derived& d, int K, int N) {
   p.groups = cdiv(c->xbar_rows, p.rhs_per_group);
   p.n_items = per_drive_sets * p.groups;
   p.onchip = (c->xbar_rows == c->xbar_cols && (c->xbar_rows == 64 || c->xbar_rows == 128)) ? c->xbar_rows : 0;
-  {  // s, the column exchange area [2][waves][16][SC] and the reduction slots
-    const int nt = 256, sc = p.onchip / 16;
-    p.lds_bytes = ((size_t)p.onchip * p.onchip + 2 * (nt / 64) * 16 * sc + nt / 64) * sizeof(double);
+  {  // s, the column exchange area [2][waves][C], the column totals and two sets of reduction slots
+    const int waves = (p.onchip == 128 ? kFcmThreads128 : kFcmThreads64) / 64;
+    p.lds_bytes = ((size_t)p.onchip * p.onchip + 2 * waves * p.onchip + p.onchip + 2 * waves) * sizeof(double);
   }
   // the workspace is sized for the general kernel in every case (it is the fallback)
   const size_t slot = (size_t)5 * c->xbar_rows * c->xbar_cols * sizeof(double);
@@ -501,13 +550,13 @@ int xbar_fcm_profile(const xbar_config* cfg, const float* W, int K, int N, float
   a.w_max = w_max; a.seed = cfg->seed; a.step = step; a.step_add = current_step_source();
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   if (p.onchip) {
-    const void* fn = p.onchip == 128 ? reinterpret_cast<const void*>(&fcm_onchip_kernel<8, 8, 256>)
-                                     : reinterpret_cast<const void*>(&fcm_onchip_kernel<4, 4, 256>);
+    const void* fn = p.onchip == 128 ? reinterpret_cast<const void*>(&fcm_onchip_kernel<4, 8, kFcmThreads128>)
+                                     : reinterpret_cast<const void*>(&fcm_onchip_kernel<4, 4, kFcmThreads64>);
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes) == hipSuccess) {
       if (p.onchip == 128)
-        hipLaunchKernelGGL((fcm_onchip_kernel<8, 8, 256>), dim3((unsigned)p.blocks), dim3(256), p.lds_bytes, st, a);
+        hipLaunchKernelGGL((fcm_onchip_kernel<4, 8, kFcmThreads128>), dim3((unsigned)p.n_items), dim3(kFcmThreads128), p.lds_bytes, st, a);
       else
-        hipLaunchKernelGGL((fcm_onchip_kernel<4, 4, 256>), dim3((unsigned)p.blocks), dim3(256), p.lds_bytes, st, a);
+        hipLaunchKernelGGL((fcm_onchip_kernel<4, 4, kFcmThreads64>), dim3((unsigned)p.n_items), dim3(kFcmThreads64), p.lds_bytes, st, a);
       return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
     }
     (void)hipGetLastError();                         // no such LDS size on this device: general kernel

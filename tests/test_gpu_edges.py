@@ -74,3 +74,16 @@ def test_pulsed_walk(xo, xb, M, K, N, density, v, ni):
         assert np.abs(Wg.cpu().numpy() - Wo).max() <= 2e-7 * np.abs(W).max()
     else:
         assert np.array_equal(Wg.cpu().numpy(), Wo)
+
+
+# Circuit-level model, state on chip: one device, one row, one column, tiles plus one; wires that matter (many iterations)
+@pytest.mark.parametrize("R,K,N,r_min", [(64, 1, 1, 1e5), (64, 65, 3, 1e3), (128, 1, 129, 1e5), (128, 130, 1, 1e4), (128, 40, 20, 1e3)])
+def test_circuit_model_on_chip(xo, xb, R, K, N, r_min):
+    from oracle import fcm
+    W, _, _ = workloads.layer_tensors_np(workloads.Gemm("t", K, N, 1, True, 1), seed=K + 5 * N)
+    co, cg = both_configs(xo, xb, xbar_rows=R, xbar_cols=R, weight_bits=2, slice_bits=2, flags=xo.VARIATION, var_sigma=0.05, seed=2,
+                          r_min=r_min, r_max=10 * r_min, r_source=2.0, r_sense=3.0)
+    w_max = float(np.abs(W).max())
+    Dg = xb.fcm_profile(cg, dev(W), w_max, step=1)
+    torch.cuda.synchronize()
+    assert np.abs(Dg.cpu().numpy() - fcm.fcm_profile(co, W, w_max, step=1)).max() <= 2e-7
