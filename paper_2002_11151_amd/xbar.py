@@ -179,7 +179,7 @@ def trace_next_vmm(before, after):
 def probe_mfma_rate(mode, iters, scratch):
     """xbar_probe_mfma_rate: enqueue the matrix-instruction probe; returns the flops (multiply + add of every
     product of every instruction) that it issues on its 2048 waves."""
-    _check(lib().xbar_probe_mfma_rate(mode, iters, C.c_void_p(scratch.data_ptr()), scratch.numel(), _stream()))
+    _check(lib().xbar_probe_mfma_rate(mode, iters, scratch.data_ptr(), scratch.numel(), _stream()))
     per_instruction = {0: 16384, 1: 16384, 2: 32768, 3: 32768}.get(mode, 65536)      # 32 x 32 x (16 | 32 | 64)
     per_iteration = 32 if mode >= 5 else 16
     return 2.0 * per_iteration * iters * 2048 * per_instruction
@@ -188,7 +188,7 @@ def probe_mfma_rate(mode, iters, scratch):
 def adc_range_from_histogram(hist, bin_width, quantile):
     """xbar_adc_range_from_histogram: converter range from the counters of adc_histogram (copied to the host)."""
     host = hist.detach().to("cpu", torch.int64).contiguous()
-    fs = lib().xbar_adc_range_from_histogram(C.c_void_p(host.data_ptr()), host.numel(), bin_width, quantile)
+    fs = lib().xbar_adc_range_from_histogram(host.data_ptr(), host.numel(), bin_width, quantile)
     if fs <= 0.0:
         raise XbarError("xbar_adc_range_from_histogram: invalid arguments")
     return float(fs)
@@ -222,31 +222,42 @@ def workspace_bytes(cfg, op, M, K, N):
     return lib().xbar_workspace_bytes(C.byref(cfg), op, M, K, N)
 
 
+# Small layers and peripheral calls take a few microseconds on the GPU, so the binding's own time counts: addresses go
+# to the library as plain integers, the current stream comes from torch's raw accessor (a Stream object takes 2.5 us to
+# make), and a buffer that the caller brings is not sized again here: the library checks it.
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(_current_device())
 
 
 def _dev(t, dtype=torch.float32):
-    assert t.is_cuda and t.dtype == dtype and t.is_contiguous(), "need a contiguous %s CUDA tensor" % dtype
-    return C.c_void_p(t.data_ptr())
+    assert t.is_cuda and t.dtype is dtype and t.is_contiguous(), "need a contiguous %s CUDA tensor" % dtype
+    return t.data_ptr()
 
 
-def _buffer(nbytes, buf, device):
+def _buffer(size, buf, device):
+    """The caller's buffer, or a new one of size() bytes."""
     if buf is None:
-        buf = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=device)
-    assert buf.is_cuda and buf.dtype == torch.uint8 and buf.is_contiguous()
+        buf = torch.empty(max(size(), 16), dtype=torch.uint8, device=device)
+    assert buf.is_cuda and buf.dtype is torch.uint8 and buf.is_contiguous()
     return buf
+
+
+def _sized(cfg, nbytes):
+    """A size query's answer; 0 means an invalid configuration or shape."""
+    if nbytes == 0:
+        _check(validate(cfg) or -2)
+    return nbytes
 
 
 def tile(cfg, W, w_max, step=0, profile=None, planes=None):
     """xbar_tile: planes of W[K][N] (float32 CUDA tensor).  Returns the opaque plane buffer."""
     K, N = W.shape
-    nbytes = planes_bytes(cfg, K, N)
-    if nbytes == 0:
-        _check(validate(cfg) or -2)
-    planes = _buffer(nbytes, planes, W.device)
+    planes = _buffer(lambda: _sized(cfg, planes_bytes(cfg, K, N)), planes, W.device)
     prof = None if profile is None else _dev(profile)
-    _check(lib().xbar_tile(C.byref(cfg), _dev(W), K, N, w_max, step, prof, C.c_void_p(planes.data_ptr()),
+    _check(lib().xbar_tile(C.byref(cfg), _dev(W), K, N, w_max, step, prof, planes.data_ptr(),
                            planes.numel(), _stream()))
     return planes
 
@@ -259,10 +270,7 @@ def _codes_shape(cfg, P, T, M, out_cols):
 
 def _vmm(fn, op, cfg, planes, inp, out_cols, K, N, w_max, in_scale, ws, out, want_codes):
     M = inp.shape[0]
-    nbytes = workspace_bytes(cfg, op, M, K, N)
-    if nbytes == 0:
-        _check(validate(cfg) or -2)
-    ws = _buffer(nbytes, ws, inp.device)
+    ws = _buffer(lambda: _sized(cfg, workspace_bytes(cfg, op, M, K, N)), ws, inp.device)
     if out is None:
         out = torch.empty((M, out_cols), dtype=torch.float32, device=inp.device)
     codes = None
@@ -272,8 +280,8 @@ def _vmm(fn, op, cfg, planes, inp, out_cols, K, N, w_max, in_scale, ws, out, wan
         lin = N if op == OP_BWD else K
         T = (lin + tile_len - 1) // tile_len
         codes = torch.zeros(_codes_shape(cfg, P, T, M, out_cols), dtype=torch.int16, device=inp.device)
-    _check(fn(C.byref(cfg), C.c_void_p(planes.data_ptr()), _dev(inp), _dev(out), M, K, N, w_max, in_scale,
-              C.c_void_p(ws.data_ptr()), ws.numel(), None if codes is None else C.c_void_p(codes.data_ptr()),
+    _check(fn(C.byref(cfg), planes.data_ptr(), _dev(inp), _dev(out), M, K, N, w_max, in_scale,
+              ws.data_ptr(), ws.numel(), None if codes is None else codes.data_ptr(),
               _stream()))
     return (out, codes) if want_codes else out
 
@@ -288,7 +296,7 @@ def fwd_static(cfg, planes, X, N, w_max, x_scale, out):
     the caller passes the output tensor)."""
     M, K = X.shape
     assert out.shape == (M, N) and out.dtype == torch.float32 and out.is_contiguous()
-    _check(lib().xbar_fwd_static(C.byref(cfg), C.c_void_p(planes.data_ptr()), _dev(X), _dev(out), M, K, N, w_max, x_scale,
+    _check(lib().xbar_fwd_static(C.byref(cfg), planes.data_ptr(), _dev(X), _dev(out), M, K, N, w_max, x_scale,
                                  _stream()))
     return out
 
@@ -303,12 +311,9 @@ def update(cfg, W, X, dY, w_max, grad_scale, lr, step=0, ws=None):
     K, N = W.shape
     M = X.shape[0]
     assert X.shape == (M, K) and dY.shape == (M, N)
-    nbytes = workspace_bytes(cfg, OP_UPDATE, M, K, N)
-    if nbytes == 0:
-        _check(validate(cfg) or -2)
-    ws = _buffer(nbytes, ws, W.device)
+    ws = _buffer(lambda: _sized(cfg, workspace_bytes(cfg, OP_UPDATE, M, K, N)), ws, W.device)
     _check(lib().xbar_update(C.byref(cfg), _dev(W), _dev(X), _dev(dY), M, K, N, w_max, grad_scale, lr, step,
-                             C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+                             ws.data_ptr(), ws.numel(), _stream()))
     return W
 
 
@@ -318,38 +323,32 @@ def update_pulsed(cfg, W, X, dY, w_max, x_range, d_range, bl, dw_min, step=0, ws
     K, N = W.shape
     M = X.shape[0]
     assert X.shape == (M, K) and dY.shape == (M, N)
-    nbytes = workspace_bytes(cfg, OP_UPDATE_PULSED, M, K, N)
-    if nbytes == 0:
-        _check(validate(cfg) or -2)
-    ws = _buffer(nbytes, ws, W.device)
+    ws = _buffer(lambda: _sized(cfg, workspace_bytes(cfg, OP_UPDATE_PULSED, M, K, N)), ws, W.device)
     pulses = torch.empty((K, N), dtype=torch.int64, device=W.device) if want_pulses else None
     _check(lib().xbar_update_pulsed(C.byref(cfg), _dev(W), _dev(X), _dev(dY), M, K, N, w_max, x_range, d_range, bl,
-                                    dw_min, step, None if pulses is None else C.c_void_p(pulses.data_ptr()),
-                                    C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+                                    dw_min, step, None if pulses is None else pulses.data_ptr(),
+                                    ws.data_ptr(), ws.numel(), _stream()))
     return (W, pulses) if want_pulses else W
 
 
 def set_step_source(counter):
     """xbar_set_step_source: `counter` is a one-element int64 CUDA tensor whose value is added to every `step`
     argument from now on (None switches it off).  Keep the tensor alive while it is in use."""
-    lib().xbar_set_step_source(None if counter is None else C.c_void_p(counter.data_ptr()))
+    lib().xbar_set_step_source(None if counter is None else counter.data_ptr())
 
 
 def step_advance(counter):
     """xbar_step_advance: counter += 1 on the current stream."""
-    _check(lib().xbar_step_advance(C.c_void_p(counter.data_ptr()), _stream()))
+    _check(lib().xbar_step_advance(counter.data_ptr(), _stream()))
 
 
 def fcm_profile(cfg, W, w_max, step=0, ws=None, profile=None):
     """xbar_fcm_profile: distortion profile [S_w][2][K][N] of the circuit-level model for W[K][N]."""
     K, N = W.shape
-    nbytes = workspace_bytes(cfg, OP_FCM, 1, K, N)
-    if nbytes == 0:
-        _check(validate(cfg) or -2)
-    ws = _buffer(nbytes, ws, W.device)
+    ws = _buffer(lambda: _sized(cfg, workspace_bytes(cfg, OP_FCM, 1, K, N)), ws, W.device)
     if profile is None:
         profile = torch.empty((cfg.weight_bits // cfg.slice_bits, 2, K, N), dtype=torch.float32, device=W.device)
-    _check(lib().xbar_fcm_profile(C.byref(cfg), _dev(W), K, N, w_max, step, _dev(profile), C.c_void_p(ws.data_ptr()),
+    _check(lib().xbar_fcm_profile(C.byref(cfg), _dev(W), K, N, w_max, step, _dev(profile), ws.data_ptr(),
                                   ws.numel(), _stream()))
     return profile
 
@@ -359,10 +358,7 @@ def conv_workspace_bytes(cfg, op, geom, N):
 
 
 def _conv_ws(cfg, op, geom, N, ws, device):
-    nbytes = conv_workspace_bytes(cfg, op, geom, N)
-    if nbytes == 0:
-        _check(validate(cfg) or -2)
-    return _buffer(nbytes, ws, device)
+    return _buffer(lambda: _sized(cfg, conv_workspace_bytes(cfg, op, geom, N)), ws, device)
 
 
 def conv_fwd(cfg, planes, X, geom, N, w_max, x_scale, ws=None, out=None, want_codes=False):
@@ -376,9 +372,9 @@ def conv_fwd(cfg, planes, X, geom, N, w_max, x_scale, ws=None, out=None, want_co
         K, M = geom.k_h * geom.k_w * geom.in_c, geom.batch * geom.out_h * geom.out_w
         T = (K + cfg.xbar_rows - 1) // cfg.xbar_rows
         codes = torch.zeros(_codes_shape(cfg, P, T, M, N), dtype=torch.int16, device=X.device)
-    _check(lib().xbar_conv_fwd(C.byref(cfg), C.c_void_p(planes.data_ptr()), _dev(X), _dev(out), C.byref(geom), N, w_max,
-                               x_scale, C.c_void_p(ws.data_ptr()), ws.numel(),
-                               None if codes is None else C.c_void_p(codes.data_ptr()), _stream()))
+    _check(lib().xbar_conv_fwd(C.byref(cfg), planes.data_ptr(), _dev(X), _dev(out), C.byref(geom), N, w_max,
+                               x_scale, ws.data_ptr(), ws.numel(),
+                               None if codes is None else codes.data_ptr(), _stream()))
     return (out, codes) if want_codes else out
 
 
@@ -387,8 +383,8 @@ def conv_bwd(cfg, planes, dY, geom, N, w_max, g_scale, ws=None, out=None):
     ws = _conv_ws(cfg, OP_BWD, geom, N, ws, dY.device)
     if out is None:
         out = torch.empty((geom.batch, geom.in_h, geom.in_w, geom.in_c), dtype=torch.float32, device=dY.device)
-    _check(lib().xbar_conv_bwd(C.byref(cfg), C.c_void_p(planes.data_ptr()), _dev(dY), _dev(out), C.byref(geom), N, w_max,
-                               g_scale, C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+    _check(lib().xbar_conv_bwd(C.byref(cfg), planes.data_ptr(), _dev(dY), _dev(out), C.byref(geom), N, w_max,
+                               g_scale, ws.data_ptr(), ws.numel(), _stream()))
     return out
 
 
@@ -397,7 +393,7 @@ def conv_update(cfg, W, X, dY, geom, w_max, grad_scale, lr, step=0, ws=None):
     N = W.shape[1]
     ws = _conv_ws(cfg, OP_UPDATE, geom, N, ws, W.device)
     _check(lib().xbar_conv_update(C.byref(cfg), _dev(W), _dev(X), _dev(dY), C.byref(geom), N, w_max, grad_scale, lr, step,
-                                  C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+                                  ws.data_ptr(), ws.numel(), _stream()))
     return W
 
 
@@ -415,12 +411,9 @@ def update_pair(cfg, Gp, Gn, W, X, dY, w_max, grad_scale, lr, step=0, ws=None):
     K, N = W.shape
     M = X.shape[0]
     assert X.shape == (M, K) and dY.shape == (M, N) and Gp.shape == (K, N) and Gn.shape == (K, N)
-    nbytes = workspace_bytes(cfg, OP_UPDATE, M, K, N)
-    if nbytes == 0:
-        _check(validate(cfg) or -2)
-    ws = _buffer(nbytes, ws, W.device)
+    ws = _buffer(lambda: _sized(cfg, workspace_bytes(cfg, OP_UPDATE, M, K, N)), ws, W.device)
     _check(lib().xbar_update_pair(C.byref(cfg), _dev(Gp), _dev(Gn), _dev(W), _dev(X), _dev(dY), M, K, N, w_max, grad_scale,
-                                  lr, step, C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+                                  lr, step, ws.data_ptr(), ws.numel(), _stream()))
     return W
 
 
@@ -429,7 +422,7 @@ def conv_update_pair(cfg, Gp, Gn, W, X, dY, geom, w_max, grad_scale, lr, step=0,
     N = W.shape[1]
     ws = _conv_ws(cfg, OP_UPDATE, geom, N, ws, W.device)
     _check(lib().xbar_conv_update_pair(C.byref(cfg), _dev(Gp), _dev(Gn), _dev(W), _dev(X), _dev(dY), C.byref(geom), N, w_max,
-                                       grad_scale, lr, step, C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+                                       grad_scale, lr, step, ws.data_ptr(), ws.numel(), _stream()))
     return W
 
 
@@ -441,8 +434,8 @@ def conv_update_pulsed(cfg, W, X, dY, geom, w_max, x_range, d_range, bl, dw_min,
     pulses = torch.empty((K, N), dtype=torch.int64, device=W.device) if want_pulses else None
     _check(lib().xbar_conv_update_pulsed(C.byref(cfg), _dev(W), _dev(X), _dev(dY), C.byref(geom), N, w_max, x_range,
                                          d_range, bl, dw_min, step,
-                                         None if pulses is None else C.c_void_p(pulses.data_ptr()),
-                                         C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+                                         None if pulses is None else pulses.data_ptr(),
+                                         ws.data_ptr(), ws.numel(), _stream()))
     return (W, pulses) if want_pulses else W
 
 
@@ -483,7 +476,7 @@ def sgd(p, g, lr):
 
 
 def _bn_ws(rows, channels, ws, device):
-    return _buffer(lib().xbar_bn_workspace_bytes(rows, channels), ws, device)
+    return _buffer(lambda: lib().xbar_bn_workspace_bytes(rows, channels), ws, device)
 
 
 def bn_fwd(x, gamma, beta, eps=1e-5, ws=None):
@@ -495,7 +488,7 @@ def bn_fwd(x, gamma, beta, eps=1e-5, ws=None):
     mean = torch.empty(channels, dtype=torch.float32, device=x.device)
     invstd = torch.empty_like(mean)
     _check(lib().xbar_bn_fwd(_dev(x), _dev(gamma), _dev(beta), _dev(y), _dev(mean), _dev(invstd), rows, channels, eps,
-                             C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+                             ws.data_ptr(), ws.numel(), _stream()))
     return y, mean, invstd
 
 
@@ -508,7 +501,7 @@ def bn_bwd(x, dy, gamma, mean, invstd, ws=None):
     dgamma = torch.empty(channels, dtype=torch.float32, device=x.device)
     dbeta = torch.empty_like(dgamma)
     _check(lib().xbar_bn_bwd(_dev(x), _dev(dy), _dev(gamma), _dev(mean), _dev(invstd), _dev(dx), _dev(dgamma), _dev(dbeta),
-                             rows, channels, C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+                             rows, channels, ws.data_ptr(), ws.numel(), _stream()))
     return dx, dgamma, dbeta
 
 
@@ -567,9 +560,9 @@ def shortcut_bwd(dy, shape, stride):
 
 def absmax(x, ws=None):
     """xbar_absmax: max |x| as a host float (synchronises: meant for calibration, not for the step)."""
-    ws = _buffer(4096, ws, x.device)
+    ws = _buffer(lambda: 4096, ws, x.device)
     res = torch.empty(4, dtype=torch.float32, device=x.device)
-    _check(lib().xbar_absmax(_dev(x), x.numel(), _dev(res), C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+    _check(lib().xbar_absmax(_dev(x), x.numel(), _dev(res), ws.data_ptr(), ws.numel(), _stream()))
     return float(res[0].item())
 
 
@@ -582,8 +575,8 @@ def conv_adc_histogram(cfg, planes, inp, geom, N, in_scale, op, bin_width, hist=
     ws = _conv_ws(cfg, op, geom, N, ws, inp.device)
     if hist is None:
         hist = torch.zeros(ADC_HIST_BINS, dtype=torch.int64, device=inp.device)
-    _check(lib().xbar_conv_adc_histogram(C.byref(cfg), C.c_void_p(planes.data_ptr()), _dev(inp), C.byref(geom), N, in_scale,
-                                         op, bin_width, _dev(hist, torch.int64), C.c_void_p(ws.data_ptr()), ws.numel(),
+    _check(lib().xbar_conv_adc_histogram(C.byref(cfg), planes.data_ptr(), _dev(inp), C.byref(geom), N, in_scale,
+                                         op, bin_width, _dev(hist, torch.int64), ws.data_ptr(), ws.numel(),
                                          _stream()))
     return hist
 
@@ -591,9 +584,9 @@ def conv_adc_histogram(cfg, planes, inp, geom, N, in_scale, op, bin_width, hist=
 def adc_histogram(cfg, planes, inp, K, N, in_scale, op, bin_width, hist=None, ws=None):
     """xbar_adc_histogram: adds the |column current| counts of this input to hist (int64[4096], device)."""
     M = inp.shape[0]
-    ws = _buffer(workspace_bytes(cfg, op, M, K, N), ws, inp.device)
+    ws = _buffer(lambda: workspace_bytes(cfg, op, M, K, N), ws, inp.device)
     if hist is None:
         hist = torch.zeros(ADC_HIST_BINS, dtype=torch.int64, device=inp.device)
-    _check(lib().xbar_adc_histogram(C.byref(cfg), C.c_void_p(planes.data_ptr()), _dev(inp), M, K, N, in_scale, op,
-                                    bin_width, _dev(hist, torch.int64), C.c_void_p(ws.data_ptr()), ws.numel(), _stream()))
+    _check(lib().xbar_adc_histogram(C.byref(cfg), planes.data_ptr(), _dev(inp), M, K, N, in_scale, op,
+                                    bin_width, _dev(hist, torch.int64), ws.data_ptr(), ws.numel(), _stream()))
     return hist
