@@ -11,6 +11,121 @@
 namespace xbar_detail {
 
 // ---------------------------------------------------------------------------------------------
+// input stage (Sec. IV: inputs are scaled and sent to the DAC)
+// ---------------------------------------------------------------------------------------------
+struct QuantArgs {
+  const float* X;
+  uint8_t* A;        // [phase][MP][T][ks][64 lanes][8 bytes]: magnitudes (fp16 path) or their nibbles (6-bit path)
+  int M, L, MP, T, ks, tile, P, input_bits;
+  int offset;        // signed inputs as offset-binary codes in one phase (P == 1)
+  int nibbles;       // 6-bit path: a lane's 8 bytes nibble by nibble (word 0: low nibbles, word 1: high nibbles)
+  float scale;
+  float inv_scale;   // 1 / scale, or NaN (every input then takes the double-precision decision) where that is no normal number
+  long long n_threads;
+  ConvGeom conv;     // used by the CONV instantiation only
+};
+
+// The 8 magnitudes of a lane (bytes of v.x, then of v.y) as the contraction kernel of the 6-bit path reads them:
+// 4-bit field 2 j of word 0 holds the low nibble of byte j of v.x, field 2 j + 1 that of byte j of v.y; word 1
+// the high nibbles in the same places.  A streaming cycle's digits are then one shift and one AND away.
+__device__ __forceinline__ u32x2 nibble_words(u32x2 v) {
+  u32x2 z;
+  z.x = (v.x & 0x0f0f0f0fu) | ((v.y & 0x0f0f0f0fu) << 4);
+  z.y = ((v.x >> 4) & 0x0f0f0f0fu) | (v.y & 0xf0f0f0f0u);
+  return z;
+}
+
+// The 8 inputs l0 .. l0 + 7 of batch row m; inputs from lend on, or of rows beyond the layer, do not exist: zero.
+template <bool CONV>
+__device__ __forceinline__ void load_inputs8(const QuantArgs& a, int m, int l0, int lend, float (&x)[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+  if (CONV) {
+    if (m < a.M) {
+      const ConvRow cr = conv_row(a.conv, m);
+      int c = l0 % a.conv.C, kk = l0 / a.conv.C;
+      int kw = kk % a.conv.KW, kh = kk / a.conv.KW;
+      if ((a.conv.C & 7) == 0 && l0 + 8 <= lend) {   // the 8 inputs are 8 channels of one pixel
+        const int ih = cr.ih0 + kh, iw = cr.iw0 + kw;
+        if (ih >= 0 && ih < a.conv.H && iw >= 0 && iw < a.conv.W) {
+          const float* px = a.X + (cr.off + ((long long)kh * a.conv.W + kw) * a.conv.C + c);
+          const float4 v0 = *reinterpret_cast<const float4*>(px);
+          const float4 v1 = *reinterpret_cast<const float4*>(px + 4);
+          x[0] = v0.x; x[1] = v0.y; x[2] = v0.z; x[3] = v0.w;
+          x[4] = v1.x; x[5] = v1.y; x[6] = v1.z; x[7] = v1.w;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (l0 + e < lend) x[e] = conv_fetch(a.X, a.conv, cr, kh, kw, c);
+          if (++c == a.conv.C) {
+            c = 0;
+            if (++kw == a.conv.KW) { kw = 0; ++kh; }
+          }
+        }
+      }
+    }
+  } else if (m < a.M) {
+    const float* row = a.X + (size_t)m * a.L;
+    if ((a.L & 3) == 0 && l0 + 8 <= lend) {
+      const float4 v0 = *reinterpret_cast<const float4*>(row + l0);
+      const float4 v1 = *reinterpret_cast<const float4*>(row + l0 + 4);
+      x[0] = v0.x; x[1] = v0.y; x[2] = v0.z; x[3] = v0.w;
+      x[4] = v1.x; x[5] = v1.y; x[6] = v1.z; x[7] = v1.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (l0 + e < lend) x[e] = row[l0 + e];
+    }
+  }
+}
+
+// Their magnitudes, packed as the contraction kernels read them: positive part, and with two phases the negative one.
+__device__ __forceinline__ void input_codes8(const QuantArgs& a, int m, int l0, int lend, const float (&x)[8], u32x2& pos_out,
+                                             u32x2& neg_out) {
+  // The code is decided in double precision (as the oracle decides it).  The same expression in single
+  // precision is within 255 x 5 x 2^-24 < 8e-5 of the exact value (the rounded 1 / scale, two products, one
+  // addition with offset coding), so it rounds to the same code unless it lies within 1e-4 of half a step:
+  // those few inputs (2e-4 of them) are decided again in double precision.
+  const float qa_f = (float)((1u << a.input_bits) - 1), lo_f = a.P == 2 ? -1.0f : 0.0f;
+  float k[8];
+  bool sure = true;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float y = x[e] * a.inv_scale;
+    if (a.offset) y = fminf(fmaxf((y + 1.0f) * 0.5f, 0.0f), 1.0f) * qa_f;
+    else y = fminf(fmaxf(y, lo_f), 1.0f) * qa_f;
+    k[e] = ::rintf(y);
+    sure = sure && ::fabsf(y - k[e]) <= 0.4999f;     // a NaN is not sure
+  }
+  if (!sure || !(a.inv_scale > 0.0f)) {
+    const double qa = (double)qa_f, lo = (double)lo_f, scale = (double)a.scale;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int c = a.offset ? (int)::rint(clampd(((double)x[e] / scale + 1.0) * 0.5, 0.0, 1.0) * qa)
+                             : (int)::rint(clampd((double)x[e] / scale, lo, 1.0) * qa);
+      k[e] = (float)c;
+    }
+  }
+  if (a.offset) {
+    // u = rne((x / scale + 1) / 2 * Qa): every input that exists is driven, a value of zero (also a
+    // position outside the image) at mid-range; rows beyond the layer are not driven at all
+    const int n_driven = m < a.M ? min(max(lend - l0, 0), 8) : 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) k[e] = e < n_driven ? k[e] : 0.0f;
+  }
+  // whole numbers to bytes: the conversion saturates at 0, so it takes the positive part by itself
+  u32x2 pos = {0, 0}, neg = {0, 0};
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    pos[e >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(k[e], e & 3, pos[e >> 2]);
+    neg[e >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(-k[e], e & 3, neg[e >> 2]);
+  }
+  pos_out = a.nibbles ? nibble_words(pos) : pos;
+  neg_out = a.nibbles ? nibble_words(neg) : neg;
+}
+
+// ---------------------------------------------------------------------------------------------
 // crossbar-tile contraction + ADC + shift-and-add (Sec. IV-B), forward and backward
 // ---------------------------------------------------------------------------------------------
 struct VmmArgs {
@@ -828,6 +943,8 @@ struct VmmPlan {
   int split_sg;        // slices per group of mode 2
   uint32_t bias_split; // kMagicBits * sum of the shift weights of one such group, mod 2^32
   int offset;          // signed inputs in one phase of offset-binary codes
+  int narrow;          // the sum over all virtual tiles fits 32 bits
+  int small;           // few output patches: one kernel does the whole pass (vmm_small.hip)
   uint32_t bias_per_vt;
   size_t a_bytes, part_bytes, ws_bytes, lds_bytes;
 };
@@ -869,6 +986,23 @@ XBAR_INTERNAL hipError_t launch_vmm_f16_a(const VmmArgs& a, const VmmPlan& p, in
 XBAR_INTERNAL hipError_t launch_vmm_f16_b(const VmmArgs& a, const VmmPlan& p, int terms, bool codes, hipStream_t st);   // tiles of up to 256 rows
 XBAR_INTERNAL hipError_t launch_vmm_f6_a(const VmmArgs& a, const VmmPlan& p, int terms, bool codes, hipStream_t st);    // 1 or 4 terms
 XBAR_INTERNAL hipError_t launch_vmm_f6_b(const VmmArgs& a, const VmmPlan& p, int terms, bool codes, hipStream_t st);    // 5 terms
+
+// A whole pass in one kernel (vmm_small.hip): input stage, contraction, conversion, adding up and scaling.
+struct SmallArgs {
+  VmmArgs v;           // A and the members of the chunked launch are unused; part: [M][Lout] sums or null (then out)
+  QuantArgs q;         // A unused
+  void* ws;            // tickets and sums of the patches that several blocks share
+  int is_conv;
+  int narrow;          // every sum fits 32 bits
+  int blocks_per_patch, slice_groups;
+  uint32_t groups_inv;
+  uint32_t bias_item;  // kMagicBits * sum of the cycles' weights, mod 2^32
+  const long long* wsum;   // offset-binary inputs: weight sum per output, else null
+  double half_range;
+};
+XBAR_INTERNAL bool vmm_small_fits(const VmmPlan& p, const Derived& d);
+XBAR_INTERNAL size_t vmm_small_ws_bytes(const VmmPlan& p, const Derived& d);
+XBAR_INTERNAL hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hipStream_t st);
 
 }  // namespace xbar_detail
 

@@ -1,0 +1,347 @@
+// Forward and backward passes of small layers: input stage, contraction, ADC, shift-and-add over tiles, slices, cycles and
+// phases and scaling in one kernel (Sec. IV, IV-B).  Same arithmetic, code for code, as the input quantiser, the contraction
+// kernels and the adding-up pass that larger layers run one after the other.
+#include "vmm_device.h"
+
+namespace xbar_detail {
+
+namespace {
+
+// A wave owns one item: an output patch of 32 batch rows x 32 outputs, one virtual tile (phase, array, tile) and one slice.
+// A block is NW slices of one patch and virtual tile: its waves quantise the tile's inputs into LDS together while the
+// items' plane fragments are on their way (to registers or to the wave's own LDS: no other wave reads them), contract
+// them with the digits of every cycle, convert, and add their codes up through LDS.  A patch that takes one block is
+// scaled and written by it; else the blocks add to the patch's sums in the workspace (integers: the order does not matter),
+// which a small kernel cleared before, and the last one to arrive scales and writes them.
+// Bound by latency, from memory and, since every line of code runs a handful of times, from the instruction cache: loads
+// are issued as early as they can be, loops stay rolled, nothing is divided.  One wave per item spreads a layer
+// of a few patches over the chip, in one launch (two with the clearing) instead of three.
+__global__ __launch_bounds__(256) void vmm_small_clear_kernel(u32x4* ws, long long n16) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i < n16) ws[i] = u32x4{0, 0, 0, 0};
+}
+
+constexpr int kSmallWaves = 4;
+
+// The inputs of this wave's 16-input steps of the tile: steps wave, wave + 4, .. (up to NSTEP of them).
+template <int NSTEP>
+struct Inputs {
+  float x[NSTEP][8];
+  __device__ __forceinline__ void load(const SmallArgs& s, int mp, int t, int wave, int lane) {
+    const int m = mp * 32 + (lane & 31), lend = min(s.v.Lin, (t + 1) * s.v.tile);
+#pragma unroll
+    for (int i = 0; i < NSTEP; ++i) {
+      const int l0 = t * s.v.tile + 16 * (wave + kSmallWaves * i) + 8 * (lane >> 5);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[i][e] = 0.0f;
+      if (l0 < lend && m < s.v.M) {
+        if (s.is_conv) load_inputs8<true>(s.q, m, l0, lend, x[i]);
+        else load_inputs8<false>(s.q, m, l0, lend, x[i]);
+      }
+    }
+  }
+  // their magnitudes into `raw`: [16-input step][64 lanes]
+  __device__ __forceinline__ void stage(const SmallArgs& s, u32x2* raw, int mp, int t, int p, int steps, int wave, int lane) const {
+    const int m = mp * 32 + (lane & 31), lend = min(s.v.Lin, (t + 1) * s.v.tile);
+#pragma unroll
+    for (int i = 0; i < NSTEP; ++i) {
+      const int j = wave + kSmallWaves * i;
+      if (j >= steps) break;
+      u32x2 pos, neg;
+      input_codes8(s.q, m, t * s.v.tile + 16 * j + 8 * (lane >> 5), lend, x[i], pos, neg);
+      raw[j * 64 + lane] = p ? neg : pos;
+    }
+  }
+};
+
+// The items' codes, summed over their cycles, to the patch's sums, or scaled and written.  Thread (q, lane) ends up with
+// the four consecutive outputs 8 q + 4 (lane / 32) .. of batch row lane % 32.
+__device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, const uint32_t (&y)[16], int wave, int slice0,
+                                              int patch, int mp, int op, int lane) {
+#pragma clang fp contract(off)   // product, product, difference: each rounded on its own
+  const VmmArgs& a = s.v;
+  __syncthreads();                                     // everyone has read what the exchange area held before
+#pragma unroll
+  for (int q = 0; q < 4; ++q) xch[(wave * 4 + q) * 64 + lane] = u32x4{y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]};
+  __syncthreads();
+  long long sum[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int w = 0; w < kSmallWaves; ++w) {
+    if (slice0 + w >= a.S_w) break;
+    const u32x4 v = xch[w * 256 + threadIdx.x];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum[e] += (long long)(int32_t)(v[e] - s.bias_item) << (a.slice_bits * (slice0 + w));
+  }
+  if (s.blocks_per_patch > 1) {
+    // workspace: tickets [patch] (blocks that have arrived), then sums [patch][4][256 threads], 32-bit where they fit
+    uint32_t* tickets = reinterpret_cast<uint32_t*>(s.ws);
+    char* sums = reinterpret_cast<char*>(s.ws) + (((size_t)a.MP * a.OP * 4 + 255) & ~(size_t)255);
+    unsigned long long* wide = reinterpret_cast<unsigned long long*>(sums) + (size_t)patch * 1024 + threadIdx.x;
+    uint32_t* narrow = reinterpret_cast<uint32_t*>(sums) + (size_t)patch * 1024 + threadIdx.x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (s.narrow) atomicAdd(&narrow[256 * e], (uint32_t)sum[e]);
+      else atomicAdd(&wide[256 * e], (unsigned long long)sum[e]);
+    }
+    __shared__ uint32_t arrived;
+    // The sums before the ticket: every wave waits until its atomics, which act on memory that all XCDs share, have been
+    // acknowledged.  A device-scope fence would write back a whole L2 per block (it took ten times the kernel's time).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) arrived = atomicAdd(&tickets[patch], 1u);
+    __syncthreads();
+    if (arrived != (uint32_t)s.blocks_per_patch - 1) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      sum[e] = s.narrow ? (long long)(int32_t)__hip_atomic_load(&narrow[256 * e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                        : (long long)__hip_atomic_load(&wide[256 * e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  const int m = mp * 32 + (lane & 31), o = op * 32 + 8 * wave + 4 * (lane >> 5);
+  if (m >= a.M) return;
+  const size_t at = (size_t)m * a.Lout + o;
+  float r[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    double v = (double)sum[e] * a.scale;
+    if (s.wsum && o + e < a.Lout) v = v - (double)s.wsum[o + e] * s.half_range;
+    r[e] = (float)v;
+  }
+  if (!a.part && (a.Lout & 3) == 0) {
+    if (o < a.Lout) *reinterpret_cast<float4*>(a.out + at) = make_float4(r[0], r[1], r[2], r[3]);
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (o + e < a.Lout) {
+      if (a.part && s.narrow) reinterpret_cast<int32_t*>(a.part)[at + e] = (int32_t)sum[e];
+      else if (a.part) reinterpret_cast<long long*>(a.part)[at + e] = sum[e];
+      else a.out[at + e] = r[e];
+    }
+}
+
+// What a wave of the launch works on: grid = (virtual tile x group of slices, output patch, row patch).
+template <bool PER_ARRAY>
+struct Item {
+  int patch, mp, op, p, pol, t, slice0, slice;
+  __device__ __forceinline__ Item(const SmallArgs& s, int wave) {
+    const VmmArgs& a = s.v;
+    op = (int)blockIdx.y;
+    mp = (int)blockIdx.z;
+    patch = mp * a.OP + op;
+    const int vt = (int)((blockIdx.x * s.groups_inv) >> 16);      // blockIdx.x / slice groups
+    slice0 = ((int)blockIdx.x - vt * s.slice_groups) * kSmallWaves;
+    slice = min(slice0 + wave, a.S_w - 1);             // a wave without a slice works along, its codes are not added
+    const int pa = (vt >= a.T ? 1 : 0) + (vt >= 2 * a.T ? 1 : 0) + (vt >= 3 * a.T ? 1 : 0);   // (phase, array)
+    t = vt - pa * a.T;
+    p = PER_ARRAY ? pa >> 1 : pa;
+    pol = PER_ARRAY ? pa & 1 : 0;
+  }
+};
+
+// fp16 planes: the wave's fragments go from memory into its share of LDS (no registers in between, all in flight at
+// once), and a short loop takes them in order (leading term first; one array alone: the residual first), every fragment
+// with the digits of all cycles at once, reading one pair of fragments ahead.
+template <int TERMS, int S_IN, bool PER_ARRAY, int NSTEP>
+__global__ __launch_bounds__(256) void vmm_small_f16_kernel(SmallArgs s) {
+  extern __shared__ u32x4 small_lds[];
+  const VmmArgs& a = s.v;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Item<PER_ARRAY> it(s, wave);
+  u32x2* raw = reinterpret_cast<u32x2*>(small_lds);    // [16-input step][64 lanes]
+  u32x4* frags = small_lds + a.ks16 * 32 + (size_t)wave * TERMS * a.ks * 64;
+  const int nk = (min(a.tile, a.Lin - it.t * a.tile) + 15) >> 4, nf = TERMS * nk;
+  Inputs<NSTEP> inputs;
+  inputs.load(s, it.mp, it.t, wave, lane);
+  const u32x4* src = a.B + (((size_t)it.t * a.OP + it.op) * a.S_w + it.slice) * TERMS * a.ks * 64 + lane;
+  if constexpr (PER_ARRAY) src += (size_t)it.pol * a.pol_stride;
+#pragma unroll
+  for (int i = 0; i < TERMS; ++i) {
+    const int term = PER_ARRAY ? TERMS - 1 - i : i;
+#pragma unroll 1
+    for (int j = 0; j < nk; ++j) copy16_global_to_lds(src + (term * a.ks + j) * 64, frags + (i * nk + j) * 64);
+  }
+  inputs.stage(s, raw, it.mp, it.t, it.p, nk, wave, lane);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  const uint32_t digit_mask8 = ((1u << a.stream_bits) - 1u) * 0x01010101u;
+  float16v acc[S_IN];
+#pragma unroll
+  for (int b = 0; b < S_IN; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[b][r] = 0.0f;
+  const u32x2* in = raw + lane;
+  auto read = [&](int f, u32x2& x, u32x4& w) __attribute__((always_inline)) {   // behind the end: the last one again
+    const int i = min(f, nf - 1);
+    x = in[(i >= nk ? i - nk : i) * 64];
+    w = frags[i * 64 + lane];
+  };
+  u32x2 x0, x1;
+  u32x4 w0, w1;
+  read(0, x0, w0);
+  read(1, x1, w1);
+#pragma unroll 1
+  for (int f = 0; f < nf; f += 2) {
+    u32x2 nx0, nx1;
+    u32x4 nw0, nw1;
+    read(f + 2, nx0, nw0);
+    read(f + 3, nx1, nw1);
+#pragma unroll
+    for (int b = 0; b < S_IN; ++b)
+      acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, w0),
+                                                      digit_fragment(x0, digit_mask8 << (a.stream_bits * b)), acc[b], 0, 0, 0);
+    if (f + 1 < nf) {
+#pragma unroll
+      for (int b = 0; b < S_IN; ++b)
+        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, w1),
+                                                        digit_fragment(x1, digit_mask8 << (a.stream_bits * b)), acc[b], 0, 0, 0);
+    }
+    x0 = nx0; x1 = nx1; w0 = nw0; w1 = nw1;
+  }
+  float gain, lo, hi;
+  adc_sign_and_range<PER_ARRAY>(a, it.p, it.pol, gain, lo, hi);
+  uint32_t y[1][16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) y[0][r] = 0;
+#pragma unroll
+  for (int b = 0; b < S_IN; ++b) {
+    const float16v one[1] = {acc[b]};
+    // operand lanes hold digit * 2^(shift - 24); undo that power of two in the ADC gain
+    vmm_adc_narrow<1>(one, ldexpf(gain, 24 - a.stream_bits * b), lo, hi, a.stream_bits * b, y);
+  }
+  add_and_write(s, small_lds + a.ks16 * 32, y[0], wave, it.slice0, it.patch, it.mp, it.op, lane);
+}
+
+// 6-bit planes: the item's fragments stay in registers while its cycles pass, two at a time (two chains of sums).
+template <int NT, int NK, bool PER_ARRAY>
+__global__ __launch_bounds__(256) void vmm_small_f6_kernel(SmallArgs s) {
+  extern __shared__ u32x4 small_lds[];
+  const VmmArgs& a = s.v;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Item<PER_ARRAY> it(s, wave);
+  u32x2* raw = reinterpret_cast<u32x2*>(small_lds);
+  const int nk = (min(a.tile, a.Lin - it.t * a.tile) + 63) >> 6;
+  Inputs<NK> inputs;
+  inputs.load(s, it.mp, it.t, wave, lane);
+  const char* src = reinterpret_cast<const char*>(a.B + (PER_ARRAY ? (size_t)it.pol * a.pol_stride : 0)) +
+                    (((size_t)it.t * a.OP + it.op) * a.S_w + it.slice) * NT * a.ks * 1536;
+  u32x4 fx[NT][NK];
+  u32x2 fy[NT][NK];
+#pragma unroll
+  for (int term = 0; term < NT; ++term)
+#pragma unroll
+    for (int J = 0; J < NK; ++J) {
+      const char* f = src + (size_t)(term * a.ks + min(J, nk - 1)) * 1536;   // a step the tile does not reach is not used
+      fx[term][J] = *reinterpret_cast<const u32x4*>(f + lane * 16);
+      fy[term][J] = *reinterpret_cast<const u32x2*>(f + 1024 + lane * 8);
+    }
+  inputs.stage(s, raw, it.mp, it.t, it.p, 4 * NK, wave, lane);   // zero beyond the tile
+  __syncthreads();
+  const uint32_t nibble_mask = ((1u << a.stream_bits) - 1u) * 0x11111111u;
+  float gain, lo, hi;
+  adc_sign_and_range<PER_ARRAY>(a, it.p, it.pol, gain, lo, hi);
+  gain *= 2.0f;                                        // a digit enters as d / 2
+  uint32_t y[1][16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) y[0][r] = 0;
+#pragma unroll 1
+  for (int b = 0; b < a.S_in; b += 2) {
+    float16v acc[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.0f;
+    int4v dg[2][NK];
+#pragma unroll
+    for (int J = 0; J < NK; ++J)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const u32x2 x = raw[(4 * J + w) * 64 + lane];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const int at = a.stream_bits * (b + c);      // the digit's place: low or high nibbles (none behind the last cycle)
+          dg[c][J][w] = (int)(((at & 4 ? x.y : x.x) >> (at & 3)) & (b + c < a.S_in ? nibble_mask : 0u));
+        }
+      }
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int J = 0; J < NK; ++J)
+        if (J < nk) {                                  // the same for the whole block
+          const int term = PER_ARRAY ? NT - 1 - i : i;
+          const u32x4 x = fx[term][J];
+          const u32x2 w = fy[term][J];
+          const int8v pa = {(int)x.x, (int)x.y, (int)x.z, (int)x.w, (int)w.x, (int)w.y, 0, 0};
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const int8v pb = {dg[c][J][0], dg[c][J][1], dg[c][J][2], dg[c][J][3], 0, 0, 0, 0};
+            acc[c] = mfma_f6_term(term, pa, pb, acc[c], a.scale_lo, a.scale_hi);
+          }
+        }
+    // a cycle that is not there leaves zero codes: their constant alone goes into the sums, and out again with the bias
+    const float16v even[1] = {acc[0]}, odd[1] = {acc[1]};
+    vmm_adc_narrow<1>(even, gain, lo, hi, a.stream_bits * b, y);
+    vmm_adc_narrow<1>(odd, gain, lo, hi, a.stream_bits * (b + 1), y);
+  }
+  add_and_write(s, small_lds + NK * 128, y[0], wave, it.slice0, it.patch, it.mp, it.op, lane);
+}
+
+int blocks_per_patch(const VmmPlan& p, const Derived& d) { return p.VT * cdiv(d.S_w, kSmallWaves); }
+// the staged inputs and the area of the final exchange (16 KiB), which the fragments of fp16 planes occupy before
+size_t small_lds_bytes(const VmmPlan& p, const Derived& d) {
+  const int steps = d.fmt == kFmtF6 ? 4 * (p.g.ks == 3 ? 4 : p.g.ks) : p.ks16;
+  const size_t frags = d.fmt == kFmtF16 ? (size_t)kSmallWaves * d.terms * p.g.ks * 1024 : 0;
+  return (size_t)steps * 512 + std::max((size_t)16384, frags);
+}
+
+template <int NSTEP>
+void (*pick_f16(int terms, int s_in, bool per_array))(SmallArgs) {
+  if (per_array) return s_in == 1 ? vmm_small_f16_kernel<2, 1, true, NSTEP> : vmm_small_f16_kernel<2, 2, true, NSTEP>;
+  if (terms == 2) return s_in == 1 ? vmm_small_f16_kernel<2, 1, false, NSTEP> : vmm_small_f16_kernel<2, 2, false, NSTEP>;
+  return s_in == 1 ? vmm_small_f16_kernel<1, 1, false, NSTEP> : vmm_small_f16_kernel<1, 2, false, NSTEP>;
+}
+
+template <int NK>
+void (*pick_f6(int terms, bool per_array))(SmallArgs) {
+  if (per_array) return vmm_small_f6_kernel<5, NK, true>;
+  if (terms == 1) return vmm_small_f6_kernel<1, NK, false>;
+  return terms == 4 ? vmm_small_f6_kernel<4, NK, false> : vmm_small_f6_kernel<5, NK, false>;
+}
+
+}  // namespace
+
+size_t vmm_small_ws_bytes(const VmmPlan& p, const Derived& d) {
+  if (blocks_per_patch(p, d) == 1) return 0;
+  const size_t patches = (size_t)p.MP * p.g.OP;
+  return align256(patches * 4) + patches * (p.narrow ? 4096 : 8192);
+}
+
+// One wave per item beats the chunked launch up to about four rounds of items on the chip's SIMDs with fp16 planes and
+// a dozen with 6-bit planes, whose chunked kernel has more to set up (measured, us per pass, chunked / this: fp16, 4-bit
+// cycles, items in all 896: 22.5 / 11.4, 3584: 26.3 / 18.7, 4096: 24.2 / 23.1, 4928: 23.9 / 27.9, 8192: 30.5 / 38.5; 6-bit,
+// 1-bit cycles, 256: 43.8 / 12.0, 7168: 51.4 / 33.7, 9856: 47.4 / 44.6, 32768: 78 / 109).
+bool vmm_small_fits(const VmmPlan& p, const Derived& d) {
+  const long long items = (long long)p.MP * p.g.OP * p.VT * d.S_w;
+  return items <= (d.fmt == kFmtF16 ? 4096 : 12288) && p.g.OP < 65536 && p.MP < 65536 &&
+         (long long)blocks_per_patch(p, d) * cdiv(d.S_w, kSmallWaves) < 65536;
+}
+
+hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hipStream_t st) {
+  const bool per_array = d.npol == 2;
+  a.blocks_per_patch = blocks_per_patch(p, d);
+  a.slice_groups = cdiv(d.S_w, kSmallWaves);
+  a.groups_inv = (65536 + a.slice_groups - 1) / a.slice_groups;   // exact for quotients of numbers below 65536 / groups
+  if (const long long n16 = (long long)(vmm_small_ws_bytes(p, d) / 16)) {
+    hipLaunchKernelGGL(vmm_small_clear_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, st, reinterpret_cast<u32x4*>(a.ws), n16);
+    if (hipError_t e = hipGetLastError()) return e;
+  }
+  void (*k)(SmallArgs);
+  if (d.fmt == kFmtF16) k = p.ks16 <= 4 ? pick_f16<1>(d.terms, d.S_in, per_array) : p.ks16 <= 8 ? pick_f16<2>(d.terms, d.S_in, per_array) : pick_f16<4>(d.terms, d.S_in, per_array);
+  else k = p.g.ks == 1 ? pick_f6<1>(d.terms, per_array) : p.g.ks == 2 ? pick_f6<2>(d.terms, per_array) : pick_f6<4>(d.terms, per_array);
+  const size_t lds = small_lds_bytes(p, d);
+  if (lds > 48 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k, dim3((unsigned)a.blocks_per_patch, (unsigned)p.g.OP, (unsigned)p.MP), dim3(64 * kSmallWaves), lds, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace xbar_detail

@@ -608,27 +608,6 @@ __global__ __launch_bounds__(256) void weight_sums_kernel(SumArgs a) {
 // ---------------------------------------------------------------------------------------------
 // input quantiser (Sec. IV: inputs are scaled and sent to the DAC)
 // ---------------------------------------------------------------------------------------------
-struct QuantArgs {
-  const float* X;
-  uint8_t* A;        // [phase][MP][T][ks][64 lanes][8 bytes]: magnitudes (fp16 path) or their nibbles (6-bit path)
-  int M, L, MP, T, ks, tile, P, input_bits;
-  int offset;        // signed inputs as offset-binary codes in one phase (P == 1)
-  int nibbles;       // 6-bit path: a lane's 8 bytes nibble by nibble (word 0: low nibbles, word 1: high nibbles)
-  float scale;
-  long long n_threads;
-  ConvGeom conv;     // used by the CONV instantiation only
-};
-
-// The 8 magnitudes of a lane (bytes of v.x, then of v.y) as the contraction kernel of the 6-bit path reads them:
-// 4-bit field 2 j of word 0 holds the low nibble of byte j of v.x, field 2 j + 1 that of byte j of v.y; word 1
-// the high nibbles in the same places.  A streaming cycle's digits are then one shift and one AND away.
-__device__ __forceinline__ u32x2 nibble_words(u32x2 v) {
-  u32x2 z;
-  z.x = (v.x & 0x0f0f0f0fu) | ((v.y & 0x0f0f0f0fu) << 4);
-  z.y = ((v.x >> 4) & 0x0f0f0f0fu) | (v.y & 0xf0f0f0f0u);
-  return z;
-}
-
 template <bool CONV>
 __global__ __launch_bounds__(256) void quantize_input_kernel(QuantArgs a) {
   const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -641,99 +620,19 @@ __global__ __launch_bounds__(256) void quantize_input_kernel(QuantArgs a) {
   const int t = (int)((wv / npair) % a.T);
   const int mp = (int)(wv / ((long long)npair * a.T));
   const int m = mp * 32 + (lane & 31);
-  const double qa = (double)((1u << a.input_bits) - 1);
-  const double lo = a.P == 2 ? -1.0 : 0.0;
-  const double scale = (double)a.scale;
   u32x2* out = reinterpret_cast<u32x2*>(a.A);
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int j = 2 * jp + h;
     if (j >= a.ks) break;
-    const int l0 = t * a.tile + j * 16 + (lane >> 5) * 8;
-    const int lend = min(a.L, (t + 1) * a.tile);
+    const int l0 = t * a.tile + j * 16 + (lane >> 5) * 8, lend = min(a.L, (t + 1) * a.tile);
     float x[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = 0.0f;
-    if (CONV) {
-      if (m < a.M) {
-        const ConvRow cr = conv_row(a.conv, m);
-        int c = l0 % a.conv.C, kk = l0 / a.conv.C;
-        int kw = kk % a.conv.KW, kh = kk / a.conv.KW;
-        if ((a.conv.C & 7) == 0 && l0 + 8 <= lend) {   // the 8 inputs are 8 channels of one pixel
-          const int ih = cr.ih0 + kh, iw = cr.iw0 + kw;
-          if (ih >= 0 && ih < a.conv.H && iw >= 0 && iw < a.conv.W) {
-            const float* px = a.X + (cr.off + ((long long)kh * a.conv.W + kw) * a.conv.C + c);
-            const float4 v0 = *reinterpret_cast<const float4*>(px);
-            const float4 v1 = *reinterpret_cast<const float4*>(px + 4);
-            x[0] = v0.x; x[1] = v0.y; x[2] = v0.z; x[3] = v0.w;
-            x[4] = v1.x; x[5] = v1.y; x[6] = v1.z; x[7] = v1.w;
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            if (l0 + e < lend) x[e] = conv_fetch(a.X, a.conv, cr, kh, kw, c);
-            if (++c == a.conv.C) {
-              c = 0;
-              if (++kw == a.conv.KW) { kw = 0; ++kh; }
-            }
-          }
-        }
-      }
-    } else if (m < a.M) {
-      const float* row = a.X + (size_t)m * a.L;
-      if ((a.L & 3) == 0 && l0 + 8 <= lend) {
-        const float4 v0 = *reinterpret_cast<const float4*>(row + l0);
-        const float4 v1 = *reinterpret_cast<const float4*>(row + l0 + 4);
-        x[0] = v0.x; x[1] = v0.y; x[2] = v0.z; x[3] = v0.w;
-        x[4] = v1.x; x[5] = v1.y; x[6] = v1.z; x[7] = v1.w;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (l0 + e < lend) x[e] = row[l0 + e];
-      }
-    }
-    union { u32x2 v; uint8_t b[8]; } pos, neg;
-    // The code is decided in double precision (as the oracle decides it).  The same expression in single
-    // precision is within 255 x 3 x 2^-24 < 5e-5 of the exact value (one correctly rounded division, one
-    // addition with offset coding, one product), so it rounds to the same code unless it lies within 1e-4 of
-    // half a step: those few inputs (2e-4 of them) are decided again in double precision.
-    int code[8];
-    bool sure = true;
-    const float qa_f = (float)qa, lo_f = (float)lo;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float r = x[e] / a.scale;
-      const float y = (a.offset ? fminf(fmaxf((r + 1.0f) * 0.5f, 0.0f), 1.0f) : fminf(fmaxf(r, lo_f), 1.0f)) * qa_f;
-      const float k = ::rintf(y);
-      sure = sure && ::fabsf(y - k) <= 0.4999f;      // a NaN is not sure
-      code[e] = (int)k;
-    }
-    if (!sure) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        code[e] = a.offset ? (int)::rint(clampd(((double)x[e] / scale + 1.0) * 0.5, 0.0, 1.0) * qa)
-                           : (int)::rint(clampd((double)x[e] / scale, lo, 1.0) * qa);
-    }
-    if (a.offset) {
-      // u = rne((x / scale + 1) / 2 * Qa): every input that exists is driven, a value of zero (also a
-      // position outside the image) at mid-range; rows beyond the layer are not driven at all
-      const int n_driven = m < a.M ? min(max(lend - l0, 0), 8) : 0;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) pos.b[e] = (uint8_t)(e < n_driven ? code[e] : 0);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        pos.b[e] = (uint8_t)(code[e] > 0 ? code[e] : 0);
-        neg.b[e] = (uint8_t)(code[e] < 0 ? -code[e] : 0);
-      }
-    }
-    if (a.nibbles) {
-      pos.v = nibble_words(pos.v);
-      if (a.P == 2) neg.v = nibble_words(neg.v);
-    }
+    u32x2 pos, neg;
+    load_inputs8<CONV>(a, m, l0, lend, x);
+    input_codes8(a, m, l0, lend, x, pos, neg);
     const size_t blk = ((size_t)mp * a.T + t) * a.ks + j;
-    out[blk * 64 + lane] = pos.v;
-    if (a.P == 2) out[((size_t)a.MP * a.T * a.ks + blk) * 64 + lane] = neg.v;
+    out[blk * 64 + lane] = pos;
+    if (a.P == 2) out[((size_t)a.MP * a.T * a.ks + blk) * 64 + lane] = neg;
   }
 }
 
@@ -1467,6 +1366,10 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
   p.a_bytes = align256((size_t)p.P * p.MP * p.g.T * p.ks16 * 512);
   p.part_bytes = align256((size_t)p.nchunk * M * p.Lout * ((p.wide || p.flush_every) ? 8 : 4));
   p.ws_bytes = p.a_bytes + p.part_bytes;
+  p.narrow = (unsigned long long)p.VT <= fit ? 1 : 0;
+  p.small = vmm_small_fits(p, d) ? 1 : 0;
+  // ... its sums, and those of a scattered pass behind them
+  if (p.small) p.ws_bytes = std::max(p.ws_bytes, align256(vmm_small_ws_bytes(p, d)) + align256((size_t)M * p.Lout * (p.narrow ? 4 : 8)));
   return p;
 }
 
@@ -1532,14 +1435,18 @@ int run_vmm(const xbar_config* cfg, const void* planes, const float* in, float* 
   qa.offset = p.offset;
   qa.nibbles = d.fmt == kFmtF6 ? 1 : 0;
   qa.scale = in_scale;
+  qa.inv_scale = in_scale > 1e-30f && in_scale < 1e30f ? 1.0f / in_scale : std::numeric_limits<float>::quiet_NaN();
   qa.n_threads = (long long)p.MP * p.g.T * ((p.ks16 + 1) / 2) * 64;
-  if (conv) {
-    qa.conv = *conv;
+  if (conv) qa.conv = *conv;
+  const bool general = codes != nullptr || hist != nullptr || level_table || (cfg->flags & XBAR_ADC_CURVE) != 0;
+  const bool small = p.small && !general;
+  if (small) {
+  } else if (conv) {
     hipLaunchKernelGGL(quantize_input_kernel<true>, dim3((unsigned)((qa.n_threads + 255) / 256)), dim3(256), 0, st, qa);
   } else {
     hipLaunchKernelGGL(quantize_input_kernel<false>, dim3((unsigned)((qa.n_threads + 255) / 256)), dim3(256), 0, st, qa);
   }
-  if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
+  if (!small && hipGetLastError() != hipSuccess) return XBAR_EHIP;
 
   const PlaneGeom gf = plane_geom(cfg, d, K, N, false);
   VmmArgs a;
@@ -1566,7 +1473,6 @@ int run_vmm(const xbar_config* cfg, const void* planes, const float* in, float* 
     if (j < 4) a.scale_lo |= byte << (8 * j);
     else a.scale_hi |= byte;
   }
-  const bool general = codes != nullptr || hist != nullptr || level_table || a.adc_curve_on;
   const bool split = p.wide == 2 && !general;          // adds its groups up in the partial-sum buffer
   a.split_sg = p.split_sg;
   a.flush_every = hist ? 0 : p.flush_every;            // the statistics pass keeps no sums
@@ -1586,29 +1492,48 @@ int run_vmm(const xbar_config* cfg, const void* planes, const float* in, float* 
   }
   hipEvent_t ev0 = g_trace_before, ev1 = g_trace_after;
   g_trace_before = g_trace_after = nullptr;
+  const long long* wsum = nullptr;
+  double half_range = 0.0;
+  if (p.offset) {      // minus the half-range times the sum of the programmed weights of this output
+    const long long* sums =
+        reinterpret_cast<const long long*>(reinterpret_cast<const char*>(planes) + weight_sums_offset(cfg, d, K, N));
+    wsum = transposed ? sums + N : sums;
+    half_range = (double)in_scale * (double)w_max / (double)((1u << cfg->weight_bits) - 1);
+  }
   if (ev0 && hipEventRecord(ev0, st) != hipSuccess) return XBAR_EHIP;
-  if ((d.fmt == kFmtF6 ? launch_vmm6(a, p, d.terms, general, st) : launch_vmm(a, p, d.terms, general, st)) != hipSuccess)
+  void* small_part = nullptr;
+  if (small) {
+    SmallArgs sa;
+    sa.v = a;
+    sa.q = qa;
+    sa.is_conv = conv ? 1 : 0;
+    sa.narrow = p.narrow;
+    sa.ws = ws;
+    small_part = reinterpret_cast<char*>(ws) + align256(vmm_small_ws_bytes(p, d));
+    sa.v.part = scatter ? small_part : nullptr;
+    sa.wsum = wsum;
+    sa.half_range = half_range;
+    unsigned long long cycles = 0;
+    // the 6-bit kernel takes cycles in pairs; one that is not there leaves the converter's constant
+    for (int b = 0; b < (d.fmt == kFmtF6 ? (d.S_in + 1) / 2 * 2 : d.S_in); ++b) cycles += 1ull << (cfg->stream_bits * b);
+    sa.bias_item = (uint32_t)((unsigned long long)kMagicBits * cycles);
+    if (launch_vmm_small(sa, p, d, st) != hipSuccess) return XBAR_EHIP;
+  } else if ((d.fmt == kFmtF6 ? launch_vmm6(a, p, d.terms, general, st) : launch_vmm(a, p, d.terms, general, st)) != hipSuccess)
     return XBAR_EHIP;
   if (ev1 && hipEventRecord(ev1, st) != hipSuccess) return XBAR_EHIP;
   if (hist) return XBAR_OK;
 
-  if (!a.direct) {
+  if (small ? scatter != nullptr : !a.direct) {
     FinishArgs f;
-    f.part = a.part;
+    f.part = small ? small_part : a.part;
     f.out = out;
     f.n = (long long)M * p.Lout;
-    f.nchunk = p.nchunk;
-    f.wide = p.wide != 0 || p.flush_every != 0;
+    f.nchunk = small ? 1 : p.nchunk;
+    f.wide = small ? !p.narrow : p.wide != 0 || p.flush_every != 0;
     f.Lout = p.Lout;
     f.scale = a.scale;
-    f.wsum = nullptr;
-    f.half_range = 0.0;
-    if (p.offset) {    // minus the half-range times the sum of the programmed weights of this output
-      const long long* sums = reinterpret_cast<const long long*>(reinterpret_cast<const char*>(planes) +
-                                                                  weight_sums_offset(cfg, d, K, N));
-      f.wsum = transposed ? sums + N : sums;
-      f.half_range = (double)in_scale * (double)w_max / (double)((1u << cfg->weight_bits) - 1);
-    }
+    f.wsum = wsum;
+    f.half_range = half_range;
     if (scatter) {     // backward convolution: out is the NHWC image of input errors
       FinishCol2imArgs fc;
       fc.f = f;

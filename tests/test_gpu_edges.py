@@ -87,3 +87,22 @@ def test_circuit_model_on_chip(xo, xb, R, K, N, r_min):
     Dg = xb.fcm_profile(cg, dev(W), w_max, step=1)
     torch.cuda.synchronize()
     assert np.abs(Dg.cpu().numpy() - fcm.fcm_profile(co, W, w_max, step=1)).max() <= 2e-7
+
+
+# One kernel for a whole pass (layers of few patches): its outputs are those of the chunked kernels, which the code tap
+# runs, bit for bit -- one row, patches plus and minus one, slices that do not fill a block's waves, arrays of 16 .. 256
+# rows, one and several blocks per patch, sums within and beyond 32 bits, every way of coding inputs and reading arrays
+@pytest.mark.parametrize("R,sb,wb,slb,adc", [(64, 4, 8, 2, 8), (128, 1, 16, 2, 8), (48, 1, 5, 1, 12), (256, 2, 16, 4, 16),
+                                             (192, 1, 6, 2, 8), (16, 8, 4, 4, 9), (256, 4, 10, 2, 15)])
+@pytest.mark.parametrize("flags", ["", "aam", "aam+signed", "var+offset+signed", "pa+signed"])
+@pytest.mark.parametrize("M,K,N", [(1, 1, 1), (33, 300, 31), (32, 65, 130)])
+def test_pass_of_a_small_layer(xb, R, sb, wb, slb, adc, flags, M, K, N):
+    f = {"": 0, "aam": xb.NI_WIRE_AAM, "var": xb.NI_VARIATION, "signed": xb.INPUT_SIGNED, "offset": xb.INPUT_OFFSET,
+         "pa": xb.ADC_PER_ARRAY}
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, "signed" in flags, 1), seed=M + K)
+    fs = 1.037 * workloads.adc_full_scale(R, sb, slb)
+    cfg = xb.make_config(xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=slb, stream_bits=sb, adc_bits=min(adc, 15), var_sigma=0.1,
+                         flags=sum(f[x] for x in flags.split("+")), adc_fs_fwd=fs, adc_fs_bwd=fs, seed=4)
+    w_max, xs, gs = float(np.abs(W).max()), float(np.abs(X).max()), float(np.abs(dY).max())
+    assert np.array_equal(gpu_fwd(xb, cfg, W, X, w_max, xs, codes=False), gpu_fwd(xb, cfg, W, X, w_max, xs)[0])
+    assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
