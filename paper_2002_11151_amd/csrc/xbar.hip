@@ -115,24 +115,32 @@ struct BothCopies {
   int nb;                    // blocks along n
 };
 
-// fp16 planes, both copies at once: a block owns 32 x 32 weights and two slices at a time (blockIdx.y counts slice
-// pairs), computes every device of them once -- in double precision, which is what bounds this kernel -- turns the
-// values through LDS as (leading term, residual) pairs of halves and writes the operand chunks of both directions,
-// 16 bytes per thread and copy.  One kernel computing each copy on its own, 8 devices of a column per thread in one
-// serial chain, took 14 + 11 us on a 256 x 256 layer of 4 slices.
-template <int NPOL>
-__global__ __launch_bounds__(256) void tile_f16_kernel(BothCopies b) {
+// fp16 planes, both copies at once: a block owns 32 x 32 weights and two slices (blockIdx.y counts slice pairs), computes
+// every device of them once -- in double precision -- turns the values through LDS as (leading term, residual) pairs
+// of halves and writes the operand chunks of both directions, 16 bytes each.  A layer of few blocks is bound by latency and
+// by the instruction cache (a line of code that runs once costs some 115 cycles to fetch), so it takes 1024 threads
+// with one weight and one chunk each; one with many blocks takes 256.  256 x 256 weights, 4 slices: one kernel per copy
+// with 8 devices of a column per thread took 14 + 11 us, this with 4 weights per thread unrolled 9.4 - 10, this 7.4.
+template <int NPOL, int NTH>
+__global__ __launch_bounds__(NTH) void tile_f16_kernel(BothCopies b) {
   __shared__ uint32_t uv[NPOL][2][32][33];           // [array][slice of the pair][k][n]: leading half | residual << 16
   const TileArgs& a = b.a;
-  const int k0 = (int)(blockIdx.x / b.nb) * 32, n0 = (int)(blockIdx.x % b.nb) * 32;
+  const int kb = (int)(blockIdx.x / b.nb), k0 = kb * 32, n0 = ((int)blockIdx.x - kb * b.nb) * 32;
   const int s0 = 2 * (int)blockIdx.y, ns = min(2, a.S_w - s0);
-  const int nl = threadIdx.x & 31, kl = threadIdx.x >> 5;
+  const int nl = threadIdx.x & 31;
   NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
   const uint32_t dmask = (1u << a.slice_bits) - 1;
-  const int n = n0 + nl, j = n % a.C;
-#pragma unroll 2
-  for (int r = 0; r < 4; ++r) {
-    const int k = k0 + kl + 8 * r;
+  const int n = n0 + nl;
+  // place in the array: a patch of 32 reaches into the next array or two where arrays are no whole patches
+  int j = n0 % a.C + nl;
+  if (j >= a.C) j -= a.C;
+  if (j >= a.C) j -= a.C;
+#pragma unroll 1
+  for (int kl = threadIdx.x >> 5; kl < 32; kl += NTH / 32) {
+    const int k = k0 + kl;
+    int i = k0 % a.R + kl;
+    if (i >= a.R) i -= a.R;
+    if (i >= a.R) i -= a.R;
     const bool real = k < a.K && n < a.N;
     const int q = real ? quantized_weight(a.W[(size_t)k * a.N + n], (double)a.w_max, a.qw, a.q_per_w) : 0;
     const int sign = (q > 0) - (q < 0);
@@ -143,39 +151,34 @@ __global__ __launch_bounds__(256) void tile_f16_kernel(BothCopies b) {
 #pragma unroll
       for (int pol = 0; pol < NPOL; ++pol) u[pol] = 0.0;
       if (real && sl < ns)
-        plane_values<NPOL>(a, rng, sign, (int)((mag >> (a.slice_bits * (s0 + sl))) & dmask), s0 + sl, k, n, k % a.R, j, u);
+        plane_values<NPOL>(a, rng, sign, (int)((mag >> (a.slice_bits * (s0 + sl))) & dmask), s0 + sl, k, n, i, j, u);
 #pragma unroll
       for (int pol = 0; pol < NPOL; ++pol) {
         // leading term on the grid 2^-hi_frac (coarser where fp16 cannot hold it), residual in fp16
         const _Float16 h = a.terms == 2 ? (_Float16)(::rint(u[pol] * a.hi_scale) * a.hi_inv_scale) : (_Float16)u[pol];
         const _Float16 l = (_Float16)(u[pol] - (double)h);
-        uv[pol][sl][kl + 8 * r][nl] = (uint32_t)__builtin_bit_cast(uint16_t, h) | ((uint32_t)__builtin_bit_cast(uint16_t, l) << 16);
+        uv[pol][sl][kl][nl] = (uint32_t)__builtin_bit_cast(uint16_t, h) | ((uint32_t)__builtin_bit_cast(uint16_t, l) << 16);
       }
     }
   }
   __syncthreads();
-  // thread = (term, 16-row step, lane) of either copy; entries c0 .. c0 + 7 of one output
-  const int lane = threadIdx.x & 63, js = (threadIdx.x >> 6) & 1, term = threadIdx.x >> 7;
-  if (term >= a.terms) return;
-  const int ol = lane & 31, c0 = 16 * js + 8 * (lane >> 5);
-#pragma unroll
-  for (int dir = 0; dir < 2; ++dir) {
+  // chunk = (slice, direction, term, 16-row step, lane): entries c0 .. c0 + 7 of one output
+#pragma unroll 1
+  for (int chunk = threadIdx.x; chunk < 1024 * NPOL; chunk += NTH) {
+    const int lane = chunk & 63, js = (chunk >> 6) & 1, term = (chunk >> 7) & 1, dir = (chunk >> 8) & 1, sl = (chunk >> 9) & 1;
+    const int pol = NPOL == 2 ? chunk >> 10 : 0;
+    const int ol = lane & 31, c0 = 16 * js + 8 * (lane >> 5);
     const int c = (dir == 0 ? k0 : n0) + 16 * js, op = (dir == 0 ? n0 : k0) >> 5;
-    if (c >= (dir == 0 ? a.K : a.N)) continue;       // the contraction never reads this k-step
+    if (term >= a.terms || sl >= ns || c >= (dir == 0 ? a.K : a.N)) continue;   // the contraction never reads that k-step
     const int t = c / b.tile[dir], step = (c - t * b.tile[dir]) >> 4;
+    const uint32_t* from = &uv[pol][sl][0][0] + (dir == 0 ? c0 * 33 + ol : ol * 33 + c0);
+    const int stride = dir == 0 ? 33 : 1;
+    const uint32_t pick = term == 0 ? 0x05040100u : 0x07060302u;                // the low or the high halves of two words
+    u32x4 v;
 #pragma unroll
-    for (int pol = 0; pol < NPOL; ++pol)
-      for (int sl = 0; sl < ns; ++sl) {
-        u32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t w0 = dir == 0 ? uv[pol][sl][c0 + 2 * e][ol] : uv[pol][sl][ol][c0 + 2 * e];
-          const uint32_t w1 = dir == 0 ? uv[pol][sl][c0 + 2 * e + 1][ol] : uv[pol][sl][ol][c0 + 2 * e + 1];
-          v[e] = term == 0 ? (w0 & 0xFFFFu) | (w1 << 16) : (w0 >> 16) | (w1 & 0xFFFF0000u);
-        }
-        const size_t chunk = (((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms + term) * b.ks[dir] + step) * 64 + lane;
-        reinterpret_cast<u32x4*>(b.base[dir] + (size_t)pol * b.pol_bytes[dir])[chunk] = v;
-      }
+    for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_perm(from[(2 * e + 1) * stride], from[2 * e * stride], pick);
+    const size_t at = (((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms + term) * b.ks[dir] + step) * 64 + lane;
+    reinterpret_cast<u32x4*>(b.base[dir] + (size_t)pol * b.pol_bytes[dir])[at] = v;
   }
 }
 
@@ -433,41 +436,34 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
         }
     }
     __syncthreads();
-    // fragment groups: (array, slice, direction, half of 32 outputs), one wave each
+    // one wave per (fragment group, term), group = (array, slice, direction, half of 32 outputs): a short loop over the
+    // lane's 32 codes of one term
     const int ol = lane & 31, half = lane >> 5;
-    for (int grp = wave; grp < 8; grp += NW) {
+#pragma unroll 1
+    for (int item = wave; item < 8 * a.terms; item += NW) {
+      const int term = item >> 3, grp = item & 7;
       const int hh = grp & 1, dir = (grp >> 1) & 1, sl = NPOL == 2 ? 0 : grp >> 2, pol = NPOL == 2 ? grp >> 2 : 0;
       const int op = ((dir ? k0 : n0) >> 5) + hh, c = dir ? n0 : k0;
       if (sl >= ns || op >= b.OP[dir]) continue;
       const int t = c / b.tile[dir], J = (c - t * b.tile[dir]) >> 6;
-      const uint32_t* from = &words[pol][sl][0][0] + (dir ? (32 * hh + ol) * 65 : 32 * hh + ol);
-      const int stride = dir ? 1 : 65;
-      uint32_t rec[kMaxTermsF6][6];
+      const uint32_t* from = &words[pol][sl][0][0] + (dir ? (32 * hh + ol) * 65 + half * 8 : 32 * hh + ol + half * 8 * 65);
+      const int stride = dir ? 1 : 65, from_bit = 6 * term;
+      uint32_t rec[6];
 #pragma unroll
-      for (int x = 0; x < kMaxTermsF6 * 6; ++x) rec[x / 6][x % 6] = 0u;
+      for (int x = 0; x < 6; ++x) rec[x] = 0u;
 #pragma unroll
       for (int w = 0; w < 4; ++w)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const uint32_t word = from[(w * 16 + half * 8 + e) * stride];
+          const uint32_t code = (from[(w * 16 + e) * stride] >> from_bit) & 63u;
           const int bit = 6 * (8 * w + 2 * (e & 3) + (e >> 2)), x = bit >> 5, sh = bit & 31;   // place among the lane's 32 codes
-#pragma unroll
-          for (int term = 0; term < kMaxTermsF6; ++term) {
-            if (term >= a.terms) break;
-            const uint32_t code = (word >> (6 * term)) & 63u;
-            rec[term][x] |= code << sh;
-            if (sh > 26) rec[term][x + 1] |= code >> (32 - sh);
-          }
+          rec[x] |= code << sh;
+          if (sh > 26) rec[x + 1] |= code >> (32 - sh);
         }
-      uint8_t* frag = b.base[dir] + (size_t)pol * b.pol_bytes[dir] +
-                      ((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms * b.ks[dir] + J) * 1536;
-#pragma unroll
-      for (int term = 0; term < kMaxTermsF6; ++term) {
-        if (term >= a.terms) break;
-        uint8_t* at = frag + (size_t)term * b.ks[dir] * 1536;
-        *reinterpret_cast<u32x4*>(at + lane * 16) = u32x4{rec[term][0], rec[term][1], rec[term][2], rec[term][3]};
-        *reinterpret_cast<u32x2*>(at + 1024 + lane * 8) = u32x2{rec[term][4], rec[term][5]};
-      }
+      uint8_t* at = b.base[dir] + (size_t)pol * b.pol_bytes[dir] +
+                    (((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms + term) * b.ks[dir] + J) * 1536;
+      *reinterpret_cast<u32x4*>(at + lane * 16) = u32x4{rec[0], rec[1], rec[2], rec[3]};
+      *reinterpret_cast<u32x2*>(at + 1024 + lane * 8) = u32x2{rec[4], rec[5]};
     }
   }
 }
@@ -1838,8 +1834,11 @@ int xbar_tile(const xbar_config* cfg, const float* W, int K, int N, float w_max,
     b.a = a;
     b.nb = cdiv(N, 32);
     const dim3 grid((unsigned)(cdiv(K, 32) * b.nb), (unsigned)pairs);
-    if (d.npol == 2) hipLaunchKernelGGL(tile_f16_kernel<2>, grid, dim3(256), 0, st, b);
-    else hipLaunchKernelGGL(tile_f16_kernel<1>, grid, dim3(256), 0, st, b);
+    const bool few = grid.x * grid.y < 1024;
+    if (d.npol == 2 && few) hipLaunchKernelGGL((tile_f16_kernel<2, 1024>), grid, dim3(1024), 0, st, b);
+    else if (d.npol == 2) hipLaunchKernelGGL((tile_f16_kernel<2, 256>), grid, dim3(256), 0, st, b);
+    else if (few) hipLaunchKernelGGL((tile_f16_kernel<1, 1024>), grid, dim3(1024), 0, st, b);
+    else hipLaunchKernelGGL((tile_f16_kernel<1, 256>), grid, dim3(256), 0, st, b);
     return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
   }
   uint32_t* table = nullptr;
