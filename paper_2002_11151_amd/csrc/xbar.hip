@@ -96,16 +96,6 @@ __device__ __forceinline__ void plane_values(const TileArgs& a, NormalStream& rn
   }
 }
 
-// Weight as its signed integer: rne(clamp(W / w_max) * Qw).  The product with the rounded factor Qw / w_max is within
-// 2 ulp (2^-36 of a step) of that quotient times Qw, so it rounds to the same integer unless it lies within 1e-9 of half
-// a step; those few are decided by the division itself, as the oracle decides all of them.
-__device__ __forceinline__ int quantized_weight(float w, double w_max, double qw, double q_per_w) {
-  double y = clampd((double)w * q_per_w, -qw, qw);
-  double q = ::rint(y);
-  if (!(::fabs(y - q) < 0.5 - 1e-9)) q = ::rint(clampd((double)w / w_max, -1.0, 1.0) * qw);
-  return (int)q;
-}
-
 // Both copies of one layer's planes.
 struct BothCopies {
   TileArgs a;                // K, N, physics; the per-copy members are unused

@@ -284,6 +284,16 @@ __device__ __forceinline__ uint64_t effective_step(uint64_t step, const unsigned
 
 __device__ __forceinline__ double clampd(double x, double lo, double hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
+// Weight as its signed integer: rne(clamp(W / w_max) * Qw).  The product with the rounded factor Qw / w_max is within
+// 2 ulp (2^-36 of a step) of that quotient times Qw, so it rounds to the same integer unless it lies within 1e-9 of half
+// a step; those few are decided by the division itself, as the oracle decides all of them.
+__device__ __forceinline__ int quantized_weight(float w, double w_max, double qw, double q_per_w) {
+  double y = clampd((double)w * q_per_w, -qw, qw);
+  double q = ::rint(y);
+  if (!(::fabs(y - q) < 0.5 - 1e-9)) q = ::rint(clampd((double)w / w_max, -1.0, 1.0) * qw);
+  return (int)q;
+}
+
 __device__ __forceinline__ double wave_inclusive_scan(double x, int lane) {
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -344,7 +354,7 @@ static inline int check_shape(int M, int K, int N) {
 // entry points of one translation unit that another one calls (not exported)
 // ---------------------------------------------------------------------------------------------
 #define XBAR_INTERNAL __attribute__((visibility("hidden")))
-// wire.hip: all-paths wire model of W into the scratch wire_u[S_w][2][K][N] (+ quantised weights behind it)
+// wire.hip: all-paths wire model of W into the scratch wire_u[S_w][2][K][N]
 XBAR_INTERNAL int launch_wire_model(const xbar_config* cfg, const float* W, int K, int N, float w_max, uint64_t step,
                                     double* wire_u, hipStream_t st);
 // fcm.hip, pulse.hip: workspace sizes of xbar_fcm_profile and xbar_update_pulsed

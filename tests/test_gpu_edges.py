@@ -106,3 +106,20 @@ def test_pass_of_a_small_layer(xb, R, sb, wb, slb, adc, flags, M, K, N):
     w_max, xs, gs = float(np.abs(W).max()), float(np.abs(X).max()), float(np.abs(dY).max())
     assert np.array_equal(gpu_fwd(xb, cfg, W, X, w_max, xs, codes=False), gpu_fwd(xb, cfg, W, X, w_max, xs)[0])
     assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
+
+
+# All-paths wire model: fewer rows than row segments, both strip widths (up to 128 rows and beyond), one to four columns
+# per lane of the row scan, partial tiles down to one row or column
+@pytest.mark.parametrize("R,C,slb", [(16, 16, 2), (48, 64, 4), (128, 128, 2), (144, 80, 1), (256, 256, 2)])
+@pytest.mark.parametrize("ni", ["", "var", "var+pa"])
+@pytest.mark.parametrize("K,N", [(1, 1), (129, 17), (65, 257), (300, 91)])
+def test_all_paths_wire_model(xo, xb, R, C, slb, ni, K, N):
+    M = 4
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=K + 7 * N)
+    flags = xo.WIRE_AAM2 | xo.INPUT_SIGNED | (xo.VARIATION if "var" in ni else 0) | (xo.ADC_PER_ARRAY if "pa" in ni else 0)
+    fs = 1.037 * workloads.adc_full_scale(max(R, C), 1, slb)
+    co, cg = both_configs(xo, xb, xbar_rows=R, xbar_cols=C, weight_bits=4, slice_bits=slb, stream_bits=1, flags=flags,
+                          var_sigma=0.1, seed=8, adc_fs_fwd=fs, adc_fs_bwd=fs, r_source=20.0, r_sense=30.0)
+    w_max, xs, gs = float(np.abs(W).max()), float(np.abs(X).max()), float(np.abs(dY).max())
+    assert close_codes(gpu_fwd(xb, cg, W, X, w_max, xs, step=2)[1], xo.fwd(co, W, X, w_max, xs, step=2, want_codes=True)[1])
+    assert close_codes(gpu_bwd(xb, cg, W, dY, w_max, gs, step=2)[1], xo.bwd(co, W, dY, w_max, gs, step=2, want_codes=True)[1])
