@@ -991,7 +991,8 @@ XBAR_INTERNAL hipError_t launch_vmm_f6_b(const VmmArgs& a, const VmmPlan& p, int
 struct SmallArgs {
   VmmArgs v;           // A and the members of the chunked launch are unused; part: [M][Lout] sums or null (then out)
   QuantArgs q;         // A unused
-  void* ws;            // tickets and sums of the patches that several blocks share
+  void* ws;            // heads and sums of the patches that several blocks share
+  unsigned long long tag;   // of this launch
   int is_conv;
   int narrow;          // every sum fits 32 bits
   int blocks_per_patch, slice_groups;

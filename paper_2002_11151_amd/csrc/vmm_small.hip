@@ -3,6 +3,9 @@
 // kernels and the adding-up pass that larger layers run one after the other.
 #include "vmm_device.h"
 
+#include <atomic>
+#include <chrono>
+
 namespace xbar_detail {
 
 namespace {
@@ -12,16 +15,56 @@ namespace {
 // items' plane fragments are on their way (to registers or to the wave's own LDS: no other wave reads them), contract
 // them with the digits of every cycle, convert, and add their codes up through LDS.  A patch that takes one block is
 // scaled and written by it; else the blocks add to the patch's sums in the workspace (integers: the order does not matter),
-// which a small kernel cleared before, and the last one to arrive scales and writes them.
+// which the first block to come has cleared, and the last one to arrive scales and writes them.
 // Bound by latency, from memory and, since every line of code runs a handful of times, from the instruction cache: loads
 // are issued as early as they can be, loops stay rolled, nothing is divided.  One wave per item spreads a layer
-// of a few patches over the chip, in one launch (two with the clearing) instead of three.
-__global__ __launch_bounds__(256) void vmm_small_clear_kernel(u32x4* ws, long long n16) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n16) ws[i] = u32x4{0, 0, 0, 0};
-}
-
+// of a few patches over the chip, in one launch instead of three.
 constexpr int kSmallWaves = 4;
+
+// The sums of a patch that several blocks share, in a workspace whose content is unknown when the launch begins: one
+// 64-byte head per patch, then 1024 sums per patch, [4][256 threads], 32-bit where they fit.  Every block begins with an
+// exchange of the head's `claim` for the launch's tag, a 64-bit number that no other launch of the process carries and
+// that no data hold but by a chance of 2^-64: the one block that finds another number there clears the sums and then sets
+// `ready`; the others look for it before they add, a few microseconds later, and wait if need be -- for a block that is
+// running and waits for nobody.  The last to arrive takes the tag back out: a launch that is replayed from a graph
+// carries the same tag again.  Everything here is a relaxed device-scope operation on memory that all XCDs share, ordered
+// by waiting until it has been acknowledged: a device-scope fence would write back a whole L2 per block (it took ten times the
+// kernel's time).  A kernel of its own to clear cost each pass 1.9 us and a second launch.
+struct PatchHead {
+  unsigned long long claim, ready;
+  uint32_t tickets, pad[11];
+};
+__device__ __forceinline__ PatchHead* patch_head(const SmallArgs& s, int patch) { return reinterpret_cast<PatchHead*>(s.ws) + patch; }
+__device__ __forceinline__ char* patch_sums(const SmallArgs& s, int patch) {
+  return reinterpret_cast<char*>(s.ws) + (size_t)s.v.MP * s.v.OP * sizeof(PatchHead) + (size_t)patch * (s.narrow ? 4096 : 8192);
+}
+template <class T>
+__device__ __forceinline__ void put(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <class T>
+__device__ __forceinline__ T look(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void acknowledged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// First wave of every block, before its loads: what `claim` held (lane 0).
+__device__ __forceinline__ unsigned long long claim_patch(const SmallArgs& s, int patch, int wave, int lane) {
+  unsigned long long before = s.tag;
+  if (s.blocks_per_patch > 1 && wave == 0 && lane == 0)
+    before = __hip_atomic_exchange(&patch_head(s, patch)->claim, s.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return before;
+}
+// The same wave, before its block's work begins in earnest: clears the sums if it came first.
+__device__ __forceinline__ bool clear_patch(const SmallArgs& s, int patch, unsigned long long before, int lane) {
+  if (__ballot(before != s.tag) == 0) return false;
+  unsigned long long* sums = reinterpret_cast<unsigned long long*>(patch_sums(s, patch)) + lane;
+#pragma unroll 1
+  for (int i = 0; i < (s.narrow ? 8 : 16); ++i) put(sums + 64 * i, 0ull);
+  if (lane == 0) put(&patch_head(s, patch)->tickets, 0u);
+  return true;
+}
+// ... and a little later, when that has been acknowledged.
+__device__ __forceinline__ void open_patch(const SmallArgs& s, int patch, int lane) {
+  acknowledged();
+  if (lane == 0) put(&patch_head(s, patch)->ready, s.tag);
+}
 
 // The inputs of this wave's 16-input steps of the tile: steps wave, wave + 4, .. (up to NSTEP of them).
 template <int NSTEP>
@@ -63,6 +106,9 @@ __device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, co
   __syncthreads();                                     // everyone has read what the exchange area held before
 #pragma unroll
   for (int q = 0; q < 4; ++q) xch[(wave * 4 + q) * 64 + lane] = u32x4{y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]};
+  PatchHead* head = patch_head(s, patch);
+  if (s.blocks_per_patch > 1 && threadIdx.x == 0)
+    while (look(&head->ready) != s.tag) __builtin_amdgcn_s_sleep(1);
   __syncthreads();
   long long sum[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -73,28 +119,26 @@ __device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, co
     for (int e = 0; e < 4; ++e) sum[e] += (long long)(int32_t)(v[e] - s.bias_item) << (a.slice_bits * (slice0 + w));
   }
   if (s.blocks_per_patch > 1) {
-    // workspace: tickets [patch] (blocks that have arrived), then sums [patch][4][256 threads], 32-bit where they fit
-    uint32_t* tickets = reinterpret_cast<uint32_t*>(s.ws);
-    char* sums = reinterpret_cast<char*>(s.ws) + (((size_t)a.MP * a.OP * 4 + 255) & ~(size_t)255);
-    unsigned long long* wide = reinterpret_cast<unsigned long long*>(sums) + (size_t)patch * 1024 + threadIdx.x;
-    uint32_t* narrow = reinterpret_cast<uint32_t*>(sums) + (size_t)patch * 1024 + threadIdx.x;
+    unsigned long long* wide = reinterpret_cast<unsigned long long*>(patch_sums(s, patch)) + threadIdx.x;
+    uint32_t* narrow = reinterpret_cast<uint32_t*>(patch_sums(s, patch)) + threadIdx.x;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if (s.narrow) atomicAdd(&narrow[256 * e], (uint32_t)sum[e]);
       else atomicAdd(&wide[256 * e], (unsigned long long)sum[e]);
     }
     __shared__ uint32_t arrived;
-    // The sums before the ticket: every wave waits until its atomics, which act on memory that all XCDs share, have been
-    // acknowledged.  A device-scope fence would write back a whole L2 per block (it took ten times the kernel's time).
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    acknowledged();                                    // the sums before the ticket
     __syncthreads();
-    if (threadIdx.x == 0) arrived = atomicAdd(&tickets[patch], 1u);
+    if (threadIdx.x == 0) arrived = atomicAdd(&head->tickets, 1u);
     __syncthreads();
     if (arrived != (uint32_t)s.blocks_per_patch - 1) return;
+    if (threadIdx.x == 0) {
+      put(&head->claim, 0ull);
+      put(&head->ready, 0ull);
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      sum[e] = s.narrow ? (long long)(int32_t)__hip_atomic_load(&narrow[256 * e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                        : (long long)__hip_atomic_load(&wide[256 * e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sum[e] = s.narrow ? (long long)(int32_t)look(&narrow[256 * e]) : (long long)look(&wide[256 * e]);
   }
   const int m = mp * 32 + (lane & 31), o = op * 32 + 8 * wave + 4 * (lane >> 5);
   if (m >= a.M) return;
@@ -150,6 +194,7 @@ __global__ __launch_bounds__(256) void vmm_small_f16_kernel(SmallArgs s) {
   u32x2* raw = reinterpret_cast<u32x2*>(small_lds);    // [16-input step][64 lanes]
   u32x4* frags = small_lds + a.ks16 * 32 + (size_t)wave * TERMS * a.ks * 64;
   const int nk = (min(a.tile, a.Lin - it.t * a.tile) + 15) >> 4, nf = TERMS * nk;
+  const unsigned long long before = claim_patch(s, it.patch, wave, lane);
   Inputs<NSTEP> inputs;
   inputs.load(s, it.mp, it.t, wave, lane);
   const u32x4* src = a.B + (((size_t)it.t * a.OP + it.op) * a.S_w + it.slice) * TERMS * a.ks * 64 + lane;
@@ -162,6 +207,7 @@ __global__ __launch_bounds__(256) void vmm_small_f16_kernel(SmallArgs s) {
   }
   inputs.stage(s, raw, it.mp, it.t, it.p, nk, wave, lane);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  const bool first = clear_patch(s, it.patch, before, lane);
   __syncthreads();
   const uint32_t digit_mask8 = ((1u << a.stream_bits) - 1u) * 0x01010101u;
   float16v acc[S_IN];
@@ -197,6 +243,7 @@ __global__ __launch_bounds__(256) void vmm_small_f16_kernel(SmallArgs s) {
     }
     x0 = nx0; x1 = nx1; w0 = nw0; w1 = nw1;
   }
+  if (first) open_patch(s, it.patch, lane);
   float gain, lo, hi;
   adc_sign_and_range<PER_ARRAY>(a, it.p, it.pol, gain, lo, hi);
   uint32_t y[1][16];
@@ -220,6 +267,7 @@ __global__ __launch_bounds__(256) void vmm_small_f6_kernel(SmallArgs s) {
   const Item<PER_ARRAY> it(s, wave);
   u32x2* raw = reinterpret_cast<u32x2*>(small_lds);
   const int nk = (min(a.tile, a.Lin - it.t * a.tile) + 63) >> 6;
+  const unsigned long long before = claim_patch(s, it.patch, wave, lane);
   Inputs<NK> inputs;
   inputs.load(s, it.mp, it.t, wave, lane);
   const char* src = reinterpret_cast<const char*>(a.B + (PER_ARRAY ? (size_t)it.pol * a.pol_stride : 0)) +
@@ -235,6 +283,7 @@ __global__ __launch_bounds__(256) void vmm_small_f6_kernel(SmallArgs s) {
       fy[term][J] = *reinterpret_cast<const u32x2*>(f + 1024 + lane * 8);
     }
   inputs.stage(s, raw, it.mp, it.t, it.p, 4 * NK, wave, lane);   // zero beyond the tile
+  if (clear_patch(s, it.patch, before, lane)) open_patch(s, it.patch, lane);
   __syncthreads();
   const uint32_t nibble_mask = ((1u << a.stream_bits) - 1u) * 0x11111111u;
   float gain, lo, hi;
@@ -283,6 +332,12 @@ __global__ __launch_bounds__(256) void vmm_small_f6_kernel(SmallArgs s) {
   add_and_write(s, small_lds + NK * 128, y[0], wave, it.slice0, it.patch, it.mp, it.op, lane);
 }
 
+// Another odd 64-bit number at every call: steps of the golden ratio from a start that differs from process to process.
+unsigned long long launch_tag() {
+  static std::atomic<unsigned long long> next{(unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() * 0xD6E8FEB86659FD93ull | 1};
+  return next.fetch_add(0x9E3779B97F4A7C16ull, std::memory_order_relaxed);
+}
+
 int blocks_per_patch(const VmmPlan& p, const Derived& d) { return p.VT * cdiv(d.S_w, kSmallWaves); }
 // the staged inputs and the area of the final exchange (16 KiB), which the fragments of fp16 planes occupy before
 size_t small_lds_bytes(const VmmPlan& p, const Derived& d) {
@@ -310,7 +365,7 @@ void (*pick_f6(int terms, bool per_array))(SmallArgs) {
 size_t vmm_small_ws_bytes(const VmmPlan& p, const Derived& d) {
   if (blocks_per_patch(p, d) == 1) return 0;
   const size_t patches = (size_t)p.MP * p.g.OP;
-  return align256(patches * 4) + patches * (p.narrow ? 4096 : 8192);
+  return align256(patches * (sizeof(PatchHead) + (p.narrow ? 4096 : 8192)));
 }
 
 // One wave per item beats the chunked launch up to about four rounds of items on the chip's SIMDs with fp16 planes and
@@ -328,10 +383,7 @@ hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hip
   a.blocks_per_patch = blocks_per_patch(p, d);
   a.slice_groups = cdiv(d.S_w, kSmallWaves);
   a.groups_inv = (65536 + a.slice_groups - 1) / a.slice_groups;   // exact for quotients of numbers below 65536 / groups
-  if (const long long n16 = (long long)(vmm_small_ws_bytes(p, d) / 16)) {
-    hipLaunchKernelGGL(vmm_small_clear_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, st, reinterpret_cast<u32x4*>(a.ws), n16);
-    if (hipError_t e = hipGetLastError()) return e;
-  }
+  a.tag = launch_tag();
   void (*k)(SmallArgs);
   if (d.fmt == kFmtF16) k = p.ks16 <= 4 ? pick_f16<1>(d.terms, d.S_in, per_array) : p.ks16 <= 8 ? pick_f16<2>(d.terms, d.S_in, per_array) : pick_f16<4>(d.terms, d.S_in, per_array);
   else k = p.g.ks == 1 ? pick_f6<1>(d.terms, per_array) : p.g.ks == 2 ? pick_f6<2>(d.terms, per_array) : pick_f6<4>(d.terms, per_array);
