@@ -81,6 +81,10 @@ __device__ __forceinline__ void plane_values(const TileArgs& a, NormalStream& rn
   }
   if (a.flags & XBAR_NI_WIRE_AAM) {
     const double rho = a.r_source + (double)(j + 1) * a.r_row + (double)(a.R - i) * a.r_col + a.r_sense;
+    if constexpr (NPOL == 1) {   // g0 / (1 + rho g0) - g1 / (1 + rho g1), with one division
+      u[0] = (g[0] - g[1]) * a.inv_dg / ((1.0 + rho * g[0]) * (1.0 + rho * g[1]));
+      return;
+    }
     g[0] = g[0] / (1.0 + rho * g[0]);
     g[1] = g[1] / (1.0 + rho * g[1]);
   } else if (a.flags & XBAR_NI_WIRE_PROFILE) {
@@ -105,12 +109,23 @@ struct BothCopies {
   int nb;                    // blocks along n
 };
 
+// Nearest half of a double: rounded to odd in single precision on the way, so that the second rounding decides as one
+// would (the compiler's own sequence takes some forty integer instructions, and it was most of a plane value's cost).
+__device__ __forceinline__ _Float16 half_of(double x) {
+  const float f = (float)x;
+  const double back = (double)f;
+  uint32_t b = __builtin_bit_cast(uint32_t, f);
+  if (back != x && !(b & 1)) b += ::fabs(back) < ::fabs(x) ? 1u : ~0u;
+  return (_Float16)__builtin_bit_cast(float, b);
+}
+
 // fp16 planes, both copies at once: a block owns 32 x 32 weights and two slices (blockIdx.y counts slice pairs), computes
 // every device of them once -- in double precision -- turns the values through LDS as (leading term, residual) pairs
 // of halves and writes the operand chunks of both directions, 16 bytes each.  A layer of few blocks is bound by latency and
 // by the instruction cache (a line of code that runs once costs some 115 cycles to fetch), so it takes 1024 threads
 // with one weight and one chunk each; one with many blocks takes 256.  256 x 256 weights, 4 slices: one kernel per copy
-// with 8 devices of a column per thread took 14 + 11 us, this with 4 weights per thread unrolled 9.4 - 10, this 7.4.
+// with 8 devices of a column per thread took 14 + 11 us, this with 4 weights per thread unrolled 9.4 - 10, this 6.2;
+// 784 x 500: 12.3 instead of 19, 2048 x 1024, 8 slices: 64 instead of 114.
 template <int NPOL, int NTH>
 __global__ __launch_bounds__(NTH) void tile_f16_kernel(BothCopies b) {
   __shared__ uint32_t uv[NPOL][2][32][33];           // [array][slice of the pair][k][n]: leading half | residual << 16
@@ -125,14 +140,19 @@ __global__ __launch_bounds__(NTH) void tile_f16_kernel(BothCopies b) {
   int j = n0 % a.C + nl;
   if (j >= a.C) j -= a.C;
   if (j >= a.C) j -= a.C;
+  const int kl0 = threadIdx.x >> 5;
+  const float* wn = a.W + min(n, a.N - 1);             // one weight ahead
+  float w = wn[(size_t)min(k0 + kl0, a.K - 1) * a.N];
 #pragma unroll 1
-  for (int kl = threadIdx.x >> 5; kl < 32; kl += NTH / 32) {
+  for (int kl = kl0; kl < 32; kl += NTH / 32) {
     const int k = k0 + kl;
+    const float w_now = w;
+    if (NTH < 1024) w = wn[(size_t)min(k + NTH / 32, a.K - 1) * a.N];
     int i = k0 % a.R + kl;
     if (i >= a.R) i -= a.R;
     if (i >= a.R) i -= a.R;
     const bool real = k < a.K && n < a.N;
-    const int q = real ? quantized_weight(a.W[(size_t)k * a.N + n], (double)a.w_max, a.qw, a.q_per_w) : 0;
+    const int q = real ? quantized_weight(w_now, (double)a.w_max, a.qw, a.q_per_w) : 0;
     const int sign = (q > 0) - (q < 0);
     const uint32_t mag = (uint32_t)::abs(q);
 #pragma unroll
@@ -145,13 +165,15 @@ __global__ __launch_bounds__(NTH) void tile_f16_kernel(BothCopies b) {
 #pragma unroll
       for (int pol = 0; pol < NPOL; ++pol) {
         // leading term on the grid 2^-hi_frac (coarser where fp16 cannot hold it), residual in fp16
-        const _Float16 h = a.terms == 2 ? (_Float16)(::rint(u[pol] * a.hi_scale) * a.hi_inv_scale) : (_Float16)u[pol];
-        const _Float16 l = (_Float16)(u[pol] - (double)h);
+        // (on the grid: exact in single precision)
+        const _Float16 h = a.terms == 2 ? (_Float16)(float)(::rint(u[pol] * a.hi_scale) * a.hi_inv_scale) : half_of(u[pol]);
+        const _Float16 l = half_of(u[pol] - (double)(float)h);
         uv[pol][sl][kl][nl] = (uint32_t)__builtin_bit_cast(uint16_t, h) | ((uint32_t)__builtin_bit_cast(uint16_t, l) << 16);
       }
     }
   }
   __syncthreads();
+  const int t_k = k0 / b.tile[0], r_k = k0 - t_k * b.tile[0], t_n = n0 / b.tile[1], r_n = n0 - t_n * b.tile[1];
   // chunk = (slice, direction, term, 16-row step, lane): entries c0 .. c0 + 7 of one output
 #pragma unroll 1
   for (int chunk = threadIdx.x; chunk < 1024 * NPOL; chunk += NTH) {
@@ -160,7 +182,8 @@ __global__ __launch_bounds__(NTH) void tile_f16_kernel(BothCopies b) {
     const int ol = lane & 31, c0 = 16 * js + 8 * (lane >> 5);
     const int c = (dir == 0 ? k0 : n0) + 16 * js, op = (dir == 0 ? n0 : k0) >> 5;
     if (term >= a.terms || sl >= ns || c >= (dir == 0 ? a.K : a.N)) continue;   // the contraction never reads that k-step
-    const int t = c / b.tile[dir], step = (c - t * b.tile[dir]) >> 4;
+    const bool next = (dir == 0 ? r_k : r_n) + 16 * js >= b.tile[dir];         // a step of 16 lies in one tile
+    const int t = (dir == 0 ? t_k : t_n) + (next ? 1 : 0), step = ((dir == 0 ? r_k : r_n) + 16 * js - (next ? b.tile[dir] : 0)) >> 4;
     const uint32_t* from = &uv[pol][sl][0][0] + (dir == 0 ? c0 * 33 + ol : ol * 33 + c0);
     const int stride = dir == 0 ? 33 : 1;
     const uint32_t pick = term == 0 ? 0x05040100u : 0x07060302u;                // the low or the high halves of two words
@@ -1824,7 +1847,9 @@ int xbar_tile(const xbar_config* cfg, const float* W, int K, int N, float w_max,
     b.a = a;
     b.nb = cdiv(N, 32);
     const dim3 grid((unsigned)(cdiv(K, 32) * b.nb), (unsigned)pairs);
-    const bool few = grid.x * grid.y < 1024;
+    // 1024 threads while all blocks fit the chip at once, two to a compute unit (us, 1024 / 256 threads: 256 x 256 weights,
+    // 4 slices, 128 blocks: 5.6 / 8.5; 784 x 500, 800 blocks: 16.4 / 15.6)
+    const bool few = grid.x * grid.y <= 512;
     if (d.npol == 2 && few) hipLaunchKernelGGL((tile_f16_kernel<2, 1024>), grid, dim3(1024), 0, st, b);
     else if (d.npol == 2) hipLaunchKernelGGL((tile_f16_kernel<2, 256>), grid, dim3(256), 0, st, b);
     else if (few) hipLaunchKernelGGL((tile_f16_kernel<1, 1024>), grid, dim3(1024), 0, st, b);
