@@ -708,6 +708,7 @@ struct GradArgs {
 
 constexpr int kGradMS = 32;   // batch rows per LDS stage = two k-steps of the bf16 matrix instruction
 constexpr int kGradKS = kGradMS / 16;
+typedef float float4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // fp32 value as a leading bf16 and a bf16 residual (together 16 significant bits).
@@ -1097,6 +1098,70 @@ __global__ __launch_bounds__(256) void update_write_kernel(WriteArgs a) {
   }
 }
 
+// The whole update of a layer with few batch rows: a block owns 16 x 16 weights, its four waves take 32 batch rows of every
+// 128 each, straight from memory to the matrix instruction (v_mfma_f32_16x16x32_bf16, split operands as above), add their
+// sums up through LDS and every thread writes one weight.  One launch and short code instead of two kernels that are both
+// latency: 256 x 256 weights at batch 64 4.2 us instead of 5.9 + 5.3, 784 x 500 at batch 128 10.4 instead of 8.9 + 7.4.
+template <bool PAIR>
+__global__ __launch_bounds__(256) void update_small_kernel(GradArgs a, WriteArgs w) {
+  __shared__ float sums[4][256];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int k = (int)blockIdx.y * 16 + (lane & 15), n = (int)blockIdx.x * 16 + (lane & 15);
+  const float* xk = a.X + min(k, a.K - 1);
+  const float* dn = a.D + min(n, a.N - 1);
+  const int m_lane = wave * 32 + 8 * (lane >> 4);
+  float x[8], d[8];
+  auto fetch = [&](int m0) __attribute__((always_inline)) {    // rows beyond the batch: its last one, not used
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const size_t m = (size_t)min(m0 + m_lane + e, a.M - 1);
+      x[e] = xk[m * a.K];
+      d[e] = dn[m * a.N];
+    }
+  };
+  float4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  fetch(0);
+#pragma unroll 1
+  for (int m0 = 0; m0 < a.M; m0 += 128) {
+    bf16x8 xh, xl, dh, dl;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool row_ok = m0 + m_lane + e < a.M;
+      __bf16 h, l;
+      split_bf16(row_ok ? x[e] : 0.0f, h, l);
+      xh[e] = h; xl[e] = l;
+      split_bf16(row_ok ? d[e] : 0.0f, h, l);
+      dh[e] = h; dl[e] = l;
+    }
+    fetch(m0 + 128);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, dh, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, dl, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, dh, acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) sums[wave][(4 * (lane >> 4) + r) * 16 + (lane & 15)] = acc[r];
+  __syncthreads();
+  const int kw = (int)blockIdx.y * 16 + (threadIdx.x >> 4), nw = (int)blockIdx.x * 16 + (threadIdx.x & 15);
+  if (kw >= a.K || nw >= a.N) return;
+  double grad = 0.0;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) grad += (double)sums[v][threadIdx.x];
+  const uint64_t i = (uint64_t)kw * a.N + nw;
+  NormalStream rng(w.seed, PAIR ? kStreamWritePair : kStreamWrite, effective_step(w.step, w.step_add));
+  double z[2] = {0.0, 0.0};
+  if constexpr (PAIR) {
+    float gp = w.Gp[i], gn = w.Gn[i];
+    if (w.flags & XBAR_NI_UPD_NOISE) rng.pair(2 * i, z[0], z[1]);
+    w.W[i] = written_pair(w, gp, gn, grad, z);
+    w.Gp[i] = gp;
+    w.Gn[i] = gn;
+  } else {
+    const float before = w.W[i];
+    if (w.flags & XBAR_NI_UPD_NOISE) z[0] = rng.get(i);
+    w.W[i] = written_weight(w, before, grad, z[0]);
+  }
+}
+
 // Weights whose batch partials one block's groups share: enough loads in flight for a layer with few weights
 // and many partials (an early convolution: 2304 weights, 512 partials), every lane busy for one with many weights.
 template <bool PAIR>
@@ -1384,8 +1449,18 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
 
 struct UpdPlan {
   int KB, NB, mchunks, m_per_chunk, parts;   // parts: partial sums per batch chunk (padding waves reused)
+  bool small;                                // one kernel for gradient and write (from matrices)
   size_t ws_bytes;
 };
+
+// One kernel for gradient and write: up to 1024 rows, beyond which its blocks, which do not split the batch, take longer than
+// two launches; as long as the operands it reads again for every 16 rows or columns of weights are few; and up to half a
+// million weights (a million from 128 rows on), beyond which drawing four normal numbers at a time pays (measured, us per call,
+// two kernels / one: 256 x 256 weights, batch 64: 10.8 / 5.5, 1024: 14.5 / 8.3; 784 x 500, 128: 14.6 / 10.5, 512: 25.9 / 17.1,
+// 1024: 28.4 / 26.1; 1024 x 1024, 64: 18.6 / 19.4, 256: 29.4 / 24.2; 64 x 16, 1024: 10.9 / 7.5, 2048: 11.3 / 12.0).
+bool update_is_small(long long M, long long K, long long N) {
+  return M <= 1024 && M * K * N <= 256ll << 20 && K * N <= (M >= 128 ? 1 << 20 : 1 << 19);
+}
 
 UpdPlan plan_update(int M, int K, int N) {
   UpdPlan p;
@@ -1399,6 +1474,7 @@ UpdPlan plan_update(int M, int K, int N) {
   p.mchunks = cdiv(M, per);
   p.parts = (K <= 64 ? 2 : 1) * (N <= 64 ? 2 : 1);
   p.ws_bytes = align256((size_t)p.mchunks * p.parts * K * N * sizeof(float));
+  p.small = update_is_small(M, K, N);
   return p;
 }
 
@@ -1582,6 +1658,17 @@ int run_update(const xbar_config* cfg, float* W, const float* X, const float* dY
   GradArgs g;
   g.X = X; g.D = dY; g.part = reinterpret_cast<float*>(ws);
   g.M = M; g.K = K; g.N = N; g.KB = p.KB; g.NB = p.NB; g.m_per_chunk = p.m_per_chunk;
+  WriteArgs w;
+  w.W = W; w.Gp = Gp; w.Gn = Gn; w.part = g.part; w.n = (long long)K * N; w.mchunks = p.mchunks * p.parts; w.flags = cfg->flags;
+  w.w_max = (double)w_max; w.grad_scale = (double)grad_scale; w.lr = (double)lr;
+  w.v = (double)cfg->upd_nl_v; w.gamma = (double)cfg->upd_noise_gamma;
+  w.seed = cfg->seed; w.step = step; w.step_add = current_step_source();
+  if (!conv && p.small) {
+    const dim3 grid((unsigned)cdiv(N, 16), (unsigned)cdiv(K, 16));
+    if (Gp) hipLaunchKernelGGL(update_small_kernel<true>, grid, dim3(256), 0, st, g, w);
+    else hipLaunchKernelGGL(update_small_kernel<false>, grid, dim3(256), 0, st, g, w);
+    return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
+  }
   {
     g.total_wg = p.KB * p.NB * p.mchunks;
     g.per_xcd = cdiv(g.total_wg, 8);
@@ -1600,11 +1687,6 @@ int run_update(const xbar_config* cfg, float* W, const float* X, const float* dY
     }
   }
   if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
-  WriteArgs w;
-  w.W = W; w.Gp = Gp; w.Gn = Gn; w.part = g.part; w.n = (long long)K * N; w.mchunks = p.mchunks * p.parts; w.flags = cfg->flags;
-  w.w_max = (double)w_max; w.grad_scale = (double)grad_scale; w.lr = (double)lr;
-  w.v = (double)cfg->upd_nl_v; w.gamma = (double)cfg->upd_noise_gamma;
-  w.seed = cfg->seed; w.step = step; w.step_add = current_step_source();
   if ((Gp ? launch_update_write<true>(w, st) : launch_update_write<false>(w, st)) != hipSuccess) return XBAR_EHIP;
   return XBAR_OK;
 }

@@ -17,8 +17,10 @@ def close_codes(got, want):
     return diff.max() <= 1 and (diff > 0).sum() <= max(2, 1e-4 * diff.size)
 
 
-# M, K, N: odd weight counts (no 16-byte rows), one batch partial, the 8- and 32-group reductions, many weights
-@pytest.mark.parametrize("M,K,N", [(5, 3, 7), (9000, 9, 5), (40000, 16, 12), (3000, 33, 65), (33, 1023, 513)])
+# M, K, N: odd weight counts (no 16-byte rows), one batch partial, the 8- and 32-group reductions, many weights; one kernel for
+# gradient and write: one row, tiles of 16 and rounds of 128 rows plus and minus one, the largest batch, many blocks
+@pytest.mark.parametrize("M,K,N", [(5, 3, 7), (9000, 9, 5), (40000, 16, 12), (3000, 33, 65), (33, 1023, 513), (1025, 40, 16), (1, 1, 1),
+                                   (31, 16, 17), (128, 15, 33), (129, 48, 16), (1024, 31, 20), (127, 65537, 5)])
 @pytest.mark.parametrize("pair", [False, True])
 def test_update_write(xo, xb, M, K, N, pair):
     W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, False, 1), seed=M + K)
