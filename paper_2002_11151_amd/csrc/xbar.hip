@@ -703,12 +703,12 @@ struct GradArgs {
   float* part;      // [mchunks][K][N]
   int M, K, N, KB, NB, m_per_chunk;
   int total_wg, per_xcd;   // blocks of the launch; logical blocks per XCD (the grid is 8 x per_xcd)
+  int shares, partials;    // update_small_kernel: partial sums of a batch chunk (its k-steps in turn) and of the batch
   ConvGeom conv;
 };
 
 constexpr int kGradMS = 32;   // batch rows per LDS stage = two k-steps of the bf16 matrix instruction
 constexpr int kGradKS = kGradMS / 16;
-typedef float float4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // fp32 value as a leading bf16 and a bf16 residual (together 16 significant bits).
@@ -1098,67 +1098,95 @@ __global__ __launch_bounds__(256) void update_write_kernel(WriteArgs a) {
   }
 }
 
-// The whole update of a layer with few batch rows: a block owns 16 x 16 weights, its four waves take 32 batch rows of every
-// 128 each, straight from memory to the matrix instruction (v_mfma_f32_16x16x32_bf16, split operands as above), add their
-// sums up through LDS and every thread writes one weight.  One launch and short code instead of two kernels that are both
-// latency: 256 x 256 weights at batch 64 4.2 us instead of 5.9 + 5.3, 784 x 500 at batch 128 10.4 instead of 8.9 + 7.4.
-template <bool PAIR>
-__global__ __launch_bounds__(256) void update_small_kernel(GradArgs a, WriteArgs w) {
-  __shared__ float sums[4][256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int k = (int)blockIdx.y * 16 + (lane & 15), n = (int)blockIdx.x * 16 + (lane & 15);
-  const float* xk = a.X + min(k, a.K - 1);
-  const float* dn = a.D + min(n, a.N - 1);
-  const int m_lane = wave * 32 + 8 * (lane >> 4);
+// The whole update of a layer with few batch rows: a block owns 32 x 32 weights.  Its waves take one batch partial each, the
+// same rows in the same order as grad_gemm_kernel's waves (split operands, v_mfma_f32_32x32x16_bf16), but straight from memory
+// to the matrix instruction; the partials meet in LDS and are added up in double precision as update_write_kernel does, so the
+// weights are those of the two kernels.  One launch and short code instead of two kernels that are both latency: 256 x 256
+// weights at batch 64 6.1 us instead of 10.5, 784 x 500 at batch 128 9.2 instead of 14.7.  E weights per thread: one where few
+// blocks are to use the chip's lanes, four that share a Philox block where there are many.
+template <int E, bool PAIR>
+__global__ __launch_bounds__(1024 / E) void update_small_kernel(GradArgs a, WriteArgs w) {
+  constexpr int WAVES = 16 / E;
+  __shared__ float sums[WAVES][1024];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const float* xk = a.X + min((int)blockIdx.y * 32 + (lane & 31), a.K - 1);
+  const float* dn = a.D + min((int)blockIdx.x * 32 + (lane & 31), a.N - 1);
+  const int k = (int)blockIdx.y * 32 + (int)threadIdx.x * E / 32, n = (int)blockIdx.x * 32 + (int)threadIdx.x * E % 32;
+  double grad[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) grad[e] = 0.0;
   float x[8], d[8];
-  auto fetch = [&](int m0) __attribute__((always_inline)) {    // rows beyond the batch: its last one, not used
+  auto fetch = [&](int m0) __attribute__((always_inline)) {        // rows beyond the batch: its last one, not used
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const size_t m = (size_t)min(m0 + m_lane + e, a.M - 1);
+      const size_t m = (size_t)min(m0 + 8 * (lane >> 5) + e, a.M - 1);
       x[e] = xk[m * a.K];
       d[e] = dn[m * a.N];
     }
   };
-  float4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  fetch(0);
+  auto start = [&](int p) __attribute__((always_inline)) { return p / a.shares * a.m_per_chunk + p % a.shares * 16; };
+  fetch(start(wave));
 #pragma unroll 1
-  for (int m0 = 0; m0 < a.M; m0 += 128) {
-    bf16x8 xh, xl, dh, dl;
+  for (int first = 0; first < a.partials; first += WAVES) {
+    const int p = first + wave;
+    if (p < a.partials) {
+      const int end = min(a.M, (p / a.shares + 1) * a.m_per_chunk);
+      float16v acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int m0 = start(p), next; m0 < end; m0 = next) {
+        bf16x8 xh, xl, dh, dl;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const bool row_ok = m0 + m_lane + e < a.M;
-      __bf16 h, l;
-      split_bf16(row_ok ? x[e] : 0.0f, h, l);
-      xh[e] = h; xl[e] = l;
-      split_bf16(row_ok ? d[e] : 0.0f, h, l);
-      dh[e] = h; dl[e] = l;
+        for (int e = 0; e < 8; ++e) {
+          const bool row_ok = m0 + 8 * (lane >> 5) + e < end;
+          __bf16 h, l;
+          split_bf16(row_ok ? x[e] : 0.0f, h, l);
+          xh[e] = h; xl[e] = l;
+          split_bf16(row_ok ? d[e] : 0.0f, h, l);
+          dh[e] = h; dl[e] = l;
+        }
+        next = m0 + 16 * a.shares;
+        fetch(next < end ? next : start(p + WAVES));
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl, dh, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh, dl, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh, dh, acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sums[wave][(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31)] = acc[r];
     }
-    fetch(m0 + 128);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, dh, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, dl, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, dh, acc, 0, 0, 0);
+    __syncthreads();
+    for (int v = 0; v < min(WAVES, a.partials - first); ++v)
+#pragma unroll
+      for (int e = 0; e < E; ++e) grad[e] += (double)sums[v][threadIdx.x * E + e];
+    __syncthreads();
   }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) sums[wave][(4 * (lane >> 4) + r) * 16 + (lane & 15)] = acc[r];
-  __syncthreads();
-  const int kw = (int)blockIdx.y * 16 + (threadIdx.x >> 4), nw = (int)blockIdx.x * 16 + (threadIdx.x & 15);
-  if (kw >= a.K || nw >= a.N) return;
-  double grad = 0.0;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) grad += (double)sums[v][threadIdx.x];
-  const uint64_t i = (uint64_t)kw * a.N + nw;
+  if (k >= a.K || n >= a.N) return;
+  const bool noisy = (w.flags & XBAR_NI_UPD_NOISE) != 0;
+  const uint64_t i = (uint64_t)k * a.N + n;
   NormalStream rng(w.seed, PAIR ? kStreamWritePair : kStreamWrite, effective_step(w.step, w.step_add));
-  double z[2] = {0.0, 0.0};
-  if constexpr (PAIR) {
-    float gp = w.Gp[i], gn = w.Gn[i];
-    if (w.flags & XBAR_NI_UPD_NOISE) rng.pair(2 * i, z[0], z[1]);
-    w.W[i] = written_pair(w, gp, gn, grad, z);
-    w.Gp[i] = gp;
-    w.Gn[i] = gn;
-  } else {
+  if constexpr (E == 4 && !PAIR) {                   // N a multiple of four
+    double z[4] = {0.0, 0.0, 0.0, 0.0};
+    if (noisy) rng.get4(i >> 2, z);
+    float4 v = *reinterpret_cast<const float4*>(w.W + i);
+    v.x = written_weight(w, v.x, grad[0], z[0]);
+    v.y = written_weight(w, v.y, grad[1], z[1]);
+    v.z = written_weight(w, v.z, grad[2], z[2]);
+    v.w = written_weight(w, v.w, grad[3], z[3]);
+    *reinterpret_cast<float4*>(w.W + i) = v;
+  } else if constexpr (!PAIR) {
     const float before = w.W[i];
-    if (w.flags & XBAR_NI_UPD_NOISE) z[0] = rng.get(i);
-    w.W[i] = written_weight(w, before, grad, z[0]);
+    double z = 0.0;
+    if (noisy) z = rng.get(i);
+    w.W[i] = written_weight(w, before, grad[0], z);
+  } else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      float gp = w.Gp[i + e], gn = w.Gn[i + e];
+      double z[2] = {0.0, 0.0};
+      if (noisy) rng.pair(2 * (i + e), z[0], z[1]);
+      w.W[i + e] = written_pair(w, gp, gn, grad[e], z);
+      w.Gp[i + e] = gp;
+      w.Gn[i + e] = gn;
+    }
   }
 }
 
@@ -1453,13 +1481,15 @@ struct UpdPlan {
   size_t ws_bytes;
 };
 
-// One kernel for gradient and write: up to 1024 rows, beyond which its blocks, which do not split the batch, take longer than
-// two launches; as long as the operands it reads again for every 16 rows or columns of weights are few; and up to half a
-// million weights (a million from 128 rows on), beyond which drawing four normal numbers at a time pays (measured, us per call,
-// two kernels / one: 256 x 256 weights, batch 64: 10.8 / 5.5, 1024: 14.5 / 8.3; 784 x 500, 128: 14.6 / 10.5, 512: 25.9 / 17.1,
-// 1024: 28.4 / 26.1; 1024 x 1024, 64: 18.6 / 19.4, 256: 29.4 / 24.2; 64 x 16, 1024: 10.9 / 7.5, 2048: 11.3 / 12.0).
-bool update_is_small(long long M, long long K, long long N) {
-  return M <= 1024 && M * K * N <= 256ll << 20 && K * N <= (M >= 128 ? 1 << 20 : 1 << 19);
+// One kernel for gradient and write: up to 1024 rows, 768 where a batch chunk has two partials (beyond, its waves take more
+// rounds than two launches cost), and up to 1024 blocks, with which all lanes are busy in either (2048 where few rows leave
+// the write to dominate).  Measured, us per call, two kernels / one: 256 x 256 weights, batch 64: 10.5 / 6.1, 1024: 14.6 / 11.4,
+// 2048: 19.2 / 17.6; 784 x 500, 128: 14.7 / 9.2, 1024: 29.4 / 21.9; 1024 x 1024, 64: 19.4 / 12.2, 256: 30.8 / 17.4; 784 x 1300,
+// 1024: 37.7 / 41.3; 2048 x 1000, 32: 25.9 / 22.6, 512: 38.3 / 42.0; 64 x 16, 128: 10.3 / 5.8, 1024: 10.5 / 11.9; 65536 x 10, 100:
+// 22.9 / 36.7.
+bool update_is_small(int M, int K, int N) {
+  const long long blocks = (long long)cdiv(K, 32) * cdiv(N, 32);
+  return M <= (std::min(K, N) <= 64 ? 768 : 1024) && blocks <= (M <= 64 && N % 4 == 0 ? 2048 : 1024);
 }
 
 UpdPlan plan_update(int M, int K, int N) {
@@ -1664,9 +1694,17 @@ int run_update(const xbar_config* cfg, float* W, const float* X, const float* dY
   w.v = (double)cfg->upd_nl_v; w.gamma = (double)cfg->upd_noise_gamma;
   w.seed = cfg->seed; w.step = step; w.step_add = current_step_source();
   if (!conv && p.small) {
-    const dim3 grid((unsigned)cdiv(N, 16), (unsigned)cdiv(K, 16));
-    if (Gp) hipLaunchKernelGGL(update_small_kernel<true>, grid, dim3(256), 0, st, g, w);
-    else hipLaunchKernelGGL(update_small_kernel<false>, grid, dim3(256), 0, st, g, w);
+    g.shares = p.parts > 1 ? 2 : 1;                  // a stage has two k-steps: of four shares two are empty
+    g.partials = p.mchunks * g.shares;
+    const dim3 grid((unsigned)cdiv(N, 32), (unsigned)cdiv(K, 32));
+    // up to 128 blocks one weight per thread: sixteen waves share the latency, half the compute units would idle anyway
+    if (N % 4 == 0 && grid.x * grid.y > 128) {
+      if (Gp) hipLaunchKernelGGL((update_small_kernel<4, true>), grid, dim3(256), 0, st, g, w);
+      else hipLaunchKernelGGL((update_small_kernel<4, false>), grid, dim3(256), 0, st, g, w);
+    } else {
+      if (Gp) hipLaunchKernelGGL((update_small_kernel<1, true>), grid, dim3(1024), 0, st, g, w);
+      else hipLaunchKernelGGL((update_small_kernel<1, false>), grid, dim3(1024), 0, st, g, w);
+    }
     return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
   }
   {

@@ -18,9 +18,11 @@ def close_codes(got, want):
 
 
 # M, K, N: odd weight counts (no 16-byte rows), one batch partial, the 8- and 32-group reductions, many weights; one kernel for
-# gradient and write: one row, tiles of 16 and rounds of 128 rows plus and minus one, the largest batch, many blocks
+# gradient and write: one row, tiles of 32 plus and minus one, one and several rounds of partials, the largest batch and both
+# sides of it, rows in fours or not, one or four weights per thread, many blocks
 @pytest.mark.parametrize("M,K,N", [(5, 3, 7), (9000, 9, 5), (40000, 16, 12), (3000, 33, 65), (33, 1023, 513), (1025, 40, 16), (1, 1, 1),
-                                   (31, 16, 17), (128, 15, 33), (129, 48, 16), (1024, 31, 20), (127, 65537, 5)])
+                                   (31, 16, 17), (128, 15, 33), (129, 48, 16), (1024, 31, 20), (127, 65537, 5),
+                                   (768, 33, 64), (769, 64, 33), (1024, 65, 516), (100, 500, 321), (17, 1000, 2044)])
 @pytest.mark.parametrize("pair", [False, True])
 def test_update_write(xo, xb, M, K, N, pair):
     W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, False, 1), seed=M + K)
@@ -125,3 +127,18 @@ def test_all_paths_wire_model(xo, xb, R, C, slb, ni, K, N):
     w_max, xs, gs = float(np.abs(W).max()), float(np.abs(X).max()), float(np.abs(dY).max())
     assert close_codes(gpu_fwd(xb, cg, W, X, w_max, xs, step=2)[1], xo.fwd(co, W, X, w_max, xs, step=2, want_codes=True)[1])
     assert close_codes(gpu_bwd(xb, cg, W, dY, w_max, gs, step=2)[1], xo.bwd(co, W, dY, w_max, gs, step=2, want_codes=True)[1])
+
+
+# One kernel for gradient and write: the partial sums of the two kernels, added up alike -- a convolution with a stride,
+# which always takes those, writes the same weights bit for bit
+@pytest.mark.parametrize("M,K,N", [(1, 5, 4), (33, 40, 16), (64, 256, 256), (700, 64, 30), (128, 784, 500), (1024, 300, 100)])
+def test_update_of_few_rows_is_that_of_many(xb, M, K, N):
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, False, 1), seed=M + N)
+    cfg = xb.make_config(flags=xb.NI_UPD_NL | xb.NI_UPD_NOISE, upd_nl_v=0.3, upd_noise_gamma=2.0, seed=5)
+    w_max = 2.0 * float(np.abs(W).max())
+    one, two = dev(W.copy()), dev(W.copy())
+    xb.update(cfg, one, dev(X), dev(dY), w_max, 1.0 / w_max, 0.01, step=4)
+    geom = xb.conv_geom(M, 1, 1, K, 1, 1, 2, 0)
+    xb.conv_update(cfg, two, dev(X).reshape(M, 1, 1, K), dev(dY).reshape(M, 1, 1, N), geom, w_max, 1.0 / w_max, 0.01, step=4)
+    torch.cuda.synchronize()
+    assert torch.equal(one, two)
