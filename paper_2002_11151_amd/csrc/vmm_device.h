@@ -43,8 +43,8 @@ __device__ __forceinline__ void load_inputs8(const QuantArgs& a, int m, int l0, 
   if (CONV) {
     if (m < a.M) {
       const ConvRow cr = conv_row(a.conv, m);
-      int c = l0 % a.conv.C, kk = l0 / a.conv.C;
-      int kw = kk % a.conv.KW, kh = kk / a.conv.KW;
+      const uint32_t kk = (uint32_t)l0 / (uint32_t)a.conv.C;
+      int c = l0 - (int)kk * a.conv.C, kh = (int)(kk / (uint32_t)a.conv.KW), kw = (int)kk - kh * a.conv.KW;
       if ((a.conv.C & 7) == 0 && l0 + 8 <= lend) {   // the 8 inputs are 8 channels of one pixel
         const int ih = cr.ih0 + kh, iw = cr.iw0 + kw;
         if (ih >= 0 && ih < a.conv.H && iw >= 0 && iw < a.conv.W) {

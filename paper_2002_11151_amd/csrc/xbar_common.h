@@ -320,8 +320,8 @@ struct ConvRow {       // patch of one output position: element (kh, kw, c) is X
 };
 
 __device__ __forceinline__ ConvRow conv_row(const ConvGeom& g, int m) {
-  const int ow = m % g.OW, t = m / g.OW;
-  const int oh = t % g.OH, b = t / g.OH;
+  const uint32_t t = (uint32_t)m / (uint32_t)g.OW, b = t / (uint32_t)g.OH;
+  const int ow = m - (int)(t * (uint32_t)g.OW), oh = (int)(t - b * (uint32_t)g.OH);
   ConvRow r;
   r.ih0 = oh * g.stride - g.pad;
   r.iw0 = ow * g.stride - g.pad;

@@ -142,3 +142,37 @@ def test_update_of_few_rows_is_that_of_many(xb, M, K, N):
     xb.conv_update(cfg, two, dev(X).reshape(M, 1, 1, K), dev(dY).reshape(M, 1, 1, N), geom, w_max, 1.0 / w_max, 0.01, step=4)
     torch.cuda.synchronize()
     assert torch.equal(one, two)
+
+
+# Convolution passes from NHWC images against the matrix passes on the patches: the same codes, and a pixel's errors added in
+# single precision by kernel row and column -- equal bit for bit.  Kernels of no whole rounds of three positions, strides that
+# leave pixels without a position, channels in fours or not, several partial sums, 64-bit sums, offset-coded inputs.
+@pytest.mark.parametrize("batch,image,cin,cout,kernel,stride,pad,more", [
+    (2, 7, 4, 33, 5, 3, 2, {}), (1, 9, 3, 16, 3, 2, 0, {}), (3, 6, 8, 40, 1, 2, 0, {}), (2, 5, 4, 17, 7, 1, 3, {}),
+    (2, 8, 5, 64, 4, 1, 1, {}), (1, 1, 4, 5, 1, 3, 1, {}), (8, 28, 64, 600, 3, 1, 1, {}), (8, 28, 12, 300, 3, 2, 1, dict(adc_bits=12)),
+    (2, 11, 6, 20, 3, 1, 1, dict(offset=True)), (2, 11, 8, 20, 4, 3, 1, dict(offset=True))])
+def test_conv_is_its_patches(xb, batch, image, cin, cout, kernel, stride, pad, more):
+    from oracle import conv
+    kw = workloads.config_kwargs("resnet50")
+    kw["flags"] |= xb.INPUT_OFFSET if more.get("offset") else xb.INPUT_SIGNED
+    kw["adc_bits"] = more.get("adc_bits", kw["adc_bits"])
+    cfg = xb.make_config(**kw)
+    geom = xb.conv_geom(batch, image, image, cin, kernel, kernel, stride, pad)
+    M, K = batch * geom.out_h * geom.out_w, kernel * kernel * cin
+    rng = np.random.default_rng(M + K)
+    W = rng.standard_normal((K, cout)).astype(np.float32) * 0.05
+    X = rng.standard_normal((batch, image, image, cin)).astype(np.float32)
+    dY = rng.standard_normal((M, cout)).astype(np.float32)
+    w_max = float(np.abs(W).max())
+    planes = xb.tile(cfg, dev(W), w_max, 0)
+    Y = xb.conv_fwd(cfg, planes, dev(X), geom, cout, w_max, 3.0)
+    patches = np.ascontiguousarray(conv.im2col(X, kernel, kernel, stride, pad).reshape(M, K))
+    assert torch.equal(Y.reshape(M, cout), xb.fwd(cfg, planes, dev(patches), cout, w_max, 3.0))
+    dX = xb.conv_bwd(cfg, planes, dev(dY).reshape(batch, geom.out_h, geom.out_w, cout), geom, cout, w_max, 3.0).cpu().numpy()
+    cols = xb.bwd(cfg, planes, dev(dY), K, w_max, 3.0).cpu().numpy().reshape(batch, geom.out_h, geom.out_w, kernel, kernel, cin)
+    side = (max(geom.out_h, geom.out_w) - 1) * stride + kernel + image + pad
+    want = np.zeros((batch, side, side, cin), np.float32)
+    for kh in range(kernel):
+        for kw_ in range(kernel):
+            want[:, kh:kh + geom.out_h * stride:stride, kw_:kw_ + geom.out_w * stride:stride] += cols[:, :, :, kh, kw_]
+    assert np.array_equal(dX, want[:, pad:pad + image, pad:pad + image])
