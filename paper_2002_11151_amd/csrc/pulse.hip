@@ -406,8 +406,10 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   uint32_t* sq = samples[grp];
   uint32_t* pq = pulses[grp];
   const double2* mv = &moves[grp * L];
-  double g = a.first ? (double)a.W[dev] / a.w_max : a.state[dev];
+  const double g_begin = a.first ? (double)a.W[dev] / a.w_max : a.state[dev];
+  double g = g_begin;
   double gx = clampd(g, -1.0, 1.0);                  // where the non-linearity finds the state
+  bool pulsed = false;
   const double up_down = 2.0 * a.dw_min;
   int n_s = 0, n_p = 0, moved = 0;
 
@@ -471,6 +473,7 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
         while (__any(n_p - done >= full)) {
           // a batch of pulses: their normal numbers side by side, then the moves one after the other
           const int run = n_p - done >= full ? min(L, n_p - done) : 0;
+          pulsed = pulsed || run > 0;
           double2 e = {0.0, 0.0};
           if (gl < run) {
             const uint32_t p = pq[done + gl];
@@ -531,6 +534,9 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   }
 #pragma unroll
   for (int d = 1; d < L; d <<= 1) moved += __shfl_xor(moved, d, L);
+  // The moves' minimum and maximum drop a NaN, which a clamp by comparison keeps; a step is finite, so the state is NaN
+  // at the end only if it began as one.  A device without a pulse keeps what it held to the bit (a moved -0 is +0).
+  if (!pulsed || g_begin != g_begin) g = g_begin;
   if (valid && gl == 0) {
     if (a.last) a.W[dev] = (float)(a.w_max * g);
     else a.state[dev] = g;

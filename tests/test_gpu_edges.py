@@ -80,6 +80,33 @@ def test_pulsed_walk(xo, xb, M, K, N, density, v, ni):
         assert np.array_equal(Wg.cpu().numpy(), Wo)
 
 
+# Weights that are no numbers or lie at or beyond the range, in devices with pulses in every batch, in some and in none (rows
+# that are driven often, rarely and never): every walk leaves what the pulse-by-pulse clamp leaves, to the bit of a zero
+@pytest.mark.parametrize("M,K,N", [(2100, 20, 40), (2100, 64, 40), (2048, 300, 170), (300, 20, 40)])
+@pytest.mark.parametrize("v,ni", [(0.01, "nl+noise"), (0.04, "nl"), (0.0, "")])
+def test_pulsed_walk_of_special_weights(xo, xb, M, K, N, v, ni):
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=M + K + N)
+    w_max = 0.5 * float(np.abs(W).max())
+    special = np.array([np.nan, -0.0, np.inf, -np.inf, 3e38, -w_max, w_max, 0.0], np.float32)
+    rng = np.random.default_rng(K)
+    at = rng.integers(0, K * N, K * N // 4)
+    W.reshape(-1)[at] = special[rng.integers(0, special.size, at.size)]
+    X[:, ::3] *= 0.02
+    X[:, 1::3] = 0.0
+    flags = (xo.UPD_NL if "nl" in ni else 0) | (xo.UPD_NOISE if "noise" in ni else 0)
+    co, cg = both_configs(xo, xb, flags=flags, upd_nl_v=v, upd_noise_gamma=0.4, seed=3)
+    Wo, pulses_o = xo.update_pulsed(co, W, X, dY, w_max, 1.0, 0.01, 31, 2.0 ** -10, step=6, want_pulses=True)
+    Wg, pulses_g = xb.update_pulsed(cg, dev(W.copy()), dev(X), dev(dY), w_max, 1.0, 0.01, 31, 2.0 ** -10, step=6, want_pulses=True)
+    Wg = Wg.cpu().numpy()
+    assert np.array_equal(pulses_g.cpu().numpy(), pulses_o)
+    assert np.array_equal(np.isnan(Wg), np.isnan(Wo)) and np.isnan(Wo).any()
+    rest = np.isfinite(Wo)
+    assert np.array_equal(Wg[~rest], Wo[~rest], equal_nan=True)
+    assert np.abs(Wg[rest] - Wo[rest]).max() <= 2e-7 * w_max       # one rounding to single precision
+    zero = Wo == 0
+    assert np.array_equal(np.signbit(Wg[zero]), np.signbit(Wo[zero]))
+
+
 # Circuit-level model, state on chip: one device, one row, one column, tiles plus one; wires that matter (many iterations)
 @pytest.mark.parametrize("R,K,N,r_min", [(64, 1, 1, 1e5), (64, 65, 3, 1e3), (128, 1, 129, 1e5), (128, 130, 1, 1e4), (128, 40, 20, 1e3)])
 def test_circuit_model_on_chip(xo, xb, R, K, N, r_min):
