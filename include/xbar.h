@@ -6,10 +6,12 @@
  * torch tensor) and that must be 16-byte aligned.  The library never allocates or frees device
  * memory and never synchronises: every call only enqueues kernels on the HIP stream that is passed
  * in (NULL = the default stream) and returns.  Scratch memory comes from the caller (`ws`); its
- * contents are undefined after a call and two calls that share one workspace must be ordered on one
- * stream.  Return value: XBAR_OK or a negative XBAR_E* code; no exception crosses this boundary and
- * the library keeps no state between calls (two per-thread settings aside: the one-shot instrumentation
- * hook at the end and the optional step counter of xbar_set_step_source).
+ * contents are undefined before and after a call, and two calls that share one workspace must not overlap
+ * (order them on one stream, or synchronise between streams): the blocks of one launch meet in it, and what
+ * overlapping calls write is undefined (every kernel ends all the same).  Return value: XBAR_OK or a negative
+ * XBAR_E* code; no exception crosses this boundary and the library keeps no state between calls (the
+ * per-thread settings aside -- the one-shot instrumentation hooks at the end and the optional step counter of
+ * xbar_set_step_source -- and a process-wide counter that gives launches different numbers).
  *
  * A layer is the GEMM  Y[M x N] = X[M x K] . W[K x N]:  K = fan-in = crossbar rows, N = fan-out =
  * crossbar columns, M = batch (times output positions after im2col).  The weight matrix is cut into
@@ -203,8 +205,9 @@ int xbar_fwd(const xbar_config* cfg, const void* planes, const float* X, float* 
  * GPU it runs on until the process ends.  The call allocates and frees nothing; its first call on a device
  * looks the array's address up (with that device current).  Shapes whose xbar_workspace_bytes(cfg,
  * XBAR_OP_FWD, M, K, N) exceeds the array return XBAR_ESCRATCH and enqueue nothing.  All calls on one GPU
- * share the array: two calls must not overlap (order them on one stream, or synchronise between streams);
- * nothing in it has to start at zero (every byte that is read is written first by the same call).
+ * share the array: two calls must not overlap (order them on one stream, or synchronise between streams).
+ * What it holds before a call does not matter: every byte is written before it is read, but for one word per
+ * output patch that the blocks of a small layer's launch exchange for the launch's number.
  */
 #define XBAR_STATIC_SCRATCH_BYTES (32u << 20)
 int xbar_fwd_static(const xbar_config* cfg, const void* planes, const float* X, float* Y, int M, int K, int N,
@@ -409,6 +412,14 @@ int xbar_fcm_profile(const xbar_config* cfg, const float* W, int K, int N, float
  * scaling after it) and `after` right behind it.  Both are hipEvent_t handles owned by the caller.
  */
 void xbar_trace_next_vmm(void* before, void* after);
+
+/*
+ * Instrumentation for tests (no part of the method): one-shot, per host thread.  The next small layer's pass (one
+ * kernel for the whole pass) whose output patches several blocks share never opens its patches, and its blocks look
+ * for that `turns` times (>= 0) before they give up, as they do after 0.14 s or more where another call overlaps
+ * on the workspace: the outputs of such patches are NaN.
+ */
+void xbar_withhold_next_small_vmm(int turns);
 
 /*
  * Instrumentation for the benchmark (no part of the method): enqueues a kernel that does nothing but

@@ -993,6 +993,8 @@ struct SmallArgs {
   QuantArgs q;         // A unused
   void* ws;            // heads and sums of the patches that several blocks share
   unsigned long long tag;   // of this launch
+  unsigned long long ready_tag;   // what opens a patch: the tag (0: a wait that is meant to end without it)
+  int wait_turns;      // how often a block looks for it
   int is_conv;
   int narrow;          // every sum fits 32 bits
   int blocks_per_patch, slice_groups;

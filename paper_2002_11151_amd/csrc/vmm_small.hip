@@ -23,11 +23,13 @@ constexpr int kSmallWaves = 4;
 
 // The sums of a patch that several blocks share, in a workspace whose content is unknown when the launch begins: one
 // 64-byte head per patch, then 1024 sums per patch, [4][256 threads], 32-bit where they fit.  Every block begins with an
-// exchange of the head's `claim` for the launch's tag, a 64-bit number that no other launch of the process carries and
+// exchange of the head's `claim` for the launch's tag, an odd 64-bit number that no other launch of the process carries and
 // that no data hold but by a chance of 2^-64: the one block that finds another number there clears the sums and then sets
 // `ready`; the others look for it before they add, a few microseconds later, and wait if need be -- for a block that is
 // running and waits for nobody.  The last to arrive takes the tag back out: a launch that is replayed from a graph
-// carries the same tag again.  Everything here is a relaxed device-scope operation on memory that all XCDs share, ordered
+// carries the same tag again.  Two launches that overlap on one workspace, which callers must not let happen, take
+// `claim` and `ready` from each other: the wait therefore has an end, after which a block takes the tag out, writes
+// NaN (unscaled sums: the lowest integer) to its patch and is done.  Everything here is a relaxed device-scope operation on memory that all XCDs share, ordered
 // by waiting until it has been acknowledged: a device-scope fence would write back a whole L2 per block (it took ten times the
 // kernel's time).  A kernel of its own to clear cost each pass 1.9 us and a second launch.
 struct PatchHead {
@@ -63,7 +65,7 @@ __device__ __forceinline__ bool clear_patch(const SmallArgs& s, int patch, unsig
 // ... and a little later, when that has been acknowledged.
 __device__ __forceinline__ void open_patch(const SmallArgs& s, int patch, int lane) {
   acknowledged();
-  if (lane == 0) put(&patch_head(s, patch)->ready, s.tag);
+  if (lane == 0) put(&patch_head(s, patch)->ready, s.ready_tag);
 }
 
 // The inputs of this wave's 16-input steps of the tile: steps wave, wave + 4, .. (up to NSTEP of them).
@@ -97,6 +99,20 @@ struct Inputs {
   }
 };
 
+// Thread (q, lane)'s four outputs when the patch's sums cannot be had.
+__device__ __forceinline__ void write_poison(const SmallArgs& s, int m, int o) {
+  const VmmArgs& a = s.v;
+  if (m >= a.M) return;
+#pragma unroll 1
+  for (int e = 0; e < 4; ++e) {
+    if (o + e >= a.Lout) return;
+    const size_t at = (size_t)m * a.Lout + o + e;
+    if (a.part && s.narrow) reinterpret_cast<uint32_t*>(a.part)[at] = 0x80000000u;
+    else if (a.part) reinterpret_cast<unsigned long long*>(a.part)[at] = 0x8000000000000000ull;
+    else a.out[at] = __builtin_nanf("");
+  }
+}
+
 // The items' codes, summed over their cycles, to the patch's sums, or scaled and written.  Thread (q, lane) ends up with
 // the four consecutive outputs 8 q + 4 (lane / 32) .. of batch row lane % 32.
 __device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, const uint32_t (&y)[16], int wave, int slice0,
@@ -107,9 +123,26 @@ __device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, co
 #pragma unroll
   for (int q = 0; q < 4; ++q) xch[(wave * 4 + q) * 64 + lane] = u32x4{y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]};
   PatchHead* head = patch_head(s, patch);
-  if (s.blocks_per_patch > 1 && threadIdx.x == 0)
-    while (look(&head->ready) != s.tag) __builtin_amdgcn_s_sleep(1);
+  const int m = mp * 32 + (lane & 31), o = op * 32 + 8 * wave + 4 * (lane >> 5);
+  __shared__ uint32_t opened, arrived;
+  if (s.blocks_per_patch > 1 && threadIdx.x == 0) {
+    bool ready = look(&head->ready) == s.tag;
+#pragma unroll 1
+    for (int turn = 0; !ready && turn < s.wait_turns; ++turn) {
+      __builtin_amdgcn_s_sleep(1);
+      ready = look(&head->ready) == s.tag;
+    }
+    if (!ready) {                                      // the tag must not meet the next replay
+      put(&head->claim, 0ull);
+      put(&head->ready, 0ull);
+    }
+    opened = ready;
+  }
   __syncthreads();
+  if (s.blocks_per_patch > 1 && !opened) {
+    write_poison(s, m, o);
+    return;
+  }
   long long sum[4] = {0, 0, 0, 0};
 #pragma unroll
   for (int w = 0; w < kSmallWaves; ++w) {
@@ -126,7 +159,6 @@ __device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, co
       if (s.narrow) atomicAdd(&narrow[256 * e], (uint32_t)sum[e]);
       else atomicAdd(&wide[256 * e], (unsigned long long)sum[e]);
     }
-    __shared__ uint32_t arrived;
     acknowledged();                                    // the sums before the ticket
     __syncthreads();
     if (threadIdx.x == 0) arrived = atomicAdd(&head->tickets, 1u);
@@ -140,7 +172,6 @@ __device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, co
     for (int e = 0; e < 4; ++e)
       sum[e] = s.narrow ? (long long)(int32_t)look(&narrow[256 * e]) : (long long)look(&wide[256 * e]);
   }
-  const int m = mp * 32 + (lane & 31), o = op * 32 + 8 * wave + 4 * (lane >> 5);
   if (m >= a.M) return;
   const size_t at = (size_t)m * a.Lout + o;
   float r[4];
@@ -332,11 +363,16 @@ __global__ __launch_bounds__(256) void vmm_small_f6_kernel(SmallArgs s) {
   add_and_write(s, small_lds + NK * 128, y[0], wave, it.slice0, it.patch, it.mp, it.op, lane);
 }
 
-// Another odd 64-bit number at every call: steps of the golden ratio from a start that differs from process to process.
+// Another odd 64-bit number at every call: even steps, the golden ratio's, from an odd start that differs from process to process.
 unsigned long long launch_tag() {
   static std::atomic<unsigned long long> next{(unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() * 0xD6E8FEB86659FD93ull | 1};
   return next.fetch_add(0x9E3779B97F4A7C16ull, std::memory_order_relaxed);
 }
+
+// Turns of the wait, 0.13 us each on an idle chip: what it waits for takes microseconds, so 0.14 s is out of reach of a
+// launch that has its workspace to itself, also on a chip that others use.
+constexpr int kWaitTurns = 1 << 20;
+thread_local int g_withheld_turns = -1;
 
 int blocks_per_patch(const VmmPlan& p, const Derived& d) { return p.VT * cdiv(d.S_w, kSmallWaves); }
 // the staged inputs and the area of the final exchange (16 KiB), which the fragments of fp16 planes occupy before
@@ -383,7 +419,13 @@ hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hip
   a.blocks_per_patch = blocks_per_patch(p, d);
   a.slice_groups = cdiv(d.S_w, kSmallWaves);
   a.groups_inv = (65536 + a.slice_groups - 1) / a.slice_groups;   // exact for quotients of numbers below 65536 / groups
-  a.tag = launch_tag();
+  a.tag = a.ready_tag = launch_tag();
+  a.wait_turns = kWaitTurns;
+  if (g_withheld_turns >= 0) {
+    a.ready_tag = 0;
+    a.wait_turns = g_withheld_turns;
+    g_withheld_turns = -1;
+  }
   void (*k)(SmallArgs);
   if (d.fmt == kFmtF16) k = p.ks16 <= 4 ? pick_f16<1>(d.terms, d.S_in, per_array) : p.ks16 <= 8 ? pick_f16<2>(d.terms, d.S_in, per_array) : pick_f16<4>(d.terms, d.S_in, per_array);
   else k = p.g.ks == 1 ? pick_f6<1>(d.terms, per_array) : p.g.ks == 2 ? pick_f6<2>(d.terms, per_array) : pick_f6<4>(d.terms, per_array);
@@ -397,3 +439,5 @@ hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hip
 }
 
 }  // namespace xbar_detail
+
+extern "C" void xbar_withhold_next_small_vmm(int turns) { xbar_detail::g_withheld_turns = turns; }

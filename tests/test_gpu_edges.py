@@ -139,6 +139,39 @@ def test_pass_of_a_small_layer(xb, R, sb, wb, slb, adc, flags, M, K, N):
     assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
 
 
+# Blocks that share a patch and find it never opened end by themselves after a bounded number of looks and say so with NaN
+# (or, behind the sums that a gather reads, with what no sum is); the next pass on the same workspace is right, and so is
+# every replay of a graph that holds one
+@pytest.mark.parametrize("sb,flags", [(1, 0), (4, 0), (1, 512)])
+def test_wait_for_a_patch_has_an_end(xb, sb, flags):
+    M, K, N = 40, 300, 70
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=6)
+    fs = 1.037 * workloads.adc_full_scale(64, sb, 2)
+    cfg = xb.make_config(xbar_rows=64, xbar_cols=64, weight_bits=8, slice_bits=2, stream_bits=sb, flags=flags | xb.INPUT_SIGNED,
+                         adc_fs_fwd=fs, adc_fs_bwd=fs, seed=4)
+    w_max = float(np.abs(W).max())
+    planes, Xd = xb.tile(cfg, dev(W), w_max, 0), dev(X)
+    ws = torch.empty(xb.workspace_bytes(cfg, xb.OP_FWD, M, K, N), dtype=torch.uint8, device="cuda").random_(0, 256)
+    want = xb.fwd(cfg, planes, Xd, N, w_max, 3.0, ws=ws).clone()
+    out = torch.empty_like(want)
+    for turns in (0, 50):
+        xb.lib().xbar_withhold_next_small_vmm(turns)
+        xb.fwd(cfg, planes, Xd, N, w_max, 3.0, ws=ws, out=out)
+        assert bool(torch.isnan(out).all())
+        xb.fwd(cfg, planes, Xd, N, w_max, 3.0, ws=ws, out=out)
+        assert torch.equal(out, want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        xb.fwd(cfg, planes, Xd, N, w_max, 3.0, ws=ws, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        xb.lib().xbar_withhold_next_small_vmm(3)
+        xb.fwd(cfg, planes, Xd, N, w_max, 3.0, ws=ws, out=torch.empty_like(out))
+
+
 # All-paths wire model: fewer rows than row segments, both strip widths (up to 128 rows and beyond), one to four columns
 # per lane of the row scan, partial tiles down to one row or column
 @pytest.mark.parametrize("R,C,slb", [(16, 16, 2), (48, 64, 4), (128, 128, 2), (144, 80, 1), (256, 256, 2)])
