@@ -42,7 +42,9 @@ struct PulseArgs {
   ConvGeom conv;                        // convolution layer: X is the NHWC image and row m of the layer's
                                         //   input matrix is gathered from it (CONV variant of the train kernel)
   int coded, tx, td;                    // 1: deterministic time coding, tx frames of td sub-slots; 2: magnitude coding
-  unsigned long long* marks;            // two-phase walk: [K N][n_words] one bit per sample and device
+  unsigned long long* marks;            // two-phase walk: one bit per sample and device, word w of device d at
+  size_t mark_device, mark_word;        //   d mark_device + w mark_word: [K N][n_words] for the streamed walk, whose lanes read
+                                        //   words of one device; else [n_words][K N], read by lanes of neighbouring devices
   unsigned long long* summary;          //   [ceil(n_words / 64)][K N] one bit per word that is not empty
   int n_words;                          //   64-sample words of the current chunk
   int seg_words;                        //   words per block of the marking pass (a multiple of 4)
@@ -210,7 +212,7 @@ __global__ __launch_bounds__(256) void pulse_apply_kernel(PulseArgs a) {
           live[w] = 0;
           if constexpr (MARKED) {
             const int word = s0 / 64 + w;
-            if (word < a.n_words && k0 + i < a.K && n0 + j < a.N) live[w] = a.marks[(size_t)dev * a.n_words + word];
+            if (word < a.n_words && k0 + i < a.K && n0 + j < a.N) live[w] = a.marks[(size_t)dev * a.mark_device + (size_t)word * a.mark_word];
             continue;
           }
 #pragma unroll
@@ -325,7 +327,7 @@ __global__ __launch_bounds__(256) void pulse_mark_kernel(PulseArgs a) {
         bits |= (unsigned long long)four << (4 * v);
       }
       if (valid && word < a.n_words) {
-        a.marks[dev * a.n_words + word] = bits;
+        a.marks[dev * a.mark_device + (size_t)word * a.mark_word] = bits;
         if (bits) summary |= 1ull << ((word - a.seg_words * seg) & 63);
       }
     }
@@ -358,7 +360,7 @@ __global__ __launch_bounds__(256) void pulse_walk_kernel(PulseArgs a) {
         if (summary == 0) break;                     // no marked sample left
         const int wi = seg_base + __builtin_ctzll(summary);
         summary &= summary - 1;
-        word = a.marks[dev * a.n_words + wi];        // not empty: its summary bit is set
+        word = a.marks[dev * a.mark_device + (size_t)wi * a.mark_word];        // not empty: its summary bit is set
         word_base = 64 * wi;
       }
       const int at = word_base + __builtin_ctzll(word);
@@ -663,6 +665,11 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
       const long long devices = (long long)K * N;
       const bool stream = devices < (noise ? 49152 : 32768);
       const unsigned tiles16 = (unsigned)(cdiv(K, 16) * cdiv(N, 16));
+      // measured, ms per update, [n_words][K N] / [K N][n_words], walks of one lane per device: noise, 65536 devices x 12544
+      // samples 2.23 / 2.27, x 50176 8.53 / 8.93, 524288 x 4096 4.12 / 4.23; without, 65536 x 50176 4.19 / 4.60, 44100 x 100352
+      // 7.06 / 7.60, 524288 x 4096 1.75 / 1.89
+      a.mark_device = stream ? (size_t)a.n_words : 1;
+      a.mark_word = stream ? 1 : (size_t)devices;
       // the plain walk needs whole summary words (64-word segments); else short ones, for some thousand blocks
       a.seg_words = !stream || tiles16 >= 256 ? 64 : tiles16 >= 64 ? 16 : 4;
       hipLaunchKernelGGL(pulse_mark_kernel, dim3(tiles16 * (unsigned)cdiv(a.n_words, a.seg_words)), dim3(256), 0, st, a);
