@@ -1477,8 +1477,13 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
   p.ws_bytes = p.a_bytes + p.part_bytes;
   p.narrow = (unsigned long long)p.VT <= fit ? 1 : 0;
   p.small = vmm_small_fits(p, d) ? 1 : 0;
-  // ... its sums, and those of a scattered pass behind them
-  if (p.small) p.ws_bytes = std::max(p.ws_bytes, align256(vmm_small_ws_bytes(p, d)) + align256((size_t)M * p.Lout * (p.narrow ? 4 : 8)));
+  if (p.small) {
+    // its sums, and those of a scattered pass behind them: the workspace may grow, but no layer that xbar_fwd_static holds
+    // with several kernels outgrows the static array with one (32 rows of 140000 outputs of one 4-bit slice: 17.9 and 36.3 MB)
+    const size_t need = align256(vmm_small_ws_bytes(p, d)) + align256((size_t)M * p.Lout * (p.narrow ? 4 : 8));
+    if (need > std::max(p.ws_bytes, (size_t)XBAR_STATIC_SCRATCH_BYTES)) p.small = 0;
+    else p.ws_bytes = std::max(p.ws_bytes, need);
+  }
   return p;
 }
 

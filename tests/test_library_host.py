@@ -153,6 +153,17 @@ def test_size_queries(xb):
     assert xb.workspace_bytes(c, xb.OP_FWD, 1 << 30, 1 << 8, 8) == 0      # M*K reaches 2^38
 
 
+def test_one_launch_pass_keeps_layers_in_the_static_array(xb):
+    # one tile, two phases, one slice: the staged digits and one 32-bit sum per output fit the static array, the heads
+    # and shared sums of the one-launch pass on top of them would not
+    base = dict(xbar_rows=64, xbar_cols=64, weight_bits=4, slice_bits=4, flags=xb.INPUT_SIGNED)
+    pad = lambda b: -(-b // 256) * 256
+    for M, K, N in ((32, 64, 140000), (32, 64, 196000), (3, 20, 190001)):
+        several = pad(2 * (64 // 16) * 512) + pad(4 * M * N)
+        assert several <= 32 << 20
+        assert xb.workspace_bytes(xb.make_config(**base), xb.OP_FWD, M, K, N) <= 32 << 20
+
+
 def test_argument_checks_precede_any_device_work(xb):
     lib = xb.lib()
     c = xb.make_config()
