@@ -225,11 +225,15 @@ def workspace_bytes(cfg, op, M, K, N):
 
 # Small layers and peripheral calls take a few microseconds on the GPU, so the binding's own time counts: addresses go
 # to the library as plain integers, the current stream comes from torch's raw accessor (a Stream object takes 2.5 us to
-# make), and a buffer that the caller brings is not sized again here: the library checks it.
-_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+# make), and a buffer that the caller brings is not sized again here: the library checks it.  The accessors are looked up
+# at the first call: a torch without a GPU build lacks them and still imports this module for its host-only calls.
+_raw_stream = _current_device = None
 
 
 def _stream():
+    global _raw_stream, _current_device
+    if _raw_stream is None:
+        _current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
     return _raw_stream(_current_device())
 
 

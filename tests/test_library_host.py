@@ -3,6 +3,8 @@ declares, validates parameter structs and rejects bad arguments before touching 
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -151,6 +153,17 @@ def test_size_queries(xb):
     assert xb.workspace_bytes(c, xb.OP_FWD, 1 << 20, 1 << 12, 8) > 0      # activations may exceed 2^31 elements
     assert xb.workspace_bytes(c, xb.OP_FWD, 8, 1 << 16, 1 << 15) == 0     # K*N reaches 2^31
     assert xb.workspace_bytes(c, xb.OP_FWD, 1 << 30, 1 << 8, 8) == 0      # M*K reaches 2^38
+
+
+def test_binding_imports_without_a_gpu_build_of_torch(xb):
+    # such a torch lacks the raw accessors of the current device and stream; the host-only calls do not need them
+    code = ("import torch\n"
+            "for name in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+            "    if hasattr(torch._C, name):\n"
+            "        delattr(torch._C, name)\n"
+            "from paper_2002_11151_amd import xbar as xb\n"
+            "assert xb.planes_bytes(xb.make_config(), 64, 64) > 0 and xb.validate(xb.make_config()) == 0\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=300)
 
 
 def test_one_launch_pass_keeps_layers_in_the_static_array(xb):
