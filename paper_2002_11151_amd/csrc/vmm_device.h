@@ -1003,7 +1003,7 @@ struct SmallArgs {
   const long long* wsum;   // offset-binary inputs: weight sum per output, else null
   double half_range;
 };
-XBAR_INTERNAL bool vmm_small_fits(const VmmPlan& p, const Derived& d);
+XBAR_INTERNAL bool vmm_small_pays(const VmmPlan& p, const Derived& d, bool gathered);   // gathered: inputs one by one from an image
 XBAR_INTERNAL size_t vmm_small_ws_bytes(const VmmPlan& p, const Derived& d);
 XBAR_INTERNAL hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hipStream_t st);
 

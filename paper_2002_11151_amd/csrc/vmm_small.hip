@@ -404,14 +404,31 @@ size_t vmm_small_ws_bytes(const VmmPlan& p, const Derived& d) {
   return align256(patches * (sizeof(PatchHead) + (p.narrow ? 4096 : 8192)));
 }
 
-// One wave per item beats the chunked launch up to about four rounds of items on the chip's SIMDs with fp16 planes and
-// a dozen with 6-bit planes, whose chunked kernel has more to set up (measured, us per pass, chunked / this: fp16, 4-bit
-// cycles, items in all 896: 22.5 / 11.4, 3584: 26.3 / 18.7, 4096: 24.2 / 23.1, 4928: 23.9 / 27.9, 8192: 30.5 / 38.5; 6-bit,
-// 1-bit cycles, 256: 43.8 / 12.0, 7168: 51.4 / 33.7, 9856: 47.4 / 44.6, 32768: 78 / 109).
-bool vmm_small_fits(const VmmPlan& p, const Derived& d) {
-  const long long items = (long long)p.MP * p.g.OP * p.VT * d.S_w;
-  return items <= (d.fmt == kFmtF16 ? 4096 : 12288) && p.g.OP < 65536 && p.MP < 65536 &&
-         (long long)blocks_per_patch(p, d) * cdiv(d.S_w, kSmallWaves) < 65536;
+// When the one launch beats the three it replaces (measured on 28000 random layers, both sides in a graph; "lost": slower
+// than the three by more than 3 %).  It costs whole blocks, four slices each, whether or not they hold four.
+// fp16 planes: a tile of more than 128 rows leaves one to three blocks the LDS of a compute unit, and beyond the blocks
+// that are resident at once a second round costs more than two launches (us, three / one: 192 rows, 1122 blocks, one resident:
+// 20 / 51; 256 rows, 2448 blocks: 31 / 119); smaller tiles bear a little more than a round.  566 of 3674 layers lost with
+// a line at 4096 items alone, 25 with this one, none by more than 16 %.
+// 6-bit planes: a block's time grows with the fragments it reads (terms x k-steps) and with gathered inputs, which every output
+// patch and slice group fetches again; that of the chunked kernel with the matrix instructions of a tile's slices and
+// cycles, with the fragments that each of its waves stages, and with the tiles of a row.  The line is where their estimates
+// meet (us, three / one: 256 rows, 1 tile, 4 terms, 8192 items: 42 / 50; 256 rows, 10 tiles, 5 terms, 8960 items: 313 / 76; 128
+// rows, 1 tile, 5 terms, 12288 items: 55 / 64, 4 terms: 50 / 49).  4519 of 22798 layers lost with a line at 12288 items,
+// up to 3.6 times; 730 with this one, up to 1.45 times.
+bool vmm_small_pays(const VmmPlan& p, const Derived& d, bool gathered) {
+  const long long patches = (long long)p.MP * p.g.OP, items = patches * p.VT * d.S_w;
+  const long long blocks = patches * blocks_per_patch(p, d);
+  if (p.g.OP >= 65536 || p.MP >= 65536 || (long long)blocks_per_patch(p, d) * cdiv(d.S_w, kSmallWaves) >= 65536) return false;
+  if (d.fmt == kFmtF16) {
+    const long long resident = 256 * (long long)std::min<size_t>(8, 160 * 1024 / small_lds_bytes(p, d));
+    return items <= 4096 && blocks <= (p.ks16 <= 8 ? std::max(1024ll, resident * 3 / 2) : resident);
+  }
+  const int read_steps = p.g.ks == 3 ? 4 : p.g.ks;                  // k-steps of a block, and those that a tile reaches
+  const int frags = d.S_w * d.terms * cdiv(std::min(p.Lin, p.g.tile), 64);
+  const double one = (double)blocks * 1e-3 * (4.0 + 1.4 * d.terms * read_steps + (gathered ? 1.8 * read_steps : 0.0));
+  const double three = 8.0 + 0.05 * frags * d.S_in + 0.55 * frags / p.nw + 5.5 * std::min(p.g.T, 4);
+  return items <= 12288 && one <= three;
 }
 
 hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hipStream_t st) {

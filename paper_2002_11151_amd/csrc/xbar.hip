@@ -1476,7 +1476,7 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
   p.part_bytes = align256((size_t)p.nchunk * M * p.Lout * ((p.wide || p.flush_every) ? 8 : 4));
   p.ws_bytes = p.a_bytes + p.part_bytes;
   p.narrow = (unsigned long long)p.VT <= fit ? 1 : 0;
-  p.small = vmm_small_fits(p, d) ? 1 : 0;
+  p.small = vmm_small_pays(p, d, false) ? 1 : 0;
   if (p.small) {
     // its sums, and those of a scattered pass behind them: the workspace may grow, but no layer that xbar_fwd_static holds
     // with several kernels outgrows the static array with one (32 rows of 140000 outputs of one 4-bit slice: 17.9 and 36.3 MB)
@@ -1566,7 +1566,7 @@ int run_vmm(const xbar_config* cfg, const void* planes, const float* in, float* 
   qa.n_threads = (long long)p.MP * p.g.T * ((p.ks16 + 1) / 2) * 64;
   if (conv) qa.conv = *conv;
   const bool general = codes != nullptr || hist != nullptr || level_table || (cfg->flags & XBAR_ADC_CURVE) != 0;
-  const bool small = p.small && !general;
+  const bool small = p.small && !general && (!conv || conv->C % 8 == 0 || vmm_small_pays(p, d, true));
   if (small) {
   } else if (conv) {
     hipLaunchKernelGGL(quantize_input_kernel<true>, dim3((unsigned)((qa.n_threads + 255) / 256)), dim3(256), 0, st, qa);

@@ -139,6 +139,36 @@ def test_pass_of_a_small_layer(xb, R, sb, wb, slb, adc, flags, M, K, N):
     assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
 
 
+# Both sides of the lines beyond which several kernels take a pass again: blocks that fill the chip once (192 rows, fp16 planes),
+# blocks whose time meets the chunked kernel's (6-bit planes), and a convolution that only its gathered inputs take beyond
+@pytest.mark.parametrize("R,sb,wb,flags,M,K,N", [(192, 4, 8, 0, 512, 192, 512), (192, 4, 8, 0, 513, 192, 512),
+                                                 (128, 1, 16, 1, 992, 64, 992), (128, 1, 16, 1, 993, 64, 992)])
+def test_lines_of_the_small_pass(xb, R, sb, wb, flags, M, K, N):
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, False, 1), seed=M + K)
+    fs = 1.037 * workloads.adc_full_scale(R, sb, 2)
+    cfg = xb.make_config(xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=2, stream_bits=sb, var_sigma=0.1,
+                         flags=xb.NI_VARIATION if flags else xb.NI_WIRE_AAM, adc_fs_fwd=fs, adc_fs_bwd=fs, seed=4)
+    w_max, xs, gs = float(np.abs(W).max()), float(np.abs(X).max()), float(np.abs(dY).max())
+    assert np.array_equal(gpu_fwd(xb, cfg, W, X, w_max, xs, codes=False), gpu_fwd(xb, cfg, W, X, w_max, xs)[0])
+    assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
+
+
+@pytest.mark.parametrize("cin,image", [(7, 31), (7, 25), (8, 31)])
+def test_gathered_inputs_of_the_small_pass(xb, cin, image):
+    from oracle import conv
+    cout, K, M = 928, 9 * cin, image * image
+    kw = dict(workloads.config_kwargs("resnet50"), var_sigma=0.1, seed=4)
+    kw["flags"] |= xb.NI_VARIATION
+    cfg = xb.make_config(**kw)
+    W, X, _ = workloads.layer_tensors_np(workloads.Gemm("t", K, cout, M, False, 1), seed=image)
+    X = np.abs(np.random.default_rng(image).standard_normal((1, image, image, cin))).astype(np.float32)
+    w_max = float(np.abs(W).max())
+    planes = xb.tile(cfg, dev(W), w_max, 0)
+    Y = xb.conv_fwd(cfg, planes, dev(X), xb.conv_geom(1, image, image, cin, 3, 3, 1, 1), cout, w_max, 3.0)
+    patches = np.ascontiguousarray(conv.im2col(X, 3, 3, 1, 1).reshape(M, K))
+    assert torch.equal(Y.reshape(M, cout), xb.fwd(cfg, planes, dev(patches), cout, w_max, 3.0))
+
+
 # Blocks that share a patch and find it never opened end by themselves after a bounded number of looks and say so with NaN
 # (or, behind the sums that a gather reads, with what no sum is); the next pass on the same workspace is right, and so is
 # every replay of a graph that holds one
