@@ -1494,14 +1494,18 @@ struct UpdPlan {
 };
 
 // One kernel for gradient and write: up to 1024 rows, 768 where a batch chunk has two partials (beyond, its waves take more
-// rounds than two launches cost), and up to 1024 blocks, with which all lanes are busy in either (2048 where few rows leave
-// the write to dominate).  Measured, us per call, two kernels / one: 256 x 256 weights, batch 64: 10.5 / 6.1, 1024: 14.6 / 11.4,
-// 2048: 19.2 / 17.6; 784 x 500, 128: 14.7 / 9.2, 1024: 29.4 / 21.9; 1024 x 1024, 64: 19.4 / 12.2, 256: 30.8 / 17.4; 784 x 1300,
-// 1024: 37.7 / 41.3; 2048 x 1000, 32: 25.9 / 22.6, 512: 38.3 / 42.0; 64 x 16, 128: 10.3 / 5.8, 1024: 10.5 / 11.9; 65536 x 10, 100:
-// 22.9 / 36.7.
+// rounds than two launches cost), up to 1024 blocks, with which all lanes are busy in either (2048 where few rows leave the
+// write to dominate), and up to 2^19 rows x blocks, beyond which fetching every operand once per block costs more than the
+// partial sums' way through memory.  Rows that are no whole quads take one weight per thread and draw every normal number's
+// Philox block for itself: with few rows, where that is most of the work, up to 576 blocks.  Measured, us per call, two kernels
+// / one: 256 x 256 weights, batch 64: 10.5 / 5.8, 1024: 14.4 / 10.9; 784 x 500, 128: 14.5 / 8.8, 1024: 29.4 / 20.2; 1024 x 1024, 64: 18.2 /
+// 10.9, 512: 31.3 / 20.3; 784 x 1000, 640: 29.4 / 26.3, 896: 30.1 / 32.0; 6721 x 84, 1024: 32.4 / 39.0; 2048 x 1000, 64: 28.0 /
+// 21.9, 512: 35.3 / 37.7; 916 x 919, 32: 16.1 / 17.9; 64 x 16, 768: 10.9 / 9.9, 1024: 10.3 / 11.7.  Of 7662 random layers inside the
+// line without the product and the quads, 75 lost more than 3 % and up to 52 %; inside this one 17, up to 23 %.
 bool update_is_small(int M, int K, int N) {
   const long long blocks = (long long)cdiv(K, 32) * cdiv(N, 32);
-  return M <= (std::min(K, N) <= 64 ? 768 : 1024) && blocks <= (M <= 64 && N % 4 == 0 ? 2048 : 1024);
+  if (M > (std::min(K, N) <= 64 ? 768 : 1024) || M * blocks > (1 << 19)) return false;
+  return blocks <= (N % 4 == 0 ? (M <= 64 ? 2048 : 1024) : (M < 96 ? 576 : 1024));
 }
 
 UpdPlan plan_update(int M, int K, int N) {
@@ -1709,8 +1713,10 @@ int run_update(const xbar_config* cfg, float* W, const float* X, const float* dY
     g.shares = p.parts > 1 ? 2 : 1;                  // a stage has two k-steps: of four shares two are empty
     g.partials = p.mchunks * g.shares;
     const dim3 grid((unsigned)cdiv(N, 32), (unsigned)cdiv(K, 32));
-    // up to 128 blocks one weight per thread: sixteen waves share the latency, half the compute units would idle anyway
-    if (N % 4 == 0 && grid.x * grid.y > 128) {
+    // up to 256 blocks, one per compute unit, one weight per thread: sixteen waves share the latency (us, four weights / one:
+    // 2400 x 40 weights, 150 blocks, batch 32: 6.1 / 5.9, 512: 13.5 / 9.0; 2400 x 96, 225 blocks: 6.0 / 6.2, 10.9 / 8.5; 2400 x 128,
+    // 300 blocks: 7.1 / 8.7, 13.3 / 13.3)
+    if (N % 4 == 0 && grid.x * grid.y > 256) {
       if (Gp) hipLaunchKernelGGL((update_small_kernel<4, true>), grid, dim3(256), 0, st, g, w);
       else hipLaunchKernelGGL((update_small_kernel<4, false>), grid, dim3(256), 0, st, g, w);
     } else {

@@ -234,6 +234,14 @@ def test_update_of_few_rows_is_that_of_many(xb, M, K, N):
     assert torch.equal(one, two)
 
 
+# ... and on both sides of the lines: rows times blocks, blocks of rows in quads and of others with few rows, one and four
+# weights per thread
+@pytest.mark.parametrize("M,K,N", [(1024, 512, 1024), (1024, 544, 1024), (513, 1024, 1024), (40, 768, 767), (40, 800, 767), (96, 800, 767),
+                                   (64, 512, 512), (64, 512, 516), (64, 2048, 1024), (64, 2080, 1024)])
+def test_lines_of_the_update_in_one_kernel(xb, M, K, N):
+    test_update_of_few_rows_is_that_of_many(xb, M, K, N)
+
+
 # Convolution passes from NHWC images against the matrix passes on the patches: the same codes, and a pixel's errors added in
 # single precision by kernel row and column -- equal bit for bit.  Kernels of no whole rounds of three positions, strides that
 # leave pixels without a position, channels in fours or not, several partial sums, 64-bit sums, offset-coded inputs.
