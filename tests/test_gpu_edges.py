@@ -242,6 +242,29 @@ def test_lines_of_the_update_in_one_kernel(xb, M, K, N):
     test_update_of_few_rows_is_that_of_many(xb, M, K, N)
 
 
+# Batch rows many orders of magnitude apart: the partial sums are no longer added exactly, and the two ways of adding them may
+# round differently, by the last bit of a weight.  Against the oracle: operands of two bfloat16 halves and products without
+# the two low ones, 2^-15 of the sum of magnitudes, and the rounding of a weight.
+@pytest.mark.parametrize("M,K,N", [(64, 256, 256), (700, 64, 30), (1024, 300, 100)])
+def test_update_of_rows_of_all_magnitudes(xo, xb, M, K, N):
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=M + N)
+    rng = np.random.default_rng(M)
+    X *= (2.0 ** rng.integers(-40, 1, (M, 1))).astype(np.float32)
+    dY *= (2.0 ** rng.integers(-40, 1, (M, 1))).astype(np.float32)
+    co, cg = both_configs(xo, xb, seed=5)
+    w_max = 2.0 * float(np.abs(W).max())
+    magnitude = np.abs(X).T.astype(np.float64) @ np.abs(dY).astype(np.float64)
+    lr = 0.4 / float(magnitude.max())
+    want = xo.update(co, W, X, dY, w_max, 1.0, lr, step=4)
+    one, two = dev(W.copy()), dev(W.copy())
+    xb.update(cg, one, dev(X), dev(dY), w_max, 1.0, lr, step=4)
+    geom = xb.conv_geom(M, 1, 1, K, 1, 1, 2, 0)
+    xb.conv_update(cg, two, dev(X).reshape(M, 1, 1, K), dev(dY).reshape(M, 1, 1, N), geom, w_max, 1.0, lr, step=4)
+    one, two = one.cpu().numpy(), two.cpu().numpy()
+    assert np.all(np.abs(one - two) <= np.spacing(np.abs(one)))
+    assert np.all(np.abs(one.astype(np.float64) - want) <= 2.0 ** -15 * w_max * lr * magnitude + np.spacing(np.abs(want)))
+
+
 # Convolution passes from NHWC images against the matrix passes on the patches: the same codes, and a pixel's errors added in
 # single precision by kernel row and column -- equal bit for bit.  Kernels of no whole rounds of three positions, strides that
 # leave pixels without a position, channels in fours or not, several partial sums, 64-bit sums, offset-coded inputs.
