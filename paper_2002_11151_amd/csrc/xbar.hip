@@ -1903,7 +1903,7 @@ int xbar_config_validate(const xbar_config* c) {
 size_t xbar_planes_bytes(const xbar_config* cfg, int K, int N) {
   if (xbar_config_validate(cfg) || check_shape(1, K, N)) return 0;
   const Derived d = derive(cfg);
-  return device_words_offset(cfg, d, K, N) + device_words_bytes(d, K, N);
+  return device_words_offset(cfg, d, K, N) + device_words_bytes(cfg, d, K, N);
 }
 
 size_t xbar_workspace_bytes(const xbar_config* cfg, int op, int M, int K, int N) {
@@ -2004,7 +2004,7 @@ int xbar_tile(const xbar_config* cfg, const float* W, int K, int N, float w_max,
     if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
     a.codes = table;
   }
-  if (a.R % 64 == 0 && a.C % 64 == 0) {
+  if (whole_steps(cfg)) {
     b.a = a;
     b.nb = cdiv(N, 64);
     const unsigned patches = (unsigned)(cdiv(K, 64) * b.nb);

@@ -173,12 +173,16 @@ static inline size_t code_table_bytes(const xbar_config* c, const Derived& d) {
   return uses_code_table(d) ? align256(2 * code_table_words(c) * sizeof(uint32_t)) : 0;
 }
 
+// Arrays of whole 64-row and 64-column steps: the 64 x 64 patches of the 6-bit generator straddle none, so one kernel writes
+// both plane copies with what they share in LDS; others write each copy on its own.
+static inline bool whole_steps(const xbar_config* c) { return c->xbar_rows % 64 == 0 && c->xbar_cols % 64 == 0; }
+
 // General 6-bit generator (variation, stored profile, all-paths model, one array alone): every device is computed
-// once -- its term codes as one 32-bit word (term j at bit 6 j), [array][slice][k][n], kept behind the table -- and
-// both plane copies are packed from those words.
+// once -- its term codes as one 32-bit word (term j at bit 6 j) -- and both plane copies are packed from those words.
+// Only arrays that are no whole steps of 64 keep them in memory: [array][slice][k][n], behind the table.
 static inline bool uses_device_words(const Derived& d) { return d.fmt == kFmtF6 && !uses_code_table(d) && d.terms > 1; }
-static inline size_t device_words_bytes(const Derived& d, int K, int N) {
-  return uses_device_words(d) ? align256((size_t)4 * d.npol * d.S_w * K * N) : 0;
+static inline size_t device_words_bytes(const xbar_config* c, const Derived& d, int K, int N) {
+  return uses_device_words(d) && !whole_steps(c) ? align256((size_t)4 * d.npol * d.S_w * K * N) : 0;
 }
 
 static inline PlaneGeom plane_geom(const xbar_config* c, const Derived& d, int K, int N, bool transposed) {
