@@ -158,7 +158,7 @@ uint32_t xbar_abi_version(void);
  *   profile  [S_w][2][K][N] float distortion D (index 1: 0 = positive array), G <- G (1 - D);
  *            required with XBAR_NI_WIRE_PROFILE, ignored otherwise
  *   planes   output, xbar_planes_bytes(cfg, K, N) bytes, opaque
- * With XBAR_NI_WIRE_AAM2 the plane buffer also holds (16 S_w + 4) K N bytes of scratch, and where 6-bit planes of
+ * With XBAR_NI_WIRE_AAM2 the plane buffer also holds 16 S_w K N bytes of scratch, and where 6-bit planes of
  * crossbars whose rows or columns are no multiple of 64 carry an array non-ideality other than the single-path wire
  * model alone (variation, profile, all-paths model, XBAR_ADC_PER_ARRAY) 4 S_w K N bytes per array: every device is
  * computed once there and both copies are packed from it (the size query includes both); tile (i, j) indices count from

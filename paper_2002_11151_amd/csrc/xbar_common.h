@@ -149,7 +149,7 @@ constexpr size_t kPlanePad = 1024;   // behind each copy: staging copies whole K
 
 // Scratch of the all-paths wire model, kept behind the two plane copies.
 static inline size_t wire_scratch_bytes(const xbar_config* c, const Derived& d, int K, int N) {
-  return (c->flags & XBAR_NI_WIRE_AAM2) ? align256((size_t)16 * d.S_w * K * N) + align256((size_t)4 * K * N) : 0;
+  return (c->flags & XBAR_NI_WIRE_AAM2) ? align256((size_t)16 * d.S_w * K * N) : 0;
 }
 
 // Weight sums for the digital correction of offset-binary inputs, kept behind the wire scratch:

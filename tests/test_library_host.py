@@ -121,7 +121,7 @@ def test_size_queries(xb):
     lut = xb.make_config(flags=xb.NI_WIRE_AAM | xb.DAC_LUT, stream_bits=2, dac_lut=[0.0, 0.3, 0.7, 1.0], **base)
     assert xb.planes_bytes(lut, K, N) == fwd + bwd
     all_paths = xb.make_config(flags=xb.NI_WIRE_AAM2, **base)
-    assert xb.planes_bytes(all_paths, K, N) == frag(5) + 16 * 8 * K * N + 4 * K * N   # scratch behind the planes
+    assert xb.planes_bytes(all_paths, K, N) == frag(5) + 16 * 8 * K * N   # scratch behind the planes
     fwd, bwd = frag(4) // 2, frag(4) // 2
     # offset-binary inputs: the 64-bit sums of the programmed weights per column and per row ride along
     coded = xb.make_config(xbar_rows=128, xbar_cols=128, weight_bits=16, slice_bits=2, flags=xb.NI_WIRE_AAM | xb.INPUT_OFFSET)
