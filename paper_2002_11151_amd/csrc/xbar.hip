@@ -483,8 +483,8 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
 
 // Term codes of the plane value of every (sign, digit, row, column): one thread per (digit, row, column)
 // computes the value with the arithmetic of plane_values, splits it into the terms of the schedule and
-// writes both signs in both orientations.
-__global__ __launch_bounds__(256) void code_table_kernel(TileArgs a, uint32_t* table) {
+// writes both signs, and with `both` the second orientation.
+__global__ __launch_bounds__(256) void code_table_kernel(TileArgs a, uint32_t* table, int both) {
   const int nd = (1 << a.slice_bits) - 1;
   const int idx = blockIdx.x * 256 + threadIdx.x;
   if (idx >= nd * a.R * a.C) return;
@@ -498,7 +498,7 @@ __global__ __launch_bounds__(256) void code_table_kernel(TileArgs a, uint32_t* t
     const uint32_t word = term_codes(u[0], a.terms, a.term_exp);
     const size_t plane = (size_t)(neg * nd + digit - 1) * a.R * a.C;
     table[plane + (size_t)i * a.C + j] = word;
-    table[words + plane + (size_t)j * a.R + i] = word;
+    if (both) table[words + plane + (size_t)j * a.R + i] = word;
   }
 }
 
@@ -2000,7 +2000,7 @@ int xbar_tile(const xbar_config* cfg, const float* W, int K, int N, float w_max,
   if (uses_code_table(d)) {
     table = reinterpret_cast<uint32_t*>(at + code_table_offset(cfg, d, K, N));
     const int entries = ((1 << cfg->slice_bits) - 1) * cfg->xbar_rows * cfg->xbar_cols;
-    hipLaunchKernelGGL(code_table_kernel, dim3((unsigned)cdiv(entries, 256)), dim3(256), 0, st, a, table);
+    hipLaunchKernelGGL(code_table_kernel, dim3((unsigned)cdiv(entries, 256)), dim3(256), 0, st, a, table, whole_steps(cfg) ? 0 : 1);
     if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
     a.codes = table;
   }

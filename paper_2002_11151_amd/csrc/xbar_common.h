@@ -158,11 +158,16 @@ static inline size_t weight_sums_bytes(const xbar_config* c, int K, int N) {
   return (c->flags & XBAR_INPUT_OFFSET) ? align256((size_t)8 * ((size_t)K + N)) : 0;
 }
 
+// Arrays of whole 64-row and 64-column steps: the 64 x 64 patches of the 6-bit generator straddle none, so one kernel writes
+// both plane copies with what they share in LDS; others write each copy on its own.
+static inline bool whole_steps(const xbar_config* c) { return c->xbar_rows % 64 == 0 && c->xbar_cols % 64 == 0; }
+
 // Term codes of every plane value that can occur, kept behind the weight sums.  With the single-path wire
 // model alone (kFmtF6, one converter per column) a plane value depends only on the digit, the sign of the
 // weight and the place of the device pair in its array, so xbar_tile computes each once and the plane
 // generators look them up: [orientation][sign][digit - 1][row][column] words of 32 bits, term j's 6-bit
-// code at bit 6 j; orientation 1 is the same table with rows and columns exchanged.
+// code at bit 6 j; orientation 1 is the same table with rows and columns exchanged, for the copy on its own of
+// arrays that are no whole steps of 64.
 static inline bool uses_code_table(const Derived& d) {
   return d.fmt == kFmtF6 && d.npol == 1 && d.array_ni == XBAR_NI_WIRE_AAM;
 }
@@ -170,12 +175,8 @@ static inline size_t code_table_words(const xbar_config* c) {
   return (size_t)2 * ((1u << c->slice_bits) - 1) * c->xbar_rows * c->xbar_cols;   // one orientation
 }
 static inline size_t code_table_bytes(const xbar_config* c, const Derived& d) {
-  return uses_code_table(d) ? align256(2 * code_table_words(c) * sizeof(uint32_t)) : 0;
+  return uses_code_table(d) ? align256((whole_steps(c) ? 1 : 2) * code_table_words(c) * sizeof(uint32_t)) : 0;
 }
-
-// Arrays of whole 64-row and 64-column steps: the 64 x 64 patches of the 6-bit generator straddle none, so one kernel writes
-// both plane copies with what they share in LDS; others write each copy on its own.
-static inline bool whole_steps(const xbar_config* c) { return c->xbar_rows % 64 == 0 && c->xbar_cols % 64 == 0; }
 
 // General 6-bit generator (variation, stored profile, all-paths model, one array alone): every device is computed
 // once -- its term codes as one 32-bit word (term j at bit 6 j) -- and both plane copies are packed from those words.

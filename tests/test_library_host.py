@@ -102,10 +102,11 @@ def test_size_queries(xb):
     base = dict(xbar_rows=128, xbar_cols=128, weight_bits=16, slice_bits=2)
     c = xb.make_config(flags=xb.NI_WIRE_AAM, **base)
     frag = lambda terms, arrays=1: ((2 * 2 + 1 * 5) * 8 * terms * 2 * 1536) * arrays + pad256(1024) * 2
-    # single-path wire model alone: the table of term codes (2 orientations x 2 signs x 3 digits x 128 x 128
-    # words) rides behind the planes
-    table = 2 * 2 * 3 * 128 * 128 * 4
+    # single-path wire model alone: the table of term codes (2 signs x 3 digits x 128 x 128 words) rides behind the
+    # planes, in both orientations where arrays are no whole steps of 64 rows and columns
+    table = 2 * 3 * 128 * 128 * 4
     assert xb.planes_bytes(c, K, N) == frag(4) + table
+    assert xb.planes_bytes(xb.make_config(flags=xb.NI_WIRE_AAM, **dict(base, xbar_rows=96)), K, N) == frag(4) + 2 * 2 * 3 * 96 * 128 * 4
     # any other array non-ideality: every device is computed once into a word of term codes, from which both copies are
     # packed -- kept on chip where arrays are whole steps of 64 rows and columns, else a word per array, slice and weight
     # behind the planes
