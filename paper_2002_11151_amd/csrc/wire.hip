@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void wire_rows_kernel(WireArgs a) {
       if (j < cols) wire_device_pair(a, rng, k0 + i, n0 + j, s, g);
       line[wave][j] = make_double2(g[0], g[1]);
     }
-    __builtin_amdgcn_wave_barrier();               // one wave: its LDS writes are ordered before its LDS reads
+    wave_exchange();
     double l0[4][2], l1[4][2];                     // inclusive prefixes inside the lane
     double run0[2] = {0.0, 0.0}, run1[2] = {0.0, 0.0};
 #pragma unroll
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void wire_rows_kernel(WireArgs a) {
         }
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_exchange();                               // the next row is written over this one
   }
 }
 

@@ -340,7 +340,7 @@ __global__ __launch_bounds__(256) void tile_planes_f6_words_kernel(TileArgs a) {
       mine[cl][lane & 31] = (o < Lo && cl < c_count) ? words[(size_t)(c_first + cl) * a.N + o] : 0u;
     }
   }
-  __builtin_amdgcn_wave_barrier();                  // one wave: its LDS writes are ordered before its LDS reads
+  wave_exchange();
   const int ol = lane & 31, half = lane >> 5;
   uint32_t rec[kMaxTermsF6][6];
 #pragma unroll

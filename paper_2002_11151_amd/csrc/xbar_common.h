@@ -287,6 +287,14 @@ __device__ __forceinline__ uint64_t effective_step(uint64_t step, const unsigned
   return step + (step_add ? (uint64_t)*step_add : 0ull);
 }
 
+// Between writing and reading LDS that the lanes of one wave exchange: orders the accesses for the compiler; one wave's LDS
+// operations complete in order, so it costs no instruction.
+__device__ __forceinline__ void wave_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ double clampd(double x, double lo, double hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
 // Weight as its signed integer: rne(clamp(W / w_max) * Qw).  The product with the rounded factor Qw / w_max is within
