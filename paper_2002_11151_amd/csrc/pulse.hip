@@ -546,9 +546,11 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   }
 }
 
+int move_mode(const PulseArgs& a, bool nl) { return !nl ? 0 : a.v <= 1.0 / 32.0 ? 1 : 2; }   // NL of pulse_stream_kernel
+
 template <int L>
 void launch_pulse_stream(const PulseArgs& a, bool nl, bool noise, hipStream_t st) {
-  const int mode = !nl ? 0 : a.v <= 1.0 / 32.0 ? 1 : 2;
+  const int mode = move_mode(a, nl);
   void (*k)(PulseArgs);
   if (noise) k = mode == 0 ? pulse_stream_kernel<L, 0, true> : mode == 1 ? pulse_stream_kernel<L, 1, true> : pulse_stream_kernel<L, 2, true>;
   else k = mode == 0 ? pulse_stream_kernel<L, 0, false> : mode == 1 ? pulse_stream_kernel<L, 1, false> : pulse_stream_kernel<L, 2, false>;
@@ -663,7 +665,13 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
     if (p.two_phase) {
       a.n_words = cdiv(a.mc, 64);
       const long long devices = (long long)K * N;
-      const bool stream = devices < (noise ? 49152 : 32768);
+      // Up to where several lanes per device (below) beat one: all of them run through every move, so the line falls with
+      // a move's own cost (linear, series, exp()) and rises where a normal number per pulse is shared out.  One lane /
+      // several, ms per update of so many devices x samples, or the ratio: linear 27916 devices 0.82, 34112 1.01; series
+      // 19561 0.87, 26112 x 52424 43.3 / 53.5; exp() 7038 0.96, 25400 x 6209 7.6 / 12.5; with noise: linear 44550 0.88, series
+      // 36386 0.91, 46506 x 2554 6.6 / 7.6, exp() 28086 0.96, 46658 x 12371 94 / 155
+      const int line[2][3] = {{32768, 20480, 8192}, {49152, 40960, 28672}};
+      const bool stream = devices < line[noise ? 1 : 0][move_mode(a, nl)];
       const unsigned tiles16 = (unsigned)(cdiv(K, 16) * cdiv(N, 16));
       // measured, ms per update, [n_words][K N] / [K N][n_words], walks of one lane per device: noise, 65536 devices x 12544
       // samples 2.23 / 2.27, x 50176 8.53 / 8.93, 524288 x 4096 4.12 / 4.23; without, 65536 x 50176 4.19 / 4.60, 44100 x 100352
@@ -675,8 +683,8 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
       hipLaunchKernelGGL(pulse_mark_kernel, dim3(tiles16 * (unsigned)cdiv(a.n_words, a.seg_words)), dim3(256), 0, st, a);
       if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
       // few devices: several lanes per device, so that about a thousand waves or more share the walk (measured with
-      // noise, ms per update, lanes per device 64 / 32 / 16 / none: 432 devices x 131072 samples 0.77 / 1.01 / 1.58 / 7.85,
-      // 2304 x 131072 2.66 / 2.55 / 2.94 / 14.2, 18432 x 8192 1.10 / 0.87 / 0.82 / 1.31, 65536 x 12544 4.6 / 3.5 / 3.0 / 2.7)
+      // noise, ms per update, lanes per device 64 / 32 / 16: 432 devices x 131072 samples 0.77 / 1.01 / 1.58, 2304 x 131072
+      // 2.66 / 2.55 / 2.94, 18432 x 8192 1.10 / 0.87 / 0.82)
       if (stream && devices < 1024) launch_pulse_stream<64>(a, nl, noise, st);
       else if (stream && devices < 12288) launch_pulse_stream<32>(a, nl, noise, st);
       else if (stream) launch_pulse_stream<16>(a, nl, noise, st);

@@ -80,6 +80,14 @@ def test_pulsed_walk(xo, xb, M, K, N, density, v, ni):
         assert np.array_equal(Wg.cpu().numpy(), Wo)
 
 
+# ... on both sides of the lines between several lanes per device and one, for each cost of a move
+@pytest.mark.parametrize("K,N,v,ni", [(128, 255, 0.0, ""), (128, 257, 0.0, ""), (128, 159, 0.01, "nl"), (128, 161, 0.01, "nl"), (64, 127, 0.04, "nl"),
+                                      (64, 129, 0.04, "nl"), (128, 383, 0.0, "noise"), (128, 385, 0.0, "noise"), (128, 319, 0.01, "nl+noise"),
+                                      (128, 321, 0.01, "nl+noise"), (128, 223, 0.04, "nl+noise"), (128, 225, 0.04, "nl+noise")])
+def test_lines_of_the_pulsed_walk(xo, xb, K, N, v, ni):
+    test_pulsed_walk(xo, xb, 2048, K, N, 0.02, v, ni)
+
+
 # Weights that are no numbers or lie at or beyond the range, in devices with pulses in every batch, in some and in none (rows
 # that are driven often, rarely and never): every walk leaves what the pulse-by-pulse clamp leaves, to the bit of a zero
 @pytest.mark.parametrize("M,K,N", [(2100, 20, 40), (2100, 64, 40), (2048, 300, 170), (300, 20, 40)])
