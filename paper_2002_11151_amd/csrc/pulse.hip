@@ -408,8 +408,8 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   uint32_t* sq = samples[grp];
   uint32_t* pq = pulses[grp];
   const double2* mv = &moves[grp * L];
-  const double g_begin = a.first ? (double)a.W[dev] / a.w_max : a.state[dev];
-  double g = g_begin;
+  auto begin = [&]() __attribute__((always_inline)) { return a.first ? (double)a.W[dev] / a.w_max : a.state[dev]; };
+  double g = begin();
   double gx = clampd(g, -1.0, 1.0);                  // where the non-linearity finds the state
   bool pulsed = false;
   const double up_down = 2.0 * a.dw_min;
@@ -538,6 +538,8 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   for (int d = 1; d < L; d <<= 1) moved += __shfl_xor(moved, d, L);
   // The moves' minimum and maximum drop a NaN, which a clamp by comparison keeps; a step is finite, so the state is NaN
   // at the end only if it began as one.  A device without a pulse keeps what it held to the bit (a moved -0 is +0).
+  // Read again rather than held in registers through the walk.
+  const double g_begin = begin();
   if (!pulsed || g_begin != g_begin) g = g_begin;
   if (valid && gl == 0) {
     if (a.last) a.W[dev] = (float)(a.w_max * g);
