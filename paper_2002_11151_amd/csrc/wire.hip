@@ -217,7 +217,8 @@ int launch_wire_model(const xbar_config* cfg, const float* W, int K, int N, floa
   const unsigned tiles = (unsigned)(cdiv(K, cfg->xbar_rows) * w.tiles_c);
   hipLaunchKernelGGL(wire_rows_kernel, dim3(tiles * (unsigned)cdiv(cfg->xbar_rows, 8), (unsigned)d.S_w), dim3(256), 0, st, w);
   if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
-  // 32 columns per block up to 128 rows, 16 beyond: four rows per thread, and the devices of two blocks fit one LDS
+  // 32 columns per block up to 128 rows, 16 beyond: at most four rows per thread, whose devices take 64 KiB of LDS beside 32 of
+  // sums, so one block of sixteen waves has a compute unit to itself
   return cfg->xbar_rows <= 128 ? launch_wire_cols<32>(w, tiles, st) : launch_wire_cols<16>(w, tiles, st);
 }
 
