@@ -305,3 +305,24 @@ def test_conv_is_its_patches(xb, batch, image, cin, cout, kernel, stride, pad, m
         for kw_ in range(kernel):
             want[:, kh:kh + geom.out_h * stride:stride, kw_:kw_ + geom.out_w * stride:stride] += cols[:, :, :, kh, kw_]
     assert np.array_equal(dX, want[:, pad:pad + image, pad:pad + image])
+
+
+# How a block leaves its sums: scaled outputs, 32- and 64-bit partial sums, sums widened on the way, rows that are whole quads
+# and others, the last patch of rows and outputs.  A row's outputs do not depend on the rows beside it, and few rows are cut
+# into more chunks of the contraction, or taken by one kernel.
+@pytest.mark.parametrize("R,sb,wb,adc,M,K,signed", [(128, 1, 16, 8, 40000, 64, False), (128, 1, 16, 8, 3000, 300, True), (16, 1, 16, 8, 52500, 128, True),
+                                                    (128, 4, 16, 8, 30000, 144, True), (64, 4, 16, 12, 3000, 300, True)])
+@pytest.mark.parametrize("N", [97, 98, 99, 100])
+def test_rows_do_not_depend_on_the_batch(xb, R, sb, wb, adc, M, K, signed, N):
+    fs = 1.037 * workloads.adc_full_scale(R, sb, 2)
+    cfg = xb.make_config(xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=2, stream_bits=sb, adc_bits=adc,
+                         flags=xb.NI_WIRE_AAM | (xb.INPUT_SIGNED if signed else 0), adc_fs_fwd=fs, adc_fs_bwd=fs, seed=4)
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    W = torch.randn((K, N), generator=gen, device="cuda")
+    X = torch.randn((M, K), generator=gen, device="cuda")
+    dY = torch.randn((M, N), generator=gen, device="cuda")
+    planes = xb.tile(cfg, W, 5.0, 0)
+    Y, dX = xb.fwd(cfg, planes, X, N, 5.0, 3.0), xb.bwd(cfg, planes, dY, K, 5.0, 3.0)
+    for rows in (slice(0, 70), slice(M - 1000, M)):
+        assert torch.equal(Y[rows], xb.fwd(cfg, planes, X[rows].clone(), N, 5.0, 3.0))
+        assert torch.equal(dX[rows], xb.bwd(cfg, planes, dY[rows].clone(), K, 5.0, 3.0))
