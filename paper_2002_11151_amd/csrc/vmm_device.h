@@ -147,13 +147,14 @@ struct VmmArgs {
   int sg;                     // kFmtF6: slices per staged group
   int scale_lo, scale_hi;     // kFmtF6: block-scale bytes (127 + exponent) of terms 0..3 and of term 4
   int vt_per_chunk, nchunk, lds_kb;
-  int split_sg;               // slices per 32-bit group of the split wide path
+  int split_sg;               // two 32-bit sums per output: slices of the lower one
   int flush_every;            // 32-bit sums: added to the block's own 64-bit partial sum every so many virtual tiles (0: never)
   int direct;                 // single chunk and nothing to correct: the kernel scales and stores the result itself
   int total_wg, per_xcd;
   float gain;          // float(Q) / adc_fs
   float clamp_lo, clamp_hi;   // kMagic -+ Q
-  uint32_t bias_per_vt;       // kMagicBits * sum of all shift weights, mod 2^32
+  uint32_t bias_per_vt;       // kMagicBits * sum of all shift weights (two sums: of the lower slices), mod 2^32
+  uint32_t bias_high_per_vt;  //   of the upper slices, relative to the first of them
   float* out;                 // final output, written directly when there is a single chunk
   double scale;               // lsb * in_scale * w_max / (Qa * Qw)
 };
@@ -473,12 +474,26 @@ __device__ __forceinline__ void vmm_tile_group(const VmmArgs& a, const u32x4* ld
 
 // One virtual tile (phase, contraction tile): load the raw magnitudes, then loop over slice groups:
 // stage the plane fragments of the group in LDS (compact: only the NK used k-steps), compute.
-// WIDE: 0 = 32-bit sums, 1 = 64-bit sums in registers (general path), 2 = one slice group per call
-// (the one that starts at slice `only_sg0`) summed in 32 bits with shifts relative to the group; the
-// caller widens and adds up the groups.
+// WIDE: 0 = 32-bit sums, 1 = 64-bit sums in registers (general path), 2 = two 32-bit sums per output: y adds up the lower
+// slices (split_sg of them), yh the upper ones, each with shifts relative to its first slice; the block widens both at the end.
+// Each sum takes its turn in y, so that one copy of the pipelined code serves both.  256 x 64 weights, 200704 rows, 10-bit
+// converter, forward, backward and update: 1802 -> 1498 us against one 32-bit sum at a time, a pass over the chunk's tiles for
+// each group of slices and a 64-bit partial result that was read and rewritten between them.
+template <int PM>
+__device__ __forceinline__ void swap_sums(uint32_t (&y)[PM][16], uint32_t (&yh)[PM][16]) {
+#pragma unroll
+  for (int pm = 0; pm < PM; ++pm)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const uint32_t t = y[pm][r];
+      y[pm][r] = yh[pm][r];
+      yh[pm][r] = t;
+    }
+}
+
 template <int PM, int KSMAX, int NK, int TERMS, int WIDE, bool CODES, bool PER_ARRAY>
 __device__ __forceinline__ void vmm_tile(const VmmArgs& a, u32x4* lds, int p, int pol, int t, int lane, int mp0, int op,
-                                         uint32_t (&y)[PM][16], long long (&y64)[PM][16], int only_sg0) {
+                                         uint32_t (&y)[PM][16], uint32_t (&yh)[PM][16], long long (&y64)[PM][16]) {
 
   u32x2 raw[PM][KSMAX];
 #pragma unroll
@@ -490,10 +505,12 @@ __device__ __forceinline__ void vmm_tile(const VmmArgs& a, u32x4* lds, int p, in
       raw[pm][j] = v;
     }
   constexpr int NF = TERMS * NK;
-  const int sg = WIDE == 2 ? a.split_sg : min(a.S_w, a.lds_kb / NF);   // slices per staged group
-  const int sg_first = WIDE == 2 ? only_sg0 : 0, sg_end = WIDE == 2 ? only_sg0 + sg : a.S_w;
-  for (int sg0 = sg_first; sg0 < sg_end; sg0 += sg) {
-    const int ns = min(sg, a.S_w - sg0);
+  const int sg_max = min(a.S_w, a.lds_kb / NF);      // slices per staged group
+  const int sg = WIDE == 2 ? sg_max & ~1 : sg_max;
+  for (int sg0 = 0, ns; sg0 < a.S_w; sg0 += ns) {
+    // sums of two halves: a staged group lies in one of them
+    ns = min(sg, (WIDE == 2 && sg0 < a.split_sg ? a.split_sg : a.S_w) - sg0);
+    if (WIDE == 2 && sg0 == a.split_sg) swap_sums<PM>(y, yh);
     const u32x4* src = a.B + (((size_t)t * a.OP + op) * a.S_w + sg0) * TERMS * a.ks * 64;
     if constexpr (PER_ARRAY) src += (size_t)pol * a.pol_stride;
     __syncthreads();                                   // everyone is done with the previous group
@@ -512,7 +529,8 @@ __device__ __forceinline__ void vmm_tile(const VmmArgs& a, u32x4* lds, int p, in
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if constexpr (WIDE == 2) {
-      vmm_tile_group_pipelined<PM, KSMAX, NK, TERMS, PER_ARRAY>(a, lds, raw, ns, 0, p, pol, lane, y);
+      vmm_tile_group_pipelined<PM, KSMAX, NK, TERMS, PER_ARRAY>(a, lds, raw, ns, sg0 < a.split_sg ? sg0 : sg0 - a.split_sg, p, pol,
+                                                                lane, y);
     } else {
       if (!WIDE && !CODES && (ns & 1) == 0)
         vmm_tile_group_pipelined<PM, KSMAX, NK, TERMS, PER_ARRAY>(a, lds, raw, ns, sg0, p, pol, lane, y);
@@ -520,6 +538,7 @@ __device__ __forceinline__ void vmm_tile(const VmmArgs& a, u32x4* lds, int p, in
         vmm_tile_group<PM, KSMAX, NK, TERMS, WIDE == 1, CODES, PER_ARRAY>(a, lds, raw, ns, sg0, p, pol, t, lane, mp0, op, y, y64);
     }
   }
+  if (WIDE == 2) swap_sums<PM>(y, yh);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -699,7 +718,7 @@ __device__ __forceinline__ void vmm6_tile_group(const VmmArgs& a, const char* ld
 // One virtual tile on the 6-bit path: NK64 k-steps of 64 rows (nk16 staged input steps of 16).
 template <int PM, int NK64, int NT, int WIDE, bool CODES, bool PER_ARRAY>
 __device__ __forceinline__ void vmm6_tile(const VmmArgs& a, u32x4* lds, int p, int pol, int t, int nk16, int lane, int mp0,
-                                          int op, uint32_t (&y)[PM][16], long long (&y64)[PM][16], int only_sg0) {
+                                          int op, uint32_t (&y)[PM][16], uint32_t (&yh)[PM][16], long long (&y64)[PM][16]) {
   u32x2 raw[PM][4 * NK64];
 #pragma unroll
   for (int pm = 0; pm < PM; ++pm)
@@ -711,10 +730,10 @@ __device__ __forceinline__ void vmm6_tile(const VmmArgs& a, u32x4* lds, int p, i
     }
   constexpr int STRIDE = f6_term_stride(NK64);
   constexpr int UNITS = STRIDE / 1024;               // KiB copies per (slice, term)
-  const int sg = WIDE == 2 ? a.split_sg : a.sg;
-  const int sg_first = WIDE == 2 ? only_sg0 : 0, sg_end = WIDE == 2 ? only_sg0 + sg : a.S_w;
-  for (int sg0 = sg_first; sg0 < sg_end; sg0 += sg) {
-    const int ns = min(sg, a.S_w - sg0);
+  for (int sg0 = 0, ns; sg0 < a.S_w; sg0 += ns) {
+    // sums of two halves: a staged group lies in one of them
+    ns = min(a.sg, (WIDE == 2 && sg0 < a.split_sg ? a.split_sg : a.S_w) - sg0);
+    if (WIDE == 2 && sg0 == a.split_sg) swap_sums<PM>(y, yh);
     // global [slice][term][k-steps of the whole tile][1.5 KiB] -> LDS [slice][term][STRIDE]: only the NK64 used steps
     const u32x4* src = a.B + (((size_t)t * a.OP + op) * a.S_w + sg0) * NT * a.ks * 96;
     if constexpr (PER_ARRAY) src += (size_t)pol * a.pol_stride;
@@ -728,7 +747,7 @@ __device__ __forceinline__ void vmm6_tile(const VmmArgs& a, u32x4* lds, int p, i
     __syncthreads();
     const char* stage = reinterpret_cast<const char*>(lds);
     if constexpr (WIDE == 2) {
-      vmm6_tile_group_pipelined<PM, NK64, NT, PER_ARRAY>(a, stage, raw, ns, 0, p, pol, lane, y);
+      vmm6_tile_group_pipelined<PM, NK64, NT, PER_ARRAY>(a, stage, raw, ns, sg0 < a.split_sg ? sg0 : sg0 - a.split_sg, p, pol, lane, y);
     } else {
       if (!WIDE && !CODES && (ns & 1) == 0)
         vmm6_tile_group_pipelined<PM, NK64, NT, PER_ARRAY>(a, stage, raw, ns, sg0, p, pol, lane, y);
@@ -736,6 +755,7 @@ __device__ __forceinline__ void vmm6_tile(const VmmArgs& a, u32x4* lds, int p, i
         vmm6_tile_group<PM, NK64, NT, WIDE == 1, CODES, PER_ARRAY>(a, stage, raw, ns, sg0, p, pol, t, lane, mp0, op, y, y64);
     }
   }
+  if (WIDE == 2) swap_sums<PM>(y, yh);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -745,12 +765,12 @@ __device__ __forceinline__ void vmm6_tile(const VmmArgs& a, u32x4* lds, int p, i
 template <int PM, int KSMAX, int TERMS, int WIDE, bool CODES, bool PER_ARRAY>
 struct TileF16 {
   __device__ __forceinline__ void operator()(const VmmArgs& a, u32x4* lds, int p, int pol, int t, int rows, int lane, int mp0,
-                                             int op, uint32_t (&y)[PM][16], long long (&y64)[PM][16], int only_sg0) const {
+                                             int op, uint32_t (&y)[PM][16], uint32_t (&yh)[PM][16], long long (&y64)[PM][16]) const {
     const int nk = (rows + 15) >> 4;
 #define XBAR_NK_CASE(n) \
   case n:               \
     if constexpr (n <= KSMAX)                                                                                       \
-      vmm_tile<PM, KSMAX, n, TERMS, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, lane, mp0, op, y, y64, only_sg0); \
+      vmm_tile<PM, KSMAX, n, TERMS, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, lane, mp0, op, y, yh, y64);       \
     break;
     switch (nk) {
       XBAR_NK_CASE(1) XBAR_NK_CASE(2) XBAR_NK_CASE(3) XBAR_NK_CASE(4) XBAR_NK_CASE(5) XBAR_NK_CASE(6)
@@ -765,13 +785,13 @@ struct TileF16 {
 template <int PM, int NT, int WIDE, bool CODES, bool PER_ARRAY>
 struct TileF6 {
   __device__ __forceinline__ void operator()(const VmmArgs& a, u32x4* lds, int p, int pol, int t, int rows, int lane, int mp0,
-                                             int op, uint32_t (&y)[PM][16], long long (&y64)[PM][16], int only_sg0) const {
+                                             int op, uint32_t (&y)[PM][16], uint32_t (&yh)[PM][16], long long (&y64)[PM][16]) const {
     const int nk16 = (rows + 15) >> 4;
     switch ((rows + 63) >> 6) {
-      case 1: vmm6_tile<PM, 1, NT, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, nk16, lane, mp0, op, y, y64, only_sg0); break;
-      case 2: vmm6_tile<PM, 2, NT, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, nk16, lane, mp0, op, y, y64, only_sg0); break;
-      case 3: vmm6_tile<PM, 3, NT, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, nk16, lane, mp0, op, y, y64, only_sg0); break;
-      case 4: vmm6_tile<PM, 4, NT, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, nk16, lane, mp0, op, y, y64, only_sg0); break;
+      case 1: vmm6_tile<PM, 1, NT, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, nk16, lane, mp0, op, y, yh, y64); break;
+      case 2: vmm6_tile<PM, 2, NT, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, nk16, lane, mp0, op, y, yh, y64); break;
+      case 3: vmm6_tile<PM, 3, NT, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, nk16, lane, mp0, op, y, yh, y64); break;
+      case 4: vmm6_tile<PM, 4, NT, WIDE, CODES, PER_ARRAY>(a, lds, p, pol, t, nk16, lane, mp0, op, y, yh, y64); break;
       default: break;
     }
   }
@@ -837,13 +857,13 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
     }
   }
 
-  uint32_t y[PM][16];
+  uint32_t y[PM][16], yh[PM][16];
   long long y64[PM][16];
 #pragma unroll
   for (int pm = 0; pm < PM; ++pm)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      y[pm][r] = 0;
+      y[pm][r] = yh[pm][r] = 0;
       y64[pm][r] = 0;
     }
 
@@ -851,44 +871,6 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
   const int vt_base = a.VT / a.nchunk, vt_rem = a.VT - vt_base * a.nchunk;
   const int vt0 = chunk * vt_base + min(chunk, vt_rem);
   const int vt1 = vt0 + vt_base + (chunk < vt_rem ? 1 : 0);
-#define XBAR_ALL_VIRTUAL_TILES                                                                              \
-  for (int vt = vt0; vt < vt1; ++vt) {                                                                      \
-    /* vt = (phase, array, tile), tile fastest */                                                           \
-    const int pa = vt / a.T, t = vt - pa * a.T;                                                             \
-    const int p = PER_ARRAY ? pa >> 1 : pa, pol = PER_ARRAY ? pa & 1 : 0;                                   \
-    const int rows = min(a.tile, a.Lin - t * a.tile);                                                       \
-    run_tile(a, lds, p, pol, t, rows, lane, mp0, op, y, y64, only_sg0);                                     \
-  }
-  if constexpr (WIDE == 2) {
-    // Sums that overflow 32 bits, fast path: one pass over the chunk's virtual tiles per slice group,
-    // each summed in 32 bits with shifts relative to the group's first slice, then widened, shifted
-    // into place and added to the chunk's 64-bit partial result (every element has one owner lane).
-    const uint32_t bias = a.bias_per_vt * (uint32_t)(vt1 - vt0);
-    long long* part = reinterpret_cast<long long*>(a.part) + (size_t)chunk * a.M * a.Lout;
-    for (int only_sg0 = 0; only_sg0 < a.S_w; only_sg0 += a.split_sg) {
-      XBAR_ALL_VIRTUAL_TILES
-      const int up = a.slice_bits * only_sg0;
-      // the element addresses are the same for every group: keep the compiler from computing all of
-      // them ahead of the loop, where they would sit in registers throughout the contraction
-      int lane_now = lane, mp_now = mp0;
-      asm volatile("" : "+v"(lane_now), "+v"(mp_now));
-#pragma unroll
-      for (int pm = 0; pm < PM; ++pm)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = (mp_now + pm) * 32 + (lane_now & 31);
-          const int o = op * 32 + 8 * (r >> 2) + 4 * (lane_now >> 5) + (r & 3);
-          if (m < a.M && o < a.Lout && mp_now + pm < a.MP) {
-            long long v = (long long)(int32_t)(y[pm][r] - bias) << up;
-            if (only_sg0) v += part[(size_t)m * a.Lout + o];
-            part[(size_t)m * a.Lout + o] = v;
-          }
-          y[pm][r] = 0;
-        }
-    }
-    return;
-  }
-#undef XBAR_ALL_VIRTUAL_TILES
   // 32-bit sums hold only a few virtual tiles (3 with 16-bit weights, 8-bit inputs and an 8-bit converter).
   // Rather than cutting the contraction into that many more chunks, each with a partial result of its own
   // in memory, a block with more virtual tiles than that adds its sums to a 64-bit partial result every
@@ -900,14 +882,16 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
     const int pa = vt / a.T, t = vt - pa * a.T;
     const int p = PER_ARRAY ? pa >> 1 : pa, pol = PER_ARRAY ? pa & 1 : 0;
     const int rows = min(a.tile, a.Lin - t * a.tile);
-    run_tile(a, lds, p, pol, t, rows, lane, mp0, op, y, y64, 0);
+    run_tile(a, lds, p, pol, t, rows, lane, mp0, op, y, yh, y64);
     ++since;
     if constexpr (WIDE == 0) {
       if (flushing && since == a.flush_every && vt + 1 < vt1) {
         const bool first = vt + 1 - vt0 == a.flush_every;
         const uint32_t bias = a.bias_per_vt * (uint32_t)since;
         long long* part = reinterpret_cast<long long*>(a.part) + (size_t)chunk * a.M * a.Lout;
-        int lane_now = lane, mp_now = mp0;              // as above: no element addresses kept across the contraction
+        // keep the compiler from computing the element addresses ahead of the loop, where they would sit in registers
+        // throughout the contraction
+        int lane_now = lane, mp_now = mp0;
         asm volatile("" : "+v"(lane_now), "+v"(mp_now));
 #pragma unroll
         for (int pm = 0; pm < PM; ++pm)
@@ -939,7 +923,7 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
     }
   }
   // partial result of this chunk
-  const uint32_t bias = a.bias_per_vt * (uint32_t)since;
+  const uint32_t bias = a.bias_per_vt * (uint32_t)since, bias_high = a.bias_high_per_vt * (uint32_t)since;
 #pragma unroll
   for (int pm = 0; pm < PM; ++pm)
 #pragma unroll
@@ -949,7 +933,10 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
         const size_t idx = ((size_t)chunk * a.M + m) * a.Lout + o;
         long long sum[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] = WIDE ? y64[pm][4 * g + e] : (long long)(int32_t)(y[pm][4 * g + e] - bias);
+        for (int e = 0; e < 4; ++e) {
+          sum[e] = WIDE == 1 ? y64[pm][4 * g + e] : (long long)(int32_t)(y[pm][4 * g + e] - bias);
+          if (WIDE == 2) sum[e] += (long long)(int32_t)(yh[pm][4 * g + e] - bias_high) << (a.slice_bits * a.split_sg);
+        }
         if (flushing) add_stored4(reinterpret_cast<const long long*>(a.part) + idx, sum, a.Lout, o);
         if (a.direct) {        // nothing to add up across chunks: scale and store the result itself
           const float4 v = make_float4((float)((double)sum[0] * a.scale), (float)((double)sum[1] * a.scale),
@@ -985,10 +972,10 @@ struct VmmPlan {
   int ks16;            // k-steps of 16 rows per tile in the staged input
   int sg;              // kFmtF6: slices per staged group
   int Lin, Lout, MP, P, VT, vt_per_chunk, nchunk, pm, nw, MB, lds_kb;
-  int wide;            // 0: sums fit 32 bits; 1: 64-bit sums; 2: 32-bit sums per slice group, widened per group
+  int wide;            // 0: sums fit 32 bits; 1: 64-bit sums; 2: two 32-bit sums, of the lower and the upper slices
   int flush_every;     // wide == 0: virtual tiles a 32-bit sum holds, when a chunk has more than that (else 0)
-  int split_sg;        // slices per group of mode 2
-  uint32_t bias_split; // kMagicBits * sum of the shift weights of one such group, mod 2^32
+  int split_sg;        // slices of the lower sum of mode 2
+  uint32_t bias_split[2];   // kMagicBits * sum of the shift weights of either sum, mod 2^32
   int offset;          // signed inputs in one phase of offset-binary codes
   int narrow;          // the sum over all virtual tiles fits 32 bits
   int small;           // few output patches: one kernel does the whole pass (vmm_small.hip)

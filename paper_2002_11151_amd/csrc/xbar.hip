@@ -1441,24 +1441,21 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
     p.lds_kb = std::max(slice_kb, std::min(d.S_w * slice_kb, 64));   // staged slice group, at most 64 KiB
   }
   p.lds_bytes = (size_t)p.lds_kb * 1024;
-  // 64-bit sums: the software-pipelined path still serves if the slices split into equal, even
-  // groups that fit the LDS stage and whose own sum fits 32 bits
+  // Sums beyond 32 bits: the software-pipelined path still serves with two 32-bit sums per output, one of the lower and one of
+  // the upper slices, widened when the block is done -- if slices come in pairs and either sum holds a virtual tile at least.
   p.split_sg = 0;
-  p.bias_split = 0;
+  p.bias_split[0] = p.bias_split[1] = 0;
   unsigned long long fit_split = 0;
-  if (p.wide) {
-    for (int sg = std::min(d.S_w, p.lds_kb / slice_kb) & ~1; sg >= 2; sg -= 2) {
-      if (d.S_w % sg) continue;
-      unsigned long long wg = 0;
-      for (int s = 0; s < sg; ++s)
-        for (int b = 0; b < d.S_in; ++b) wg += 1ull << (c->slice_bits * s + c->stream_bits * b);
-      const unsigned long long f = ((1ull << 31) - 1) / (wg * (unsigned long long)d.q_adc);
-      if (f < 1) continue;
+  if (p.wide && d.S_w % 2 == 0 && d.S_w > 2 && p.lds_kb / slice_kb >= 2) {
+    const int low = (d.S_w / 2 + 1) & ~1;
+    unsigned long long wg[2] = {0, 0};
+    for (int s = 0; s < d.S_w; ++s)
+      for (int b = 0; b < d.S_in; ++b) wg[s >= low] += 1ull << (c->slice_bits * (s >= low ? s - low : s) + c->stream_bits * b);
+    fit_split = ((1ull << 31) - 1) / (std::max(wg[0], wg[1]) * (unsigned long long)d.q_adc);
+    if (fit_split >= 1) {
       p.wide = 2;
-      p.split_sg = sg;
-      p.bias_split = (uint32_t)((unsigned long long)kMagicBits * wg);
-      fit_split = f;
-      break;
+      p.split_sg = low;
+      for (int h = 0; h < 2; ++h) p.bias_split[h] = (uint32_t)((unsigned long long)kMagicBits * wg[h]);
     }
   }
   p.pm = (d.fmt == kFmtF6 || p.g.ks <= 8) ? 2 : 1;
@@ -1606,16 +1603,17 @@ int run_vmm(const xbar_config* cfg, const void* planes, const float* in, float* 
     if (j < 4) a.scale_lo |= byte << (8 * j);
     else a.scale_hi |= byte;
   }
-  const bool split = p.wide == 2 && !general;          // adds its groups up in the partial-sum buffer
+  const bool split = p.wide == 2 && !general;
   a.split_sg = p.split_sg;
   a.flush_every = hist ? 0 : p.flush_every;            // the statistics pass keeps no sums
-  a.direct = (p.nchunk == 1 && !p.offset && !split && !scatter) ? 1 : 0;   // a scatter gathers from the partial sums
+  a.direct = (p.nchunk == 1 && !p.offset && !scatter) ? 1 : 0;   // a scatter gathers from the partial sums
   a.total_wg = p.nchunk * p.g.OP * p.MB;
   a.per_xcd = cdiv(a.total_wg, 8);
   a.gain = (float)d.q_adc / adc_fs * dac_gain;
   a.clamp_lo = kMagic - (float)d.q_adc;
   a.clamp_hi = kMagic + (float)d.q_adc;
-  a.bias_per_vt = split ? p.bias_split : p.bias_per_vt;
+  a.bias_per_vt = split ? p.bias_split[0] : p.bias_per_vt;
+  a.bias_high_per_vt = split ? p.bias_split[1] : 0;
   a.out = out;
   {
     const double lsb = (double)adc_fs / (double)d.q_adc;
