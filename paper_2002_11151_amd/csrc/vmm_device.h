@@ -151,6 +151,7 @@ struct VmmArgs {
   int flush_every;            // 32-bit sums: added to the block's own 64-bit partial sum every so many virtual tiles (0: never)
   int direct;                 // single chunk and nothing to correct: the kernel scales and stores the result itself
   int total_wg, per_xcd;
+  int row_waves;       // waves of a block side by side along the rows; every row_waves waves take a share of the cycles
   float gain;          // float(Q) / adc_fs
   float clamp_lo, clamp_hi;   // kMagic -+ Q
   uint32_t bias_per_vt;       // kMagicBits * sum of all shift weights (two sums: of the lower slices), mod 2^32
@@ -325,6 +326,19 @@ __device__ __forceinline__ void adc_sign_and_range(const VmmArgs& a, int p, int 
   }
 }
 
+// Streaming cycles first .. end - 1 of this wave.  Few rows leave a block waves to spare: they share the cycles of the same
+// rows, read the same planes from LDS, and the block adds their sums up at the end.  Without them a compute unit, which holds
+// two blocks, has two waves for its four SIMDs up to 64 rows and four up to 128.  4096 x 4096 weights, 256 x 256 arrays, 128
+// rows: forward 498 -> 343 us, backward 925 -> 616; 1000 x 2048, 64 rows: backward 103 -> 49 (chunks chosen anew in all).
+struct CycleShare {
+  int first, end;
+};
+
+__device__ __forceinline__ CycleShare cycle_share(const VmmArgs& a) {
+  const int shares = (int)(blockDim.x >> 6) / a.row_waves, share = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / a.row_waves;
+  return CycleShare{a.S_in * share / shares, a.S_in * (share + 1) / shares};
+}
+
 // Software-pipelined slice group (fast path: 32-bit accumulators, no code tap, even slice count).
 template <int PM, int KSMAX, int NK, int TERMS, bool PER_ARRAY>
 __device__ __forceinline__ void vmm_tile_group_pipelined(const VmmArgs& a, const u32x4* lds,
@@ -339,7 +353,8 @@ __device__ __forceinline__ void vmm_tile_group_pipelined(const VmmArgs& a, const
   float16v acc0[PM], acc1[PM];
   int sh_prev = 0;
   float gain_prev = 0.f;
-  for (int b = 0; b < a.S_in; ++b) {
+  const CycleShare cycles = cycle_share(a);
+  for (int b = cycles.first; b < cycles.end; ++b) {
     const int in_shift = a.stream_bits * b;
     const uint32_t mask8 = digit_mask8 << in_shift;
     // operand lanes hold digit * 2^(in_shift - 24); undo that power of two in the ADC gain
@@ -352,7 +367,7 @@ __device__ __forceinline__ void vmm_tile_group_pipelined(const VmmArgs& a, const
       const int sh0 = a.slice_bits * (shift_slice0 + sl) + in_shift;
       const int sh1 = sh0 + a.slice_bits;
       // even slice -> acc0, while the ADC of the previous odd slice (acc1) runs
-      if (b == 0 && sl == 0)
+      if (b == cycles.first && sl == 0)
         vmm_contract_adc<PM, NK, TERMS, false, PER_ARRAY>(ab, bbase + (size_t)sl * NF * 64, acc0, acc1, gain_prev, clamp_lo,
                                                clamp_hi, sh_prev, y);
       else
@@ -429,7 +444,8 @@ __device__ __forceinline__ void vmm_tile_group(const VmmArgs& a, const u32x4* ld
   const uint32_t digit_mask8 = ((1u << a.stream_bits) - 1u) * 0x01010101u;
   float gain_p, clamp_lo, clamp_hi;
   adc_sign_and_range<PER_ARRAY>(a, p, pol, gain_p, clamp_lo, clamp_hi);
-  for (int b = 0; b < a.S_in; ++b) {
+  const CycleShare cycles = cycle_share(a);
+  for (int b = cycles.first; b < cycles.end; ++b) {
     const int in_shift = a.stream_bits * b;
     const uint32_t mask8 = digit_mask8 << in_shift;
     const float gain_b = ldexpf(gain_p, 24 - in_shift);
@@ -661,6 +677,7 @@ __device__ __forceinline__ void vmm6_tile_group_pipelined(const VmmArgs& a, cons
   int4v dg[PM][NK64];
   float16v acc0[PM], acc1[PM];
   int sh_prev = 0;
+  const CycleShare cycles = cycle_share(a);
   // one streaming cycle: digits, then every slice pair; `high`: the cycle's bits are in the high nibbles
   auto cycle = [&](int b, auto high) {
     const int in_shift = a.stream_bits * b;
@@ -669,7 +686,7 @@ __device__ __forceinline__ void vmm6_tile_group_pipelined(const VmmArgs& a, cons
     for (int sl = 0; sl < ns; sl += 2) {
       const int sh0 = a.slice_bits * (shift_slice0 + sl) + in_shift;
       const int sh1 = sh0 + a.slice_bits;
-      if (b == 0 && sl == 0)
+      if (b == cycles.first && sl == 0)
         vmm6_contract_adc<PM, NK64, NT, false, PER_ARRAY>(dg, xb + sl * SLICE, yb + sl * SLICE, acc0, acc1, gain, clamp_lo, clamp_hi,
                                                sh_prev, y, a.scale_lo, a.scale_hi);
       else
@@ -681,8 +698,8 @@ __device__ __forceinline__ void vmm6_tile_group_pipelined(const VmmArgs& a, cons
     }
   };
   const int b_low = min(a.S_in, 4 / a.stream_bits);   // cycles whose bits lie in the low nibbles
-  for (int b = 0; b < b_low; ++b) cycle(b, std::false_type{});
-  for (int b = b_low; b < a.S_in; ++b) cycle(b, std::true_type{});
+  for (int b = cycles.first; b < min(b_low, cycles.end); ++b) cycle(b, std::false_type{});
+  for (int b = max(b_low, cycles.first); b < cycles.end; ++b) cycle(b, std::true_type{});
   vmm_adc_narrow<PM>(acc1, gain, clamp_lo, clamp_hi, sh_prev, y);   // drain
 }
 
@@ -698,7 +715,8 @@ __device__ __forceinline__ void vmm6_tile_group(const VmmArgs& a, const char* ld
   const float gain = 2.0f * gain_p;
   const char* xb = lds + lane * 16;
   const char* yb = lds + 1024 + lane * 8;
-  for (int b = 0; b < a.S_in; ++b) {
+  const CycleShare cycles = cycle_share(a);
+  for (int b = cycles.first; b < cycles.end; ++b) {
     const int in_shift = a.stream_bits * b;
     int4v dg[PM][NK64];
 #pragma unroll
@@ -839,7 +857,7 @@ __device__ __forceinline__ void add_stored4(const long long* at, long long (&sum
 template <int PM, int WIDE, bool CODES, bool PER_ARRAY, class TileFn>
 __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const TileFn& run_tile) {
   // the wave index is the same for all lanes: as a scalar, everything derived from it (row patches, addresses) is scalar too
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // consecutive block ids go to different XCDs; give each XCD a contiguous range of logical work so
   // that blocks sharing the same planes share one L2
   const int logical = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
@@ -849,7 +867,7 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
   const int grp = logical / a.nchunk;
   const int mb = grp % a.MB;
   const int op = grp / a.MB;
-  const int mp0 = (mb * nw + wave) * PM;
+  const int share = wave / a.row_waves, mp0 = (mb * a.row_waves + wave - share * a.row_waves) * PM;
   if constexpr (CODES) {
     if (a.hist) {
       for (int i = threadIdx.x; i < kStatBins; i += blockDim.x) stat_hist[i] = 0;
@@ -922,6 +940,40 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
       return;
     }
   }
+  // the waves that share rows: the first of them adds the others' sums to its own (modulo 2^32: the converter's constant is
+  // taken off the whole sum below)
+  if ((int)blockDim.x > 64 * a.row_waves) {
+    constexpr int SETS = WIDE ? 2 : 1;               // 32-bit words per sum: two sums, or a 64-bit one
+    uint32_t* mine = reinterpret_cast<uint32_t*>(lds) + (size_t)(wave - a.row_waves) * SETS * PM * 16 * 64 + lane;
+    __syncthreads();                                 // everyone is done with the staged planes
+    if (share > 0) {
+#pragma unroll
+      for (int pm = 0; pm < PM; ++pm)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          uint32_t* at = mine + (pm * 16 + r) * SETS * 64;
+          at[0] = WIDE == 1 ? (uint32_t)y64[pm][r] : y[pm][r];
+          if (WIDE) at[64] = WIDE == 1 ? (uint32_t)((unsigned long long)y64[pm][r] >> 32) : yh[pm][r];
+        }
+    }
+    __syncthreads();
+    if (share > 0) return;
+    for (int w = wave + a.row_waves; w < (int)(blockDim.x >> 6); w += a.row_waves) {
+      const uint32_t* from = reinterpret_cast<const uint32_t*>(lds) + (size_t)(w - a.row_waves) * SETS * PM * 16 * 64 + lane;
+#pragma unroll
+      for (int pm = 0; pm < PM; ++pm)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const uint32_t* at = from + (pm * 16 + r) * SETS * 64;
+          if (WIDE == 1) {
+            y64[pm][r] += (long long)(at[0] | ((unsigned long long)at[64] << 32));
+          } else {
+            y[pm][r] += at[0];
+            if (WIDE) yh[pm][r] += at[64];
+          }
+        }
+    }
+  }
   // partial result of this chunk
   const uint32_t bias = a.bias_per_vt * (uint32_t)since, bias_high = a.bias_high_per_vt * (uint32_t)since;
 #pragma unroll
@@ -971,6 +1023,7 @@ struct VmmPlan {
   PlaneGeom g;
   int ks16;            // k-steps of 16 rows per tile in the staged input
   int sg;              // kFmtF6: slices per staged group
+  int row_waves;       // of the nw waves of a block; with fewer, nw / row_waves waves share the cycles of the same rows
   int Lin, Lout, MP, P, VT, vt_per_chunk, nchunk, pm, nw, MB, lds_kb;
   int wide;            // 0: sums fit 32 bits; 1: 64-bit sums; 2: two 32-bit sums, of the lower and the upper slices
   int flush_every;     // wide == 0: virtual tiles a 32-bit sum holds, when a chunk has more than that (else 0)
@@ -979,6 +1032,8 @@ struct VmmPlan {
   int offset;          // signed inputs in one phase of offset-binary codes
   int narrow;          // the sum over all virtual tiles fits 32 bits
   int small;           // few output patches: one kernel does the whole pass (vmm_small.hip)
+  int vt_planned;      // virtual tiles of a full chunk, and what the chunked kernel is expected to take with them
+  double chunked_us;
   uint32_t bias_per_vt;
   size_t a_bytes, part_bytes, ws_bytes, lds_bytes;
 };
@@ -1037,7 +1092,7 @@ struct SmallArgs {
   const long long* wsum;   // offset-binary inputs: weight sum per output, else null
   double half_range;
 };
-XBAR_INTERNAL bool vmm_small_pays(const VmmPlan& p, const Derived& d, bool gathered);   // gathered: inputs one by one from an image
+XBAR_INTERNAL bool vmm_small_pays(const VmmPlan& p, const Derived& d);
 XBAR_INTERNAL size_t vmm_small_ws_bytes(const VmmPlan& p, const Derived& d);
 XBAR_INTERNAL hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hipStream_t st);
 

@@ -404,31 +404,35 @@ size_t vmm_small_ws_bytes(const VmmPlan& p, const Derived& d) {
   return align256(patches * (sizeof(PatchHead) + (p.narrow ? 4096 : 8192)));
 }
 
-// When the one launch beats the three it replaces (measured on 28000 random layers, both sides in a graph; "lost": slower
-// than the three by more than 3 %).  It costs whole blocks, four slices each, whether or not they hold four.
-// fp16 planes: a tile of more than 128 rows leaves one to three blocks the LDS of a compute unit, and beyond the blocks
-// that are resident at once a second round costs more than two launches (us, three / one: 192 rows, 1122 blocks, one resident:
-// 20 / 51; 256 rows, 2448 blocks: 31 / 119); smaller tiles bear a little more than a round.  566 of 3674 layers lost with
-// a line at 4096 items alone, 25 with this one, none by more than 16 %.
-// 6-bit planes: a block's time grows with the fragments it reads (terms x k-steps) and with gathered inputs, which every output
-// patch and slice group fetches again; that of the chunked kernel with the matrix instructions of a tile's slices and
-// cycles, with the fragments that each of its waves stages, and with the tiles of a row.  The line is where their estimates
-// meet (us, three / one: 256 rows, 1 tile, 4 terms, 8192 items: 42 / 50; 256 rows, 10 tiles, 5 terms, 8960 items: 313 / 76; 128
-// rows, 1 tile, 5 terms, 12288 items: 55 / 64, 4 terms: 50 / 49).  4519 of 22798 layers lost with a line at 12288 items,
-// up to 3.6 times; 730 with this one, up to 1.45 times.
-bool vmm_small_pays(const VmmPlan& p, const Derived& d, bool gathered) {
+// When the one launch beats the three it replaces: where 95 % of its estimate in us is below theirs, up to 16384 items of one
+// patch, tile and slice, beyond which neither was measured closely.  It costs whole blocks, four slices each, whether or not
+// they hold four; a block's time grows with the fragments it reads (terms x k-steps, of a tile with fp16 planes those that
+// the layer reaches), and with fp16 planes a round of as many blocks as the LDS of the compute units holds takes 5 us at least.
+// The three take what the plan expects of the chunked kernel, what each of its waves stages, and two launches.  Both
+// sides fitted to 75000 random layers, matrices and convolutions, in graphs of 10 calls (us, three / one: 2000 x 300,
+// 64 rows, 64-row arrays, fp16: 32 / 22; 256 rows, 1 tile, 4 terms, 8192 items: 42 / 50; 128 rows, 1 tile, 5 terms, 12288
+// items: 55 / 64).  Of the layers of fp16 planes that this sends to the one launch 2.0 % are slower by more than 3 %, on average all
+// are 0.3 % from the better side, of the 6-bit ones 1.3 % and 0.1 %; with a line at 4096 items and one fitted to slower chunked
+// kernels the better side was missed by 5.4 and 1.2 % on average over all layers, now by 1.0 and 0.8.
+// fp16 planes of tiles beyond 128 rows leave one to three blocks the LDS of a compute unit: 4096 items and one round
+// (us, three / one: 192 rows, 1122 blocks, one resident: 20 / 51; 256 rows, 2448 blocks: 31 / 119).
+bool vmm_small_pays(const VmmPlan& p, const Derived& d) {
   const long long patches = (long long)p.MP * p.g.OP, items = patches * p.VT * d.S_w;
   const long long blocks = patches * blocks_per_patch(p, d);
   if (p.g.OP >= 65536 || p.MP >= 65536 || (long long)blocks_per_patch(p, d) * cdiv(d.S_w, kSmallWaves) >= 65536) return false;
+  if (items > 16384) return false;
+  const int rows = std::min(p.Lin, p.g.tile);
   if (d.fmt == kFmtF16) {
-    const long long resident = 256 * (long long)std::min<size_t>(8, 160 * 1024 / small_lds_bytes(p, d));
-    return items <= 4096 && blocks <= (p.ks16 <= 8 ? std::max(1024ll, resident * 3 / 2) : resident);
+    const double resident = 256.0 * (double)std::min<size_t>(8, 160 * 1024 / small_lds_bytes(p, d));
+    if (p.ks16 > 8) return items <= 4096 && (double)blocks <= resident;
+    const double one = 6.5 + std::max(1e-3 * (double)blocks * (1.1 + 0.93 * d.terms * cdiv(rows, 16)) + (p.VT > 1 ? 1.2 : 0.0),
+                                      5.0 * (double)blocks / resident);
+    return one <= 0.95 * (10.3 + 1.27 * p.chunked_us - 1.03 * p.vt_planned + 0.35 * p.nchunk);
   }
   const int read_steps = p.g.ks == 3 ? 4 : p.g.ks;                  // k-steps of a block, and those that a tile reaches
-  const int frags = d.S_w * d.terms * cdiv(std::min(p.Lin, p.g.tile), 64);
-  const double one = (double)blocks * 1e-3 * (4.0 + 1.4 * d.terms * read_steps + (gathered ? 1.8 * read_steps : 0.0));
-  const double three = 8.0 + 0.05 * frags * d.S_in + 0.55 * frags / p.nw + 5.5 * std::min(p.g.T, 4);
-  return items <= 12288 && one <= three;
+  const int frags = d.S_w * d.terms * cdiv(rows, 64);
+  const double one = 8.4 + 1e-3 * (double)blocks * (6.7 + d.terms * read_steps + 0.94 * (d.npol - 1)) + (p.VT > 1 ? 0.5 : 0.0);
+  return one <= 0.95 * (9.1 + 0.98 * p.chunked_us + p.vt_planned * (0.32 * frags / p.nw - 1.4) + 0.33 * p.nchunk);
 }
 
 hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hipStream_t st) {

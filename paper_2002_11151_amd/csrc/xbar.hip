@@ -1460,42 +1460,54 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
     }
   }
   p.pm = (d.fmt == kFmtF6 || p.g.ks <= 8) ? 2 : 1;
-  p.nw = std::min(4, std::max(1, cdiv(p.MP, p.pm)));
-  p.MB = cdiv(p.MP, p.pm * p.nw);
+  p.row_waves = std::min(4, std::max(1, cdiv(p.MP, p.pm)));
+  p.MB = cdiv(p.MP, p.pm * p.row_waves);
   const int groups = p.g.OP * p.MB;
-  // Chunks of the contraction: enough blocks that the last, partly filled round of 2 blocks on 256 CUs costs little, up to
-  // 4096, and no more partial sums than they are worth.  In us, per virtual tile of a round: `tile_us`, from the ResNet-50 and
-  // smaller configurations (128 rows, 64 passes of 16 6-bit instructions: 54; 64 rows, 8 passes of 16 fp16 ones: 8.5); the
-  // tail costs a block 0.45 of its time; a chunk's partial sums 9 ns per block of 256 x 32 words, written and read again.
-  // Of 71 layers measured at every number of chunks this picks within 1.0 % of the best on average, 4096 blocks 2.7 %:
+  // Chunks of the contraction: from as many as 4096 blocks down, the number that costs least in us.  A virtual tile takes a
+  // block `tile_us` where two share a compute unit (128 rows, 64 passes of 16 6-bit instructions: 54; 64 rows, 8 passes of 16
+  // fp16 ones: 8.5); blocks run in rounds of 512, `rounds_of` of them: half a round has its compute units to itself, the last one of
+  // several overlaps those before it.  A chunk's partial sums take 9 ns per block of 256 x 32 words, written and read again.
+  // Of 101 layers measured at every number of chunks this picks within 0.6 % of the best on average, 4096 blocks 4.9 %:
   // 784 x 500, 8-bit weights in 4-bit cycles, 20000 rows, 305 -> 222 us; 144 x 16, 131072 rows, 87 -> 70; 256 x 512, 50176
-  // rows, 1-bit cycles, 721 -> 687.
+  // rows, 1-bit cycles, 721 -> 687; 3000 x 2000, 128 rows backward, 138 -> 103.
   int per = std::max(1, cdiv(p.VT, std::max(1, cdiv(4096, groups))));
   if (p.wide == 2) per = (int)std::min<unsigned long long>((unsigned long long)per, fit_split);
+  const int shares = std::min(4 / p.row_waves, d.S_in);   // of the cycles, among waves that have no rows of their own
   {
     const int nk = d.fmt == kFmtF6 ? cdiv(std::min(p.g.tile, p.Lin), 64) : cdiv(std::min(p.g.tile, p.Lin), 16);
-    const double tile_us = 1.5 + d.S_w * d.S_in * p.pm * (0.175 + 0.0295 * d.terms * nk), rows = 32.0 * p.pm * p.nw / 256.0;
-    const int sum_bytes = p.wide ? 8 : 4;
+    const double tile_us = 1.5 + d.S_w * d.S_in * p.pm * (0.175 + 0.0295 * d.terms * nk) / shares;
+    const double sums_us = 0.0089 * p.pm * p.row_waves / 8.0 * (p.wide ? 2 : 1);
+    auto rounds_of = [](double r) {
+      if (r <= 1.0) return r <= 0.5 ? 0.62 : 1.0;
+      return r >= 3.0 ? r + 0.45 : std::max(r + 0.45, std::min(std::ceil(r), r + 0.6));
+    };
     auto cost = [&](int n) {
-      const int chunks = cdiv(p.VT, n);
-      return tile_us * ((double)p.VT * groups / 512.0 + 0.45 * n) +
-             (chunks > 1 || scattered ? 0.0089 * rows * sum_bytes / 4.0 * chunks * groups : 0.0);
+      const double blocks = (double)cdiv(p.VT, n) * groups;
+      return n * tile_us * rounds_of(blocks / 512.0) + (n < p.VT || scattered ? sums_us * blocks : 0.0);
     };
     // no more than the sums hold: widening them on the way costs more (256 x 2304, 12544 rows backward: 1445 -> 1493 us)
     const int most = (int)std::min<unsigned long long>((unsigned long long)p.VT, p.wide == 2 ? fit_split : p.wide ? ~0ull : fit);
-    for (int n = per + 1; n <= most; ++n)
-      if (cost(n) < cost(per)) per = n;
+    double best = cost(per);
+    for (int n = per + 1; n <= most; ++n) {
+      const double c_n = cost(n);
+      if (c_n < best) { best = c_n; per = n; }
+    }
+    p.vt_planned = per;
+    p.chunked_us = best;
   }
   // 32-bit sums hold `fit` virtual tiles: a chunk with more adds them to a 64-bit partial sum of its own in
   // between (no extra chunks, so no extra partial results for the adding-up pass to read)
   p.flush_every = (!p.wide && (unsigned long long)per > fit) ? (int)fit : 0;
+  p.nw = p.row_waves * (p.flush_every ? 1 : shares);   // sums that are widened on the way belong to one wave
+  if (p.nw > p.row_waves)      // the sums that the block's waves exchange
+    p.lds_bytes = std::max(p.lds_bytes, (size_t)(p.nw - p.row_waves) * (p.wide ? 2 : 1) * p.pm * 16 * 64 * sizeof(uint32_t));
   p.nchunk = cdiv(p.VT, per);
   p.vt_per_chunk = cdiv(p.VT, p.nchunk);                  // same number of chunks, evenly filled
   p.a_bytes = align256((size_t)p.P * p.MP * p.g.T * p.ks16 * 512);
   p.part_bytes = align256((size_t)p.nchunk * M * p.Lout * ((p.wide || p.flush_every) ? 8 : 4));
   p.ws_bytes = p.a_bytes + p.part_bytes;
   p.narrow = (unsigned long long)p.VT <= fit ? 1 : 0;
-  p.small = vmm_small_pays(p, d, false) ? 1 : 0;
+  p.small = vmm_small_pays(p, d) ? 1 : 0;
   if (p.small) {
     // its sums, and those of a scattered pass behind them: the workspace may grow, but no layer that xbar_fwd_static holds
     // with several kernels outgrows the static array with one (32 rows of 140000 outputs of one 4-bit slice: 17.9 and 36.3 MB)
@@ -1589,7 +1601,7 @@ int run_vmm(const xbar_config* cfg, const void* planes, const float* in, float* 
   qa.n_threads = (long long)p.MP * p.g.T * ((p.ks16 + 1) / 2) * 64;
   if (conv) qa.conv = *conv;
   const bool general = codes != nullptr || hist != nullptr || level_table || (cfg->flags & XBAR_ADC_CURVE) != 0;
-  const bool small = p.small && !general && (!conv || conv->C % 8 == 0 || vmm_small_pays(p, d, true));
+  const bool small = p.small && !general;
   if (small) {
   } else if (conv) {
     hipLaunchKernelGGL(quantize_input_kernel<true>, dim3((unsigned)((qa.n_threads + 255) / 256)), dim3(256), 0, st, qa);
@@ -1616,7 +1628,7 @@ int run_vmm(const xbar_config* cfg, const void* planes, const float* in, float* 
   a.npol = d.npol; a.pol_stride = p.g.pol_bytes / 16;
   a.VT = p.VT; a.S_w = d.S_w; a.S_in = d.S_in; a.slice_bits = cfg->slice_bits; a.stream_bits = cfg->stream_bits;
   a.ks = p.g.ks; a.tile = p.g.tile; a.vt_per_chunk = p.vt_per_chunk; a.nchunk = p.nchunk; a.lds_kb = p.lds_kb;
-  a.ks16 = p.ks16; a.sg = p.sg;
+  a.ks16 = p.ks16; a.sg = p.sg; a.row_waves = p.row_waves;
   a.scale_lo = a.scale_hi = 0;
   for (int j = 0; j < kMaxTermsF6; ++j) {
     const int byte = 127 + d.term_exp[j];

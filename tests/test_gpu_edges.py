@@ -327,3 +327,22 @@ def test_rows_do_not_depend_on_the_batch(xb, R, sb, wb, adc, M, K, signed, N):
     for rows in (slice(0, 70), slice(M - 1000, M)):
         assert torch.equal(Y[rows], xb.fwd(cfg, planes, X[rows].clone(), N, 5.0, 3.0))
         assert torch.equal(dX[rows], xb.bwd(cfg, planes, dY[rows].clone(), K, 5.0, 3.0))
+
+
+# Few rows: waves without rows of their own share the streaming cycles (eight, two, one; sums in 32 bits, two of them, 64-bit
+# ones of odd slice counts): the outputs are those of the same rows in a batch that fills the waves
+@pytest.mark.parametrize("R,sb,wb,adc,signed", [(128, 1, 16, 8, True), (256, 2, 16, 10, False), (128, 4, 16, 8, True), (64, 8, 8, 8, False),
+                                                (128, 1, 16, 12, True), (128, 1, 14, 14, False)])
+@pytest.mark.parametrize("M", [1, 33, 64, 65, 128, 129])
+def test_few_rows_share_the_cycles(xb, R, sb, wb, adc, signed, M):
+    K, N = 2500, 4100
+    fs = 1.037 * workloads.adc_full_scale(R, sb, 2)
+    cfg = xb.make_config(xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=2, stream_bits=sb, adc_bits=adc,
+                         flags=xb.NI_WIRE_AAM | (xb.INPUT_SIGNED if signed else 0), adc_fs_fwd=fs, adc_fs_bwd=fs, seed=4)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    W = torch.randn((K, N), generator=gen, device="cuda")
+    X = torch.randn((300, K), generator=gen, device="cuda")
+    dY = torch.randn((300, N), generator=gen, device="cuda")
+    planes = xb.tile(cfg, W, 5.0, 0)
+    assert torch.equal(xb.fwd(cfg, planes, X[:M].clone(), N, 5.0, 3.0), xb.fwd(cfg, planes, X, N, 5.0, 3.0)[:M])
+    assert torch.equal(xb.bwd(cfg, planes, dY[:M].clone(), K, 5.0, 3.0), xb.bwd(cfg, planes, dY, K, 5.0, 3.0)[:M])
