@@ -268,15 +268,62 @@ struct NormalStream {
     box_muller(v[0], v[1], z[0], z[1]);
     box_muller(v[2], v[3], z[2], z[3]);
   }
+  // Both numbers of a Box-Muller draw: sqrt(-2 ln u1) times cosine and sine of 2 pi u2, u = (word + 1/2) / 2^32.  The logarithm,
+  // the root and the angle take only arguments of 33 bits, so they need none of the library's special cases and second words
+  // (204 instructions with them, 90 here, in kernels that are bound by the issue of double-precision arithmetic).  Errors
+  // against 80-bit arithmetic over 3e6 draws: 2.6 units in the last place at most, 1.23e-16 rms; correctly rounded functions
+  // would leave 2.2 and 1.21e-16.
   static __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, double& even, double& odd) {
-    const double u1 = ((double)a + 0.5) * (1.0 / 4294967296.0);
-    const double u2 = ((double)b + 0.5) * (1.0 / 4294967296.0);
-    const double r = ::sqrt(-2.0 * ::log(u1));
-    // angle 2 pi u2: the half-turn form reduces the argument exactly and costs a fraction of sin / cos
-    double sn, cs;
-    ::sincospi(2.0 * u2, &sn, &cs);
-    even = r * cs;
-    odd = r * sn;
+    // u1 = 2^k m, m within a factor of root 2 of 1; m has 33 bits, so m - 1 and m + 1 are exact
+    const double u = __builtin_fma((double)a, 0x1p-32, 0x1p-33);
+    const int high = __double2hiint(u), k = (high - 0x3FE6A09E) >> 20;
+    const double m = __hiloint2double(high - (int)((uint32_t)k << 20), __double2loint(u)), f = m - 1.0, d = m + 1.0;
+    double y = __builtin_amdgcn_rcp(d);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    double s = f * y;
+    s = __builtin_fma(__builtin_fma(-d, s, f), y, s);
+    // ln m = 2 artanh s = 2 s + s^3 q(s^2) = f - s (f - s^2 q): q of degree 6 fitted to 2^-51 on s^2 <= 0.0295
+    const double z = s * s;
+    double q = 0x1.2b5b5fb2eac92p-3;
+    q = __builtin_fma(q, z, 0x1.39fe208c33457p-3);
+    q = __builtin_fma(q, z, 0x1.7462b69705382p-3);
+    q = __builtin_fma(q, z, 0x1.c71c62debf86bp-3);
+    q = __builtin_fma(q, z, 0x1.2492492df6947p-2);
+    q = __builtin_fma(q, z, 0x1.99999999952b2p-2);
+    q = __builtin_fma(q, z, 0x1.5555555555558p-1);
+    const double kd = (double)k, top = __builtin_fma(kd, 0x1.62e42fefa39efp-1, f);           // k ln 2, in two words, plus f
+    const double rest = __builtin_fma(kd, 0x1.62e42fefa39efp-1, -top) + f;
+    const double ln = top + __builtin_fma(-s, __builtin_fma(-z, q, f), __builtin_fma(kd, 0x1.abc9e3b39803fp-56, rest));
+    // the root by Goldschmidt's iteration and one correction; the argument lies in 2^-32 .. 2^6
+    const double t = -2.0 * ln, e = __builtin_amdgcn_rsq(t);
+    double g = t * e, h = 0.5 * e;
+    const double left = __builtin_fma(-g, h, 0.5);
+    g = __builtin_fma(g, left, g);
+    h = __builtin_fma(h, left, h);
+    const double r = __builtin_fma(__builtin_fma(-g, g, t), h, g);
+    // angle: the nearest quarter turn and x eighths of a turn, -1 < x < 1, exact; sine and cosine of pi x / 4 fitted to 2^-58
+    const uint32_t quarter = (b + 0x20000000u) >> 30;
+    const double x = __builtin_fma((double)(int)(b - (quarter << 30)), 0x1p-29, 0x1p-30), xx = x * x;
+    double sn = 0x1.e3f38399551bfp-38;
+    sn = __builtin_fma(sn, xx, -0x1.e30071afc3e59p-30);
+    sn = __builtin_fma(sn, xx, 0x1.50782fda12d96p-22);
+    sn = __builtin_fma(sn, xx, -0x1.32d2cce2e5b19p-15);
+    sn = __builtin_fma(sn, xx, 0x1.466bc677587f8p-9);
+    sn = __builtin_fma(sn, xx, -0x1.4abbce625be41p-4);
+    sn = __builtin_fma(x, 0x1.921fb54442d18p-1, __builtin_fma(x * xx, sn, x * 0x1.1a62633145c07p-55));   // pi / 4 in two words
+    double cs = -0x1.b264ba152378ap-42;
+    cs = __builtin_fma(cs, xx, 0x1.f9cc41140bb60p-34);
+    cs = __builtin_fma(cs, xx, -0x1.a6d1ec7906c20p-26);
+    cs = __builtin_fma(cs, xx, 0x1.e1f5068355e15p-19);
+    cs = __builtin_fma(cs, xx, -0x1.55d3c7e3c90f8p-12);
+    cs = __builtin_fma(cs, xx, 0x1.03c1f081b5aacp-6);
+    // ... its first two terms, and the square of x, in two words
+    const double big = __builtin_fma(xx, -0x1.3bd3cc9be45dep-2, 1.0), small = __builtin_fma(xx, -0x1.3bd3cc9be45dep-2, 1.0 - big);
+    cs = big + __builtin_fma(cs * xx, xx, __builtin_fma(__builtin_fma(x, x, -xx), -0x1.3bd3cc9be45dep-2, small));
+    const double c = (quarter & 1u) ? sn : cs, v = (quarter & 1u) ? cs : sn;
+    even = r * __hiloint2double(__double2hiint(c) ^ (int)(((quarter + 1u) & 2u) << 30), __double2loint(c));
+    odd = r * __hiloint2double(__double2hiint(v) ^ (int)((quarter & 2u) << 30), __double2loint(v));
   }
 };
 
