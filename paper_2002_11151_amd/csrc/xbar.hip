@@ -373,22 +373,43 @@ __global__ __launch_bounds__(256) void tile_planes_f6_words_kernel(TileArgs a) {
   }
 }
 
+// 32 values as E2M3 numbers of unit `scale` (a power of two; nearest, ties to even, saturating), one 6-bit code after the other,
+// and back: value i < 16 is code 2 i, value 16 + i code 2 i + 1.  Inline because the instructions write their result while
+// they still read, and the builtins of this compiler let it share registers with the sources; the wait states cover what the
+// compiler would know of a builtin.
+typedef float float32v __attribute__((ext_vector_type(32)));
+typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
+
+__device__ __forceinline__ u32x6 e2m3_codes(const float16v& even, const float16v& odd, float scale) {
+  u32x6 r;
+  asm("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, %3\n\ts_nop 1" : "=&v"(r) : "v"(even), "v"(odd), "s"(scale));
+  return r;
+}
+
+__device__ __forceinline__ float32v e2m3_values(const u32x6& codes, float scale) {
+  float32v r;
+  asm("v_cvt_scalef32_pk32_f32_fp6 %0, %1, %2\n\ts_nop 1" : "=&v"(r) : "v"(codes), "s"(scale));
+  return r;
+}
+
 // Where tile_f6_kernel gets its term codes from.
 constexpr int kFromDigits = 0;    // ideal arrays: the plane value is the digit
 constexpr int kFromTable = 1;     // single-path wire model alone: looked up by (sign, digit, place in the array)
 constexpr int kFromDevices = 2;   // anything else: every device of the patch computed
 
 // Planes in the 6-bit format, both copies at once, for arrays of whole 64-row and 64-column steps: a block owns 64 x 64
-// weights and two slices at a time, gets the term codes of every one of them once, as one word per array and slice in
-// LDS, and its waves pack the records of the 2 x 2 fragments per slice that either direction reads, each lane one
-// 24-byte record per term.  Devices: bound by the double-precision arithmetic of the normal numbers and the wire model
-// (one Philox block for the four devices of a slice pair); the words never reach memory, and each weight is quantised
-// once per slice pair instead of once per slice and copy.  On 4096 x 4096 weights with variation, 8 slices, 5 terms, the
-// three kernels this replaces (a word per device to memory, then one packing pass per copy) took 2.71 + 0.41 + 0.39 ms.
+// weights and two slices at a time, gets the plane values (devices: two single-precision words, 48 bits) or term codes (table,
+// digits: one word) of every one of them once, into LDS, and its waves pack the records of the 2 x 2 fragments per slice that
+// either direction reads, each lane one 24-byte record per term.  Devices: bound by the double-precision arithmetic of the normal
+// numbers and the wire model (one Philox block for the four devices of a slice pair); each weight is quantised once per slice
+// pair.  The terms of 32 values come out of the conversion instructions a record at a time, twice (either direction), which is
+// a tenth of the integer work of finding every value's term codes and picking the records' bits from them: 4096 x 4096 weights
+// with variation, 8 slices, 5 terms, 1485 -> 1181 us, and 1658 -> 1485 with the shorter normal numbers.
 template <int SRC, int NPOL, int NTH>
 __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns) {
   constexpr int SL = NPOL == 2 ? 1 : 2;              // slices per turn: as many words in LDS either way
-  __shared__ uint32_t words[NPOL][SL][64][65];       // [array][slice of the turn][k][n]
+  constexpr int WORDS = SRC == kFromDevices ? 2 : 1; // plane values in two single-precision words, or term codes
+  __shared__ uint32_t words[WORDS][NPOL][SL][64][65];   // [word][array][slice of the turn][k][n]
   const TileArgs& a = b.a;
   constexpr int NW = NTH / 64, PER = 64 / NW;        // waves; weights per thread
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -419,17 +440,17 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
         const uint32_t mag = (uint32_t)::abs(w);
 #pragma unroll
         for (int sl = 0; sl < SL; ++sl) {
-          uint32_t word[NPOL];
+          double u[NPOL];
 #pragma unroll
-          for (int pol = 0; pol < NPOL; ++pol) word[pol] = 0;
-          if (real && sl < ns) {
-            double u[NPOL];
+          for (int pol = 0; pol < NPOL; ++pol) u[pol] = 0.0;
+          if (real && sl < ns)
             plane_values<NPOL>(a, rng, sign, (int)((mag >> (a.slice_bits * (s0 + sl))) & dmask), s0 + sl, k, n, i0 + kl, j, u);
 #pragma unroll
-            for (int pol = 0; pol < NPOL; ++pol) word[pol] = term_codes(u[pol], a.terms, a.term_exp);
+          for (int pol = 0; pol < NPOL; ++pol) {
+            const float high = (float)u[pol];
+            words[0][pol][sl][kl][lane] = __builtin_bit_cast(uint32_t, high);
+            words[WORDS - 1][pol][sl][kl][lane] = __builtin_bit_cast(uint32_t, (float)(u[pol] - (double)high));
           }
-#pragma unroll
-          for (int pol = 0; pol < NPOL; ++pol) words[pol][sl][kl][lane] = word[pol];
         }
       }
     } else {
@@ -445,38 +466,74 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
           } else {
             word = term_codes(q[r] < 0 ? -(double)digit : (double)digit, 1, a.term_exp);
           }
-          words[0][sl][kl][lane] = word;
+          words[0][0][sl][kl][lane] = word;
         }
     }
     __syncthreads();
-    // one wave per (fragment group, term), group = (array, slice, direction, half of 32 outputs): a short loop over the
-    // lane's 32 codes of one term
     const int ol = lane & 31, half = lane >> 5;
+    if constexpr (SRC == kFromDevices) {
+      // one wave per fragment group = (array, slice, direction, half of 32 outputs): a lane reads the 32 plane values of its
+      // record and takes the terms off them one after the other.  What is left is exact in single precision (it only gets
+      // smaller on the values' own grid); the second words join when it is small enough not to round them.
 #pragma unroll 1
-    for (int item = wave; item < 8 * a.terms; item += NW) {
-      const int term = item >> 3, grp = item & 7;
-      const int hh = grp & 1, dir = (grp >> 1) & 1, sl = NPOL == 2 ? 0 : grp >> 2, pol = NPOL == 2 ? grp >> 2 : 0;
-      const int op = ((dir ? k0 : n0) >> 5) + hh, c = dir ? n0 : k0;
-      if (sl >= ns || op >= b.OP[dir]) continue;
-      const int t = c / b.tile[dir], J = (c - t * b.tile[dir]) >> 6;
-      const uint32_t* from = &words[pol][sl][0][0] + (dir ? (32 * hh + ol) * 65 + half * 8 : 32 * hh + ol + half * 8 * 65);
-      const int stride = dir ? 1 : 65, from_bit = 6 * term;
-      uint32_t rec[6];
+      for (int grp = wave; grp < 8; grp += NW) {
+        const int hh = grp & 1, dir = (grp >> 1) & 1, sl = NPOL == 2 ? 0 : grp >> 2, pol = NPOL == 2 ? grp >> 2 : 0;
+        const int op = ((dir ? k0 : n0) >> 5) + hh, c = dir ? n0 : k0;
+        if (sl >= ns || op >= b.OP[dir]) continue;
+        const int t = c / b.tile[dir], J = (c - t * b.tile[dir]) >> 6;
+        const uint32_t* from = &words[0][pol][sl][0][0] + (dir ? (32 * hh + ol) * 65 + half * 8 : 32 * hh + ol + half * 8 * 65);
+        const uint32_t* second = from + (&words[WORDS - 1][0][0][0][0] - &words[0][0][0][0][0]);
+        const int stride = dir ? 1 : 65;
+        float16v left[2];                            // rows 16 w + e of the half's eights at 4 w + e, rows 16 w + 4 + e in the other
 #pragma unroll
-      for (int x = 0; x < 6; ++x) rec[x] = 0u;
+        for (int x = 0; x < 32; ++x) left[(x >> 2) & 1][4 * (x >> 3) + (x & 3)] = __builtin_bit_cast(float, from[(16 * (x >> 3) + (x & 7)) * stride]);
+        uint8_t* at = b.base[dir] + (size_t)pol * b.pol_bytes[dir] +
+                      ((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms * b.ks[dir] + J) * 1536;
+#pragma unroll 1
+        for (int term = 0; term < a.terms; ++term, at += (size_t)b.ks[dir] * 1536) {
+          const float scale = __builtin_bit_cast(float, (uint32_t)(127 + a.term_exp[term]) << 23);
+          if (term == 2) {
 #pragma unroll
-      for (int w = 0; w < 4; ++w)
+            for (int x = 0; x < 32; ++x) left[(x >> 2) & 1][4 * (x >> 3) + (x & 3)] += __builtin_bit_cast(float, second[(16 * (x >> 3) + (x & 7)) * stride]);
+          }
+          const u32x6 rec = e2m3_codes(left[0], left[1], scale);
+          *reinterpret_cast<u32x4*>(at + lane * 16) = u32x4{rec[0], rec[1], rec[2], rec[3]};
+          *reinterpret_cast<u32x2*>(at + 1024 + lane * 8) = u32x2{rec[4], rec[5]};
+          const float32v v = e2m3_values(rec, scale);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t code = (from[(w * 16 + e) * stride] >> from_bit) & 63u;
-          const int bit = 6 * (8 * w + 2 * (e & 3) + (e >> 2)), x = bit >> 5, sh = bit & 31;   // place among the lane's 32 codes
-          rec[x] |= code << sh;
-          if (sh > 26) rec[x + 1] |= code >> (32 - sh);
+          for (int i = 0; i < 16; ++i) {
+            left[0][i] -= v[2 * i];
+            left[1][i] -= v[2 * i + 1];
+          }
         }
-      uint8_t* at = b.base[dir] + (size_t)pol * b.pol_bytes[dir] +
-                    (((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms + term) * b.ks[dir] + J) * 1536;
-      *reinterpret_cast<u32x4*>(at + lane * 16) = u32x4{rec[0], rec[1], rec[2], rec[3]};
-      *reinterpret_cast<u32x2*>(at + 1024 + lane * 8) = u32x2{rec[4], rec[5]};
+      }
+    } else {
+      // one wave per (fragment group, term): a short loop over the lane's 32 codes of one term
+#pragma unroll 1
+      for (int item = wave; item < 8 * a.terms; item += NW) {
+        const int term = item >> 3, grp = item & 7;
+        const int hh = grp & 1, dir = (grp >> 1) & 1, sl = grp >> 2;
+        const int op = ((dir ? k0 : n0) >> 5) + hh, c = dir ? n0 : k0;
+        if (sl >= ns || op >= b.OP[dir]) continue;
+        const int t = c / b.tile[dir], J = (c - t * b.tile[dir]) >> 6;
+        const uint32_t* from = &words[0][0][sl][0][0] + (dir ? (32 * hh + ol) * 65 + half * 8 : 32 * hh + ol + half * 8 * 65);
+        const int stride = dir ? 1 : 65, from_bit = 6 * term;
+        uint32_t rec[6];
+#pragma unroll
+        for (int x = 0; x < 6; ++x) rec[x] = 0u;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const uint32_t code = (from[(w * 16 + e) * stride] >> from_bit) & 63u;
+            const int bit = 6 * (8 * w + 2 * (e & 3) + (e >> 2)), x = bit >> 5, sh = bit & 31;   // place among the lane's 32 codes
+            rec[x] |= code << sh;
+            if (sh > 26) rec[x + 1] |= code >> (32 - sh);
+          }
+        uint8_t* at = b.base[dir] + (((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms + term) * b.ks[dir] + J) * 1536;
+        *reinterpret_cast<u32x4*>(at + lane * 16) = u32x4{rec[0], rec[1], rec[2], rec[3]};
+        *reinterpret_cast<u32x2*>(at + 1024 + lane * 8) = u32x2{rec[4], rec[5]};
+      }
     }
   }
 }
