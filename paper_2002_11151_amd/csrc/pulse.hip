@@ -1,5 +1,6 @@
 // Pulse-level weight update with stochastic pulse trains (Sec. IV-C): kernels and xbar_update_pulsed.
 #include "xbar_common.h"
+#include <type_traits>
 
 using namespace xbar_detail;
 
@@ -48,7 +49,7 @@ struct PulseArgs {
   unsigned long long* summary;          //   [ceil(n_words / 64)][K N] one bit per word that is not empty
   int n_words;                          //   64-sample words of the current chunk
   int seg_words;                        //   words per block of the marking pass (a multiple of 4)
-  double series[8];                     // streamed walk: exp(-v y) = sum of series[i] y^i for v up to 1 / 32
+  double series[7];                     // streamed walk, v up to 1 / 32: dw_min / 2 exp(-v y) = sum of series[i] (y - 1/2)^i
 };
 
 __device__ __forceinline__ uint32_t pulse_train(uint32_t k0, uint32_t k1, uint64_t step, uint64_t index, double p, int bl) {
@@ -386,10 +387,14 @@ __global__ __launch_bounds__(256) void pulse_walk_kernel(PulseArgs a) {
 // group of L lanes reads L mark words of its device at a time, lists the marked samples in LDS, fetches the trains of L
 // of them side by side, lists their pulses, evaluates L normal numbers side by side, and then all its lanes walk through
 // those L moves in step, each move a handful of dependent double-precision operations.  Samples and pulses that do not
-// fill a batch of L wait for the next one.  What bounds it: the walk's dependent chain (about 60 cycles per pulse) plus
-// a normal number (about 1000 instructions) per L pulses.
-// NL: 0 linear device; 1 write non-linearity by its power series (v <= 1/32: seven powers leave less than 3e-17 of
-// exp(-v y) on 0 <= y <= 1); 2 by exp().
+// fill a batch of L wait for the next one.  What bounds it: the walk's dependent chain (some 50 cycles per pulse) plus
+// a normal number (some 300 instructions) per L pulses.
+// NL: 0 linear device; 1 write non-linearity by its power series about mid-range (v <= 1/32: six powers leave less than 5e-17
+// of exp(-v y) on 0 <= y <= 1); 2 by exp().
+// With the series the state is held as x = (g + 1) / 2, h = x - 1/2: an upward pulse moves it by dw_min / 2 exp(-v x), a downward
+// one back by dw_min / 2 exp(-v (1 - x)), that is by direction times the even powers of h plus the odd ones as they are, and the
+// instruction that adds the last of it clamps to 0 .. 1 by itself: eleven operations a pulse, six of them in a chain, instead of
+// sixteen and nine.  The 144 x 16 layer at 131072 samples, whole update: 2160 -> 1813 us, with 64 lanes per device 1590.
 template <int L, int NL, bool NOISE>
 __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
 #pragma clang fp contract(off)
@@ -397,7 +402,7 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   constexpr int SQ = 33 * L, PQ = 32 * L;            // queues: up to L - 1 waiting, plus 32 words' halves / 31 pulses per sample
   __shared__ uint32_t samples[D][SQ];
   __shared__ uint32_t pulses[D][PQ];                 // sample << 6 | ordinal << 1 | upwards
-  __shared__ double2 moves[64];                      // noise of a pulse; half its direction (+-0.5, 0: no pulse)
+  __shared__ double2 moves[64];                      // noise of a pulse; half its direction (whole with the series; 0: no pulse)
   const int lane = threadIdx.x, gl = lane & (L - 1), grp = lane / L;
   const size_t kn = (size_t)a.K * a.N, want = (size_t)blockIdx.x * D + grp;
   const bool valid = want < kn;
@@ -409,10 +414,12 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   uint32_t* pq = pulses[grp];
   const double2* mv = &moves[grp * L];
   auto begin = [&]() __attribute__((always_inline)) { return a.first ? (double)a.W[dev] / a.w_max : a.state[dev]; };
+  constexpr bool CENTRED = NL == 1;
   double g = begin();
-  double gx = clampd(g, -1.0, 1.0);                  // where the non-linearity finds the state
+  if constexpr (CENTRED) g = __builtin_fma(0.5, g, 0.5);
+  double gx = clampd(g, CENTRED ? 0.0 : -1.0, 1.0);  // where the non-linearity finds the state
   bool pulsed = false;
-  const double up_down = 2.0 * a.dw_min;
+  const double up_down = 2.0 * a.dw_min, unit = CENTRED ? 1.0 : 0.5, sigma = CENTRED ? 0.5 * a.sigma : a.sigma;
   int n_s = 0, n_p = 0, moved = 0;
 
   auto scan = [&](int v) __attribute__((always_inline)) {   // inclusive, over the lanes of the group
@@ -480,42 +487,60 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
           if (gl < run) {
             const uint32_t p = pq[done + gl];
             const bool upwards = (p & 1u) != 0;
-            e.y = upwards ? 0.5 : -0.5;
+            e.y = upwards ? unit : -unit;
             moved += upwards ? 1 : -1;
-            if constexpr (NOISE) e.x = a.sigma * rng.get((uint64_t)(a.m0 + (int)(p >> 6)) * 32 + ((p >> 1) & 31u));
+            if constexpr (NOISE) e.x = sigma * rng.get((uint64_t)(a.m0 + (int)(p >> 6)) * 32 + ((p >> 1) & 31u));
           }
           moves[lane] = e;
           __syncthreads();
           // a device without a pulse in this batch keeps its state, also one beyond the range
-          const double lo = run > 0 ? -1.0 : -INFINITY, hi = run > 0 ? 1.0 : INFINITY;
+          if constexpr (CENTRED) {
+            const double g_kept = g, gx_kept = gx;
+            auto moves_of = [&](auto partial) __attribute__((always_inline)) {
 #pragma unroll 1
-          for (int t0 = 0; t0 < L; t0 += 8) {
-            if (!__any(t0 < run)) break;
-            double2 b[8];
+              for (int t0 = 0; t0 < L; t0 += 8) {
+                if (!__any(t0 < run)) break;
+                double2 b[8];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) b[t] = mv[t0 + t];
+                for (int t = 0; t < 8; ++t) b[t] = mv[t0 + t];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-              const double step = b[t].y * up_down;
-              double next;
-              if constexpr (NL == 0) {
-                next = g + step;
-              } else {
-                const double y = __builtin_fma(b[t].y, gx, 0.5);   // x upwards, 1 - x downwards
-                double f;
-                if constexpr (NL == 1) {
-                  const double y2 = y * y, y4 = y2 * y2;
-                  const double p0 = __builtin_fma(a.series[1], y, a.series[0]), p1 = __builtin_fma(a.series[3], y, a.series[2]);
-                  const double p2 = __builtin_fma(a.series[5], y, a.series[4]), p3 = __builtin_fma(a.series[7], y, a.series[6]);
-                  f = __builtin_fma(y4, __builtin_fma(y2, p3, p2), __builtin_fma(y2, p1, p0));
-                } else {
-                  f = ::exp(-a.v * y);
+                for (int t = 0; t < 8; ++t) {
+                  const double h = gx - 0.5, z = h * h, zz = z * z;
+                  const double odd = __builtin_fma(zz, a.series[5], __builtin_fma(z, a.series[3], a.series[1]));
+                  const double even = __builtin_fma(zz, __builtin_fma(z, a.series[6], a.series[4]), __builtin_fma(z, a.series[2], a.series[0]));
+                  const double so_far = __builtin_fma(b[t].y, even, NOISE ? g + b[t].x : g);
+                  double next;
+                  asm("v_fma_f64 %0, %1, %2, %3 clamp" : "=v"(next) : "v"(h), "v"(odd), "v"(so_far));
+                  if (decltype(partial)::value && t0 + t >= run) continue;
+                  g = gx = next;
                 }
-                next = g + step * f;
               }
-              if constexpr (NOISE) next += b[t].x;
-              g = ::fmin(::fmax(next, lo), hi);
-              if constexpr (NL != 0) gx = run > 0 ? g : gx;
+            };
+            // short batches are the last ones of a device
+            if (__any(run > 0 && run < L)) moves_of(std::true_type{});
+            else moves_of(std::false_type{});
+            if (run <= 0) {
+              g = g_kept;
+              gx = gx_kept;
+            }
+          } else {
+            const double lo = run > 0 ? -1.0 : -INFINITY, hi = run > 0 ? 1.0 : INFINITY;
+#pragma unroll 1
+            for (int t0 = 0; t0 < L; t0 += 8) {
+              if (!__any(t0 < run)) break;
+              double2 b[8];
+#pragma unroll
+              for (int t = 0; t < 8; ++t) b[t] = mv[t0 + t];
+#pragma unroll
+              for (int t = 0; t < 8; ++t) {
+                const double step = b[t].y * up_down;
+                double next;
+                if constexpr (NL == 0) next = g + step;
+                else next = g + step * ::exp(-a.v * __builtin_fma(b[t].y, gx, 0.5));   // x upwards, 1 - x downwards
+                if constexpr (NOISE) next += b[t].x;
+                g = ::fmin(::fmax(next, lo), hi);
+                if constexpr (NL != 0) gx = run > 0 ? g : gx;
+              }
             }
           }
           done += run;
@@ -536,10 +561,11 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   }
 #pragma unroll
   for (int d = 1; d < L; d <<= 1) moved += __shfl_xor(moved, d, L);
-  // The moves' minimum and maximum drop a NaN, which a clamp by comparison keeps; a step is finite, so the state is NaN
+  // The moves' clamps drop a NaN, which a clamp by comparison keeps; a step is finite, so the state is NaN
   // at the end only if it began as one.  A device without a pulse keeps what it held to the bit (a moved -0 is +0).
   // Read again rather than held in registers through the walk.
   const double g_begin = begin();
+  if constexpr (CENTRED) g = __builtin_fma(2.0, g, -1.0);
   if (!pulsed || g_begin != g_begin) g = g_begin;
   if (valid && gl == 0) {
     if (a.last) a.W[dev] = (float)(a.w_max * g);
@@ -634,8 +660,8 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
   a.sigma = (double)cfg->upd_noise_gamma * std::sqrt(lr_eq * (double)dw_min);
   a.seed = cfg->seed; a.step = step; a.step_add = current_step_source();
   a.conv = conv ? *conv : ConvGeom{};
-  a.series[0] = 1.0;
-  for (int i = 1; i < 8; ++i) a.series[i] = a.series[i - 1] * -a.v / (double)i;
+  a.series[0] = 0.5 * a.dw_min * std::exp(-0.5 * a.v);
+  for (int i = 1; i < 7; ++i) a.series[i] = a.series[i - 1] * -a.v / (double)i;
   // 4 x 4 devices per thread when that still fills the chip, else one device per thread
   const bool patch4 = (long long)cdiv(K, 64) * cdiv(N, 64) >= 512;
   const int edge = patch4 ? 64 : 16;
@@ -684,11 +710,13 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
       a.seg_words = !stream || tiles16 >= 256 ? 64 : tiles16 >= 64 ? 16 : 4;
       hipLaunchKernelGGL(pulse_mark_kernel, dim3(tiles16 * (unsigned)cdiv(a.n_words, a.seg_words)), dim3(256), 0, st, a);
       if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
-      // few devices: several lanes per device, so that about a thousand waves or more share the walk (measured with
-      // noise, ms per update, lanes per device 64 / 32 / 16: 432 devices x 131072 samples 0.77 / 1.01 / 1.58, 2304 x 131072
-      // 2.66 / 2.55 / 2.94, 18432 x 8192 1.10 / 0.87 / 0.82)
-      if (stream && devices < 1024) launch_pulse_stream<64>(a, nl, noise, st);
-      else if (stream && devices < 12288) launch_pulse_stream<32>(a, nl, noise, st);
+      // few devices: several lanes per device, so that about a thousand waves or more share the walk; a move by exp() holds the
+      // issue for longer, so fewer waves do (us per update with noise, lanes per device 64 / 32 / 16: series 432 devices x 131072
+      // samples 474 / 712 / 1257, 2304 x 131072 1594 / 1822 / 2371, 4608 x 32768 664 / 564 / 714, 9216 x 32768 1502 / 1300 / 1232;
+      // linear 2304 1184 / 1442 / 2010, 3200 x 40000 634 / 616 / 936, 6912 x 32768 855 / 888 / 818; exp() 1152 x 30000 336 / 329 /
+      // 482, 4608 1196 / 891 / 985, 6912 1871 / 1631 / 1196)
+      if (stream && devices < (move_mode(a, nl) == 2 ? 1024 : 2560)) launch_pulse_stream<64>(a, nl, noise, st);
+      else if (stream && devices < 6144) launch_pulse_stream<32>(a, nl, noise, st);
       else if (stream) launch_pulse_stream<16>(a, nl, noise, st);
       else if (noise) {
         // lanes decoupled over the whole chunk: with a normal number per pulse every turn counts

@@ -63,7 +63,8 @@ def test_generator(xo, xb, R, sb, wb, slb, ni, K, N):
 @pytest.mark.parametrize("M,K,N,density,v,ni", [
     (2048, 1, 1, 4.0, 0.01, "nl+noise"), (2100, 31, 33, 4.0, 1.0 / 32, "nl"), (4200, 31, 33, 0.02, 0.01, "nl+noise"),
     (2049, 23, 45, 0.3, 0.0, ""), (4200, 96, 37, 0.5, 0.04, "nl+noise"), (2100, 96, 37, 0.05, 0.0, ""),
-    (2049, 160, 80, 0.05, 0.01, "nl+noise"), (2048, 160, 80, 0.05, 0.04, "nl"), (2048, 300, 170, 0.02, 0.01, "nl+noise")])
+    (2049, 160, 80, 0.05, 0.01, "nl+noise"), (2048, 160, 80, 0.05, 0.04, "nl"), (2048, 300, 170, 0.02, 0.01, "nl+noise"),
+    (2048, 51, 50, 0.3, 1.0 / 32, "nl+noise"), (2048, 51, 51, 0.3, 1.0 / 32, "nl"), (2048, 96, 63, 0.1, 0.01, "nl"), (2048, 96, 64, 0.1, 0.01, "nl")])
 def test_pulsed_walk(xo, xb, M, K, N, density, v, ni):
     W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=M + K + N)
     w_max = 0.5 * float(np.abs(W).max())
