@@ -148,7 +148,7 @@ struct VmmArgs {
   int scale_lo, scale_hi;     // kFmtF6: block-scale bytes (127 + exponent) of terms 0..3 and of term 4
   int vt_per_chunk, nchunk, lds_kb;
   int split_sg;               // two 32-bit sums per output: slices of the lower one
-  int flush_every;            // 32-bit sums: added to the block's own 64-bit partial sum every so many virtual tiles (0: never)
+  int flush_every;            // one or two 32-bit sums: added to the block's own 64-bit partial sum every so many virtual tiles (0: never)
   int direct;                 // single chunk and nothing to correct: the kernel scales and stores the result itself
   int total_wg, per_xcd;
   int row_waves;       // waves of a block side by side along the rows; every row_waves waves take a share of the cycles
@@ -894,7 +894,7 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
   // in memory, a block with more virtual tiles than that adds its sums to a 64-bit partial result every
   // `flush_every` tiles: every element has one owner lane, which reads back only what it wrote itself.
   int since = 0;
-  const bool flushing = WIDE == 0 && a.flush_every > 0 && vt1 - vt0 > a.flush_every;
+  const bool flushing = WIDE != 1 && a.flush_every > 0 && vt1 - vt0 > a.flush_every;
   for (int vt = vt0; vt < vt1; ++vt) {
     /* vt = (phase, array, tile), tile fastest */
     const int pa = vt / a.T, t = vt - pa * a.T;
@@ -902,10 +902,10 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
     const int rows = min(a.tile, a.Lin - t * a.tile);
     run_tile(a, lds, p, pol, t, rows, lane, mp0, op, y, yh, y64);
     ++since;
-    if constexpr (WIDE == 0) {
+    if constexpr (WIDE != 1) {
       if (flushing && since == a.flush_every && vt + 1 < vt1) {
         const bool first = vt + 1 - vt0 == a.flush_every;
-        const uint32_t bias = a.bias_per_vt * (uint32_t)since;
+        const uint32_t bias = a.bias_per_vt * (uint32_t)since, bias_high = a.bias_high_per_vt * (uint32_t)since;
         long long* part = reinterpret_cast<long long*>(a.part) + (size_t)chunk * a.M * a.Lout;
         // keep the compiler from computing the element addresses ahead of the loop, where they would sit in registers
         // throughout the contraction
@@ -921,6 +921,10 @@ __device__ __forceinline__ void vmm_block(const VmmArgs& a, u32x4* lds, const Ti
             for (int e = 0; e < 4; ++e) {
               sum[e] = (long long)(int32_t)(y[pm][4 * g + e] - bias);
               y[pm][4 * g + e] = 0;
+              if constexpr (WIDE == 2) {
+                sum[e] += (long long)(int32_t)(yh[pm][4 * g + e] - bias_high) << (a.slice_bits * a.split_sg);
+                yh[pm][4 * g + e] = 0;
+              }
             }
             if (m < a.M && o < a.Lout && mp_now + pm < a.MP) {
               long long* at = part + (size_t)m * a.Lout + o;
@@ -1026,7 +1030,7 @@ struct VmmPlan {
   int row_waves;       // of the nw waves of a block; with fewer, nw / row_waves waves share the cycles of the same rows
   int Lin, Lout, MP, P, VT, vt_per_chunk, nchunk, pm, nw, MB, lds_kb;
   int wide;            // 0: sums fit 32 bits; 1: 64-bit sums; 2: two 32-bit sums, of the lower and the upper slices
-  int flush_every;     // wide == 0: virtual tiles a 32-bit sum holds, when a chunk has more than that (else 0)
+  int flush_every;     // wide 0 or 2: virtual tiles a 32-bit sum holds, when a chunk has more than that (else 0)
   int split_sg;        // slices of the lower sum of mode 2
   uint32_t bias_split[2];   // kMagicBits * sum of the shift weights of either sum, mod 2^32
   int offset;          // signed inputs in one phase of offset-binary codes

@@ -1528,7 +1528,7 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
   // 784 x 500, 8-bit weights in 4-bit cycles, 20000 rows, 305 -> 222 us; 144 x 16, 131072 rows, 87 -> 70; 256 x 512, 50176
   // rows, 1-bit cycles, 721 -> 687; 3000 x 2000, 128 rows backward, 138 -> 103.
   int per = std::max(1, cdiv(p.VT, std::max(1, cdiv(4096, groups))));
-  if (p.wide == 2) per = (int)std::min<unsigned long long>((unsigned long long)per, fit_split);
+  const unsigned long long held = p.wide == 2 ? fit_split : p.wide ? ~0ull : fit;   // virtual tiles in one sum
   const int shares = std::min(4 / p.row_waves, d.S_in);   // of the cycles, among waves that have no rows of their own
   {
     const int nk = d.fmt == kFmtF6 ? cdiv(std::min(p.g.tile, p.Lin), 64) : cdiv(std::min(p.g.tile, p.Lin), 16);
@@ -1543,7 +1543,7 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
       return n * tile_us * rounds_of(blocks / 512.0) + (n < p.VT || scattered ? sums_us * blocks : 0.0);
     };
     // no more than the sums hold: widening them on the way costs more (256 x 2304, 12544 rows backward: 1445 -> 1493 us)
-    const int most = (int)std::min<unsigned long long>((unsigned long long)p.VT, p.wide == 2 ? fit_split : p.wide ? ~0ull : fit);
+    const int most = (int)std::min<unsigned long long>((unsigned long long)p.VT, held);
     double best = cost(per);
     for (int n = per + 1; n <= most; ++n) {
       const double c_n = cost(n);
@@ -1553,8 +1553,9 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
     p.chunked_us = best;
   }
   // 32-bit sums hold `fit` virtual tiles: a chunk with more adds them to a 64-bit partial sum of its own in
-  // between (no extra chunks, so no extra partial results for the adding-up pass to read)
-  p.flush_every = (!p.wide && (unsigned long long)per > fit) ? (int)fit : 0;
+  // between (no extra chunks, so no extra partial results for the adding-up pass to read, and no workspace that grows with
+  // the tiles: 2907 x 1029 weights of 14 one-bit slices, 96-row arrays, 13-bit converter, 109547 rows: 1.6 GB instead of 28.6)
+  p.flush_every = (unsigned long long)per > held ? (int)held : 0;
   p.nw = p.row_waves * (p.flush_every ? 1 : shares);   // sums that are widened on the way belong to one wave
   if (p.nw > p.row_waves)      // the sums that the block's waves exchange
     p.lds_bytes = std::max(p.lds_bytes, (size_t)(p.nw - p.row_waves) * (p.wide ? 2 : 1) * p.pm * 16 * 64 * sizeof(uint32_t));

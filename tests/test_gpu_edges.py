@@ -308,12 +308,13 @@ def test_conv_is_its_patches(xb, batch, image, cin, cout, kernel, stride, pad, m
     assert np.array_equal(dX, want[:, pad:pad + image, pad:pad + image])
 
 
-# How a block leaves its sums: scaled outputs, 32- and 64-bit partial sums, sums widened on the way, rows that are whole quads
+# How a block leaves its sums: scaled outputs, 32- and 64-bit partial sums, one or two sums widened on the way, rows that are whole quads
 # and others, the last patch of rows and outputs.  A row's outputs do not depend on the rows beside it, and few rows are cut
 # into more chunks of the contraction, or taken by one kernel.
 @pytest.mark.parametrize("R,sb,wb,adc,M,K,signed", [(128, 1, 16, 8, 40000, 64, False), (128, 1, 16, 8, 3000, 300, True), (16, 1, 16, 8, 52500, 128, True),
                                                     (128, 4, 16, 8, 30000, 144, True), (64, 4, 16, 12, 3000, 300, True),
-                                                    (128, 1, 16, 10, 40000, 64, False), (128, 1, 12, 13, 3000, 300, True), (256, 1, 16, 10, 9000, 300, True)])
+                                                    (128, 1, 16, 10, 40000, 64, False), (128, 1, 12, 13, 3000, 300, True), (256, 1, 16, 10, 9000, 300, True),
+                                                    (128, 1, 16, 15, 20000, 2000, True)])
 @pytest.mark.parametrize("N", [97, 98, 99, 100])
 def test_rows_do_not_depend_on_the_batch(xb, R, sb, wb, adc, M, K, signed, N):
     fs = 1.037 * workloads.adc_full_scale(R, sb, 2)

@@ -183,6 +183,14 @@ def test_one_launch_pass_keeps_layers_in_the_static_array(xb):
         assert xb.workspace_bytes(xb.make_config(**base), xb.OP_FWD, M, K, N) <= 32 << 20
 
 
+def test_wide_sums_do_not_take_a_partial_result_per_tile(xb):
+    # sums beyond 32 bits that hold a tile or two: with blocks enough for the chip there is one 64-bit partial result
+    for M, K, N, R, wb, adc in ((109547, 2907, 1029, 96, 14, 13), (48548, 2866, 2003, 32, 14, 13), (20000, 4000, 4000, 128, 16, 16)):
+        cfg = xb.make_config(xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=1, stream_bits=1, adc_bits=adc, flags=xb.INPUT_SIGNED)
+        digits = 2 * (M + 32) * (K + R)
+        assert xb.workspace_bytes(cfg, xb.OP_FWD, M, K, N) <= digits + 8 * M * N + 256
+
+
 def test_argument_checks_precede_any_device_work(xb):
     lib = xb.lib()
     c = xb.make_config()
