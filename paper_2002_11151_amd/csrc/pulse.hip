@@ -49,7 +49,7 @@ struct PulseArgs {
   unsigned long long* summary;          //   [ceil(n_words / 64)][K N] one bit per word that is not empty
   int n_words;                          //   64-sample words of the current chunk
   int seg_words;                        //   words per block of the marking pass (a multiple of 4)
-  double series[7];                     // streamed walk, v up to 1 / 32: dw_min / 2 exp(-v y) = sum of series[i] (y - 1/2)^i
+  double series[7];                     // streamed walk, v up to 1 / 32: dw_min exp(-v (g + 1) / 2) = sum of series[i] g^i
 };
 
 __device__ __forceinline__ uint32_t pulse_train(uint32_t k0, uint32_t k1, uint64_t step, uint64_t index, double p, int bl) {
@@ -389,12 +389,14 @@ __global__ __launch_bounds__(256) void pulse_walk_kernel(PulseArgs a) {
 // those L moves in step, each move a handful of dependent double-precision operations.  Samples and pulses that do not
 // fill a batch of L wait for the next one.  What bounds it: the walk's dependent chain (some 50 cycles per pulse) plus
 // a normal number (some 300 instructions) per L pulses.
-// NL: 0 linear device; 1 write non-linearity by its power series about mid-range (v <= 1/32: six powers leave less than 5e-17
+// NL: 0 linear device; 1 write non-linearity by its power series about mid-range (v <= 1/32: six powers leave less than 1e-18
 // of exp(-v y) on 0 <= y <= 1); 2 by exp().
-// With the series the state is held as x = (g + 1) / 2, h = x - 1/2: an upward pulse moves it by dw_min / 2 exp(-v x), a downward
-// one back by dw_min / 2 exp(-v (1 - x)), that is by direction times the even powers of h plus the odd ones as they are, and the
-// instruction that adds the last of it clamps to 0 .. 1 by itself: eleven operations a pulse, six of them in a chain, instead of
-// sixteen and nine.  The 144 x 16 layer at 131072 samples, whole update: 2160 -> 1813 us, with 64 lanes per device 1590.
+// With the series an upward pulse moves the state g by dw_min exp(-v (1 + g) / 2), a downward one back by dw_min exp(-v (1 - g) / 2),
+// that is by direction times the even powers of g plus the odd ones as they are.  A move is complete, noise included, before it
+// joins the state, which is rounded once per pulse: 2.4e-16 rms after 200 pulses against 113-bit arithmetic (noise joining the state
+// by itself: 3.5e-16; a state held on 0 .. 1, which the last operation could clamp by itself: 1.2e-15).
+// Twelve operations a pulse, eight of them in a chain: the 144 x 16 layer at 131072 samples, whole update, 1657 us (on 0 .. 1 eleven
+// and six, 1599; eight powers of (1 + g) / 2 or (1 - g) / 2 sixteen and nine, 32 lanes per device 2160).
 template <int L, int NL, bool NOISE>
 __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
 #pragma clang fp contract(off)
@@ -414,12 +416,10 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   uint32_t* pq = pulses[grp];
   const double2* mv = &moves[grp * L];
   auto begin = [&]() __attribute__((always_inline)) { return a.first ? (double)a.W[dev] / a.w_max : a.state[dev]; };
-  constexpr bool CENTRED = NL == 1;
   double g = begin();
-  if constexpr (CENTRED) g = __builtin_fma(0.5, g, 0.5);
-  double gx = clampd(g, CENTRED ? 0.0 : -1.0, 1.0);  // where the non-linearity finds the state
+  double gx = clampd(g, -1.0, 1.0);                  // where the non-linearity finds the state
   bool pulsed = false;
-  const double up_down = 2.0 * a.dw_min, unit = CENTRED ? 1.0 : 0.5, sigma = CENTRED ? 0.5 * a.sigma : a.sigma;
+  const double up_down = 2.0 * a.dw_min, unit = NL == 1 ? 1.0 : 0.5;
   int n_s = 0, n_p = 0, moved = 0;
 
   auto scan = [&](int v) __attribute__((always_inline)) {   // inclusive, over the lanes of the group
@@ -489,12 +489,12 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
             const bool upwards = (p & 1u) != 0;
             e.y = upwards ? unit : -unit;
             moved += upwards ? 1 : -1;
-            if constexpr (NOISE) e.x = sigma * rng.get((uint64_t)(a.m0 + (int)(p >> 6)) * 32 + ((p >> 1) & 31u));
+            if constexpr (NOISE) e.x = a.sigma * rng.get((uint64_t)(a.m0 + (int)(p >> 6)) * 32 + ((p >> 1) & 31u));
           }
           moves[lane] = e;
           __syncthreads();
           // a device without a pulse in this batch keeps its state, also one beyond the range
-          if constexpr (CENTRED) {
+          if constexpr (NL == 1) {
             const double g_kept = g, gx_kept = gx;
             auto moves_of = [&](auto partial) __attribute__((always_inline)) {
 #pragma unroll 1
@@ -505,14 +505,13 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
                 for (int t = 0; t < 8; ++t) b[t] = mv[t0 + t];
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
-                  const double h = gx - 0.5, z = h * h, zz = z * z;
+                  const double z = gx * gx, zz = z * z;
                   const double odd = __builtin_fma(zz, a.series[5], __builtin_fma(z, a.series[3], a.series[1]));
                   const double even = __builtin_fma(zz, __builtin_fma(z, a.series[6], a.series[4]), __builtin_fma(z, a.series[2], a.series[0]));
-                  const double so_far = __builtin_fma(b[t].y, even, NOISE ? g + b[t].x : g);
-                  double next;
-                  asm("v_fma_f64 %0, %1, %2, %3 clamp" : "=v"(next) : "v"(h), "v"(odd), "v"(so_far));
+                  const double directed = NOISE ? __builtin_fma(b[t].y, even, b[t].x) : b[t].y * even;
+                  const double next = g + __builtin_fma(gx, odd, directed);
                   if (decltype(partial)::value && t0 + t >= run) continue;
-                  g = gx = next;
+                  g = gx = ::fmin(::fmax(next, -1.0), 1.0);
                 }
               }
             };
@@ -561,11 +560,10 @@ __global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
   }
 #pragma unroll
   for (int d = 1; d < L; d <<= 1) moved += __shfl_xor(moved, d, L);
-  // The moves' clamps drop a NaN, which a clamp by comparison keeps; a step is finite, so the state is NaN
+  // The moves' minimum and maximum drop a NaN, which a clamp by comparison keeps; a step is finite, so the state is NaN
   // at the end only if it began as one.  A device without a pulse keeps what it held to the bit (a moved -0 is +0).
   // Read again rather than held in registers through the walk.
   const double g_begin = begin();
-  if constexpr (CENTRED) g = __builtin_fma(2.0, g, -1.0);
   if (!pulsed || g_begin != g_begin) g = g_begin;
   if (valid && gl == 0) {
     if (a.last) a.W[dev] = (float)(a.w_max * g);
@@ -660,8 +658,13 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
   a.sigma = (double)cfg->upd_noise_gamma * std::sqrt(lr_eq * (double)dw_min);
   a.seed = cfg->seed; a.step = step; a.step_add = current_step_source();
   a.conv = conv ? *conv : ConvGeom{};
-  a.series[0] = 0.5 * a.dw_min * std::exp(-0.5 * a.v);
-  for (int i = 1; i < 7; ++i) a.series[i] = a.series[i - 1] * -a.v / (double)i;
+  a.series[0] = a.dw_min * std::exp(-0.5 * a.v);
+  for (int i = 1; i < 7; ++i) a.series[i] = a.series[i - 1] * (-0.5 * a.v) / (double)i;
+  // the seventh power, spread over the lower odd ones: on -1 .. 1 it is (112 g^5 - 56 g^3 + 7 g) / 64 but for a 64th
+  const double seventh = a.series[6] * (-0.5 * a.v) / 7.0;
+  a.series[5] += seventh * (112.0 / 64.0);
+  a.series[3] -= seventh * (56.0 / 64.0);
+  a.series[1] += seventh * (7.0 / 64.0);
   // 4 x 4 devices per thread when that still fills the chip, else one device per thread
   const bool patch4 = (long long)cdiv(K, 64) * cdiv(N, 64) >= 512;
   const int edge = patch4 ? 64 : 16;

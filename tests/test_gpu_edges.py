@@ -81,6 +81,22 @@ def test_pulsed_walk(xo, xb, M, K, N, density, v, ni):
         assert np.array_equal(Wg.cpu().numpy(), Wo)
 
 
+# Moves far below the range, from weights of zero: the state is as exact about zero as a double is (moves of 2^-40 on a grid of
+# 2^-53 would be off by 1e-4 of themselves); each pulse adds a few units in the last place of a move
+@pytest.mark.parametrize("K,N", [(31, 33), (60, 60), (96, 70)])     # 64, 32 and 16 lanes per device
+@pytest.mark.parametrize("ni", ["nl", "nl+noise"])
+def test_pulsed_walk_of_short_moves(xo, xb, K, N, ni):
+    M = 2100
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=K + N)
+    W[:] = 0.0
+    flags = xo.UPD_NL | (xo.UPD_NOISE if "noise" in ni else 0)
+    co, cg = both_configs(xo, xb, flags=flags, upd_nl_v=1.0 / 32, upd_noise_gamma=0.4, seed=3)
+    Wo = xo.update_pulsed(co, W, X, dY, 0.7, 1.0, 0.01, 31, 2.0 ** -40, step=6)
+    Wg = xb.update_pulsed(cg, dev(W.copy()), dev(X), dev(dY), 0.7, 1.0, 0.01, 31, 2.0 ** -40, step=6).cpu().numpy()
+    assert np.abs(Wo).max() > 2.0 ** -39
+    assert np.abs(Wg - Wo).max() <= 2.0 ** -23 * np.abs(Wo).max()
+
+
 # ... on both sides of the lines between several lanes per device and one, for each cost of a move
 @pytest.mark.parametrize("K,N,v,ni", [(128, 255, 0.0, ""), (128, 257, 0.0, ""), (128, 159, 0.01, "nl"), (128, 161, 0.01, "nl"), (64, 127, 0.04, "nl"),
                                       (64, 129, 0.04, "nl"), (128, 383, 0.0, "noise"), (128, 385, 0.0, "noise"), (128, 319, 0.01, "nl+noise"),
