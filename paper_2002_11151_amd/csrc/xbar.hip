@@ -447,6 +447,9 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
             plane_values<NPOL>(a, rng, sign, (int)((mag >> (a.slice_bits * (s0 + sl))) & dmask), s0 + sl, k, n, i0 + kl, j, u);
 #pragma unroll
           for (int pol = 0; pol < NPOL; ++pol) {
+            // beyond 15 units of the first term every term saturates; infinities and what is no number must not meet below
+            const double most = __hiloint2double((1023 + 3 + a.term_exp[0]) * 0x100000 + 0xE0000, 0);
+            u[pol] = ::copysign(::fmin(::fabs(u[pol]), most), u[pol]);
             const float high = (float)u[pol];
             words[0][pol][sl][kl][lane] = __builtin_bit_cast(uint32_t, high);
             words[WORDS - 1][pol][sl][kl][lane] = __builtin_bit_cast(uint32_t, (float)(u[pol] - (double)high));

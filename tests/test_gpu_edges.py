@@ -58,6 +58,75 @@ def test_generator(xo, xb, R, sb, wb, slb, ni, K, N):
     assert close_codes(gpu_bwd(xb, cg, W, dY, w_max, gs, step=2)[1], xo.bwd(co, W, dY, w_max, gs, step=2, want_codes=True)[1])
 
 
+E2M3 = np.array([m / 8 if e == 0 else (8 + m) / 8 * 2 ** (e - 1) for e in range(4) for m in range(8)])
+
+
+def plane_terms(planes, R, K, N, S_w, arrays, exps, backward):
+    """The terms of every plane value of one copy of a 6-bit plane buffer: [array][term][slice][K][N]."""
+    Lc, Lo = (N, K) if backward else (K, N)
+    T, OP, ks, terms = -(-Lc // R), -(-Lo // 32), -(-R // 64), len(exps)
+    pol_bytes = T * OP * S_w * terms * ks * 1536
+    start = 0
+    if backward:
+        start = (-(-K // R) * -(-N // 32) * S_w * terms * ks * 1536 * arrays + 1024 + 255) // 256 * 256
+    raw = planes[start:start + pol_bytes * arrays].reshape(arrays, T, OP, S_w, terms, ks, 1536)
+    records = np.concatenate([raw[..., :1024].reshape(raw.shape[:-1] + (64, 16)), raw[..., 1024:].reshape(raw.shape[:-1] + (64, 8))], axis=-1)
+    bits = np.unpackbits(records, axis=-1, bitorder="little").reshape(raw.shape[:-1] + (64, 32, 6))
+    codes = bits @ (1 << np.arange(6))
+    values = E2M3[codes & 31] * np.where(codes & 32, -1.0, 1.0) * (2.0 ** np.array(exps))[None, None, None, None, :, None, None, None]
+    lane, e = np.meshgrid(np.arange(64), np.arange(32), indexing="ij")
+    row = 16 * (e // 8) + 8 * (lane // 32) + (e % 8) // 2 + 4 * (e % 2)
+    out = np.zeros((arrays, terms, S_w, T, ks, 64, OP, 32))
+    out[:, :, :, :, :, row, :, lane % 32] = values.transpose(6, 7, 0, 4, 3, 1, 5, 2)
+    out = out.reshape(arrays, terms, S_w, T, ks * 64, OP * 32)[:, :, :, :, :R].reshape(arrays, terms, S_w, T * R, OP * 32)[..., :Lc, :Lo]
+    return out.swapaxes(-1, -2) if backward else out
+
+
+def nearest_terms(u, exps):
+    """The E2M3 number nearest to what the terms before it left, times its power of two, term after term, in double precision
+    (where that is exact the terms are); what cannot be held saturates."""
+    terms = []
+    for x in exps:
+        a = np.fmin(np.abs(u), 7.5 * 2.0 ** x) / 2.0 ** x
+        step = np.where(a < 2, 0.125, np.where(a < 4, 0.25, 0.5))
+        terms.append(np.copysign(np.rint(a / step) * step * 2.0 ** x, u))
+        u = u - terms[-1]
+    return np.stack(terms, axis=1)
+
+
+def profile_planes(xb, R, arrays, adc, distortion, seed):
+    """Planes of 100 x 70 weights of two 2-bit slices with that stored distortion [slice][array][K][N], and what their terms have to be:
+    conductances of whole quarters, so that every plane value of a distortion of 40 bits is exact in double precision."""
+    K, N = 100, 70
+    exps = [0, -4, -9, -14, -19]
+    rng = np.random.default_rng(seed)
+    q = rng.integers(-15, 16, size=(K, N))
+    q[0, 0] = 15
+    cfg = xb.make_config(xbar_rows=R, xbar_cols=R, weight_bits=4, slice_bits=2, stream_bits=1, adc_bits=adc, r_min=1.0, r_max=4.0,
+                         flags=xb.NI_WIRE_PROFILE | (xb.ADC_PER_ARRAY if arrays == 2 else 0))
+    planes = xb.tile(cfg, dev((q / 15.0).astype(np.float32)), 1.0, 0, dev(distortion.astype(np.float32))).cpu().numpy()
+    digit = np.stack([(np.abs(q) >> (2 * s)) & 3 for s in range(2)])
+    g = np.stack([np.where(q > 0, digit, 0), np.where(q < 0, digit, 0)]) * 0.25 + 0.25     # [array][slice][K][N]
+    with np.errstate(invalid="ignore"):
+        g = g * (1.0 - distortion.astype(np.float32).astype(np.float64).swapaxes(0, 1))
+        u = g * 4.0 if arrays == 2 else (g[0] - g[1])[None] * 4.0
+        want = nearest_terms(u, exps)
+    return [plane_terms(planes, R, K, N, 2, arrays, exps, backward) for backward in (False, True)], want, u
+
+
+# Arrays of whole 64-row steps and others write their planes through different kernels
+@pytest.mark.parametrize("R", [64, 128, 48])
+@pytest.mark.parametrize("arrays", [1, 2])
+def test_plane_values_beyond_the_format(xb, R, arrays):
+    rng = np.random.default_rng(7)
+    distortion = rng.choice([np.inf, -np.inf, -1e30, -3.0, -6.25, -20.0, 0.5, 1.0, 0.0, np.nan], size=(2, 2, 100, 70))
+    copies, want, u = profile_planes(xb, R, arrays, 13, distortion, seed=5)
+    for got in copies:
+        number = np.broadcast_to(~np.isnan(u)[:, None], want.shape)
+        assert np.array_equal(got[number], want[number])
+        assert np.array_equal(np.abs(got), np.abs(want))       # what is no number: the largest of either sign
+
+
 # Streamed walk: 64 / 32 / 16 lanes per device and none, one device, queues that never fill and ones that always do,
 # the power series of the non-linearity (v up to 1 / 32) and exp(), states that start beyond the range
 @pytest.mark.parametrize("M,K,N,density,v,ni", [
