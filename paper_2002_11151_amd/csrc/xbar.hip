@@ -392,13 +392,26 @@ __device__ __forceinline__ float32v e2m3_values(const u32x6& codes, float scale)
   return r;
 }
 
+// Plane value as a whole number of 2^(x0 - kTermGrid), x0 the exponent of the first term: towards zero, and odd unless exact.
+// The midpoints between the numbers that a term can take are even on this grid (those of the last of five terms, two apart at
+// least), so the terms of the result are the terms of the value itself.  Beyond 15 units of the first term all of them saturate:
+// what is larger, infinite or no number becomes that.
+constexpr int kTermGrid = 24;
+
+__device__ __forceinline__ int on_term_grid(double u, int x0) {
+  const double most = 15.0 * (1 << kTermGrid), y = ::fmin(::fabs(u) * __hiloint2double((1023 + kTermGrid - x0) << 20, 0), most);
+  uint32_t whole = (uint32_t)y;
+  whole |= (double)whole != y ? 1u : 0u;
+  return __double2hiint(u) < 0 ? -(int)whole : (int)whole;
+}
+
 // Where tile_f6_kernel gets its term codes from.
 constexpr int kFromDigits = 0;    // ideal arrays: the plane value is the digit
 constexpr int kFromTable = 1;     // single-path wire model alone: looked up by (sign, digit, place in the array)
 constexpr int kFromDevices = 2;   // anything else: every device of the patch computed
 
 // Planes in the 6-bit format, both copies at once, for arrays of whole 64-row and 64-column steps: a block owns 64 x 64
-// weights and two slices at a time, gets the plane values (devices: two single-precision words, 48 bits) or term codes (table,
+// weights and two slices at a time, gets the plane values (devices: two single-precision words) or term codes (table,
 // digits: one word) of every one of them once, into LDS, and its waves pack the records of the 2 x 2 fragments per slice that
 // either direction reads, each lane one 24-byte record per term.  Devices: bound by the double-precision arithmetic of the normal
 // numbers and the wire model (one Philox block for the four devices of a slice pair); each weight is quantised once per slice
@@ -447,12 +460,9 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
             plane_values<NPOL>(a, rng, sign, (int)((mag >> (a.slice_bits * (s0 + sl))) & dmask), s0 + sl, k, n, i0 + kl, j, u);
 #pragma unroll
           for (int pol = 0; pol < NPOL; ++pol) {
-            // beyond 15 units of the first term every term saturates; infinities and what is no number must not meet below
-            const double most = __hiloint2double((1023 + 3 + a.term_exp[0]) * 0x100000 + 0xE0000, 0);
-            u[pol] = ::copysign(::fmin(::fabs(u[pol]), most), u[pol]);
-            const float high = (float)u[pol];
-            words[0][pol][sl][kl][lane] = __builtin_bit_cast(uint32_t, high);
-            words[WORDS - 1][pol][sl][kl][lane] = __builtin_bit_cast(uint32_t, (float)(u[pol] - (double)high));
+            const int whole = on_term_grid(u[pol], a.term_exp[0]), low = whole & 31, high = (whole & ~31) | (low ? 16 : 0);
+            words[0][pol][sl][kl][lane] = __builtin_bit_cast(uint32_t, (float)high);
+            words[WORDS - 1][pol][sl][kl][lane] = __builtin_bit_cast(uint32_t, (float)(whole - high));
           }
         }
       }
@@ -476,8 +486,9 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
     const int ol = lane & 31, half = lane >> 5;
     if constexpr (SRC == kFromDevices) {
       // one wave per fragment group = (array, slice, direction, half of 32 outputs): a lane reads the 32 plane values of its
-      // record and takes the terms off them one after the other.  What is left is exact in single precision (it only gets
-      // smaller on the values' own grid); the second words join when it is small enough not to round them.
+      // record and takes the terms off them one after the other, all exact in single precision: the first words are whole
+      // multiples of 16 on the terms' grid below 2^28 (odd multiples where the second word is not zero, so that they lie on no
+      // midpoint of the first two terms), and the second words join when at most 2^18 is left of a value in range.
 #pragma unroll 1
       for (int grp = wave; grp < 8; grp += NW) {
         const int hh = grp & 1, dir = (grp >> 1) & 1, sl = NPOL == 2 ? 0 : grp >> 2, pol = NPOL == 2 ? grp >> 2 : 0;
@@ -494,7 +505,7 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
                       ((((size_t)t * b.OP[dir] + op) * a.S_w + s0 + sl) * a.terms * b.ks[dir] + J) * 1536;
 #pragma unroll 1
         for (int term = 0; term < a.terms; ++term, at += (size_t)b.ks[dir] * 1536) {
-          const float scale = __builtin_bit_cast(float, (uint32_t)(127 + a.term_exp[term]) << 23);
+          const float scale = __builtin_bit_cast(float, (uint32_t)(127 + kTermGrid + a.term_exp[term] - a.term_exp[0]) << 23);
           if (term == 2) {
 #pragma unroll
             for (int x = 0; x < 32; ++x) left[(x >> 2) & 1][4 * (x >> 3) + (x & 3)] += __builtin_bit_cast(float, second[(16 * (x >> 3) + (x & 7)) * stride]);

@@ -127,6 +127,26 @@ def test_plane_values_beyond_the_format(xb, R, arrays):
         assert np.array_equal(np.abs(got), np.abs(want))       # what is no number: the largest of either sign
 
 
+# Values of some 40 bits, and values on the midpoints between two codes of a term or one bit of 2^-40 beside them: the terms are
+# those that double precision gives, to the bit
+@pytest.mark.parametrize("R", [64, 128, 48])
+@pytest.mark.parametrize("arrays", [1, 2])
+@pytest.mark.parametrize("kind", ["any", "midpoints", "beside"])
+def test_terms_of_plane_values(xb, R, arrays, kind):
+    rng = np.random.default_rng(R + arrays)
+    shape = (2, 2, 100, 70)
+    distortion = rng.uniform(2.0 ** -16, 0.3, size=shape).astype(np.float32)     # multiples of 2^-41
+    if kind != "any":
+        depth = rng.integers(4, 23, size=shape)                                  # odd multiples of 2^-depth, below 0.5
+        distortion = (2 * rng.integers(0, 2 ** (depth - 2)) + 1) / 2.0 ** depth
+        if kind == "beside":
+            # ... and one single-precision step of that beside it: far below the last term's codes where it is small
+            distortion = distortion.astype(np.float32) + np.ldexp(distortion, -23) * rng.choice([-1, 1], size=shape)
+    copies, want, _ = profile_planes(xb, R, arrays, 13, distortion, seed=3)
+    for got in copies:
+        assert np.array_equal(got, want)
+
+
 # Streamed walk: 64 / 32 / 16 lanes per device and none, one device, queues that never fill and ones that always do,
 # the power series of the non-linearity (v up to 1 / 32) and exp(), states that start beyond the range
 @pytest.mark.parametrize("M,K,N,density,v,ni", [
