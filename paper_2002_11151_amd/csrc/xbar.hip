@@ -1559,9 +1559,13 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
     // no more than the sums hold: widening them on the way costs more (256 x 2304, 12544 rows backward: 1445 -> 1493 us)
     const int most = (int)std::min<unsigned long long>((unsigned long long)p.VT, held);
     double best = cost(per);
-    for (int n = per + 1; n <= most; ++n) {
+    // of the numbers that give as many chunks the smallest costs least: some 2 sqrt(VT) numbers instead of VT
+    for (int chunks = cdiv(p.VT, per); chunks > 1;) {
+      const int n = cdiv(p.VT, chunks - 1);
+      if (n > most) break;
       const double c_n = cost(n);
       if (c_n < best) { best = c_n; per = n; }
+      chunks = cdiv(p.VT, n);
     }
     p.vt_planned = per;
     p.chunked_us = best;

@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 import sys
+import time
 
 import pytest
 
@@ -189,6 +190,17 @@ def test_wide_sums_do_not_take_a_partial_result_per_tile(xb):
         cfg = xb.make_config(xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=1, stream_bits=1, adc_bits=adc, flags=xb.INPUT_SIGNED)
         digits = 2 * (M + 32) * (K + R)
         assert xb.workspace_bytes(cfg, xb.OP_FWD, M, K, N) <= digits + 8 * M * N + 256
+
+
+def test_plan_of_a_long_contraction_is_quick(xb):
+    # two million virtual tiles, which one sum holds: the plan weighs numbers of chunks, not every length of a chunk (9 ms)
+    cfg = xb.make_config(xbar_rows=16, xbar_cols=16, weight_bits=4, slice_bits=4, stream_bits=8, adc_bits=4, flags=xb.INPUT_SIGNED)
+    times = []
+    for _ in range(7):
+        begin = time.perf_counter()
+        assert xb.workspace_bytes(cfg, xb.OP_FWD, 4096, 1 << 24, 100) > 0
+        times.append(time.perf_counter() - begin)
+    assert min(times) < 1e-3
 
 
 def test_argument_checks_precede_any_device_work(xb):
