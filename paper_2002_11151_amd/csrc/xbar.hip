@@ -1544,9 +1544,16 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
   int per = std::max(1, cdiv(p.VT, std::max(1, cdiv(4096, groups))));
   const unsigned long long held = p.wide == 2 ? fit_split : p.wide ? ~0ull : fit;   // virtual tiles in one sum
   const int shares = std::min(4 / p.row_waves, d.S_in);   // of the cycles, among waves that have no rows of their own
+  p.a_bytes = align256((size_t)p.P * p.MP * p.g.T * p.ks16 * 512);
+  auto part_bytes = [&](int n) {
+    return align256((size_t)cdiv(p.VT, n) * M * p.Lout * (p.wide || (unsigned long long)n > held ? 8 : 4));
+  };
+  auto exchange_bytes = [&](int share) {   // LDS for the sums that a block's waves exchange
+    return (size_t)p.row_waves * (share - 1) * (p.wide ? 2 : 1) * p.pm * 16 * 64 * sizeof(uint32_t);
+  };
   {
     const int nk = d.fmt == kFmtF6 ? cdiv(std::min(p.g.tile, p.Lin), 64) : cdiv(std::min(p.g.tile, p.Lin), 16);
-    const double tile_us = 1.5 + d.S_w * d.S_in * p.pm * (0.175 + 0.0295 * d.terms * nk) / shares;
+    const double work_us = d.S_w * d.S_in * p.pm * (0.175 + 0.0295 * d.terms * nk), tile_us = 1.5 + work_us / shares;
     const double sums_us = 0.0089 * p.pm * p.row_waves / 8.0 * (p.wide ? 2 : 1);
     auto rounds_of = [](double r) {
       if (r <= 1.0) return r <= 0.5 ? 0.62 : 1.0;
@@ -1567,6 +1574,31 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
       if (c_n < best) { best = c_n; per = n; }
       chunks = cdiv(p.VT, n);
     }
+    // Few rows: chunks of what the sums hold let waves without rows share the cycles, which sums that are widened on the way do not; they
+    // leave more partial sums.  Either runs in rounds of the blocks that a compute unit holds, eight waves of them as far as LDS
+    // goes: without sharing, the planes of a tile leave room for two or three waves unless they are small.  Us, widened / shared: signed
+    // inputs, 64-row arrays, 8-bit converter, 4096 x 4096 weights, 16 rows: 807 / 365, 64: 842 / 434, 128: 1034 / 651; 4096 x 8192, 128-row
+    // arrays, 64 rows: 917 / 575; ideal arrays (one term): 4096 x 4096, 64 rows: 247 / 284, 7131 x 1656, 9-bit, 9 rows: 172 / 230.
+    // Of 100 random layers that have the choice none is 2.5 % slower than widened, those with wires are 1.7 times as fast.
+    // No layer outgrows the static array, and partial sums stay below the planes that the pass reads.
+    if ((unsigned long long)per > held && shares > 1) {
+      const double rows = (double)M / (32 * p.pm * p.row_waves);     // of a block's, those that there are
+      auto few_rows_us = [&](int n, int share) {
+        const size_t lds = std::max(p.lds_bytes, exchange_bytes(share));
+        const double blocks = (double)cdiv(p.VT, n) * groups;
+        const int resident = std::min(8 / (p.row_waves * share), (int)(160 * 1024 / lds)), widened = share > 1 ? 0 : (int)((n - 1) / held);
+        const double block_us = n * (1.5 + work_us / share) + (share > 1 ? 2.5 : 0.0);
+        return block_us * blocks / (256.0 * resident) + (1 + widened) * (widened ? 2 : 1) * sums_us * rows * blocks;
+      };
+      const double widened_us = few_rows_us(per, 1), shared_us = few_rows_us((int)held, shares);
+      const size_t more = part_bytes((int)held), less = part_bytes(per), fixed = XBAR_STATIC_SCRATCH_BYTES;
+      best = widened_us;
+      if (shared_us < widened_us &&
+          (p.a_bytes + more <= fixed || ((transposed || p.a_bytes + less > fixed) && more <= std::max(less, p.g.bytes)))) {
+        per = (int)held;
+        best = shared_us;
+      }
+    }
     p.vt_planned = per;
     p.chunked_us = best;
   }
@@ -1575,12 +1607,10 @@ VmmPlan plan_vmm(const xbar_config* c, const Derived& d, int M, int K, int N, bo
   // the tiles: 2907 x 1029 weights of 14 one-bit slices, 96-row arrays, 13-bit converter, 109547 rows: 1.6 GB instead of 28.6)
   p.flush_every = (unsigned long long)per > held ? (int)held : 0;
   p.nw = p.row_waves * (p.flush_every ? 1 : shares);   // sums that are widened on the way belong to one wave
-  if (p.nw > p.row_waves)      // the sums that the block's waves exchange
-    p.lds_bytes = std::max(p.lds_bytes, (size_t)(p.nw - p.row_waves) * (p.wide ? 2 : 1) * p.pm * 16 * 64 * sizeof(uint32_t));
+  p.lds_bytes = std::max(p.lds_bytes, exchange_bytes(p.nw / p.row_waves));
   p.nchunk = cdiv(p.VT, per);
   p.vt_per_chunk = cdiv(p.VT, p.nchunk);                  // same number of chunks, evenly filled
-  p.a_bytes = align256((size_t)p.P * p.MP * p.g.T * p.ks16 * 512);
-  p.part_bytes = align256((size_t)p.nchunk * M * p.Lout * ((p.wide || p.flush_every) ? 8 : 4));
+  p.part_bytes = part_bytes(per);
   p.ws_bytes = p.a_bytes + p.part_bytes;
   p.narrow = (unsigned long long)p.VT <= fit ? 1 : 0;
   p.small = vmm_small_pays(p, d) ? 1 : 0;

@@ -437,9 +437,10 @@ def test_rows_do_not_depend_on_the_batch(xb, R, sb, wb, adc, M, K, signed, N):
 
 
 # Few rows: waves without rows of their own share the streaming cycles (eight, two, one; sums in 32 bits, two of them, 64-bit
-# ones of odd slice counts): the outputs are those of the same rows in a batch that fills the waves
+# ones of odd slice counts), also in shorter chunks where sums hold fewer tiles than a batch that fills the waves has in one
+# (32-row arrays): the outputs are those of the same rows in such a batch
 @pytest.mark.parametrize("R,sb,wb,adc,signed", [(128, 1, 16, 8, True), (256, 2, 16, 10, False), (128, 4, 16, 8, True), (64, 8, 8, 8, False),
-                                                (128, 1, 16, 12, True), (128, 1, 14, 14, False)])
+                                                (128, 1, 16, 12, True), (128, 1, 14, 14, False), (32, 1, 16, 8, True)])
 @pytest.mark.parametrize("M", [1, 33, 64, 65, 128, 129])
 def test_few_rows_share_the_cycles(xb, R, sb, wb, adc, signed, M):
     K, N = 2500, 4100

@@ -192,6 +192,21 @@ def test_wide_sums_do_not_take_a_partial_result_per_tile(xb):
         assert xb.workspace_bytes(cfg, xb.OP_FWD, M, K, N) <= digits + 8 * M * N + 256
 
 
+def test_few_rows_take_chunks_that_their_sums_hold(xb):
+    # 64-row arrays, 8-bit converter: a 32-bit sum holds three tiles.  Chunks of more would be widened on the way by one wave of a
+    # block, the others of which have no rows: 4096 x 4096 weights took 2.7 times as long as 3072 x 4096.  Chunks are of three at most
+    cfg = xb.make_config(xbar_rows=64, xbar_cols=64, weight_bits=16, slice_bits=2, input_bits=8, stream_bits=1, adc_bits=8,
+                         flags=xb.INPUT_SIGNED | xb.NI_WIRE_AAM)
+    pad = lambda b: -(-b // 256) * 256
+    for M in (1, 16, 64, 128):
+        for K, N in ((3072, 4096), (3136, 4096), (4096, 4096), (4096, 4160), (6144, 4096), (4097, 8192)):
+            for op, Lin, Lout in ((xb.OP_FWD, K, N), (xb.OP_BWD, N, K)):
+                tiles = -(-Lin // 64)
+                partials = xb.workspace_bytes(cfg, op, M, K, N) - pad(2 * -(-M // 32) * tiles * 4 * 512)
+                assert partials >= pad(4 * M * Lout * -(-2 * tiles // 3))
+                assert partials % (4 * M * Lout) < 256
+
+
 def test_plan_of_a_long_contraction_is_quick(xb):
     # two million virtual tiles, which one sum holds: the plan weighs numbers of chunks, not every length of a chunk (9 ms)
     cfg = xb.make_config(xbar_rows=16, xbar_cols=16, weight_bits=4, slice_bits=4, stream_bits=8, adc_bits=4, flags=xb.INPUT_SIGNED)
