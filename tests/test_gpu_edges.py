@@ -413,7 +413,7 @@ def test_conv_is_its_patches(xb, batch, image, cin, cout, kernel, stride, pad, m
     assert np.array_equal(dX, want[:, pad:pad + image, pad:pad + image])
 
 
-# How a block leaves its sums: scaled outputs, 32- and 64-bit partial sums, one or two sums widened on the way, rows that are whole quads
+# How a block leaves its sums: scaled outputs, 32- and 64-bit partial sums, sums widened on the way, rows that are whole quads
 # and others, the last patch of rows and outputs.  A row's outputs do not depend on the rows beside it, and few rows are cut
 # into more chunks of the contraction, or taken by one kernel.
 @pytest.mark.parametrize("R,sb,wb,adc,M,K,signed", [(128, 1, 16, 8, 40000, 64, False), (128, 1, 16, 8, 3000, 300, True), (16, 1, 16, 8, 52500, 128, True),
@@ -434,6 +434,42 @@ def test_rows_do_not_depend_on_the_batch(xb, R, sb, wb, adc, M, K, signed, N):
     for rows in (slice(0, 70), slice(M - 1000, M)):
         assert torch.equal(Y[rows], xb.fwd(cfg, planes, X[rows].clone(), N, 5.0, 3.0))
         assert torch.equal(dX[rows], xb.bwd(cfg, planes, dY[rows].clone(), K, 5.0, 3.0))
+
+
+# Two 32-bit sums per output, widened on the way because a chunk has more virtual tiles than they hold: five, seven and six of three,
+# 46 of 45 (fp16 planes), five of three with one converter per array.  Ideal arrays: the oracle's bits, of the first and the last rows
+@pytest.mark.parametrize("R,sb,adc,M,K,N,backward,per_array", [
+    (64, 1, 16, 20000, 2000, 97, False, False), (64, 1, 16, 20000, 100, 2000, True, False), (16, 1, 16, 20000, 700, 99, False, False),
+    (16, 4, 16, 40000, 2576, 100, False, False), (128, 1, 15, 20000, 2000, 98, False, True)])
+def test_two_sums_widened_on_the_way(xo, xb, R, sb, adc, M, K, N, backward, per_array):
+    fs = workloads.adc_full_scale(R, sb, 2)
+    co, cg = both_configs(xo, xb, xbar_rows=R, xbar_cols=R, weight_bits=16, slice_bits=2, input_bits=8, stream_bits=sb, adc_bits=adc,
+                          flags=xo.INPUT_SIGNED | (xo.ADC_PER_ARRAY if per_array else 0), adc_fs_fwd=fs, adc_fs_bwd=fs)
+    # what the plan has to be for the case to be one, read off the workspace
+    Lin, Lout = (N, K) if backward else (K, N)
+    q_adc = 2 ** adc - 1 if per_array else 2 ** (adc - 1) - 1
+    weights = [sum(1 << (2 * s + sb * b) for s in range(n) for b in range(8 // sb)) for n in (4, 8)]
+    held = (2 ** 31 - 1) // (weights[0] * q_adc)
+    tiles = -(-Lin // R)
+    digits = -(-(2 * -(-M // 32) * tiles * (R // 16) * 512) // 256) * 256
+    chunks = (xb.workspace_bytes(cg, xb.OP_BWD if backward else xb.OP_FWD, M, K, N) - digits) // (8 * M * Lout)
+    longest = -(-2 * tiles * (2 if per_array else 1) // chunks)
+    assert weights[1] * q_adc >= 2 ** 31 and 1 <= held < longest and longest % held
+
+    rng = np.random.default_rng(M + N)
+    W = rng.standard_normal((K, N), dtype=np.float32)
+    rows = np.r_[0:40, M - 40:M]
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    A = torch.randn((M, Lin), generator=gen, device="cuda")
+    planes = xb.tile(cg, dev(W), 5.0, 0)
+    got = (xb.bwd(cg, planes, A, K, 5.0, 4.0) if backward else xb.fwd(cg, planes, A, N, 5.0, 4.0))[rows].cpu().numpy()
+    want = (xo.bwd if backward else xo.fwd)(co, W, A[rows].cpu().numpy(), 5.0, 4.0)
+    if per_array:
+        # planes that are no whole device levels: the bits of the launch that reports codes and adds them up in 64 bits, and the output bar
+        assert np.array_equal(got, xb.fwd(cg, planes, A[rows].clone(), N, 5.0, 4.0, want_codes=True)[0].cpu().numpy())
+        assert rel_l2(got, want) <= 1e-3
+    else:
+        assert np.array_equal(got, want)
 
 
 # Few rows: waves without rows of their own share the streaming cycles (eight, two, one; sums in 32 bits, two of them, 64-bit

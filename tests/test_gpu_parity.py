@@ -128,13 +128,13 @@ IDEAL_CASES = [
     (128, 128, 8, 2, 4, False, 3, 1, 1, 8),
     (128, 128, 1, 2, 6, True, 50, 260, 40, 8),          # 3 slices: odd group, unpipelined path
     (32, 48, 1, 1, 5, False, 20, 70, 100, 6),           # 5 one-bit slices, 32-row / 48-column tiles
-    # sums beyond 32 bits: 32-bit sums per group of slices, widened group by group ...
+    # sums beyond 32 bits: two 32-bit sums per output, of the lower and the upper slices, widened at the end ...
     (128, 128, 1, 2, 16, False, 70, 600, 64, 12),
     (64, 64, 1, 2, 16, True, 40, 200, 70, 11),
     (256, 256, 1, 2, 16, False, 40, 520, 48, 13),
     (128, 128, 4, 4, 16, True, 33, 260, 50, 16),
     (128, 128, 1, 2, 16, True, 300, 2100, 40, 10),      # many tiles per chunk
-    # ... and 64-bit sums in registers where the slices do not split into even groups
+    # ... and 64-bit sums in registers where the slices do not come in pairs
     (128, 128, 1, 1, 15, False, 20, 200, 40, 12),
 ]
 
@@ -308,7 +308,7 @@ def test_plane_terms_follow_the_converter(xo, xb, adc_bits, ni, terms):
 @pytest.mark.parametrize("ni,adc_bits", [("aam+var", 12), ("pa+aam2", 12), ("ob+aam", 11)])
 def test_wide_sums_nonideal(xo, xb, ni, adc_bits):
     """Converters of 10 bits and more with 16-bit weights: the shift-and-add sum exceeds 32 bits.  The
-    production launch (32-bit sums per slice group, widened per group) returns the bits of the code-tap
+    production launch (two 32-bit sums per output, of the lower and the upper slices) returns the bits of the code-tap
     launch (64-bit sums), and both stay within the output bar of the oracle."""
     M, K, N = 70, 300, 100
     g = workloads.Gemm("t", K, N, M, True, 1)
