@@ -714,10 +714,15 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
       hipLaunchKernelGGL(pulse_mark_kernel, dim3(tiles16 * (unsigned)cdiv(a.n_words, a.seg_words)), dim3(256), 0, st, a);
       if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
       // few devices: several lanes per device, so that about a thousand waves or more share the walk; a move by exp() holds the
-      // issue for longer, so fewer waves do (us per update with noise, lanes per device 64 / 32 / 16: series 432 devices x 131072
-      // samples 474 / 712 / 1257, 2304 x 131072 1594 / 1822 / 2371, 4608 x 32768 664 / 564 / 714, 9216 x 32768 1502 / 1300 / 1232;
-      // linear 2304 1184 / 1442 / 2010, 3200 x 40000 634 / 616 / 936, 6912 x 32768 855 / 888 / 818; exp() 1152 x 30000 336 / 329 /
-      // 482, 4608 1196 / 891 / 985, 6912 1871 / 1631 / 1196)
+      // issue for longer, so fewer waves do.  One line serves moves with and without a normal number: what the lanes share out
+      // without one, marks and trains, has the walks cross at much the same sizes (us per update, lanes per device 64 / 32 / 16,
+      // without noise | with it:
+      //   series  432 devices x 131072 samples 452 / 637 / 1040 | 488 / 725 / 1264, 2304 x 131072 1486 / 1552 / 1937 | 1647 / 1820 /
+      //           2323, 3200 x 40000 405 / 353 / 485 | 446 / 407 / 611, 6144 x 32768 611 / 541 / 482 | 683 / 633 / 605
+      //   linear  1600 x 60000 271 / 351 / 505 | 317 / 423 / 602, 2304 x 131072 983 / 1217 / 1747 | 1236 / 1516 / 2099, 3200 x 40000 310 /
+      //           290 / 414 | 356 / 347 / 533, 6912 x 32768 485 / 484 / 439 | 602 / 620 / 561, 12288 x 16384 417 / 371 / 397 | 510 / 468 / 504
+      //   exp()   432 x 131072 691 / 890 / 1345 | 733 / 993 / 1598, 1152 x 65536 960 / 903 / 1259 | 1051 / 987 / 1469, 4608 x 32768 823 / 613 /
+      //           626 | 918 / 710 / 755, 6912 x 32768 1211 / 999 / 704 | 1328 / 1144 / 844)
       if (stream && devices < (move_mode(a, nl) == 2 ? 1024 : 2560)) launch_pulse_stream<64>(a, nl, noise, st);
       else if (stream && devices < 6144) launch_pulse_stream<32>(a, nl, noise, st);
       else if (stream) launch_pulse_stream<16>(a, nl, noise, st);
