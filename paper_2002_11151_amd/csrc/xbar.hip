@@ -417,7 +417,7 @@ constexpr int kFromDevices = 2;   // anything else: every device of the patch co
 // numbers and the wire model (one Philox block for the four devices of a slice pair); each weight is quantised once per slice
 // pair.  The terms of 32 values come out of the conversion instructions a record at a time, twice (either direction), which is
 // a tenth of the integer work of finding every value's term codes and picking the records' bits from them: 4096 x 4096 weights
-// with variation, 8 slices, 5 terms, 1485 -> 1181 us, and 1658 -> 1485 with the shorter normal numbers.
+// with variation, 8 slices, 5 terms, 1485 -> 1197 us, and 1658 -> 1485 with the shorter normal numbers.
 template <int SRC, int NPOL, int NTH>
 __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns) {
   constexpr int SL = NPOL == 2 ? 1 : 2;              // slices per turn: as many words in LDS either way
