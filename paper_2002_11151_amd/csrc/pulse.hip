@@ -54,16 +54,19 @@ struct PulseArgs {
 
 __device__ __forceinline__ uint32_t pulse_train(uint32_t k0, uint32_t k1, uint64_t step, uint64_t index, double p, int bl) {
   const uint64_t threshold = (uint64_t)::rint(clampd(p, 0.0, 1.0) * 4294967296.0);
+  const uint32_t last = (uint32_t)(threshold - 1);   // word < threshold as word <= last; threshold 0 is dealt with at the end
+  // slot 0 first, four slots at a time: it ends up in the highest of the bits made
   uint32_t bits = 0;
-  for (int j = 0; j < bl; j += 4) {
-    const uint64_t blk = index * 8 + (uint64_t)(j >> 2);
+  const int blocks = (bl + 3) >> 2;
+  for (int j = 0; j < blocks; ++j) {
+    const uint64_t blk = index * 8 + (uint64_t)j;
     uint32_t w[4];
     philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), (uint32_t)step, (uint32_t)(step >> 32), k0, k1, w);
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (j + e < bl && (uint64_t)w[e] < threshold) bits |= 1u << (j + e);
+    for (int e = 0; e < 4; ++e) bits = bits + bits + (w[e] <= last ? 1u : 0u);
   }
-  return bits;
+  bits = __builtin_bitreverse32(bits) >> (32 - 4 * blocks);   // slot j at bit j
+  return threshold ? bits & ((1u << bl) - 1u) : 0u;
 }
 
 // Deterministic code of a value: slot = frame * td + sub-slot; a row takes the first rne(p tx) frames
@@ -93,9 +96,10 @@ __global__ __launch_bounds__(256) void pulse_trains_kernel(PulseArgs a) {
     const uint64_t index = (uint64_t)a.m0 * a.K + (uint64_t)t;               // m K + k
     double x;
     if constexpr (CONV) {        // element (m, k) of the patch matrix: k = (kh KW + kw) C + c
-      const int m = a.m0 + (int)(t / a.K), k = (int)(t % a.K);
-      const int c = k % a.conv.C, kk = k / a.conv.C;
-      x = (double)conv_fetch(a.X, a.conv, conv_row(a.conv, m), kk / a.conv.KW, kk % a.conv.KW, c);
+      const int sample = n_rows < (1ll << 32) ? (int)((uint32_t)t / (uint32_t)a.K) : (int)(t / a.K);   // the short division
+      const uint32_t k = (uint32_t)(t - (long long)sample * a.K), kk = k / (uint32_t)a.conv.C, kh = kk / (uint32_t)a.conv.KW;
+      x = (double)conv_fetch(a.X, a.conv, conv_row(a.conv, a.m0 + sample), (int)kh, (int)(kk - kh * (uint32_t)a.conv.KW),
+                             (int)(k - kk * (uint32_t)a.conv.C));
     } else {
       x = (double)a.X[index];
     }
