@@ -386,206 +386,261 @@ __global__ __launch_bounds__(256) void pulse_walk_kernel(PulseArgs a) {
   if (a.pulses) a.pulses[dev] = (a.first ? 0 : a.pulses[dev]) + moved;
 }
 
-// The streamed walk: L lanes share a device, so that a layer with few devices spreads over the chip.  Only the moves of
-// a device are sequential; which samples it is pulsed in, the trains and the normal numbers of its pulses are not.  A
-// group of L lanes reads L mark words of its device at a time, lists the marked samples in LDS, fetches the trains of L
-// of them side by side, lists their pulses, evaluates L normal numbers side by side, and then all its lanes walk through
-// those L moves in step, each move a handful of dependent double-precision operations.  Samples and pulses that do not
-// fill a batch of L wait for the next one.  What bounds it: the walk's dependent chain (some 50 cycles per pulse) plus
-// a normal number (some 300 instructions) per L pulses.
+// The streamed walk: a block has one wave that walks and, for each of its devices, one that feeds it.  Only the moves of a
+// device are sequential; which samples it is pulsed in, the trains and the normal numbers of its pulses are not.  A feeding
+// wave lists its device's marked samples (ring in LDS), fetches the trains of 64 of them side by side, lists their pulses (a
+// second ring) and evaluates 64 normal numbers side by side; the walking wave, a lane per device, takes the 64 moves before
+// while the next ones are made.  One barrier per 64 pulses of every device hands them over.  Without marks (MARKED false: too
+// few samples for a marking pass to pay) a feeding wave takes the trains of 256 samples at a time, marked or not.
+// What bounds it: few devices, the walk's chain of dependent double-precision operations beside the latency of the lists;
+// many, the normal numbers (some 300 instructions per 64 pulses).  Whole update of 144 x 16 devices and 131072 samples, series
+// and noise: 1669 -> 894 us (300 of it trains, 96 marks) against 64 lanes per device that all ran through every move; 27 x 16 506 ->
+// 300, 576 x 64 and 8192 samples 1151 -> 765.
 // NL: 0 linear device; 1 write non-linearity by its power series about mid-range (v <= 1/32: six powers leave less than 1e-18
 // of exp(-v y) on 0 <= y <= 1); 2 by exp().
 // With the series an upward pulse moves the state g by dw_min exp(-v (1 + g) / 2), a downward one back by dw_min exp(-v (1 - g) / 2),
 // that is by direction times the even powers of g plus the odd ones as they are.  A move is complete, noise included, before it
 // joins the state, which is rounded once per pulse: 2.4e-16 rms after 200 pulses against 113-bit arithmetic (noise joining the state
 // by itself: 3.5e-16; a state held on 0 .. 1, which the last operation could clamp by itself: 1.2e-15).
-// Twelve operations a pulse, eight of them in a chain: the 144 x 16 layer at 131072 samples, whole update, 1657 us (on 0 .. 1 eleven
-// and six, 1599; eight powers of (1 + g) / 2 or (1 - g) / 2 sixteen and nine, 32 lanes per device 2160).
-template <int L, int NL, bool NOISE>
-__global__ __launch_bounds__(64) void pulse_stream_kernel(PulseArgs a) {
+constexpr int kStreamRing = 256;                     // entries of a ring: fewer than 64 waiting, plus what a fetch brings
+constexpr int kStreamMoves = 65;                     // moves of a device and batch, one more to spread the devices over the banks
+constexpr int kStreamMaxDevices = 15;                // per block: 16 waves
+
+constexpr size_t stream_lds_bytes(int devices) {
+  return (size_t)devices * (2 * kStreamMoves * sizeof(double2) + 2 * kStreamRing * sizeof(uint32_t)) + 2 * 16 * sizeof(int) + 2 * sizeof(int);
+}
+
+// Inclusive sum over the lanes of a wave: DPP row shifts by 1, 2, 4 and 8, then the last lane of a row or half to the rows behind.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+template <int NL, bool NOISE, bool MARKED>
+__global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int devices) {
 #pragma clang fp contract(off)
-  constexpr int D = 64 / L;                          // devices per wave
-  constexpr int SQ = 33 * L, PQ = 32 * L;            // queues: up to L - 1 waiting, plus 32 words' halves / 31 pulses per sample
-  __shared__ uint32_t samples[D][SQ];
-  __shared__ uint32_t pulses[D][PQ];                 // sample << 6 | ordinal << 1 | upwards
-  __shared__ double2 moves[64];                      // noise of a pulse; half its direction (whole with the series; 0: no pulse)
-  const int lane = threadIdx.x, gl = lane & (L - 1), grp = lane / L;
-  const size_t kn = (size_t)a.K * a.N, want = (size_t)blockIdx.x * D + grp;
-  const bool valid = want < kn;
-  const size_t dev = valid ? want : kn - 1;
+  extern __shared__ __align__(16) char stream_lds[];
+  double2* moves = reinterpret_cast<double2*>(stream_lds);      // [2][devices][kStreamMoves]: noise, direction (half of it: linear, exp())
+  uint32_t* rings = reinterpret_cast<uint32_t*>(moves + 2 * devices * kStreamMoves);   // [devices][samples, pulses][kStreamRing]
+  int* runs = reinterpret_cast<int*>(rings + devices * 2 * kStreamRing);               // [2][16] moves of a device in a batch
+  int* alive = runs + 2 * 16;                                   // [2] batch number + 1 where a device had moves in it
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const size_t kn = (size_t)a.K * a.N, dev0 = (size_t)blockIdx.x * devices;
+  if (threadIdx.x < 2) alive[threadIdx.x] = 0;
+  __syncthreads();
+
+  if (wave == 0) {
+    __builtin_amdgcn_s_setprio(3);                   // the chain: what feeds it has time
+    const bool valid = lane < devices && dev0 + lane < kn;
+    const size_t dev = valid ? dev0 + lane : kn - 1;
+    const double2* mine = moves + min(lane, devices - 1) * kStreamMoves;
+    auto begin = [&]() __attribute__((always_inline)) { return a.first ? (double)a.W[dev] / a.w_max : a.state[dev]; };
+    double g = begin();
+    double gx = clampd(g, -1.0, 1.0);                // where the non-linearity finds the state
+    bool pulsed = false;
+    const double up_down = 2.0 * a.dw_min;
+    auto move = [&](const double2 b) __attribute__((always_inline)) {
+      double next;
+      if constexpr (NL == 1) {
+        const double z = gx * gx, zz = z * z;
+        const double odd = __builtin_fma(zz, a.series[5], __builtin_fma(z, a.series[3], a.series[1]));
+        const double even = __builtin_fma(zz, __builtin_fma(z, a.series[6], a.series[4]), __builtin_fma(z, a.series[2], a.series[0]));
+        const double directed = NOISE ? __builtin_fma(b.y, even, b.x) : b.y * even;
+        next = g + __builtin_fma(gx, odd, directed);
+      } else {
+        const double step = b.y * up_down;
+        if constexpr (NL == 0) next = g + step;
+        else next = g + step * ::exp(-a.v * __builtin_fma(b.y, gx, 0.5));   // x upwards, 1 - x downwards
+        if constexpr (NOISE) next += b.x;
+      }
+      return ::fmin(::fmax(next, -1.0), 1.0);
+    };
+    for (int batch = 0;; ++batch) {
+      if (batch > 0) {                               // the moves before, while the next ones are made
+        const double2* mv = mine + ((batch - 1) & 1) * devices * kStreamMoves;
+        const int run = valid ? runs[((batch - 1) & 1) * 16 + lane] : 0;
+        pulsed = pulsed || run > 0;
+        auto walk = [&](auto partial) __attribute__((always_inline)) {
+          double2 b[8], ahead[8];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) ahead[t] = mv[t];
+#pragma unroll 1
+          for (int t0 = 0; t0 < 64; t0 += 8) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) b[t] = ahead[t];
+            const int behind = min(t0 + 8, 56);      // read under this turn's moves
+#pragma unroll
+            for (int t = 0; t < 8; ++t) ahead[t] = mv[behind + t];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+              const double next = move(b[t]);
+              if (decltype(partial)::value && t0 + t >= run) continue;   // a device without a pulse keeps its state, also beyond the range
+              g = gx = next;
+            }
+          }
+        };
+        if (__any(valid && run < 64)) walk(std::true_type{});
+        else walk(std::false_type{});
+      }
+      __syncthreads();
+      if (alive[batch & 1] != batch + 1) break;      // no device had moves in this batch: none has any left
+    }
+    // The moves' minimum and maximum drop a NaN, which a clamp by comparison keeps; a step is finite, so the state is NaN
+    // at the end only if it began as one.  A device without a pulse keeps what it held to the bit (a moved -0 is +0).
+    // Read again rather than held in registers through the walk.
+    const double g_begin = begin();
+    if (!pulsed || g_begin != g_begin) g = g_begin;
+    if (valid) {
+      if (a.last) a.W[dev] = (float)(a.w_max * g);
+      else a.state[dev] = g;
+    }
+    return;
+  }
+
+  const int slot = wave - 1;
+  const bool valid = dev0 + slot < kn;
+  const size_t dev = valid ? dev0 + slot : kn - 1;
   const int k = (int)(dev / a.N), n = (int)(dev % a.N);
   NormalStream rng(a.seed, kStreamPulseNoise, (effective_step(a.step, a.step_add) << 31) | dev);
+  uint32_t* sq = rings + slot * 2 * kStreamRing;     // marked samples
+  uint32_t* pq = sq + kStreamRing;                   // pulses: sample << 6 | ordinal << 1 | upwards
+  const double unit = NL == 1 ? 1.0 : 0.5;
+  int n_s = 0, s_head = 0, n_p = 0, p_head = 0, moved = 0;   // entries waiting, and where they begin
+  // Marked: the next word of marks, this lane's word and its sample; else the next sample and four of this lane
+  constexpr int U = MARKED ? 1 : 4;
   const unsigned long long* marks = a.marks + dev * a.n_words;
-  uint32_t* sq = samples[grp];
-  uint32_t* pq = pulses[grp];
-  const double2* mv = &moves[grp * L];
-  auto begin = [&]() __attribute__((always_inline)) { return a.first ? (double)a.W[dev] / a.w_max : a.state[dev]; };
-  double g = begin();
-  double gx = clampd(g, -1.0, 1.0);                  // where the non-linearity finds the state
-  bool pulsed = false;
-  const double up_down = 2.0 * a.dw_min, unit = NL == 1 ? 1.0 : 0.5;
-  int n_s = 0, n_p = 0, moved = 0;
+  const int n_next = !valid ? 0 : MARKED ? a.n_words : a.mc;
+  int next = 0;
+  uint32_t at[U], q[U], up[U];                       // number, shared slots, direction
+  unsigned long long word = 0;
 
-  auto scan = [&](int v) __attribute__((always_inline)) {   // inclusive, over the lanes of the group
-#pragma unroll
-    for (int d = 1; d < L; d <<= 1) {
-      const int o = __shfl_up(v, d, L);
-      if (gl >= d) v += o;
-    }
-    return v;
+  auto trains = [&](int u) __attribute__((always_inline)) {
+    const uint32_t rw = a.rows[(size_t)at[u] * a.K + k], cw = a.cols[(size_t)at[u] * a.N + n];
+    q[u] = rw & cw & 0x7FFFFFFFu;
+    up[u] = (rw ^ cw) >> 31;                         // against the sign of x d
   };
-  // All loops below run as long as any device of the wave has work (their conditions are the same for all lanes).  The
-  // last turn (`flush`) lists nothing and takes what is left in the queues.
-  unsigned long long next_word = (valid && gl < a.n_words) ? marks[gl] : 0ull;
-  bool flush = false;
-  for (int w0 = 0; !flush; w0 += L) {
-    flush = w0 >= a.n_words;
-    const unsigned long long word = next_word;
-    next_word = (valid && w0 + L + gl < a.n_words) ? marks[w0 + L + gl] : 0ull;
-    // the words of one half of the lanes at a time: the queue holds that many samples
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-      {
-        unsigned long long bits = (gl >= L / 2) == (half == 1) ? word : 0ull;
-        const int c = __popcll(bits), inc = scan(c);
-        int pos = n_s + inc - c;
-        const uint32_t base = (uint32_t)(w0 + gl) * 64u;
+  auto left = [&]() __attribute__((always_inline)) { return n_s > 0 || next < n_next; };
+  // Trains of up to 64 marked samples, and the next 64 words where they may be needed; or of the next 256 samples.
+  auto fetch = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      q[u] = 0;
+      if constexpr (MARKED) {
+        if (lane < n_s) {
+          at[u] = sq[(s_head + lane) & (kStreamRing - 1)];
+          trains(u);
+        }
+      } else {
+        at[u] = (uint32_t)(next + 64 * u + lane);
+        if ((int)at[u] < n_next) trains(u);
+      }
+    }
+    if constexpr (MARKED) word = (n_s < 128 && next + lane < n_next) ? marks[next + lane] : 0ull;
+  };
+  // The pulses of 64 samples into their ring, as many samples as there is room for; returns how many.
+  auto append_pulses = [&](int u, bool there) __attribute__((always_inline)) {
+    const int c = __popc(q[u]), inc = wave_scan(c);
+    const bool fits = there && n_p + inc <= kStreamRing;
+    const int taken = __popcll(__ballot(fits));      // the first lanes: inc does not fall with the lane
+    uint32_t bits = fits ? q[u] : 0u, pos = (uint32_t)(p_head + n_p + inc - c);
+    for (uint32_t ord = 0; __any(bits != 0); ++ord)
+      if (bits) {
+        pq[pos++ & (kStreamRing - 1)] = (at[u] << 6) | (ord << 1) | up[u];
+        bits &= bits - 1;
+      }
+    if (taken > 0) n_p += __builtin_amdgcn_readlane(inc, taken - 1);
+    return taken;
+  };
+  auto append = [&]() __attribute__((always_inline)) {
+    if constexpr (MARKED) {
+      const bool more_words = n_s < 128 && next < n_next;
+      if (n_s > 0) {
+        const int taken = append_pulses(0, lane < n_s);
+        n_s -= taken;
+        s_head += taken;
+      }
+      if (more_words) {
+        const int c = __popcll(word), inc = wave_scan(c);
+        const bool fits = n_s + inc <= kStreamRing;
+        const int taken = __popcll(__ballot(fits));
+        unsigned long long bits = fits ? word : 0ull;
+        uint32_t pos = (uint32_t)(s_head + n_s + inc - c);
+        const uint32_t base = (uint32_t)(next + lane) * 64u;
         while (__any(bits != 0))
           if (bits) {
-            sq[pos++] = base + (uint32_t)__builtin_ctzll(bits);
+            sq[pos++ & (kStreamRing - 1)] = base + (uint32_t)__builtin_ctzll(bits);
             bits &= bits - 1;
           }
-        n_s += __shfl(inc, L - 1, L);
+        if (taken > 0) n_s += __builtin_amdgcn_readlane(inc, taken - 1);
+        next += taken;
       }
-      __syncthreads();
-      int taken = 0;
-      while (__any(n_s - taken >= (flush ? 1 : L) || (flush && n_p > 0))) {
-        // a batch of samples: their trains, and their pulses
-        const int take = n_s - taken >= L ? L : (flush ? n_s - taken : 0);
-        uint32_t at = 0, q = 0, up = 0;
-        if (gl < take) {
-          at = sq[taken + gl];
-          const uint32_t rw = a.rows[(size_t)at * a.K + k], cw = a.cols[(size_t)at * a.N + n];
-          q = rw & cw & 0x7FFFFFFFu;
-          up = (rw ^ cw) >> 31;                      // against the sign of x d
+    } else {
+      int taken = 64;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (taken == 64) {                           // else the rest is fetched again
+          taken = append_pulses(u, true);
+          next += taken;
         }
-        taken += take;
-        {
-          const int c = __popc(q), inc = scan(c);
-          int pos = n_p + inc - c;
-          for (uint32_t ord = 0; __any(q != 0); ++ord)
-            if (q) {
-              pq[pos++] = (at << 6) | (ord << 1) | up;
-              q &= q - 1;
-            }
-          n_p += __shfl(inc, L - 1, L);
-        }
-        __syncthreads();
-        const int full = flush && taken >= n_s ? 1 : L;   // the device's very last pulses need not fill a batch
-        int done = 0;
-        while (__any(n_p - done >= full)) {
-          // a batch of pulses: their normal numbers side by side, then the moves one after the other
-          const int run = n_p - done >= full ? min(L, n_p - done) : 0;
-          pulsed = pulsed || run > 0;
-          double2 e = {0.0, 0.0};
-          if (gl < run) {
-            const uint32_t p = pq[done + gl];
-            const bool upwards = (p & 1u) != 0;
-            e.y = upwards ? unit : -unit;
-            moved += upwards ? 1 : -1;
-            if constexpr (NOISE) e.x = a.sigma * rng.get((uint64_t)(a.m0 + (int)(p >> 6)) * 32 + ((p >> 1) & 31u));
-          }
-          moves[lane] = e;
-          __syncthreads();
-          // a device without a pulse in this batch keeps its state, also one beyond the range
-          if constexpr (NL == 1) {
-            const double g_kept = g, gx_kept = gx;
-            auto moves_of = [&](auto partial) __attribute__((always_inline)) {
-#pragma unroll 1
-              for (int t0 = 0; t0 < L; t0 += 8) {
-                if (!__any(t0 < run)) break;
-                double2 b[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) b[t] = mv[t0 + t];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                  const double z = gx * gx, zz = z * z;
-                  const double odd = __builtin_fma(zz, a.series[5], __builtin_fma(z, a.series[3], a.series[1]));
-                  const double even = __builtin_fma(zz, __builtin_fma(z, a.series[6], a.series[4]), __builtin_fma(z, a.series[2], a.series[0]));
-                  const double directed = NOISE ? __builtin_fma(b[t].y, even, b[t].x) : b[t].y * even;
-                  const double next = g + __builtin_fma(gx, odd, directed);
-                  if (decltype(partial)::value && t0 + t >= run) continue;
-                  g = gx = ::fmin(::fmax(next, -1.0), 1.0);
-                }
-              }
-            };
-            // short batches are the last ones of a device
-            if (__any(run > 0 && run < L)) moves_of(std::true_type{});
-            else moves_of(std::false_type{});
-            if (run <= 0) {
-              g = g_kept;
-              gx = gx_kept;
-            }
-          } else {
-            const double lo = run > 0 ? -1.0 : -INFINITY, hi = run > 0 ? 1.0 : INFINITY;
-#pragma unroll 1
-            for (int t0 = 0; t0 < L; t0 += 8) {
-              if (!__any(t0 < run)) break;
-              double2 b[8];
-#pragma unroll
-              for (int t = 0; t < 8; ++t) b[t] = mv[t0 + t];
-#pragma unroll
-              for (int t = 0; t < 8; ++t) {
-                const double step = b[t].y * up_down;
-                double next;
-                if constexpr (NL == 0) next = g + step;
-                else next = g + step * ::exp(-a.v * __builtin_fma(b[t].y, gx, 0.5));   // x upwards, 1 - x downwards
-                if constexpr (NOISE) next += b[t].x;
-                g = ::fmin(::fmax(next, lo), hi);
-                if constexpr (NL != 0) gx = run > 0 ? g : gx;
-              }
-            }
-          }
-          done += run;
-          __syncthreads();
-        }
-        const uint32_t rest = gl < n_p - done ? pq[done + gl] : 0u;
-        __syncthreads();
-        pq[gl] = rest;
-        n_p -= done;
-        __syncthreads();
-      }
-      const uint32_t rest = gl < n_s - taken ? sq[taken + gl] : 0u;
-      __syncthreads();
-      sq[gl] = rest;
-      n_s -= taken;
-      __syncthreads();
     }
+    wave_exchange();
+  };
+  // With fewer than 64 pulses waiting there is room for a sample's (at most 31); where no marked sample waits, for a word's:
+  // every turn of this loop takes one of them.
+  auto fill = [&]() __attribute__((always_inline)) {
+    while (n_p < 64 && left()) {
+      fetch();
+      append();
+    }
+  };
+  bool ahead = false;
+  for (int batch = 0;; ++batch) {
+    if (ahead) append();
+    fill();
+    // the loads of the batch after this one are on their way under the normal numbers
+    ahead = n_p < 128 && left();
+    if (ahead) fetch();
+    const int run = min(n_p, 64);
+    double2 e = {0.0, 0.0};
+    if (lane < run) {
+      const uint32_t p = pq[(p_head + lane) & (kStreamRing - 1)];
+      const bool upwards = (p & 1u) != 0;
+      e.y = upwards ? unit : -unit;
+      moved += upwards ? 1 : -1;
+      if constexpr (NOISE) e.x = a.sigma * rng.get((uint64_t)(a.m0 + (int)(p >> 6)) * 32 + ((p >> 1) & 31u));
+    }
+    moves[((batch & 1) * devices + slot) * kStreamMoves + lane] = e;
+    if (lane == 0) {
+      runs[(batch & 1) * 16 + slot] = run;
+      if (run > 0) alive[batch & 1] = batch + 1;
+    }
+    n_p -= run;
+    p_head += run;
+    __syncthreads();
+    if (alive[batch & 1] != batch + 1) break;
   }
 #pragma unroll
-  for (int d = 1; d < L; d <<= 1) moved += __shfl_xor(moved, d, L);
-  // The moves' minimum and maximum drop a NaN, which a clamp by comparison keeps; a step is finite, so the state is NaN
-  // at the end only if it began as one.  A device without a pulse keeps what it held to the bit (a moved -0 is +0).
-  // Read again rather than held in registers through the walk.
-  const double g_begin = begin();
-  if (!pulsed || g_begin != g_begin) g = g_begin;
-  if (valid && gl == 0) {
-    if (a.last) a.W[dev] = (float)(a.w_max * g);
-    else a.state[dev] = g;
-    if (a.pulses) a.pulses[dev] = (a.first ? 0 : a.pulses[dev]) + moved;
-  }
+  for (int d = 1; d < 64; d <<= 1) moved += __shfl_xor(moved, d, 64);
+  if (a.pulses && valid && lane == 0) a.pulses[dev] = (a.first ? 0 : a.pulses[dev]) + moved;
 }
 
 int move_mode(const PulseArgs& a, bool nl) { return !nl ? 0 : a.v <= 1.0 / 32.0 ? 1 : 2; }   // NL of pulse_stream_kernel
 
-template <int L>
+template <bool MARKED>
 void launch_pulse_stream(const PulseArgs& a, bool nl, bool noise, hipStream_t st) {
   const int mode = move_mode(a, nl);
-  void (*k)(PulseArgs);
-  if (noise) k = mode == 0 ? pulse_stream_kernel<L, 0, true> : mode == 1 ? pulse_stream_kernel<L, 1, true> : pulse_stream_kernel<L, 2, true>;
-  else k = mode == 0 ? pulse_stream_kernel<L, 0, false> : mode == 1 ? pulse_stream_kernel<L, 1, false> : pulse_stream_kernel<L, 2, false>;
-  const long long kn = (long long)a.K * a.N;
-  hipLaunchKernelGGL(k, dim3((unsigned)((kn * L + 63) / 64)), dim3(64), 0, st, a);
+  void (*k)(PulseArgs, int);
+  if (noise) k = mode == 0 ? pulse_stream_kernel<0, true, MARKED> : mode == 1 ? pulse_stream_kernel<1, true, MARKED> : pulse_stream_kernel<2, true, MARKED>;
+  else k = mode == 0 ? pulse_stream_kernel<0, false, MARKED> : mode == 1 ? pulse_stream_kernel<1, false, MARKED> : pulse_stream_kernel<2, false, MARKED>;
+  // a block per compute unit at a time, the devices spread evenly over the rounds that takes
+  const long long kn = (long long)a.K * a.N, per_round = 256 * kStreamMaxDevices, rounds = (kn + per_round - 1) / per_round;
+  const int devices = (int)((kn + 256 * rounds - 1) / (256 * rounds));
+  hipLaunchKernelGGL(k, dim3((unsigned)((kn + devices - 1) / devices)), dim3(64 * (devices + 1)), stream_lds_bytes(devices), st, a, devices);
 }
 
 constexpr int kTwoPhaseBlocks = 4096;
@@ -700,12 +755,13 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
     if (p.two_phase) {
       a.n_words = cdiv(a.mc, 64);
       const long long devices = (long long)K * N;
-      // Up to where several lanes per device (below) beat one: all of them run through every move, so the line falls with
-      // a move's own cost (linear, series, exp()) and rises where a normal number per pulse is shared out.  One lane /
-      // several, ms per update of so many devices x samples, or the ratio: linear 27916 devices 0.82, 34112 1.01; series
-      // 19561 0.87, 26112 x 52424 43.3 / 53.5; exp() 7038 0.96, 25400 x 6209 7.6 / 12.5; with noise: linear 44550 0.88, series
-      // 36386 0.91, 46506 x 2554 6.6 / 7.6, exp() 28086 0.96, 46658 x 12371 94 / 155
-      const int line[2][3] = {{32768, 20480, 8192}, {49152, 40960, 28672}};
+      // Up to where the streamed walk beats a lane per device that does everything by itself: the walk that others feed does
+      // not take longer for more devices until the feeding waves fill the chip, from then on it does, and an exp() per move
+      // fills it sooner.  Streamed / not, us per update, around each line:
+      //   linear  576 x 96 devices, 8192 samples 597 / 686, 576 x 128 x 4096 499 / 476; series 576 x 128 x 4096 574 / 603, 576 x 256
+      //   961 / 711; exp() 288 x 96 x 8192 566 / 744, 576 x 64 944 / 879; with noise: linear 576 x 128 x 4096 740 / 799, 576 x 256
+      //   1330 / 986; series 576 x 96 x 8192 1078 / 1502, 576 x 128 x 4096 874 / 856; exp() 576 x 64 x 8192 1043 / 1284, 576 x 96 1478 / 1502
+      const int line[2][3] = {{65536, 77824, 32768}, {90112, 69632, 53248}};
       const bool stream = devices < line[noise ? 1 : 0][move_mode(a, nl)];
       const unsigned tiles16 = (unsigned)(cdiv(K, 16) * cdiv(N, 16));
       // measured, ms per update, [n_words][K N] / [K N][n_words], walks of one lane per device: noise, 65536 devices x 12544
@@ -717,19 +773,7 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
       a.seg_words = !stream || tiles16 >= 256 ? 64 : tiles16 >= 64 ? 16 : 4;
       hipLaunchKernelGGL(pulse_mark_kernel, dim3(tiles16 * (unsigned)cdiv(a.n_words, a.seg_words)), dim3(256), 0, st, a);
       if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
-      // few devices: several lanes per device, so that about a thousand waves or more share the walk; a move by exp() holds the
-      // issue for longer, so fewer waves do.  One line serves moves with and without a normal number: what the lanes share out
-      // without one, marks and trains, has the walks cross at much the same sizes (us per update, lanes per device 64 / 32 / 16,
-      // without noise | with it:
-      //   series  432 devices x 131072 samples 452 / 637 / 1040 | 488 / 725 / 1264, 2304 x 131072 1486 / 1552 / 1937 | 1647 / 1820 /
-      //           2323, 3200 x 40000 405 / 353 / 485 | 446 / 407 / 611, 6144 x 32768 611 / 541 / 482 | 683 / 633 / 605
-      //   linear  1600 x 60000 271 / 351 / 505 | 317 / 423 / 602, 2304 x 131072 983 / 1217 / 1747 | 1236 / 1516 / 2099, 3200 x 40000 310 /
-      //           290 / 414 | 356 / 347 / 533, 6912 x 32768 485 / 484 / 439 | 602 / 620 / 561, 12288 x 16384 417 / 371 / 397 | 510 / 468 / 504
-      //   exp()   432 x 131072 691 / 890 / 1345 | 733 / 993 / 1598, 1152 x 65536 960 / 903 / 1259 | 1051 / 987 / 1469, 4608 x 32768 823 / 613 /
-      //           626 | 918 / 710 / 755, 6912 x 32768 1211 / 999 / 704 | 1328 / 1144 / 844)
-      if (stream && devices < (move_mode(a, nl) == 2 ? 1024 : 2560)) launch_pulse_stream<64>(a, nl, noise, st);
-      else if (stream && devices < 6144) launch_pulse_stream<32>(a, nl, noise, st);
-      else if (stream) launch_pulse_stream<16>(a, nl, noise, st);
+      if (stream) launch_pulse_stream<true>(a, nl, noise, st);
       else if (noise) {
         // lanes decoupled over the whole chunk: with a normal number per pulse every turn counts
         void (*walk)(PulseArgs) = nl ? pulse_walk_kernel<true, true> : pulse_walk_kernel<false, true>;
@@ -740,6 +784,14 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
         void (*staged)(PulseArgs) = nl ? pulse_apply_kernel<1, true, false, true> : pulse_apply_kernel<1, false, false, true>;
         hipLaunchKernelGGL(staged, dim3(tiles16), dim3(256), 0, st, a);
       }
+      if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
+      continue;
+    }
+    // Few devices and samples: streamed without marks.  Streamed / staged, us per update with noise | without: 64 x 10 devices, 64
+    // samples 15 / 21 | 14 / 14, 2000 samples 40 / 232 | 37 / 138; 784 x 10, 32 samples 28 / 21 | 20 / 15, 64 29 / 32 | 21 / 21, 1024
+    // 91 / 236 | 72 / 135; 400 x 40, 256 samples 61 / 60 | 47 / 35, 2000 253 / 328 | 248 / 192
+    if ((long long)K * N <= 8192 && M >= 64) {
+      launch_pulse_stream<false>(a, nl, noise, st);
       if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
       continue;
     }

@@ -147,7 +147,7 @@ def test_terms_of_plane_values(xb, R, arrays, kind):
         assert np.array_equal(got, want)
 
 
-# Streamed walk: 64 / 32 / 16 lanes per device and none, one device, queues that never fill and ones that always do,
+# Streamed walk: blocks of one device to fifteen, one device, queues that never fill and ones that always do,
 # the power series of the non-linearity (v up to 1 / 32) and exp(), states that start beyond the range
 @pytest.mark.parametrize("M,K,N,density,v,ni", [
     (2048, 1, 1, 4.0, 0.01, "nl+noise"), (2100, 31, 33, 4.0, 1.0 / 32, "nl"), (4200, 31, 33, 0.02, 0.01, "nl+noise"),
@@ -172,7 +172,7 @@ def test_pulsed_walk(xo, xb, M, K, N, density, v, ni):
 
 # Moves far below the range, from weights of zero: the state is as exact about zero as a double is (moves of 2^-40 on a grid of
 # 2^-53 would be off by 1e-4 of themselves); each pulse adds a few units in the last place of a move
-@pytest.mark.parametrize("K,N", [(31, 33), (60, 60), (96, 70)])     # 64, 32 and 16 lanes per device
+@pytest.mark.parametrize("K,N", [(31, 33), (60, 60), (96, 70)])     # 4, 15 and 14 devices per block
 @pytest.mark.parametrize("ni", ["nl", "nl+noise"])
 def test_pulsed_walk_of_short_moves(xo, xb, K, N, ni):
     M = 2100
@@ -186,12 +186,30 @@ def test_pulsed_walk_of_short_moves(xo, xb, K, N, ni):
     assert np.abs(Wg - Wo).max() <= 2.0 ** -23 * np.abs(Wo).max()
 
 
-# ... on both sides of the lines between several lanes per device and one, for each cost of a move
+# ... layers of a wide range of device counts, for each cost of a move
 @pytest.mark.parametrize("K,N,v,ni", [(128, 255, 0.0, ""), (128, 257, 0.0, ""), (128, 159, 0.01, "nl"), (128, 161, 0.01, "nl"), (64, 127, 0.04, "nl"),
                                       (64, 129, 0.04, "nl"), (128, 383, 0.0, "noise"), (128, 385, 0.0, "noise"), (128, 319, 0.01, "nl+noise"),
                                       (128, 321, 0.01, "nl+noise"), (128, 223, 0.04, "nl+noise"), (128, 225, 0.04, "nl+noise")])
 def test_lines_of_the_pulsed_walk(xo, xb, K, N, v, ni):
     test_pulsed_walk(xo, xb, 2048, K, N, 0.02, v, ni)
+
+
+# ... on both sides of the lines between the streamed walk and a lane per device
+@pytest.mark.parametrize("K,N,v,ni", [(128, 511, 0.0, ""), (128, 513, 0.0, ""), (128, 607, 0.01, "nl"), (128, 609, 0.01, "nl"), (128, 703, 0.0, "noise"),
+                                      (128, 705, 0.0, "noise"), (128, 543, 0.01, "nl+noise"), (128, 545, 0.01, "nl+noise"),
+                                      (128, 415, 0.04, "nl+noise"), (128, 417, 0.04, "nl+noise")])
+def test_lines_of_the_streamed_walk(xo, xb, K, N, v, ni):
+    test_pulsed_walk(xo, xb, 2048, K, N, 0.02, v, ni)
+
+
+# ... without marks: up to 8192 devices and fewer than 2048 samples; samples that fill no group of 64 or 256, rings that run full in the
+# middle of a group, a last block of fewer devices, one block per compute unit and one device more
+@pytest.mark.parametrize("M,K,N,density,v,ni", [
+    (64, 1, 1, 4.0, 0.01, "nl+noise"), (63, 31, 33, 4.0, 0.01, "nl+noise"), (65, 31, 33, 4.0, 0.0, ""), (255, 31, 33, 4.0, 0.04, "nl+noise"),
+    (257, 15, 17, 0.05, 0.01, "nl"), (320, 60, 64, 0.5, 0.01, "nl+noise"), (513, 60, 65, 0.02, 0.0, "noise"), (2047, 3, 7, 4.0, 0.01, "nl+noise"),
+    (2047, 128, 64, 0.05, 0.04, "nl"), (300, 128, 65, 0.3, 0.01, "nl+noise")])
+def test_streamed_walk_without_marks(xo, xb, M, K, N, density, v, ni):
+    test_pulsed_walk(xo, xb, M, K, N, density, v, ni)
 
 
 # Weights that are no numbers or lie at or beyond the range, in devices with pulses in every batch, in some and in none (rows
