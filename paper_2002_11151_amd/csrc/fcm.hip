@@ -1,6 +1,7 @@
 // Circuit-level crossbar model (Sec. IV-A) producing the stored distortion profile of Sec. IV-D:
 // kernels and xbar_fcm_profile.
 #include "xbar_common.h"
+#include <type_traits>
 
 using namespace xbar_detail;
 
@@ -222,18 +223,25 @@ __global__ __launch_bounds__(256) void fcm_kernel(FcmArgs a) {
   }
 }
 
-// Same solve for 64 x 64 and 128 x 128 crossbars with the whole state on chip.  NT threads form a (NT / 16) x 16 grid;
-// thread (ty, tx) owns the SR x SC devices at rows SR ty.., columns SC tx..; residual and search direction live in its
-// registers (two waves per SIMD: one alone leaves the double-precision pipe waiting for its own results), sqrt(G) in
-// LDS.  With u = s p, S_k the sum of a row's u from column k on and P_k that of a column's u down to row k,
-//   (Lr u)_j = r_source S_0 + r_row sum_{k <= j} S_k,     u.Lr u = r_source S_0^2 + r_row sum_k S_k^2,
-//   (Lc u)_i = r_sense P_last + r_col sum_{k >= i} P_k,   u.Lc u = r_sense P_last^2 + r_col sum_k P_k^2,
-// so p.Ap comes out of the pass that forms p and its sums (9 operations per device: squares of the sums inside the
-// thread's patch, completed with what lies outside it after the scans), and the residual pass rebuilds A p from
-// running sums (9 more); A p is never stored.  Sums along a row run over the 16 consecutive lanes that share ty (DPP row
-// shifts), along a column over the 4 lane groups of a wave (shuffles) and over the waves (LDS, one thread per column).
-// Measured on the 784 x 500 layer of the 784-500-10 perceptron (128 x 128 arrays, 4 slices): 12.4 -> 5.0 ms against
-// 8 x 8 devices per thread, one wave per SIMD and A p evaluated twice (40 operations per device and iteration).
+// Same solve for 64 x 64 and 128 x 128 crossbars with the whole state on chip, in device currents: with u = S r and w = S p
+// (S = sqrt(G)) an iteration is  w <- u + beta w;  u <- u - alpha (w + G L w),  and x, whose column sums are wanted, grows by
+// alpha w.  NT threads form a (NT / 16) x 16 grid; thread (ty, tx) owns the SR x SC devices at rows SR ty.., columns SC tx..; u and
+// w live in its registers (two waves per SIMD: one alone leaves the double-precision pipe waiting for its own results), G in LDS.
+// With S_k the sum of a row's w from column k on and P_k that of a column's w down to row k,
+//   (Lr w)_j = r_source S_0 + r_row sum_{k <= j} S_k,     w.Lr w = r_source S_0^2 + r_row sum_k S_k^2,
+//   (Lc w)_i = r_sense P_last + r_col sum_{k >= i} P_k,   w.Lc w = r_sense P_last^2 + r_col sum_k P_k^2.
+// Sums along a row run over the 16 consecutive lanes that share ty (DPP row shifts), along a column over the 4 lane groups of
+// a wave (row swaps) and over the waves (LDS, one thread per column and kind of sum).
+// The driven rows of a crossbar differ in the right-hand side alone and excite much the same part of the spectrum, so only a
+// block's first solve works out alpha and beta (conjugate gradients, stopped at half the tolerance); the others run the same
+// coefficients -- a fixed polynomial in the matrix -- without the scalar products and their barriers, and measure the residual
+// once at the end.  One that misses the tolerance is finished by conjugate gradients, and the next starts anew.  (On the CPU,
+// 128 x 128 devices at 1e-11: as many iterations as conjugate gradients of its own or one more, for Rmin of 1e3 .. 1e5 Ohm, 10 %
+// variation, ragged tiles.)
+// What bounds it: the issue of vector instructions, 770 per thread and iteration of 32 devices (353 the recurrences at 11 per
+// device, the rest sums across lanes and waves), some 70 % of the time.  784 x 500 layer of the 784-500-10 perceptron (128 x 128
+// arrays, 4 slices): 5.1 -> 3.4 ms against scalar products in every iteration (1130 instructions, four barriers for two, 15 of
+// them spills); 256 x 256 weights on 64 x 64 arrays 345 -> 258 us, 64 x 10 61 -> 35.
 template <int CTRL>
 __device__ __forceinline__ double dpp_row_f64(double x) {   // lanes whose source lies outside the row of 16 get 0
   union { double d; int i[2]; } v, o;
@@ -251,20 +259,29 @@ __device__ __forceinline__ double row16_inclusive_scan(double x) {
   return x;
 }
 
-// Inclusive sum over the four groups of 16 lanes of a wave (lane by lane), by row swaps: even and odd rows, then halves.
-__device__ __forceinline__ double group16_inclusive_scan(double x, int lane) {
-  union { double d; uint32_t i[2]; } v, even, odd, t, low;
-  v.d = x;
+// Inclusive sums of two values over the four groups (rows) of 16 lanes of a wave, lane by lane.  Row swaps between the two values
+// line both up for one addition; upper: 1.0 in rows 2 and 3, else 0.0.
+__device__ __forceinline__ void group16_inclusive_scans(double& x, double& y, double upper) {
+  union Word { double d; uint32_t i[2]; } a, b, t, u, v;
+  auto swap16 = [](Word& p, Word& q) __attribute__((always_inline)) {   // the odd rows of p with the even rows of q
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const auto s = __builtin_amdgcn_permlane16_swap(v.i[h], v.i[h], false, false);
-    even.i[h] = s[0];                               // rows 0, 0, 2, 2
-    odd.i[h] = s[1];                                // rows 1, 1, 3, 3
-  }
-  t.d = even.d + odd.d;
+    for (int h = 0; h < 2; ++h) {
+      const auto s = __builtin_amdgcn_permlane16_swap(p.i[h], q.i[h], false, false);
+      p.i[h] = s[0];
+      q.i[h] = s[1];
+    }
+  };
+  a.d = x;
+  b.d = y;
+  swap16(a, b);                                      // a: x0 y0 x2 y2, b: x1 y1 x3 y3
+  t.d = a.d + b.d;                                   // x0 + x1, y0 + y1, x2 + x3, y2 + y3
 #pragma unroll
-  for (int h = 0; h < 2; ++h) low.i[h] = __builtin_amdgcn_permlane32_swap(t.i[h], t.i[h], false, false)[0];   // rows 0 + 1
-  return ((lane & 16) ? t.d : x) + (lane >= 32 ? low.d : 0.0);
+  for (int h = 0; h < 2; ++h) u.i[h] = __builtin_amdgcn_permlane32_swap(t.i[h], t.i[h], false, false)[0];   // rows 0, 1, 0, 1 of t
+  v = u;
+  swap16(u, v);                                      // x0 + x1 in every row of u, y0 + y1 in every row of v
+  swap16(a, t);                                      // a: x0, x0 + x1, x2, x2 + x3; t: the same of y
+  x = __builtin_fma(upper, u.d, a.d);
+  y = __builtin_fma(upper, v.d, t.d);
 }
 
 // Sum over the block, returned to every thread, in a fixed order: rows of 16 lanes by DPP, the four rows of a wave by
@@ -287,213 +304,321 @@ __device__ __forceinline__ double block_sum_n(double v, double* red) {
 }
 
 template <int SR, int SC, int NT>
+struct FcmShape {
+  static constexpr int NW = NT / 64;                 // waves; 4 thread rows (ty) per wave
+  static constexpr int R = (NT / 16) * SR, C = 16 * SC;          // == a.R, a.C
+  static constexpr int kSums = 2 * NW * C;
+  // G, a wave's column sums, what lies before / behind a wave; the last wave has nothing behind it: that line holds the slots
+  // of the block sums and the coefficients
+  static constexpr size_t kLdsBytes = (size_t)(R * C + 2 * kSums) * sizeof(double);
+  static constexpr int kSteps = (C - 2 * NW) / 2;    // coefficients kept
+};
+
+template <int SR, int SC, int NT>
 __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
   extern __shared__ double fcm_lds[];
-  constexpr int NW = NT / 64;                        // waves; 4 thread rows (ty) per wave
-  constexpr int R = (NT / 16) * SR, C = 16 * SC;     // == a.R, a.C
-  double* s_lds = fcm_lds;                           // [SR * SC][NT]: element (ar, bc) of thread tid
-  double* xch = s_lds + SR * SC * NT;                // [2][NW][C]: a wave's column sums, then what the waves before / behind it
-                                                     //   hold; column SC tx + bc at 16 bc + tx (no bank conflicts)
-  double* tot = xch + 2 * NW * C;                    // [C] column totals
-  double* red = tot + C;                             // [2][NW]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  using Shape = FcmShape<SR, SC, NT>;
+  constexpr int NW = Shape::NW, R = Shape::R, C = Shape::C, kSteps = Shape::kSteps;
+  double* g_lds = fcm_lds;                           // [SR * SC][NT]: element (ar, bc) of thread tid
+  double* sums = g_lds + SR * SC * NT;               // [2][NW][C]: a wave's column sums; column SC tx + bc at 16 bc + tx (no bank
+                                                     //   conflicts).  Written before the first barrier of an iteration, read before the second, but
+                                                     //   for a wave's own
+  double* rest = sums + Shape::kSums;                // [2][NW][C]: of the waves above (of the first wave: all), of those below.  Written
+                                                     //   between the barriers, read behind the second
+  double* total = rest;                              // [C] column totals
+  double* red = rest + (2 * NW - 1) * C;             // [2][NW]
+  double* coef = red + 2 * NW;                       // [2][kSteps]: alpha, beta
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int tx = tid & 15, ty = tid >> 4;
   const int i0 = ty * SR, j0 = tx * SC;
-  NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
+  // Places in LDS as an opaque start plus constants, which the instructions hold; taken apart by the compiler they are an address
+  // register for each.  G reaches beyond what an instruction holds: two starts.
+  constexpr int kHalf = SR * SC / 2;
+  int at_g0 = tid, at_g1 = kHalf * NT + tid, at_wave = wave * C + tx, at_column = tx;
+  asm("" : "+v"(at_g0), "+v"(at_g1), "+v"(at_wave), "+v"(at_column));
+  auto g_of = [&](int e) __attribute__((always_inline)) -> double& { return g_lds[e < kHalf ? at_g0 + e * NT : at_g1 + (e - kHalf) * NT]; };
+  const double upper = lane >= 32 ? 1.0 : 0.0;
 
+  const int group = blockIdx.x % a.groups;
+  const int t1 = blockIdx.x / a.groups;
+  const int pol = t1 & 1;
+  const int s = (t1 >> 1) % a.S_w;
+  const int tile = (t1 >> 1) / a.S_w;
+  const int k0 = (tile / a.tiles_c) * R, n0 = (tile % a.tiles_c) * C;
+  const int rows = min(R, a.K - k0), cols = min(C, a.N - n0);
+  const int rhs_begin = group * a.rhs_per_group, rhs_end = min(rows, rhs_begin + a.rhs_per_group);
+  if (rhs_begin >= rhs_end) return;                  // a ragged tile: no row left for this block
+
+  // every thread reads back only what it wrote itself: no barrier needed for g_lds.  Weights first, all loads side by side
+#pragma unroll
+  for (int ar = 0; ar < SR; ++ar)
+#pragma unroll
+    for (int bc = 0; bc < SC; ++bc) {
+      const int i = min(i0 + ar, rows - 1), j = min(j0 + bc, cols - 1);
+      g_lds[(ar * SC + bc) * NT + tid] = (double)a.W[(size_t)(k0 + i) * a.N + n0 + j];
+    }
   {
-    const int item = blockIdx.x;
-    const int group = item % a.groups;
-    const int t1 = item / a.groups;
-    const int pol = t1 & 1;
-    const int s = (t1 >> 1) % a.S_w;
-    const int tile = (t1 >> 1) / a.S_w;
-    const int k0 = (tile / a.tiles_c) * R, n0 = (tile % a.tiles_c) * C;
-    const int rows = min(R, a.K - k0), cols = min(C, a.N - n0);
+    const double qw = (double)((1u << a.weight_bits) - 1), w_max = (double)a.w_max;
+    NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
+#pragma unroll 1
+    for (int e = 0; e < SR * SC; ++e) {
+      const int i = i0 + e / SC, j = j0 + e % SC;
+      double g = 0.0;
+      if (i < rows && j < cols) {
+        const int wq = quantized_weight((float)g_lds[e * NT + tid], w_max, qw, qw / w_max);
+        const int digit = (int)(((uint32_t)abs(wq) >> (a.slice_bits * s)) & ((1u << a.slice_bits) - 1));
+        const bool mine = pol == 0 ? wq > 0 : wq < 0;
+        g = a.g_min + (mine ? digit * a.dg : 0.0);
+        if (a.flags & XBAR_NI_VARIATION) {
+          const uint64_t dev = (((uint64_t)(k0 + i) * (uint64_t)a.N + (uint64_t)(n0 + j)) * (uint64_t)a.S_w + (uint64_t)s) * 2 + pol;
+          g *= 1.0 + a.var_sigma * rng.get(dev);
+        }
+      }
+      g_lds[e * NT + tid] = ::fmax(g, 0.0);
+    }
+  }
 
-#pragma unroll 1
-    for (int ar = 0; ar < SR; ++ar)
-#pragma unroll 1
-      for (int bc = 0; bc < SC; ++bc) {
-        const int i = i0 + ar, j = j0 + bc;
-        double g = 0.0;
-        if (i < rows && j < cols) {
-          const double qw = (double)((1u << a.weight_bits) - 1);
-          const double wq =
-              ::rint(clampd((double)a.W[(size_t)(k0 + i) * a.N + n0 + j] / (double)a.w_max, -1.0, 1.0) * qw);
-          const int digit = (int)(((uint32_t)::fabs(wq) >> (a.slice_bits * s)) & ((1u << a.slice_bits) - 1));
-          const bool mine = pol == 0 ? wq > 0.0 : wq < 0.0;
-          g = a.g_min + (mine ? digit * a.dg : 0.0);
-          if (a.flags & XBAR_NI_VARIATION) {
-            const uint64_t dev =
-                (((uint64_t)(k0 + i) * (uint64_t)a.N + (uint64_t)(n0 + j)) * (uint64_t)a.S_w + (uint64_t)s) * 2 + pol;
-            g *= 1.0 + a.var_sigma * rng.get(dev);
+  int steps = 0;                                     // coefficients known
+  for (int rhs = rhs_begin; rhs < rhs_end; ++rhs) {
+    double u[SR][SC], w[SR][SC], e = 0.0;            // e: solution summed over column tid % C
+    double beta = 0.0, alpha = 0.0, part = 0.0;
+    // v^2 / g; a device that is not there has v = 0.  The instruction's reciprocal is good to 2^-26 or so: scalar products that
+    // choose a step and a stop need no more
+    auto over_g = [&](double v, double g) __attribute__((always_inline)) { return v * v * __builtin_amdgcn_rcp(::fmax(g, 1e-300)); };
+    // Computed here: left alone, the compiler moves the arithmetic behind the next branch and keeps all that it waits for
+    auto pin = [](double& x, double& y, double& z) __attribute__((always_inline)) { asm volatile("" : "+v"(x), "+v"(y), "+v"(z)); };
+    // One iteration; CG: alpha from w.A w and, in `part`, the square of what is left.  `first`: w is 0 outside the driven row.
+    auto iterate = [&](auto is_cg, bool first, double rr) __attribute__((always_inline)) {
+      constexpr bool CG = decltype(is_cg)::value;
+      // Column by column in both passes: two running sums per row, those of one column at a time.  (Row by row the running sums
+      // of all columns are alive beside u and w, and the registers spill.)
+      double row0[SR], row1[SR], col0[SC], col1[SC], cross[SC] = {};   // row0: sum of w from the column on; row1: sum of those sums
+      double pq = 0.0, energy = 0.0, row_sq = 0.0, col_sq = 0.0;
+      if (CG || !first || (rhs >= 4 * SR * wave && rhs < 4 * SR * (wave + 1))) {
+        // w <- u + beta w: sums, sums of the sums (and their squares) inside this thread's patch, rows from the right, columns
+        // from above
+#pragma unroll
+        for (int bc = SC - 1; bc >= 0; --bc) {
+          double run = 0.0, runs = 0.0;
+#pragma unroll
+          for (int ar = 0; ar < SR; ++ar) {
+            w[ar][bc] = __builtin_fma(beta, w[ar][bc], u[ar][bc]);
+            row0[ar] = bc == SC - 1 ? w[ar][bc] : row0[ar] + w[ar][bc];   // no sums that begin with 0: they are not free
+            row1[ar] = bc == SC - 1 ? row0[ar] : row1[ar] + row0[ar];
+            run = ar == 0 ? w[ar][bc] : run + w[ar][bc];
+            runs = ar == 0 ? run : runs + run;
+            if constexpr (CG) {
+              pq += over_g(w[ar][bc], g_of(ar * SC + bc));
+              row_sq = __builtin_fma(row0[ar], row0[ar], row_sq);
+              col_sq = __builtin_fma(run, run, col_sq);
+              pin(pq, row_sq, col_sq);
+            }
+          }
+          // sums over the lane groups above inside the wave.  Kept per column: the sum and the sum of (R - i) w down to and
+          // with this thread inside the wave, and what multiplies the sum above the wave in the squares of P
+          col0[bc] = run;
+          col1[bc] = __builtin_fma((double)(R - SR - i0), run, runs);
+          group16_inclusive_scans(col0[bc], col1[bc], upper);
+          if constexpr (CG) {
+            const double in0 = col0[bc] - run;       // above this thread, inside the wave
+            col_sq = __builtin_fma(in0, __builtin_fma((double)SR, in0, 2.0 * runs), col_sq);
+            cross[bc] = 2.0 * __builtin_fma((double)SR, in0, runs);
+          }
+          pin(col0[bc], col1[bc], cross[bc]);
+#pragma unroll
+          for (int ar = 0; ar < SR; ++ar) pin(w[ar][bc], row0[ar], row1[ar]);
+        }
+        energy = a.r_row * row_sq;
+      } else {
+#pragma unroll
+        for (int bc = 0; bc < SC; ++bc) col0[bc] = col1[bc] = 0.0;
+#pragma unroll
+        for (int ar = 0; ar < SR; ++ar) row0[ar] = row1[ar] = 0.0;
+      }
+      if (lane >= 48) {                              // last group of the wave holds the wave's sums
+#pragma unroll
+        for (int bc = 0; bc < SC; ++bc) {
+          sums[at_wave + 16 * bc] = col0[bc];
+          sums[at_wave + NW * C + 16 * bc] = col1[bc];
+        }
+      }
+      __syncthreads();
+      if (tid < 2 * C) {                             // one thread per column and kind of sum: prefix / suffix over the waves
+        const int kind = tid / C, j = tid % C;
+        const double* from = sums + kind * NW * C + j;
+        double* to = rest + kind * NW * C + j;
+        double v[NW], run = 0.0;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) v[x] = from[x * C];
+        if (kind == 0) {
+#pragma unroll
+          for (int x = 0; x < NW; ++x) {
+            if (x > 0) to[x * C] = run;
+            run += v[x];
+          }
+          to[0] = run;
+        } else {
+#pragma unroll
+          for (int x = NW - 1; x > 0; --x) {
+            run += v[x];
+            to[(x - 1) * C] = run;
           }
         }
-        s_lds[(ar * SC + bc) * NT + tid] = ::sqrt(::fmax(g, 0.0));
       }
-    // every thread reads back only what it wrote itself: no barrier needed for s_lds
+      // rows: what lies outside the patch, and w.A w's row part.  From here on row0 is S at the patch's first column, row1
+      // the drop up to it.  (Between the barriers: half of the waves have nothing else to do there)
+#pragma unroll
+      for (int ar = 0; ar < SR; ++ar) {
+        const double full1 = __builtin_fma((double)j0, row0[ar], row1[ar]);   // sum of (j + 1) w
+        const double inc0 = row16_inclusive_scan(row0[ar]), inc1 = row16_inclusive_scan(full1);
+        const double all = dpp_row_f64<0x15F>(inc0);   // row_newbcast:15
+        const double right = all - inc0;           // sum of w to the right of the patch
+        if constexpr (CG) {                        // the driver's share
+          energy = __builtin_fma(a.r_row * right, __builtin_fma((double)SC, right, 2.0 * row1[ar]), energy);
+          energy = __builtin_fma(tx == 0 ? a.r_source * all : 0.0, all, energy);
+        }
+        row1[ar] = __builtin_fma(a.r_row, __builtin_fma((double)j0, all - (inc0 - row0[ar]), inc1 - full1), a.r_source * all);
+        row0[ar] = a.r_row * (right + row0[ar]);
+        pin(row0[ar], row1[ar], energy);
+      }
+      __syncthreads();
+      auto outside = [&](int bc, double& above, double& below1, double& all) __attribute__((always_inline)) {
+        const double in_above = rest[at_wave + 16 * bc], in_below = rest[at_wave + NW * C + 16 * bc];
+        all = total[at_column + 16 * bc];
+        above = wave == 0 ? 0.0 : in_above;
+        below1 = (wave == NW - 1 ? 0.0 : in_below) + (sums[at_wave + NW * C + 16 * bc] - col1[bc]);
+      };
+      if constexpr (CG) {
+#pragma unroll
+        for (int bc = 0; bc < SC; ++bc) {
+          double above, below1, all;
+          outside(bc, above, below1, all);
+          col_sq = __builtin_fma(above, __builtin_fma((double)SR, above, cross[bc]), col_sq);
+          energy = __builtin_fma(ty == 0 ? a.r_sense * all : 0.0, all, energy);
+          pin(col_sq, energy, cross[bc]);
+        }
+        pq += __builtin_fma(a.r_col, col_sq, energy);
+        alpha = rr / block_sum_n<NW>(pq, red + NW);
+        part = 0.0;
+      }
+      // u <- u - alpha A w
+#pragma unroll
+      for (int bc = 0; bc < SC; ++bc) {
+        double above, below1, all;
+        outside(bc, above, below1, all);
+        // from the row below the patch up: the drop; P at the patch's last row (both in Ohm units)
+        const double last = above + col0[bc];
+        double pre = a.r_col * last, lc = __builtin_fma(a.r_col, __builtin_fma((double)(R - SR - i0), last, below1), a.r_sense * all);
+#pragma unroll
+        for (int ar = SR - 1; ar >= 0; --ar) {
+          const double g = g_of(ar * SC + bc);
+          row1[ar] += row0[ar];
+          row0[ar] = __builtin_fma(-a.r_row, w[ar][bc], row0[ar]);
+          lc += pre;
+          pre = __builtin_fma(-a.r_col, w[ar][bc], pre);
+          const double q = __builtin_fma(g, row1[ar] + lc, w[ar][bc]);
+          u[ar][bc] = __builtin_fma(-alpha, q, u[ar][bc]);
+          if constexpr (CG) part += over_g(u[ar][bc], g);
+          pin(u[ar][bc], row0[ar], row1[ar]);
+          if constexpr (CG) pin(part, lc, pre);
+        }
+      }
+      e = __builtin_fma(alpha, total[tid & (C - 1)], e);   // column sum of x = sum alpha w
+    };
 
-    const int rhs_end = min(rows, (group + 1) * a.rhs_per_group);
-    for (int rhs = group * a.rhs_per_group; rhs < rhs_end; ++rhs) {
-      double r[SR][SC], p[SR][SC], e = 0.0;          // e: solution summed over column tid
-      double part = 0.0;
+    double b2 = 0.0;                                 // square of the right-hand side S v
+#pragma unroll
+    for (int ar = 0; ar < SR; ++ar)
+#pragma unroll
+      for (int bc = 0; bc < SC; ++bc) {
+        u[ar][bc] = (i0 + ar == rhs) ? g_of(ar * SC + bc) : 0.0;
+        w[ar][bc] = 0.0;
+        b2 += u[ar][bc];
+      }
+    double rr = block_sum_n<NW>(b2, red + NW);
+    const double stop = a.tol2 * rr;
+    const bool known = steps > 0;
+    if (known) {
+      for (int it = 0; it < steps; ++it) {
+        alpha = coef[it];
+        beta = coef[kSteps + it];
+        iterate(std::false_type{}, it == 0, 0.0);
+      }
+      part = 0.0;
 #pragma unroll
       for (int ar = 0; ar < SR; ++ar)
 #pragma unroll
-        for (int bc = 0; bc < SC; ++bc) {
-          r[ar][bc] = (i0 + ar == rhs) ? s_lds[(ar * SC + bc) * NT + tid] : 0.0;
-          p[ar][bc] = 0.0;
-          part += r[ar][bc] * r[ar][bc];
-        }
-      double rr = block_sum_n<NW>(part, red);
-      const double stop = a.tol2 * rr;
-      double beta = 0.0;
-      for (int it = 0; it < a.max_iter && rr > stop; ++it) {
-        // p <- r + beta p; u = s p: sums, sums of the sums and their squares inside this thread's patch, rows from the
-        // right, columns from above
-        double row0[SR], row1[SR], col0[SC], col1[SC];
-        double pq = 0.0, row_sq = 0.0, col_sq = 0.0;
-#pragma unroll
-        for (int x = 0; x < SC; ++x) col0[x] = col1[x] = 0.0;
-#pragma unroll
-        for (int ar = 0; ar < SR; ++ar) {
-          double run = 0.0, runs = 0.0;
-#pragma unroll
-          for (int bc = SC - 1; bc >= 0; --bc) {
-            p[ar][bc] = __builtin_fma(beta, p[ar][bc], r[ar][bc]);
-            const double u = s_lds[(ar * SC + bc) * NT + tid] * p[ar][bc];
-            pq = __builtin_fma(p[ar][bc], p[ar][bc], pq);
-            run += u;
-            runs += run;
-            row_sq = __builtin_fma(run, run, row_sq);
-            col0[bc] += u;
-            col1[bc] += col0[bc];
-            col_sq = __builtin_fma(col0[bc], col0[bc], col_sq);
-          }
-          row0[ar] = run;                            // sum of u
-          row1[ar] = runs;                           // sum of (j - j0 + 1) u
-          // a row at a time: left alone, the compiler sets the chains of squares aside and spills what they wait for
-          asm volatile("" : "+v"(pq), "+v"(row_sq), "+v"(col_sq));
-        }
-        // rows: what lies outside the patch, and p.Ap's row part
-        double suffix[SR], left1[SR], energy = a.r_row * row_sq;
-#pragma unroll
-        for (int ar = 0; ar < SR; ++ar) {
-          const double full1 = __builtin_fma((double)j0, row0[ar], row1[ar]);   // sum of (j + 1) u
-          const double inc0 = row16_inclusive_scan(row0[ar]), inc1 = row16_inclusive_scan(full1);
-          const double total = dpp_row_f64<0x15F>(inc0);   // row_newbcast:15
-          const double right = total - inc0;         // sum of u to the right of the patch
-          suffix[ar] = a.r_row * (right + row0[ar]); // S at the patch's first column; then the sum over k < j0 of S_k with
-          left1[ar] = __builtin_fma(a.r_row, __builtin_fma((double)j0, total - (inc0 - row0[ar]), inc1 - full1), a.r_source * total);
-          energy = __builtin_fma(a.r_row * right, __builtin_fma((double)SC, right, 2.0 * row1[ar]), energy);   // the driver's share
-          if (tx == 0) energy = __builtin_fma(a.r_source * total, total, energy);
-          if (ar & 1) asm volatile("" : "+v"(suffix[ar]), "+v"(left1[ar]), "+v"(energy));
-        }
-        // columns: sums over the lane groups above inside the wave.  Kept per column: the sum and the sum of (R - i) u down
-        // to and with this thread inside the wave, and what multiplies the sum above the wave in the squares of P
-        double cross[SC];
-#pragma unroll
-        for (int bc = 0; bc < SC; ++bc) {
-          double inc0 = col0[bc], inc1 = __builtin_fma((double)(R - SR - i0), col0[bc], col1[bc]);
-          inc0 = group16_inclusive_scan(inc0, lane);
-          inc1 = group16_inclusive_scan(inc1, lane);
-          const double in0 = inc0 - col0[bc];        // above this thread, inside the wave
-          col_sq = __builtin_fma(in0, __builtin_fma((double)SR, in0, 2.0 * col1[bc]), col_sq);
-          cross[bc] = 2.0 * __builtin_fma((double)SR, in0, col1[bc]);
-          col0[bc] = inc0;
-          col1[bc] = inc1;
-          if (bc & 1) asm volatile("" : "+v"(col0[bc]), "+v"(col1[bc]), "+v"(cross[bc]), "+v"(col_sq));
-        }
-        if (lane >= 48) {                            // last group of the wave holds the wave's sums
-#pragma unroll
-          for (int bc = 0; bc < SC; ++bc) {
-            xch[(0 * NW + wave) * C + 16 * bc + tx] = col0[bc];
-            xch[(1 * NW + wave) * C + 16 * bc + tx] = col1[bc];
-          }
-        }
-        __syncthreads();
-        if (tid < 2 * C) {                           // one thread per column and kind of sum: prefix / suffix over the waves
-          const int kind = tid / C, j = tid % C;
-          double* line = xch + kind * NW * C + j;
-          double v[NW], run = 0.0;
-#pragma unroll
-          for (int w = 0; w < NW; ++w) v[w] = line[w * C];
-          if (kind == 0) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w) { line[w * C] = run; run += v[w]; }   // above this wave
-            tot[j] = run;
-          } else {
-#pragma unroll
-            for (int w = NW - 1; w >= 0; --w) { run += v[w]; line[w * C] = run; }   // this wave and below
-          }
-        }
-        __syncthreads();
-        double lc[SC], pre[SC];                      // from the row below the patch up; P at the patch's last row (both in Ohm units)
-#pragma unroll
-        for (int bc = 0; bc < SC; ++bc) {
-          const double total = tot[16 * bc + tx], above = xch[(0 * NW + wave) * C + 16 * bc + tx];
-          const double below1 = xch[(1 * NW + wave) * C + 16 * bc + tx] - col1[bc];
-          col_sq = __builtin_fma(above, __builtin_fma((double)SR, above, cross[bc]), col_sq);
-          if (ty == 0) energy = __builtin_fma(a.r_sense * total, total, energy);
-          const double last = above + col0[bc];
-          pre[bc] = a.r_col * last;
-          lc[bc] = __builtin_fma(a.r_col, __builtin_fma((double)(R - SR - i0), last, below1), a.r_sense * total);
-          if (bc & 1) asm volatile("" : "+v"(pre[bc]), "+v"(lc[bc]), "+v"(col_sq), "+v"(energy));
-        }
-        pq += __builtin_fma(a.r_col, col_sq, energy);
-        pq = block_sum_n<NW>(pq, red + NW);
-        const double alpha = rr / pq;
-        // r <- r - alpha A p, walking up the rows
-        part = 0.0;
-#pragma unroll
-        for (int ar = SR - 1; ar >= 0; --ar) {
-          double suf = suffix[ar], lr = left1[ar];
-#pragma unroll
-          for (int bc = 0; bc < SC; ++bc) {
-            const double sv = s_lds[(ar * SC + bc) * NT + tid];
-            const double u = sv * p[ar][bc];
-            lr += suf;
-            suf = __builtin_fma(-a.r_row, u, suf);
-            lc[bc] += pre[bc];
-            pre[bc] = __builtin_fma(-a.r_col, u, pre[bc]);
-            const double q = __builtin_fma(sv, lr + lc[bc], p[ar][bc]);
-            const double rn = __builtin_fma(-alpha, q, r[ar][bc]);
-            r[ar][bc] = rn;
-            part = __builtin_fma(rn, rn, part);
-          }
-          asm volatile("" : "+v"(part));
-        }
-        if (tid < C) e = __builtin_fma(alpha, tot[tid], e);   // column sum of x = s y, y = sum alpha p
-        const double rr_new = block_sum_n<NW>(part, red);
-        beta = rr_new / rr;
-        rr = rr_new;
-      }
-      if (tid < C) tot[tid] = e;                     // everyone has read the totals: the reduction of rr came after
-      __syncthreads();
-      if (rhs >= i0 && rhs < i0 + SR) {
-#pragma unroll
-        for (int bc = 0; bc < SC; ++bc) {
-          const int j = j0 + bc;
-          if (j < cols) {
-            const double sv = s_lds[((rhs - i0) * SC + bc) * NT + tid];
-            const double g = sv * sv;
-            a.profile[((size_t)(2 * s + pol) * a.K + k0 + rhs) * a.N + n0 + j] =
-                g > 0.0 ? (float)((g - tot[16 * bc + tx]) / g) : 0.0f;
-          }
-        }
-      }
-      // the next solve writes the totals only behind the barriers of its first reduction
+        for (int bc = 0; bc < SC; ++bc) part += over_g(u[ar][bc], g_of(ar * SC + bc));
+      rr = block_sum_n<NW>(part, red);
+      beta = 0.0;
     }
+    // conjugate gradients: all of the first solve, what a later one may have left
+    const double goal = known ? stop : 0.25 * stop;
+    int it = 0;
+    for (; it < a.max_iter && rr > goal; ++it) {
+      iterate(std::true_type{}, false, rr);
+      if (!known && tid == 0 && it < kSteps) {
+        coef[it] = alpha;
+        coef[kSteps + it] = beta;
+      }
+      const double rr_new = block_sum_n<NW>(part, red);
+      beta = rr_new / rr;
+      rr = rr_new;
+    }
+    // a solve that missed the tolerance drives what the first one hardly did (a row of off-state devices, say): the next starts anew
+    steps = known ? (it > 0 ? 0 : steps) : it <= kSteps ? it : 0;
+    if (tid < C) sums[tid] = e;                      // the sums of the last iteration have been read: two barriers ago at least
+    __syncthreads();
+    if (rhs >= i0 && rhs < i0 + SR) {
+#pragma unroll
+      for (int bc = 0; bc < SC; ++bc) {
+        const int j = j0 + bc;
+        if (j < cols) {
+          const double g = g_lds[((rhs - i0) * SC + bc) * NT + tid];
+          a.profile[((size_t)(2 * s + pol) * a.K + k0 + rhs) * a.N + n0 + j] = g > 0.0 ? (float)((g - sums[at_column + 16 * bc]) / g) : 0.0f;
+        }
+      }
+    }
+    // the next solve writes these sums only behind the barrier of its first block sum
   }
 }
 
-constexpr int kFcmThreads128 = 512, kFcmThreads64 = 256;   // fcm_onchip_kernel: 4 x 8 and 4 x 4 devices per thread
+// False: no such LDS size on this device.  PER_CU: blocks that a compute unit holds.  The driven rows of a crossbar are split over
+// several blocks, as many as fill the chip evenly: every block sets its devices up and has one solve without known coefficients,
+// together worth about kSetupRows rows.
+constexpr double kSetupRows = 1.2;
+template <int SR, int SC, int NT, int PER_CU>
+bool launch_onchip(FcmArgs a, hipStream_t st) {
+  constexpr int lds_bytes = (int)FcmShape<SR, SC, NT>::kLdsBytes, slots = 256 * PER_CU;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&fcm_onchip_kernel<SR, SC, NT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          lds_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  // Whole tiles' blocks come first and take so many rounds over the chip; the last tile row's rows fill the last round's gaps
+  const int tiles_r = cdiv(a.K, a.R), sets = a.tiles_c * a.S_w * 2, last = a.K - (tiles_r - 1) * a.R;
+  double best = 0.0;
+  for (int g = 1; g <= a.R; ++g) {
+    const int per = cdiv(a.R, g);
+    const double whole = kSetupRows + per, part = kSetupRows + std::min(per, last);
+    const long long n_whole = (long long)sets * (tiles_r - 1) * cdiv(a.R, per), n_part = (long long)sets * cdiv(last, per);
+    const long long rounds = n_whole / slots, rest = n_whole % slots, gaps = rest ? slots - rest : 0;
+    const long long more = std::max(0ll, n_part - gaps);
+    const double cost = (rounds + (rest ? 1 : 0)) * whole + (double)((more + slots - 1) / slots) * part;
+    if (g == 1 || cost < best) {
+      best = cost;
+      a.rhs_per_group = per;
+    }
+  }
+  a.groups = cdiv(a.R, a.rhs_per_group);
+  hipLaunchKernelGGL((fcm_onchip_kernel<SR, SC, NT>), dim3((unsigned)(tiles_r * sets * a.groups)), dim3(NT), lds_bytes, st, a);
+  return true;
+}
 
 struct FcmPlan {
   int n_items, groups, rhs_per_group, blocks;
   int onchip;            // 0: state in the workspace; 64 / 128: square crossbars of that size, state on chip
-  size_t lds_bytes, ws_bytes;
+  size_t ws_bytes;
 };
 
 FcmPlan plan_fcm(const xbar_config* c, const Derived& d, int K, int N) {
@@ -505,10 +630,6 @@ FcmPlan plan_fcm(const xbar_config* c, const Derived& d, int K, int N) {
   p.groups = cdiv(c->xbar_rows, p.rhs_per_group);
   p.n_items = per_drive_sets * p.groups;
   p.onchip = (c->xbar_rows == c->xbar_cols && (c->xbar_rows == 64 || c->xbar_rows == 128)) ? c->xbar_rows : 0;
-  {  // s, the column exchange area [2][waves][C], the column totals and two sets of reduction slots
-    const int waves = (p.onchip == 128 ? kFcmThreads128 : kFcmThreads64) / 64;
-    p.lds_bytes = ((size_t)p.onchip * p.onchip + 2 * waves * p.onchip + p.onchip + 2 * waves) * sizeof(double);
-  }
   // the workspace is sized for the general kernel in every case (it is the fallback)
   const size_t slot = (size_t)5 * c->xbar_rows * c->xbar_cols * sizeof(double);
   p.blocks = std::min(p.n_items, slot > (size_t)1 << 20 ? 1024 : 2048);
@@ -549,18 +670,8 @@ int xbar_fcm_profile(const xbar_config* cfg, const float* W, int K, int N, float
   a.tol2 = 1e-22;                                   // relative residual 1e-11
   a.w_max = w_max; a.seed = cfg->seed; a.step = step; a.step_add = current_step_source();
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  if (p.onchip) {
-    const void* fn = p.onchip == 128 ? reinterpret_cast<const void*>(&fcm_onchip_kernel<4, 8, kFcmThreads128>)
-                                     : reinterpret_cast<const void*>(&fcm_onchip_kernel<4, 4, kFcmThreads64>);
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes) == hipSuccess) {
-      if (p.onchip == 128)
-        hipLaunchKernelGGL((fcm_onchip_kernel<4, 8, kFcmThreads128>), dim3((unsigned)p.n_items), dim3(kFcmThreads128), p.lds_bytes, st, a);
-      else
-        hipLaunchKernelGGL((fcm_onchip_kernel<4, 4, kFcmThreads64>), dim3((unsigned)p.n_items), dim3(kFcmThreads64), p.lds_bytes, st, a);
-      return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
-    }
-    (void)hipGetLastError();                         // no such LDS size on this device: general kernel
-  }
+  if (p.onchip == 128 ? launch_onchip<4, 8, 512, 1>(a, st) : p.onchip == 64 && launch_onchip<4, 4, 256, 3>(a, st))
+    return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
   hipLaunchKernelGGL(fcm_kernel, dim3((unsigned)p.blocks), dim3(256), 0, st, a);
   if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
   return XBAR_OK;

@@ -252,6 +252,25 @@ def test_circuit_model_on_chip(xo, xb, R, K, N, r_min):
     assert np.abs(Dg.cpu().numpy() - fcm.fcm_profile(co, W, w_max, step=1)).max() <= 2e-7
 
 
+# ... solves that take over the coefficients of a block's first one: every fourth row or all but one device of the first off, so that
+# the first solve hardly sees what the others do; more iterations than coefficients are kept (64 x 64 arrays, 100 Ohm); several
+# blocks per array and several rounds of blocks
+@pytest.mark.parametrize("R,K,N,r_min,off", [(64, 70, 64, 1e2, "rows"), (64, 64, 40, 1e3, "device"), (128, 128, 128, 1e2, "rows"),
+                                             (128, 150, 128, 1e3, "device"), (128, 140, 30, 1e5, "rows"), (64, 300, 200, 1e4, "rows")])
+def test_circuit_model_with_shared_coefficients(xo, xb, R, K, N, r_min, off):
+    from oracle import fcm
+    W, _, _ = workloads.layer_tensors_np(workloads.Gemm("t", K, N, 1, True, 1), seed=K + N)
+    w_max = float(np.abs(W).max())
+    if off == "rows":
+        W[::4] = 0.0
+    else:
+        W[::R // 4, 1:] = 0.0
+    co, cg = both_configs(xo, xb, xbar_rows=R, xbar_cols=R, weight_bits=2, slice_bits=2, flags=0, r_min=r_min, r_max=10 * r_min,
+                          r_source=2.0, r_sense=3.0)
+    Dg = xb.fcm_profile(cg, dev(W), w_max, step=1).cpu().numpy()
+    assert np.abs(Dg - fcm.fcm_profile(co, W, w_max, step=1)).max() <= 2e-7
+
+
 # One kernel for a whole pass (layers of few patches): its outputs are those of the chunked kernels, which the code tap
 # runs, bit for bit -- one row, patches plus and minus one, slices that do not fill a block's waves, arrays of 16 .. 256
 # rows, one and several blocks per patch, sums within and beyond 32 bits, every way of coding inputs and reading arrays
