@@ -11,7 +11,7 @@ namespace xbar_detail {
 namespace {
 
 // A wave owns one item: an output patch of 32 batch rows x 32 outputs, one virtual tile (phase, array, tile) and one slice.
-// A block is NW slices of one patch and virtual tile: its waves quantise the tile's inputs into LDS together while the
+// A block is NW slices (four or eight) of one patch and virtual tile: its waves quantise the tile's inputs into LDS together while the
 // items' plane fragments are on their way (to registers or to the wave's own LDS: no other wave reads them), contract
 // them with the digits of every cycle, convert, and add their codes up through LDS.  A patch that takes one block is
 // scaled and written by it; else the blocks add to the patch's sums in the workspace (integers: the order does not matter),
@@ -19,7 +19,20 @@ namespace {
 // Bound by latency, from memory and, since every line of code runs a handful of times, from the instruction cache: loads
 // are issued as early as they can be, loops stay rolled, nothing is divided.  One wave per item spreads a layer
 // of a few patches over the chip, in one launch instead of three.
-constexpr int kSmallWaves = 4;
+// Waves of a block.  Weights of more than four slices take eight where their fragments have room in LDS: twice the items share
+// the staged inputs, and half as many blocks meet in the patch's sums (or one is left, and none meet).  Where the blocks are few
+// and meet all the same, four on more compute units are faster: up to one block of four per compute unit.  us, four / eight waves:
+// one block a patch, 73 x 14, 31 rows 12.8 / 10.8, 42 x 32, 1280 rows 9.5 / 8.0; several, 131 x 111, 20 rows backward 11.1 / 12.3,
+// 188 x 225, 49 rows 14.1 / 14.9; beyond the line 144 x 82, 646 rows 13.7 / 12.6, 113 x 1396, 736 rows 50.4 / 30.3, 212 x 1116, 200
+// rows 50.0 / 37.5; but with few rows of inputs to share and a little more than one block of eight per compute unit, 25 x 416, 363
+// rows backward, 312 blocks 14.2 / 15.5.  (Same results.)
+int waves_of(const VmmPlan& p, const Derived& d) {
+  if (d.S_w <= 4 || (d.fmt == kFmtF16 && d.terms * p.g.ks > 16)) return 4;
+  const long long tiles = (long long)p.MP * p.g.OP * p.VT, eights = tiles * cdiv(d.S_w, 8);
+  if (p.VT * cdiv(d.S_w, 8) == 1) return 8;
+  if (std::min(p.Lin, p.g.tile) <= 64 && eights > 256 && eights <= 384) return 4;
+  return tiles * cdiv(d.S_w, 4) > 256 ? 8 : 4;
+}
 
 // The sums of a patch that several blocks share, in a workspace whose content is unknown when the launch begins: one
 // 64-byte head per patch, then 1024 sums per patch, [4][256 threads], 32-bit where they fit.  Every block begins with an
@@ -68,15 +81,15 @@ __device__ __forceinline__ void open_patch(const SmallArgs& s, int patch, int la
   if (lane == 0) put(&patch_head(s, patch)->ready, s.ready_tag);
 }
 
-// The inputs of this wave's 16-input steps of the tile: steps wave, wave + 4, .. (up to NSTEP of them).
-template <int NSTEP>
+// The inputs of this wave's 16-input steps of the tile: steps wave, wave + NW, .. (up to NSTEP of them).
+template <int NW, int NSTEP>
 struct Inputs {
   float x[NSTEP][8];
   __device__ __forceinline__ void load(const SmallArgs& s, int mp, int t, int wave, int lane) {
     const int m = mp * 32 + (lane & 31), lend = min(s.v.Lin, (t + 1) * s.v.tile);
 #pragma unroll
     for (int i = 0; i < NSTEP; ++i) {
-      const int l0 = t * s.v.tile + 16 * (wave + kSmallWaves * i) + 8 * (lane >> 5);
+      const int l0 = t * s.v.tile + 16 * (wave + NW * i) + 8 * (lane >> 5);
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[i][e] = 0.0f;
       if (l0 < lend && m < s.v.M) {
@@ -90,7 +103,7 @@ struct Inputs {
     const int m = mp * 32 + (lane & 31), lend = min(s.v.Lin, (t + 1) * s.v.tile);
 #pragma unroll
     for (int i = 0; i < NSTEP; ++i) {
-      const int j = wave + kSmallWaves * i;
+      const int j = wave + NW * i;
       if (j >= steps) break;
       u32x2 pos, neg;
       input_codes8(s.q, m, t * s.v.tile + 16 * j + 8 * (lane >> 5), lend, x[i], pos, neg);
@@ -113,8 +126,9 @@ __device__ __forceinline__ void write_poison(const SmallArgs& s, int m, int o) {
   }
 }
 
-// The items' codes, summed over their cycles, to the patch's sums, or scaled and written.  Thread (q, lane) ends up with
-// the four consecutive outputs 8 q + 4 (lane / 32) .. of batch row lane % 32.
+// The items' codes, summed over their cycles, to the patch's sums, or scaled and written.  Thread (q, lane) of the first four
+// waves ends up with the four consecutive outputs 8 q + 4 (lane / 32) .. of batch row lane % 32.
+template <int NW>
 __device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, const uint32_t (&y)[16], int wave, int slice0,
                                               int patch, int mp, int op, int lane) {
 #pragma clang fp contract(off)   // product, product, difference: each rounded on its own
@@ -139,31 +153,35 @@ __device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, co
     opened = ready;
   }
   __syncthreads();
+  const bool sums = NW == 4 || wave < 4;
   if (s.blocks_per_patch > 1 && !opened) {
-    write_poison(s, m, o);
+    if (sums) write_poison(s, m, o);
     return;
   }
+  if (!sums && s.blocks_per_patch == 1) return;
   long long sum[4] = {0, 0, 0, 0};
 #pragma unroll
-  for (int w = 0; w < kSmallWaves; ++w) {
+  for (int w = 0; w < NW; ++w) {
     if (slice0 + w >= a.S_w) break;
-    const u32x4 v = xch[w * 256 + threadIdx.x];
+    const u32x4 v = xch[w * 256 + (threadIdx.x & 255)];
 #pragma unroll
     for (int e = 0; e < 4; ++e) sum[e] += (long long)(int32_t)(v[e] - s.bias_item) << (a.slice_bits * (slice0 + w));
   }
   if (s.blocks_per_patch > 1) {
-    unsigned long long* wide = reinterpret_cast<unsigned long long*>(patch_sums(s, patch)) + threadIdx.x;
-    uint32_t* narrow = reinterpret_cast<uint32_t*>(patch_sums(s, patch)) + threadIdx.x;
+    unsigned long long* wide = reinterpret_cast<unsigned long long*>(patch_sums(s, patch)) + (threadIdx.x & 255);
+    uint32_t* narrow = reinterpret_cast<uint32_t*>(patch_sums(s, patch)) + (threadIdx.x & 255);
+    if (sums) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (s.narrow) atomicAdd(&narrow[256 * e], (uint32_t)sum[e]);
-      else atomicAdd(&wide[256 * e], (unsigned long long)sum[e]);
+      for (int e = 0; e < 4; ++e) {
+        if (s.narrow) atomicAdd(&narrow[256 * e], (uint32_t)sum[e]);
+        else atomicAdd(&wide[256 * e], (unsigned long long)sum[e]);
+      }
     }
     acknowledged();                                    // the sums before the ticket
     __syncthreads();
     if (threadIdx.x == 0) arrived = atomicAdd(&head->tickets, 1u);
     __syncthreads();
-    if (arrived != (uint32_t)s.blocks_per_patch - 1) return;
+    if (!sums || arrived != (uint32_t)s.blocks_per_patch - 1) return;
     if (threadIdx.x == 0) {
       put(&head->claim, 0ull);
       put(&head->ready, 0ull);
@@ -195,7 +213,7 @@ __device__ __forceinline__ void add_and_write(const SmallArgs& s, u32x4* xch, co
 }
 
 // What a wave of the launch works on: grid = (virtual tile x group of slices, output patch, row patch).
-template <bool PER_ARRAY>
+template <int NW, bool PER_ARRAY>
 struct Item {
   int patch, mp, op, p, pol, t, slice0, slice;
   __device__ __forceinline__ Item(const SmallArgs& s, int wave) {
@@ -204,7 +222,7 @@ struct Item {
     mp = (int)blockIdx.z;
     patch = mp * a.OP + op;
     const int vt = (int)((blockIdx.x * s.groups_inv) >> 16);      // blockIdx.x / slice groups
-    slice0 = ((int)blockIdx.x - vt * s.slice_groups) * kSmallWaves;
+    slice0 = ((int)blockIdx.x - vt * s.slice_groups) * NW;
     slice = min(slice0 + wave, a.S_w - 1);             // a wave without a slice works along, its codes are not added
     const int pa = (vt >= a.T ? 1 : 0) + (vt >= 2 * a.T ? 1 : 0) + (vt >= 3 * a.T ? 1 : 0);   // (phase, array)
     t = vt - pa * a.T;
@@ -216,17 +234,17 @@ struct Item {
 // fp16 planes: the wave's fragments go from memory into its share of LDS (no registers in between, all in flight at
 // once), and a short loop takes them in order (leading term first; one array alone: the residual first), every fragment
 // with the digits of all cycles at once, reading one pair of fragments ahead.
-template <int TERMS, int S_IN, bool PER_ARRAY, int NSTEP>
-__global__ __launch_bounds__(256) void vmm_small_f16_kernel(SmallArgs s) {
+template <int NW, int TERMS, int S_IN, bool PER_ARRAY, int NSTEP>
+__global__ __launch_bounds__(64 * NW) void vmm_small_f16_kernel(SmallArgs s) {
   extern __shared__ u32x4 small_lds[];
   const VmmArgs& a = s.v;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Item<PER_ARRAY> it(s, wave);
+  const Item<NW, PER_ARRAY> it(s, wave);
   u32x2* raw = reinterpret_cast<u32x2*>(small_lds);    // [16-input step][64 lanes]
   u32x4* frags = small_lds + a.ks16 * 32 + (size_t)wave * TERMS * a.ks * 64;
   const int nk = (min(a.tile, a.Lin - it.t * a.tile) + 15) >> 4, nf = TERMS * nk;
   const unsigned long long before = claim_patch(s, it.patch, wave, lane);
-  Inputs<NSTEP> inputs;
+  Inputs<NW, NSTEP> inputs;
   inputs.load(s, it.mp, it.t, wave, lane);
   const u32x4* src = a.B + (((size_t)it.t * a.OP + it.op) * a.S_w + it.slice) * TERMS * a.ks * 64 + lane;
   if constexpr (PER_ARRAY) src += (size_t)it.pol * a.pol_stride;
@@ -286,20 +304,22 @@ __global__ __launch_bounds__(256) void vmm_small_f16_kernel(SmallArgs s) {
     // operand lanes hold digit * 2^(shift - 24); undo that power of two in the ADC gain
     vmm_adc_narrow<1>(one, ldexpf(gain, 24 - a.stream_bits * b), lo, hi, a.stream_bits * b, y);
   }
-  add_and_write(s, small_lds + a.ks16 * 32, y[0], wave, it.slice0, it.patch, it.mp, it.op, lane);
+  add_and_write<NW>(s, small_lds + a.ks16 * 32, y[0], wave, it.slice0, it.patch, it.mp, it.op, lane);
 }
 
-// 6-bit planes: the item's fragments stay in registers while its cycles pass, two at a time (two chains of sums).
-template <int NT, int NK, bool PER_ARRAY>
-__global__ __launch_bounds__(256) void vmm_small_f6_kernel(SmallArgs s) {
+// 6-bit planes: the item's fragments stay in registers while its cycles pass, two at a time (two chains of sums); with eight waves and
+// two k-steps one at a time, which leaves room for a second block on the compute unit (113 x 1396, 736 rows, 5 terms: 38.7 -> 30.3 us).
+template <int NW, int NT, int NK, bool PER_ARRAY>
+__global__ __launch_bounds__(64 * NW, NW == 8 && NK <= 2 ? 4 : 1) void vmm_small_f6_kernel(SmallArgs s) {
+  constexpr int CH = NW == 8 && NK == 2 ? 1 : 2;
   extern __shared__ u32x4 small_lds[];
   const VmmArgs& a = s.v;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Item<PER_ARRAY> it(s, wave);
+  const Item<NW, PER_ARRAY> it(s, wave);
   u32x2* raw = reinterpret_cast<u32x2*>(small_lds);
   const int nk = (min(a.tile, a.Lin - it.t * a.tile) + 63) >> 6;
   const unsigned long long before = claim_patch(s, it.patch, wave, lane);
-  Inputs<NK> inputs;
+  Inputs<NW, (4 * NK + NW - 1) / NW> inputs;
   inputs.load(s, it.mp, it.t, wave, lane);
   const char* src = reinterpret_cast<const char*>(a.B + (PER_ARRAY ? (size_t)it.pol * a.pol_stride : 0)) +
                     (((size_t)it.t * a.OP + it.op) * a.S_w + it.slice) * NT * a.ks * 1536;
@@ -324,18 +344,20 @@ __global__ __launch_bounds__(256) void vmm_small_f6_kernel(SmallArgs s) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) y[0][r] = 0;
 #pragma unroll 1
-  for (int b = 0; b < a.S_in; b += 2) {
-    float16v acc[2];
+  for (int b = 0; b < ((a.S_in + 1) & ~1); b += CH) {
+    float16v acc[CH];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.0f;
-    int4v dg[2][NK];
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[c][r] = 0.0f;
+    int4v dg[CH][NK];
 #pragma unroll
     for (int J = 0; J < NK; ++J)
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         const u32x2 x = raw[(4 * J + w) * 64 + lane];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
+        for (int c = 0; c < CH; ++c) {
           const int at = a.stream_bits * (b + c);      // the digit's place: low or high nibbles (none behind the last cycle)
           dg[c][J][w] = (int)(((at & 4 ? x.y : x.x) >> (at & 3)) & (b + c < a.S_in ? nibble_mask : 0u));
         }
@@ -350,17 +372,19 @@ __global__ __launch_bounds__(256) void vmm_small_f6_kernel(SmallArgs s) {
           const u32x2 w = fy[term][J];
           const int8v pa = {(int)x.x, (int)x.y, (int)x.z, (int)x.w, (int)w.x, (int)w.y, 0, 0};
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {
+          for (int c = 0; c < CH; ++c) {
             const int8v pb = {dg[c][J][0], dg[c][J][1], dg[c][J][2], dg[c][J][3], 0, 0, 0, 0};
             acc[c] = mfma_f6_term(term, pa, pb, acc[c], a.scale_lo, a.scale_hi);
           }
         }
     // a cycle that is not there leaves zero codes: their constant alone goes into the sums, and out again with the bias
-    const float16v even[1] = {acc[0]}, odd[1] = {acc[1]};
-    vmm_adc_narrow<1>(even, gain, lo, hi, a.stream_bits * b, y);
-    vmm_adc_narrow<1>(odd, gain, lo, hi, a.stream_bits * (b + 1), y);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const float16v one[1] = {acc[c]};
+      vmm_adc_narrow<1>(one, gain, lo, hi, a.stream_bits * (b + c), y);
+    }
   }
-  add_and_write(s, small_lds + NK * 128, y[0], wave, it.slice0, it.patch, it.mp, it.op, lane);
+  add_and_write<NW>(s, small_lds + NK * 128, y[0], wave, it.slice0, it.patch, it.mp, it.op, lane);
 }
 
 // Another odd 64-bit number at every call: even steps, the golden ratio's, from an odd start that differs from process to process.
@@ -374,26 +398,36 @@ unsigned long long launch_tag() {
 constexpr int kWaitTurns = 1 << 20;
 thread_local int g_withheld_turns = -1;
 
-int blocks_per_patch(const VmmPlan& p, const Derived& d) { return p.VT * cdiv(d.S_w, kSmallWaves); }
-// the staged inputs and the area of the final exchange (16 KiB), which the fragments of fp16 planes occupy before
+int blocks_per_patch(const VmmPlan& p, const Derived& d) { return p.VT * cdiv(d.S_w, waves_of(p, d)); }
+// the staged inputs and the area of the final exchange (4 KiB a wave), which the fragments of fp16 planes occupy before
 size_t small_lds_bytes(const VmmPlan& p, const Derived& d) {
-  const int steps = d.fmt == kFmtF6 ? 4 * (p.g.ks == 3 ? 4 : p.g.ks) : p.ks16;
-  const size_t frags = d.fmt == kFmtF16 ? (size_t)kSmallWaves * d.terms * p.g.ks * 1024 : 0;
-  return (size_t)steps * 512 + std::max((size_t)16384, frags);
+  const int steps = d.fmt == kFmtF6 ? 4 * (p.g.ks == 3 ? 4 : p.g.ks) : p.ks16, waves = waves_of(p, d);
+  const size_t frags = d.fmt == kFmtF16 ? (size_t)waves * d.terms * p.g.ks * 1024 : 0;
+  return (size_t)steps * 512 + std::max((size_t)4096 * waves, frags);
 }
 
-template <int NSTEP>
+template <int NW, int NSTEP>
 void (*pick_f16(int terms, int s_in, bool per_array))(SmallArgs) {
-  if (per_array) return s_in == 1 ? vmm_small_f16_kernel<2, 1, true, NSTEP> : vmm_small_f16_kernel<2, 2, true, NSTEP>;
-  if (terms == 2) return s_in == 1 ? vmm_small_f16_kernel<2, 1, false, NSTEP> : vmm_small_f16_kernel<2, 2, false, NSTEP>;
-  return s_in == 1 ? vmm_small_f16_kernel<1, 1, false, NSTEP> : vmm_small_f16_kernel<1, 2, false, NSTEP>;
+  if (per_array) return s_in == 1 ? vmm_small_f16_kernel<NW, 2, 1, true, NSTEP> : vmm_small_f16_kernel<NW, 2, 2, true, NSTEP>;
+  if (terms == 2) return s_in == 1 ? vmm_small_f16_kernel<NW, 2, 1, false, NSTEP> : vmm_small_f16_kernel<NW, 2, 2, false, NSTEP>;
+  return s_in == 1 ? vmm_small_f16_kernel<NW, 1, 1, false, NSTEP> : vmm_small_f16_kernel<NW, 1, 2, false, NSTEP>;
 }
 
-template <int NK>
+template <int NW, int NK>
 void (*pick_f6(int terms, bool per_array))(SmallArgs) {
-  if (per_array) return vmm_small_f6_kernel<5, NK, true>;
-  if (terms == 1) return vmm_small_f6_kernel<1, NK, false>;
-  return terms == 4 ? vmm_small_f6_kernel<4, NK, false> : vmm_small_f6_kernel<5, NK, false>;
+  if (per_array) return vmm_small_f6_kernel<NW, 5, NK, true>;
+  if (terms == 1) return vmm_small_f6_kernel<NW, 1, NK, false>;
+  return terms == 4 ? vmm_small_f6_kernel<NW, 4, NK, false> : vmm_small_f6_kernel<NW, 5, NK, false>;
+}
+
+template <int NW>
+void (*pick_small(const VmmPlan& p, const Derived& d))(SmallArgs) {
+  const bool per_array = d.npol == 2;
+  if (d.fmt == kFmtF6) return p.g.ks == 1 ? pick_f6<NW, 1>(d.terms, per_array) : p.g.ks == 2 ? pick_f6<NW, 2>(d.terms, per_array) : pick_f6<NW, 4>(d.terms, per_array);
+  const int steps = cdiv(p.ks16, NW);                  // 16-input steps that a wave stages
+  if (steps <= 1) return pick_f16<NW, 1>(d.terms, d.S_in, per_array);
+  if (steps <= 2 || NW == 8) return pick_f16<NW, 2>(d.terms, d.S_in, per_array);
+  return pick_f16<NW, NW == 8 ? 2 : 4>(d.terms, d.S_in, per_array);
 }
 
 }  // namespace
@@ -405,40 +439,42 @@ size_t vmm_small_ws_bytes(const VmmPlan& p, const Derived& d) {
 }
 
 // When the one launch beats the three it replaces: where 95 % of its estimate in us is below theirs, up to 16384 items of one
-// patch, tile and slice, beyond which neither was measured closely.  It costs whole blocks, four slices each, whether or not
-// they hold four; a block's time grows with the fragments it reads (terms x k-steps, of a tile with fp16 planes those that
-// the layer reaches), and with fp16 planes a round of as many blocks as the LDS of the compute units holds takes 5 us at least.
-// The three take what the plan expects of the chunked kernel, what each of its waves stages, and two launches.  Both
-// sides fitted to 75000 random layers, matrices and convolutions, in graphs of 10 calls (us, three / one: 2000 x 300,
-// 64 rows, 64-row arrays, fp16: 32 / 22; 256 rows, 1 tile, 4 terms, 8192 items: 42 / 50; 128 rows, 1 tile, 5 terms, 12288
-// items: 55 / 64).  Of the layers of fp16 planes that this sends to the one launch 2.0 % are slower by more than 3 %, on average all
-// are 0.3 % from the better side, of the 6-bit ones 1.3 % and 0.1 %; with a line at 4096 items and one fitted to slower chunked
-// kernels the better side was missed by 5.4 and 1.2 % on average over all layers, now by 1.0 and 0.8.
+// patch, tile and slice, with 6-bit planes and eight waves 65536, beyond which neither was measured closely.  It costs whole
+// blocks, whether or not they hold as many slices as waves; a block's time grows with the fragments it reads (terms x k-steps, of
+// a tile with fp16 planes those that the layer reaches), and with fp16 planes a round of as many blocks as the LDS of the compute
+// units holds takes 5 us at least.  The three take what the plan expects of the chunked kernel, what each of its waves stages,
+// and two launches.  Fitted in graphs of 10 calls to random layers, matrices and convolutions, 75000 with blocks of four waves and
+// 800 with eight (us, three / one: 2000 x 300, 64 rows, 64-row arrays, fp16: 32 / 22; four waves, 256 rows, 1 tile, 4 terms, 8192
+// items: 42 / 50; eight, 113 x 1396, 736 rows, 5 terms, 8096 items: 47 / 30, 1396 x 113 backward, 16192 items: 85 / 58).  From the
+// better side the layers are 0.3 % away on average with 6-bit planes, 0.1 % with fp16 planes.
 // fp16 planes of tiles beyond 128 rows leave one to three blocks the LDS of a compute unit: 4096 items and one round
 // (us, three / one: 192 rows, 1122 blocks, one resident: 20 / 51; 256 rows, 2448 blocks: 31 / 119).
 bool vmm_small_pays(const VmmPlan& p, const Derived& d) {
+  const int waves = waves_of(p, d);
   const long long patches = (long long)p.MP * p.g.OP, items = patches * p.VT * d.S_w;
   const long long blocks = patches * blocks_per_patch(p, d);
-  if (p.g.OP >= 65536 || p.MP >= 65536 || (long long)blocks_per_patch(p, d) * cdiv(d.S_w, kSmallWaves) >= 65536) return false;
-  if (items > 16384) return false;
+  if (p.g.OP >= 65536 || p.MP >= 65536 || (long long)blocks_per_patch(p, d) * cdiv(d.S_w, waves) >= 65536) return false;
+  if (items > (d.fmt == kFmtF6 && waves == 8 ? 65536 : 16384)) return false;
   const int rows = std::min(p.Lin, p.g.tile);
   if (d.fmt == kFmtF16) {
-    const double resident = 256.0 * (double)std::min<size_t>(8, 160 * 1024 / small_lds_bytes(p, d));
-    if (p.ks16 > 8) return items <= 4096 && (double)blocks <= resident;
-    const double one = 6.5 + std::max(1e-3 * (double)blocks * (1.1 + 0.93 * d.terms * cdiv(rows, 16)) + (p.VT > 1 ? 1.2 : 0.0),
-                                      5.0 * (double)blocks / resident);
+    // in groups of four waves
+    const double groups = (double)(patches * p.VT * cdiv(d.S_w, 4));
+    const double resident = 256.0 * (double)std::min<size_t>(32 / waves, 160 * 1024 / small_lds_bytes(p, d)) * (waves / 4);
+    if (p.ks16 > 8) return items <= 4096 && groups <= resident;
+    const double group_us = (waves == 8 ? 0.85e-3 : 1e-3) * (1.1 + 0.93 * d.terms * cdiv(rows, 16));
+    const double one = 6.5 + std::max(groups * group_us + (blocks > patches ? 1.2 : 0.0), 5.0 * groups / resident);
     return one <= 0.95 * (10.3 + 1.27 * p.chunked_us - 1.03 * p.vt_planned + 0.35 * p.nchunk);
   }
   const int read_steps = p.g.ks == 3 ? 4 : p.g.ks;                  // k-steps of a block, and those that a tile reaches
   const int frags = d.S_w * d.terms * cdiv(rows, 64);
-  const double one = 8.4 + 1e-3 * (double)blocks * (6.7 + d.terms * read_steps + 0.94 * (d.npol - 1)) + (p.VT > 1 ? 0.5 : 0.0);
+  const double one = waves == 8 ? 8.5 + 1e-3 * (double)blocks * (5.5 + 2.15 * d.terms * read_steps) + (blocks > patches ? 0.7 : 0.0)
+                                : 8.4 + 1e-3 * (double)blocks * (6.7 + d.terms * read_steps + 0.94 * (d.npol - 1)) + (p.VT > 1 ? 0.5 : 0.0);
   return one <= 0.95 * (9.1 + 0.98 * p.chunked_us + p.vt_planned * (0.32 * frags / p.nw - 1.4) + 0.33 * p.nchunk);
 }
 
 hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hipStream_t st) {
-  const bool per_array = d.npol == 2;
   a.blocks_per_patch = blocks_per_patch(p, d);
-  a.slice_groups = cdiv(d.S_w, kSmallWaves);
+  a.slice_groups = cdiv(d.S_w, waves_of(p, d));
   a.groups_inv = (65536 + a.slice_groups - 1) / a.slice_groups;   // exact for quotients of numbers below 65536 / groups
   a.tag = a.ready_tag = launch_tag();
   a.wait_turns = kWaitTurns;
@@ -447,15 +483,14 @@ hipError_t launch_vmm_small(SmallArgs a, const VmmPlan& p, const Derived& d, hip
     a.wait_turns = g_withheld_turns;
     g_withheld_turns = -1;
   }
-  void (*k)(SmallArgs);
-  if (d.fmt == kFmtF16) k = p.ks16 <= 4 ? pick_f16<1>(d.terms, d.S_in, per_array) : p.ks16 <= 8 ? pick_f16<2>(d.terms, d.S_in, per_array) : pick_f16<4>(d.terms, d.S_in, per_array);
-  else k = p.g.ks == 1 ? pick_f6<1>(d.terms, per_array) : p.g.ks == 2 ? pick_f6<2>(d.terms, per_array) : pick_f6<4>(d.terms, per_array);
+  const int waves = waves_of(p, d);
+  void (*k)(SmallArgs) = waves == 8 ? pick_small<8>(p, d) : pick_small<4>(p, d);
   const size_t lds = small_lds_bytes(p, d);
   if (lds > 48 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k, dim3((unsigned)a.blocks_per_patch, (unsigned)p.g.OP, (unsigned)p.MP), dim3(64 * kSmallWaves), lds, st, a);
+  hipLaunchKernelGGL(k, dim3((unsigned)a.blocks_per_patch, (unsigned)p.g.OP, (unsigned)p.MP), dim3(64 * waves), lds, st, a);
   return hipGetLastError();
 }
 

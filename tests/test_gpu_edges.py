@@ -304,6 +304,23 @@ def test_lines_of_the_small_pass(xb, R, sb, wb, flags, M, K, N):
     assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
 
 
+# Blocks of eight waves: weights of more than four slices whose patches take one block, or more blocks of four than there are
+# compute units (240, 264); five, eight and sixteen slices, an odd number of cycles, one to four k-steps, one term, fp16 planes
+@pytest.mark.parametrize("R,ib,sb,wb,slb,M,K,N", [(128, 8, 1, 16, 2, 320, 200, 180), (128, 8, 1, 16, 2, 350, 200, 180), (64, 8, 1, 10, 2, 350, 100, 180),
+                                                  (192, 8, 1, 16, 1, 96, 300, 130), (128, 6, 2, 16, 2, 350, 200, 180), (128, 8, 4, 16, 2, 350, 200, 180),
+                                                  (256, 8, 4, 16, 2, 97, 300, 180), (48, 8, 1, 14, 2, 350, 90, 180)])
+@pytest.mark.parametrize("flags", ["", "aam", "aam+signed", "pa+signed"])
+def test_eight_waves_of_the_small_pass(xb, R, ib, sb, wb, slb, M, K, N, flags):
+    f = {"": 0, "aam": xb.NI_WIRE_AAM, "signed": xb.INPUT_SIGNED, "pa": xb.ADC_PER_ARRAY}
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, "signed" in flags, 1), seed=M + K)
+    fs = 1.037 * workloads.adc_full_scale(R, sb, slb)
+    cfg = xb.make_config(xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=slb, input_bits=ib, stream_bits=sb, adc_fs_fwd=fs, adc_fs_bwd=fs,
+                         flags=sum(f[x] for x in flags.split("+")), seed=4)
+    w_max, xs, gs = float(np.abs(W).max()), float(np.abs(X).max()), float(np.abs(dY).max())
+    assert np.array_equal(gpu_fwd(xb, cfg, W, X, w_max, xs, codes=False), gpu_fwd(xb, cfg, W, X, w_max, xs)[0])
+    assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
+
+
 @pytest.mark.parametrize("cin,image", [(7, 31), (7, 25), (8, 31)])
 def test_gathered_inputs_of_the_small_pass(xb, cin, image):
     from oracle import conv
@@ -324,11 +341,10 @@ def test_gathered_inputs_of_the_small_pass(xb, cin, image):
 # (or, behind the sums that a gather reads, with what no sum is); the next pass on the same workspace is right, and so is
 # every replay of a graph that holds one
 @pytest.mark.parametrize("sb,flags", [(1, 0), (4, 0), (1, 512)])
-def test_wait_for_a_patch_has_an_end(xb, sb, flags):
-    M, K, N = 40, 300, 70
+def test_wait_for_a_patch_has_an_end(xb, sb, flags, M=40, K=300, N=70, wb=8):
     W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=6)
     fs = 1.037 * workloads.adc_full_scale(64, sb, 2)
-    cfg = xb.make_config(xbar_rows=64, xbar_cols=64, weight_bits=8, slice_bits=2, stream_bits=sb, flags=flags | xb.INPUT_SIGNED,
+    cfg = xb.make_config(xbar_rows=64, xbar_cols=64, weight_bits=wb, slice_bits=2, stream_bits=sb, flags=flags | xb.INPUT_SIGNED,
                          adc_fs_fwd=fs, adc_fs_bwd=fs, seed=4)
     w_max = float(np.abs(W).max())
     planes, Xd = xb.tile(cfg, dev(W), w_max, 0), dev(X)
@@ -351,6 +367,11 @@ def test_wait_for_a_patch_has_an_end(xb, sb, flags):
         assert torch.equal(out, want)
         xb.lib().xbar_withhold_next_small_vmm(3)
         xb.fwd(cfg, planes, Xd, N, w_max, 3.0, ws=ws, out=torch.empty_like(out))
+
+
+@pytest.mark.parametrize("sb,flags", [(1, 0), (4, 0), (1, 512)])
+def test_wait_for_a_patch_of_eight_waves_has_an_end(xb, sb, flags):
+    test_wait_for_a_patch_has_an_end(xb, sb, flags, 200, 300, 130, 16)
 
 
 # All-paths wire model: fewer rows than row segments, both strip widths (up to 128 rows and beyond), one to four columns
