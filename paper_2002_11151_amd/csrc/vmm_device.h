@@ -18,6 +18,7 @@ struct QuantArgs {
   uint8_t* A;        // [phase][MP][T][ks][64 lanes][8 bytes]: magnitudes (fp16 path) or their nibbles (6-bit path)
   int M, L, MP, T, ks, tile, P, input_bits;
   int offset;        // signed inputs as offset-binary codes in one phase (P == 1)
+  int pairs;         // pairs of k-steps that a row patch has: whole tiles, and those that the last one reaches
   int nibbles;       // 6-bit path: a lane's 8 bytes nibble by nibble (word 0: low nibbles, word 1: high nibbles)
   float scale;
   float inv_scale;   // 1 / scale, or NaN (every input then takes the double-precision decision) where that is no normal number
