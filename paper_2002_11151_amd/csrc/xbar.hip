@@ -774,6 +774,7 @@ struct GradArgs {
   float* part;      // [mchunks][K][N]
   int M, K, N, KB, NB, m_per_chunk;
   int total_wg, per_xcd;   // blocks of the launch; logical blocks per XCD (the grid is 8 x per_xcd)
+  int tile_rows;           // grad_quads_kernel: rows of W per block
   int shares, partials;    // update_small_kernel: partial sums of a batch chunk (its k-steps in turn) and of the batch
   ConvGeom conv;
 };
@@ -794,9 +795,9 @@ __device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
 // the work of eight fp32 ones of 2 rows at a relative error near 2^-16 per product, far inside the
 // tolerance of the update.  When the layer has at most 64 rows (SPLIT_K) or columns (SPLIT_N) the
 // waves that would work on padding take a share of the batch rows instead and write a partial sum of
-// their own.  CONV: X is an NHWC image and the patch rows are gathered on the fly.
+// their own.  CONV: X is an NHWC image and the patch rows are gathered on the fly.  (Layers whose rows are no whole quads.)
 template <bool SPLIT_K, bool SPLIT_N, bool CONV>
-__global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
+__global__ __launch_bounds__(256, 2) void grad_gemm_kernel(GradArgs a) {
   // [term][group of 8 batch rows][column] -> 8 bf16 along the batch
   __shared__ bf16x8 xs[2][kGradMS / 8][128];
   __shared__ bf16x8 ds[2][kGradMS / 8][128];
@@ -932,6 +933,148 @@ __global__ __launch_bounds__(256) void grad_gemm_kernel(GradArgs a) {
         const int n = n0 + noff + j * 32 + (lane & 31);
         if (k < a.K && n < a.N) out[(size_t)k * a.N + n] = acc[i][j][r];
       }
+}
+
+// The same product for layers whose rows are whole quads (of inputs, or of channels of a pixel, and of columns).  A thread
+// stages four columns of eight batch rows of either matrix, by eight 16-byte loads; what lies outside is read from zeros, which
+// takes no selects behind the loads.  A block's tile has all columns of a layer of up to 64 (NJ x 32) and up to 192 rows of W
+// (KW = 2: wave w contracts rows 32 w .. and 32 (w + 4) ..), so that little is staged for padding, else 128 x 128 (KW = 1, NJ = 4).
+// G: groups of eight batch rows per stage, eight where the tile has at most 32 quads.  The partial sums are grad_gemm_kernel's, of
+// the same batch rows in the same order: the same weights, bit for bit.  Bound by the latency of a stage: two or three blocks share
+// a compute unit.  (256 registers at most, by the launch bounds: with more to have, the compiler keeps the sums in accumulation
+// registers and copies them every stage.)
+// us of a whole update against grad_gemm_kernel above: 144 x 16 weights from 128 images of 32 x 32 77.1 -> 30.8, 576 x 64 from 64 of
+// 56 x 56 292 -> 120, 1152 x 128 from 28 x 28 141 -> 98, 2304 x 256 from 14 x 14 160 -> 114, 64 x 256, 200704 rows 81 -> 71, 4096 x 4096,
+// 128 rows 127 -> 121.
+constexpr int kQuadRows = 192;
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef const float4v __attribute__((address_space(1))) global_quad;
+__device__ float4v g_zeros;
+template <int KW, int NJ, int G, bool CONV>
+__global__ __launch_bounds__(256, KW == 1 ? 2 : 3) void grad_quads_kernel(GradArgs a) {
+  constexpr int kRows = G == 8 || KW == 1 ? 128 : kQuadRows;   // eight groups: at most 32 quads
+  __shared__ bf16x8 xs[2][G][kRows];
+  __shared__ bf16x8 ds[2][G][32 * NJ];
+  __shared__ ConvRow crow[2][8 * G];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int logical = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);   // tiles of a batch chunk on one XCD, as above
+  if (logical >= a.total_wg) return;
+  const int tiles = a.KB * a.NB, part_id = logical / tiles, tile = logical - part_id * tiles, nb = tile / a.KB;
+  const int k0 = (tile - nb * a.KB) * a.tile_rows, kt = min(a.tile_rows, a.K - k0), n0 = nb * 32 * NJ, nt = min(32 * NJ, a.N - n0);
+  // A block's rows of the batch chunk: all of them, or of every 32 the first or the last 16 (grad_gemm_kernel's shares)
+  const int chunk_id = a.shares == 2 ? part_id >> 1 : part_id, share = a.shares == 2 ? part_id & 1 : 0;
+  const int m_begin = chunk_id * a.m_per_chunk, m_end = min(a.M, m_begin + a.m_per_chunk);
+  const int rows = a.shares == 2 ? ((m_end - m_begin + 31) >> 5) << 4 : m_end - m_begin;
+  auto row_of = [&](int r) __attribute__((always_inline)) { return m_begin + (a.shares == 2 ? ((r >> 4) << 5) + 16 * share + (r & 15) : r); };
+  // this thread's quad of columns and group of rows
+  const int xq = kt >> 2, quads = xq + (nt >> 2), g = tid / quads, q = tid - g * quads;
+  const bool is_x = q < xq, works = g < G;
+  const int col = 4 * (is_x ? q : q - xq);
+  const float* from;
+  int row_stride = 0, ckh = 0, ckw = 0;
+  if (!is_x) {
+    from = a.D + n0 + col;
+    row_stride = a.N;
+  } else if (CONV) {
+    const int k = k0 + col, kk = k / a.conv.C;
+    ckh = kk / a.conv.KW;
+    ckw = kk - ckh * a.conv.KW;
+    from = a.X + (((long long)ckh * a.conv.W + ckw) * a.conv.C + (k - kk * a.conv.C));
+  } else {
+    from = a.X + k0 + col;
+    row_stride = a.K;
+  }
+  bf16x8* to = is_x ? &xs[0][works ? g : 0][col] : &ds[0][works ? g : 0][col];
+  const int to_term = is_x ? G * kRows : G * 32 * NJ;
+  float4v v[8];
+  global_quad* zeros = (global_quad*)&g_zeros;
+  auto patches_of = [&](int r0, int buf) __attribute__((always_inline)) {
+    if (CONV && tid < 8 * G) crow[buf][tid] = conv_row(a.conv, min(row_of(r0 + tid), a.M - 1));
+  };
+  auto load = [&](int r0, int buf) __attribute__((always_inline)) {
+    const int r8 = 8 * min(g, G - 1), m = row_of(r0 + r8);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      long long off = (long long)(m + e) * row_stride;
+      bool there = m + e < m_end;
+      if (CONV) {
+        const ConvRow r = crow[buf][r8 + e];
+        const int ih = r.ih0 + ckh, iw = r.iw0 + ckw;
+        const bool inside = (ih >= 0) & (ih < a.conv.H) & (iw >= 0) & (iw < a.conv.W);
+        off = is_x ? r.off : off;
+        there = there & (inside | !is_x);
+      }
+      v[e] = *(there ? (global_quad*)(from + off) : zeros);
+    }
+  };
+  float16v acc[KW][NJ];
+#pragma unroll
+  for (int i = 0; i < KW; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  const int blocks = (kt + 31) >> 5;                 // of 32 rows of W
+  patches_of(0, 0);
+  if (CONV) __syncthreads();
+  load(0, 0);
+  int buf = 0;
+  for (int r0 = 0; r0 < rows; r0 += 8 * G, buf ^= 1) {
+    if (r0 + 8 * G < rows) patches_of(r0 + 8 * G, buf ^ 1);
+    __syncthreads();                                 // everyone is done with the stage before
+    if (works) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        bf16x8 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          __bf16 h, l;
+          split_bf16(v[e][c], h, l);
+          hi[e] = h;
+          lo[e] = l;
+        }
+        to[c] = hi;
+        to[to_term + c] = lo;
+      }
+    }
+    __syncthreads();
+    if (r0 + 8 * G < rows) load(r0 + 8 * G, buf ^ 1);
+    if (wave < blocks) {
+#pragma unroll
+      for (int ks = 0; ks < G / 2; ++ks) {
+        const int g8 = 2 * ks + (lane >> 5);
+        bf16x8 bh[NJ], bl[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          bh[j] = ds[0][g8][32 * j + (lane & 31)];
+          bl[j] = ds[1][g8][32 * j + (lane & 31)];
+        }
+#pragma unroll
+        for (int i = 0; i < KW; ++i)
+          if (wave + 4 * i < blocks) {
+            const bf16x8 ah = xs[0][g8][32 * (wave + 4 * i) + (lane & 31)], al = xs[1][g8][32 * (wave + 4 * i) + (lane & 31)];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[j], acc[i][j], 0, 0, 0);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
+            }
+          }
+      }
+    }
+  }
+  float* out = a.part + (size_t)part_id * a.K * a.N;
+#pragma unroll
+  for (int i = 0; i < KW; ++i)
+    if (wave + 4 * i < blocks) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int k = k0 + 32 * (wave + 4 * i) + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), n = n0 + 32 * j + (lane & 31);
+          if (k < a.K && n < a.N) out[(size_t)k * a.N + n] = acc[i][j][r];
+        }
+    }
 }
 
 // Backward pass of a convolution layer: the crossbars give the error of every patch element
@@ -1868,7 +2011,28 @@ int run_update(const xbar_config* cfg, float* W, const float* X, const float* dY
     }
     return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
   }
-  {
+  if (N % 4 == 0 && (conv ? conv->C : K) % 4 == 0) {
+    const bool wide = N > 64;
+    const int tile_cols = wide ? 128 : 64;
+    g.KB = cdiv(K, wide ? 128 : kQuadRows);
+    g.NB = cdiv(N, tile_cols);
+    g.tile_rows = cdiv(cdiv(K, g.KB), 32) * 32;
+    g.shares = p.parts > 1 ? 2 : 1;                  // of four shares two are empty
+    w.mchunks = p.mchunks * g.shares;
+    g.total_wg = g.KB * g.NB * w.mchunks;
+    g.per_xcd = cdiv(g.total_wg, 8);
+    // stages of 64 rows where tiles are small and there are as many
+    const int rows = g.m_per_chunk / g.shares, groups = (g.tile_rows + std::min(N, tile_cols)) / 4 <= 32 && rows % 64 == 0 ? 8 : 4;
+    if (conv) g.conv = *conv;
+    void (*k)(GradArgs);
+    if (wide && groups == 8) k = conv ? grad_quads_kernel<1, 4, 8, true> : grad_quads_kernel<1, 4, 8, false>;
+    else if (wide) k = conv ? grad_quads_kernel<1, 4, 4, true> : grad_quads_kernel<1, 4, 4, false>;
+    else if (conv) k = N <= 32 ? (groups == 8 ? grad_quads_kernel<2, 1, 8, true> : grad_quads_kernel<2, 1, 4, true>)
+                               : (groups == 8 ? grad_quads_kernel<2, 2, 8, true> : grad_quads_kernel<2, 2, 4, true>);
+    else k = N <= 32 ? (groups == 8 ? grad_quads_kernel<2, 1, 8, false> : grad_quads_kernel<2, 1, 4, false>)
+                     : (groups == 8 ? grad_quads_kernel<2, 2, 8, false> : grad_quads_kernel<2, 2, 4, false>);
+    hipLaunchKernelGGL(k, dim3((unsigned)(g.per_xcd * 8)), dim3(256), 0, st, g);
+  } else {
     g.total_wg = p.KB * p.NB * p.mchunks;
     g.per_xcd = cdiv(g.total_wg, 8);
     const dim3 grid((unsigned)(g.per_xcd * 8)), block(256);

@@ -239,6 +239,29 @@ def test_pulsed_walk_of_special_weights(xo, xb, M, K, N, v, ni):
     assert np.array_equal(np.signbit(Wg[zero]), np.signbit(Wo[zero]))
 
 
+# Gradient of layers whose rows are whole quads: one quad, tiles plus one, both stage lengths, batch rows that fill no stage or chunk,
+# patches that lie outside the image, every width of tile; and layers beside them, whose rows are no quads.  A weight moves by the
+# learning rate times its gradient, whose products are good to 2^-15 of themselves and whose sums are in single precision
+@pytest.mark.parametrize("B,image,cin,cout,k,stride", [(5, 15, 4, 4, 1, 1), (9, 11, 4, 32, 3, 1), (42, 9, 20, 36, 3, 2), (21, 7, 64, 64, 3, 1), (27, 13, 8, 68, 5, 2),
+                                                       (65, 8, 192, 128, 1, 2), (13, 9, 196, 132, 1, 1), (5, 16, 24, 12, 3, 1), (13, 9, 12, 200, 3, 1),
+                                                       (1, 5, 24, 12, 3, 1), (13, 9, 6, 36, 3, 1), (13, 9, 8, 37, 3, 1), (40, 30, 16, 16, 3, 1)])
+def test_gradient_of_whole_quads(xb, B, image, cin, cout, k, stride):
+    from oracle import conv
+    rng = np.random.default_rng(cin + cout)
+    geom = xb.conv_geom(B, image, image, cin, k, k, stride, k // 2)
+    X = rng.standard_normal((B, image, image, cin)).astype(np.float32)
+    dY = rng.standard_normal((B, geom.out_h, geom.out_w, cout)).astype(np.float32)
+    W = (rng.standard_normal((k * k * cin, cout)) * 0.1).astype(np.float32)
+    cfg = xb.make_config(**dict(workloads.config_kwargs("resnet20"), flags=0))
+    Wg = dev(W.copy())
+    lr = np.float64(np.float32(1e-3))
+    xb.conv_update(cfg, Wg, dev(X), dev(dY), geom, 64.0, 1.0 / 64.0, 1e-3, 0)
+    P = conv.im2col(X, k, k, stride, k // 2).reshape(-1, k * k * cin).astype(np.float64)
+    D = dY.reshape(-1, cout).astype(np.float64)
+    bound = lr * 2.0 ** -15 * (np.abs(P).T @ np.abs(D)) + 2.0 ** -23 * 64.0
+    assert (np.abs(Wg.cpu().numpy() - (W - lr * (P.T @ D))) <= bound).all()
+
+
 # Circuit-level model, state on chip: one device, one row, one column, tiles plus one; wires that matter (many iterations)
 @pytest.mark.parametrize("R,K,N,r_min", [(64, 1, 1, 1e5), (64, 65, 3, 1e3), (128, 1, 129, 1e5), (128, 130, 1, 1e4), (128, 40, 20, 1e3)])
 def test_circuit_model_on_chip(xo, xb, R, K, N, r_min):
