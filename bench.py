@@ -101,6 +101,8 @@ def end_to_end(args, torch, workloads, xb, device):
     records = []
 
     class Traced:                      # the binding, with HIP events around every contraction kernel
+        joins_passes = True            # the step is the one the binding runs
+
         def __getattr__(self, name):
             fn = getattr(xb, name)
             if name not in ("fwd", "bwd", "conv_fwd", "conv_bwd") or not self.timed:

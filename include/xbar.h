@@ -329,6 +329,11 @@ int xbar_conv_update_pulsed(const xbar_config* cfg, float* W, const float* X, co
  *   bn_fwd        training mode: per-channel batch mean and biased variance; writes y, mean and
  *                 invstd = 1 / sqrt(var + eps) (kept for bn_bwd)
  *   bn_bwd        dx, dgamma = sum dy xhat, dbeta = sum dy; ws: xbar_bn_workspace_bytes(rows, channels)
+ *   bn_relu_fwd   y = relu(bn(x) + skip) in the passes of bn_fwd, same bits; skip (rows x channels) may be NULL
+ *   bn_bwd_sgd    bn_bwd; with relu of the errors where bn(x), evaluated again from x, mean, invstd, gamma and beta,
+ *                 is positive (the backward pass of relu(bn(x)): as relu_bwd and bn_bwd after it); with update
+ *                 gamma and beta take their sgd step behind it.  Same ws
+ *   add_relu_bwd  dx = a + b where the forward output y > 0, else 0
  *   avgpool       global average over the `positions` of every (sample, channel)
  *   maxpool       square window k_h = k_w with stride and padding from the geometry struct (in_c =
  *                 channels, 2 pad <= k); argmax[out element] = position ih * in_w + iw of the first
@@ -347,11 +352,17 @@ int xbar_sigmoid_fwd(const float* x, float* y, size_t n, void* hip_stream);
 int xbar_sigmoid_bwd(const float* y, const float* dy, float* dx, size_t n, void* hip_stream);
 int xbar_add(const float* a, const float* b, float* y, size_t n, void* hip_stream);
 int xbar_sgd(float* p, const float* g, size_t n, float lr, void* hip_stream);
+int xbar_add_relu_bwd(const float* y, const float* a, const float* b, float* dx, size_t n, void* hip_stream);
 size_t xbar_bn_workspace_bytes(size_t rows, int channels);
 int xbar_bn_fwd(const float* x, const float* gamma, const float* beta, float* y, float* mean, float* invstd, size_t rows,
                 int channels, float eps, void* ws, size_t ws_bytes, void* hip_stream);
 int xbar_bn_bwd(const float* x, const float* dy, const float* gamma, const float* mean, const float* invstd, float* dx,
                 float* dgamma, float* dbeta, size_t rows, int channels, void* ws, size_t ws_bytes, void* hip_stream);
+int xbar_bn_relu_fwd(const float* x, const float* gamma, const float* beta, const float* skip, float* y, float* mean, float* invstd,
+                     size_t rows, int channels, float eps, void* ws, size_t ws_bytes, void* hip_stream);
+int xbar_bn_bwd_sgd(const float* x, const float* dy, float* gamma, float* beta, const float* mean, const float* invstd, float* dx,
+                    float* dgamma, float* dbeta, size_t rows, int channels, int relu, int update, float lr, void* ws, size_t ws_bytes,
+                    void* hip_stream);
 int xbar_avgpool_fwd(const float* x, float* y, int batch, int positions, int channels, void* hip_stream);
 int xbar_avgpool_bwd(const float* dy, float* dx, int batch, int positions, int channels, void* hip_stream);
 int xbar_maxpool_fwd(const float* x, float* y, int32_t* argmax, const xbar_conv_geom* geom, void* hip_stream);

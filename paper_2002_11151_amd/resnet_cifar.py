@@ -146,9 +146,29 @@ class BatchNorm:
         self.saved = (x, mean, invstd)
         return y
 
-    def backward(self, dy, lr, ws):
+    def forward_relu(self, x, ws, skip=None):
+        """relu(normalised x + skip); skip: a tensor or a function that gives one."""
+        ops = self.net.ops
+        if self.net.joins_passes():
+            skip = skip() if callable(skip) else skip
+            y, mean, invstd = ops.bn_relu_fwd(x, self.gamma, self.beta, 1e-5, skip, ws=ws)
+            self.saved = (x, mean, invstd)
+            return y
+        y = self.forward(x, ws)
+        skip = skip() if callable(skip) else skip
+        return ops.relu_fwd(y if skip is None else ops.add(y, skip))
+
+    def backward_relu(self, y, dy, lr, ws):
+        """Error through the ReLU whose output y was (forward_relu without a skip) and the normalisation."""
+        if self.net.joins_passes():
+            return self.backward(dy, lr, ws, relu=True)
+        return self.backward(self.net.ops.relu_bwd(y, dy), lr, ws)
+
+    def backward(self, dy, lr, ws, relu=False):
         x, mean, invstd = self.saved
         ops = self.net.ops
+        if self.net.joins_passes():
+            return ops.bn_bwd_sgd(x, dy, self.gamma, self.beta, mean, invstd, relu, None if self.net.calibrating else lr, ws=ws)[0]
         dx, dgamma, dbeta = ops.bn_bwd(x, dy, self.gamma, mean, invstd, ws=ws)
         if not self.net.calibrating:
             ops.sgd(self.gamma, dgamma, lr)
@@ -167,6 +187,18 @@ class Network:
     adc_quantile = None   # set while the converter ranges are being measured
     pulse = None     # dict(bl=slots per train, dw_min=state change per pulse): pulse-level updates of the crossbar layers
     pair_devices = False   # aggregate updates keep the positive and the negative device of a weight as states of their own
+
+    def joins_passes(self):
+        """Normalisation, addition, ReLU and the normalisation's parameter step as few passes over memory (same bits), or one
+        operation per call: what a stand-in for the binding sees, unless its class says `joins_passes = True`."""
+        return self.ops is xb or getattr(type(self.ops), "joins_passes", False)
+
+    def _join_errors(self, a, b, out):
+        """Sum of two branches' errors; with `out` (an activation after a ReLU) through that ReLU too."""
+        ops = self.ops
+        if out is None:
+            return ops.add(a, b)
+        return ops.add_relu_bwd(out, a, b) if self.joins_passes() else ops.relu_bwd(out, ops.add(a, b))
 
     def train_step(self, x, labels, lr):
         """One SGD step on a batch: returns the per-sample losses (device tensor)."""
@@ -282,15 +314,15 @@ class ResNetCifar(Network):
     # ---- forward / backward ---------------------------------------------------------------------
     def forward(self, images, step):
         ws, ops = self.ws, self.ops
-        a = ops.relu_fwd(self.stem_bn.forward(self.stem.forward(images, step, ws), ws))
+        a = self.stem_bn.forward_relu(self.stem.forward(images, step, ws), ws)
         self.stem_out = a
         for blk in self.blocks:
             blk["in"] = a
-            h = ops.relu_fwd(blk["bn_a"].forward(blk["a"].forward(a, step, ws), ws))
+            h = blk["bn_a"].forward_relu(blk["a"].forward(a, step, ws), ws)
             blk["mid"] = h
-            h = blk["bn_b"].forward(blk["b"].forward(h, step, ws), ws)
-            skip = a if (blk["stride"] == 1 and blk["cin"] == blk["width"]) else ops.shortcut_fwd(a, blk["stride"], blk["width"])
-            a = ops.relu_fwd(ops.add(h, skip))
+            same = blk["stride"] == 1 and blk["cin"] == blk["width"]
+            skip = a if same else lambda: ops.shortcut_fwd(blk["in"], blk["stride"], blk["width"])
+            a = blk["bn_b"].forward_relu(blk["b"].forward(h, step, ws), ws, skip)
             blk["out"] = a
         self.pooled = ops.avgpool_fwd(a)
         self.feat_shape = tuple(a.shape)
@@ -299,13 +331,13 @@ class ResNetCifar(Network):
     def backward(self, dlogits, step, lr):
         ws, ops = self.ws, self.ops
         d = ops.avgpool_bwd(self.fc.backward(dlogits, step, lr, ws), self.feat_shape)
-        for blk in reversed(self.blocks):
-            d = ops.relu_bwd(blk["out"], d)                       # error of the sum: goes to both branches
+        d = ops.relu_bwd(self.blocks[-1]["out"], d)               # error of a block's sum: goes to both branches
+        for i in range(len(self.blocks) - 1, -1, -1):
+            blk = self.blocks[i]
             h = blk["b"].backward(blk["bn_b"].backward(d, lr, ws), step, lr, ws)
-            h = blk["a"].backward(blk["bn_a"].backward(ops.relu_bwd(blk["mid"], h), lr, ws), step, lr, ws)
-            if blk["stride"] == 1 and blk["cin"] == blk["width"]:
-                d = ops.add(h, d)
-            else:
-                d = ops.add(h, ops.shortcut_bwd(d, tuple(blk["in"].shape), blk["stride"]))
-        d = self.stem_bn.backward(ops.relu_bwd(self.stem_out, d), lr, ws)
+            h = blk["a"].backward(blk["bn_a"].backward_relu(blk["mid"], h, lr, ws), step, lr, ws)
+            if not (blk["stride"] == 1 and blk["cin"] == blk["width"]):
+                d = ops.shortcut_bwd(d, tuple(blk["in"].shape), blk["stride"])
+            d = self._join_errors(h, d, self.blocks[i - 1]["out"] if i else None)
+        d = self.stem_bn.backward_relu(self.stem_out, d, lr, ws)
         self.stem.backward(d, step, lr, ws, need_dx=False)

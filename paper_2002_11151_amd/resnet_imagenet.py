@@ -49,17 +49,17 @@ class ResNetBottleneck(Network):
 
     def forward(self, images, step):
         ws, ops = self.ws, self.ops
-        a = ops.relu_fwd(self.stem_bn.forward(self.stem.forward(images, step, ws), ws))
+        a = self.stem_bn.forward_relu(self.stem.forward(images, step, ws), ws)
         self.stem_out = a
         a, self.pool_arg = ops.maxpool_fwd(a, self.pool_geom)
         for blk in self.blocks:
-            h = ops.relu_fwd(blk["bn_a"].forward(blk["a"].forward(a, step, ws), ws))
+            blk["in"] = a
+            h = blk["bn_a"].forward_relu(blk["a"].forward(a, step, ws), ws)
             blk["act_a"] = h
-            h = ops.relu_fwd(blk["bn_b"].forward(blk["b"].forward(h, step, ws), ws))
+            h = blk["bn_b"].forward_relu(blk["b"].forward(h, step, ws), ws)
             blk["act_b"] = h
-            h = blk["bn_c"].forward(blk["c"].forward(h, step, ws), ws)
-            skip = blk["bn_down"].forward(blk["down"].forward(a, step, ws), ws) if "down" in blk else a
-            a = ops.relu_fwd(ops.add(h, skip))
+            down = lambda: blk["bn_down"].forward(blk["down"].forward(blk["in"], step, ws), ws)
+            a = blk["bn_c"].forward_relu(blk["c"].forward(h, step, ws), ws, down if "down" in blk else a)
             blk["out"] = a
         self.pooled = ops.avgpool_fwd(a)
         self.feat_shape = tuple(a.shape)
@@ -68,14 +68,15 @@ class ResNetBottleneck(Network):
     def backward(self, dlogits, step, lr):
         ws, ops = self.ws, self.ops
         d = ops.avgpool_bwd(self.fc.backward(dlogits, step, lr, ws), self.feat_shape)
-        for blk in reversed(self.blocks):
-            d = ops.relu_bwd(blk["out"], d)                       # error of the sum: goes to both branches
+        d = ops.relu_bwd(self.blocks[-1]["out"], d)               # error of a block's sum: goes to both branches
+        for i in range(len(self.blocks) - 1, -1, -1):
+            blk = self.blocks[i]
             h = blk["c"].backward(blk["bn_c"].backward(d, lr, ws), step, lr, ws)
-            h = blk["b"].backward(blk["bn_b"].backward(ops.relu_bwd(blk["act_b"], h), lr, ws), step, lr, ws)
-            h = blk["a"].backward(blk["bn_a"].backward(ops.relu_bwd(blk["act_a"], h), lr, ws), step, lr, ws)
+            h = blk["b"].backward(blk["bn_b"].backward_relu(blk["act_b"], h, lr, ws), step, lr, ws)
+            h = blk["a"].backward(blk["bn_a"].backward_relu(blk["act_a"], h, lr, ws), step, lr, ws)
             if "down" in blk:
                 d = blk["down"].backward(blk["bn_down"].backward(d, lr, ws), step, lr, ws)
-            d = ops.add(h, d)
+            d = self._join_errors(h, d, self.blocks[i - 1]["out"] if i else None)
         d = ops.maxpool_bwd(d, self.pool_arg, self.pool_geom)
-        d = self.stem_bn.backward(ops.relu_bwd(self.stem_out, d), lr, ws)
+        d = self.stem_bn.backward_relu(self.stem_out, d, lr, ws)
         self.stem.backward(d, step, lr, ws, need_dx=False)

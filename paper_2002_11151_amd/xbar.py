@@ -124,6 +124,10 @@ _SIGNATURES = {
     "xbar_bn_workspace_bytes": (C.c_size_t, [C.c_size_t, C.c_int]),
     "xbar_bn_fwd": (C.c_int, [C.c_void_p] * 6 + [C.c_size_t, C.c_int, C.c_float, C.c_void_p, C.c_size_t, C.c_void_p]),
     "xbar_bn_bwd": (C.c_int, [C.c_void_p] * 8 + [C.c_size_t, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "xbar_bn_relu_fwd": (C.c_int, [C.c_void_p] * 7 + [C.c_size_t, C.c_int, C.c_float, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "xbar_bn_bwd_sgd": (C.c_int, [C.c_void_p] * 9 + [C.c_size_t, C.c_int, C.c_int, C.c_int, C.c_float, C.c_void_p, C.c_size_t,
+                                                     C.c_void_p]),
+    "xbar_add_relu_bwd": (C.c_int, [C.c_void_p] * 4 + [C.c_size_t, C.c_void_p]),
     "xbar_avgpool_fwd": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p]),
     "xbar_avgpool_bwd": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p]),
     "xbar_maxpool_fwd": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(ConvGeom), C.c_void_p]),
@@ -475,6 +479,13 @@ def add(a, b, out=None):
     return out
 
 
+def add_relu_bwd(y, a, b, out=None):
+    """xbar_add_relu_bwd: relu_bwd(y, a + b)."""
+    out = torch.empty_like(a) if out is None else out
+    _check(lib().xbar_add_relu_bwd(_dev(y), _dev(a), _dev(b), _dev(out), a.numel(), _stream()))
+    return out
+
+
 def sgd(p, g, lr):
     _check(lib().xbar_sgd(_dev(p), _dev(g), p.numel(), lr, _stream()))
     return p
@@ -507,6 +518,33 @@ def bn_bwd(x, dy, gamma, mean, invstd, ws=None):
     dbeta = torch.empty_like(dgamma)
     _check(lib().xbar_bn_bwd(_dev(x), _dev(dy), _dev(gamma), _dev(mean), _dev(invstd), _dev(dx), _dev(dgamma), _dev(dbeta),
                              rows, channels, ws.data_ptr(), ws.numel(), _stream()))
+    return dx, dgamma, dbeta
+
+
+def bn_relu_fwd(x, gamma, beta, eps=1e-5, skip=None, ws=None):
+    """xbar_bn_relu_fwd: relu(bn(x) + skip) as (y, mean, invstd)."""
+    channels = x.shape[-1]
+    rows = x.numel() // channels
+    ws = _bn_ws(rows, channels, ws, x.device)
+    y = torch.empty_like(x)
+    mean = torch.empty(channels, dtype=torch.float32, device=x.device)
+    invstd = torch.empty_like(mean)
+    _check(lib().xbar_bn_relu_fwd(_dev(x), _dev(gamma), _dev(beta), None if skip is None else _dev(skip), _dev(y), _dev(mean),
+                                  _dev(invstd), rows, channels, eps, ws.data_ptr(), ws.numel(), _stream()))
+    return y, mean, invstd
+
+
+def bn_bwd_sgd(x, dy, gamma, beta, mean, invstd, relu=False, lr=None, ws=None):
+    """xbar_bn_bwd_sgd: returns (dx, dgamma, dbeta); with a learning rate gamma and beta are written."""
+    channels = x.shape[-1]
+    rows = x.numel() // channels
+    ws = _bn_ws(rows, channels, ws, x.device)
+    dx = torch.empty_like(x)
+    dgamma = torch.empty(channels, dtype=torch.float32, device=x.device)
+    dbeta = torch.empty_like(dgamma)
+    _check(lib().xbar_bn_bwd_sgd(_dev(x), _dev(dy), _dev(gamma), _dev(beta), _dev(mean), _dev(invstd), _dev(dx), _dev(dgamma),
+                                 _dev(dbeta), rows, channels, relu, lr is not None, 0.0 if lr is None else lr, ws.data_ptr(),
+                                 ws.numel(), _stream()))
     return dx, dgamma, dbeta
 
 

@@ -86,3 +86,99 @@ def test_softmax_cross_entropy(xb, B, classes):
     bad[0] = classes                                          # unknown class: NaN loss, no fault
     loss, _ = xb.softmax_xent(dev(z), dev(bad, np.int32), 1.0)
     assert np.isnan(loss.cpu().numpy()[0]) and not np.isnan(loss.cpu().numpy()[1:]).any()
+
+
+@pytest.mark.parametrize("rows,C", [(3, 4), (513, 7), (700, 16), (1100, 36), (2000, 64), (65, 1028), (7, 257), (40000, 64),
+                                    (524289, 16), (140001, 61)])
+def test_joined_normalisation_passes(xb, rows, C):
+    """Sums and passes at the edges of their strips (16 and 64 channels, quads or not), of 512 rows and of one or four rows per
+    thread, against 64 bits; normalisation, addition, ReLU and parameter step in one against the single operations, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(rows + C)
+    x, dy, skip = (torch.randn((rows, C), generator=g, device="cuda") for _ in range(3))
+    gamma, beta = torch.rand(C, generator=g, device="cuda") + 0.5, torch.randn(C, generator=g, device="cuda")
+    y, mean, invstd = xb.bn_fwd(x, gamma, beta)
+    X, D = x.double(), dy.double()
+    mu, var = X.mean(0), X.var(0, unbiased=False)
+    close(mean, mu.cpu().numpy())
+    close(invstd, (1 / (var + 1e-5).sqrt()).cpu().numpy(), 1e-6)
+    xhat = (X - mean.double()) * invstd.double()
+    close(y, (gamma.double() * xhat + beta.double()).cpu().numpy())
+    for s in (None, skip):
+        y1, mean1, invstd1 = xb.bn_relu_fwd(x, gamma, beta, skip=s)
+        want = xb.relu_fwd(y if s is None else xb.add(y, s))
+        assert torch.equal(y1, want) and torch.equal(mean1, mean) and torch.equal(invstd1, invstd)
+    act = xb.relu_fwd(y)
+    assert torch.equal(act, torch.where(y > 0, y, torch.zeros_like(y)))
+    assert torch.equal(xb.add_relu_bwd(act, dy, skip), xb.relu_bwd(act, xb.add(dy, skip)))
+    for relu in (False, True):
+        d = xb.relu_bwd(act, dy) if relu else dy
+        assert not relu or torch.equal(d, torch.where(act > 0, dy, torch.zeros_like(dy)))
+        want = xb.bn_bwd(x, d, gamma, mean, invstd)
+        dg, db = (d.double() * xhat).sum(0), d.double().sum(0)
+        scale = rows ** 0.5
+        close(want[1] / scale, (dg / scale).cpu().numpy())
+        close(want[2] / scale, (db / scale).cpu().numpy())
+        dx = gamma.double() * invstd.double() * (d.double() - want[2].double() / rows - xhat * want[1].double() / rows)
+        close(want[0], dx.cpu().numpy())
+        for lr in (None, 0.1):
+            g1, b1 = gamma.clone(), beta.clone()
+            got = xb.bn_bwd_sgd(x, dy, g1, b1, mean, invstd, relu=relu, lr=lr)
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
+            g2, b2 = gamma.clone(), beta.clone()
+            if lr is not None:
+                xb.sgd(g2, want[1], lr)
+                xb.sgd(b2, want[2], lr)
+            assert torch.equal(g1, g2) and torch.equal(b1, b2)
+
+
+def test_joined_passes_keep_nan_and_signs(xb):
+    """What is not a number passes no ReLU, forward or backward, and a zero or negative output passes no error."""
+    y = torch.tensor([1.0, 0.0, -0.0, -1.0, float("nan"), float("inf"), 2.0], device="cuda")
+    a = torch.tensor([1.0, float("nan"), 3.0, 4.0, 5.0, 6.0, float("nan")], device="cuda")
+    got, want = xb.add_relu_bwd(y, a, a), xb.relu_bwd(y, xb.add(a, a))
+    assert torch.equal(torch.nan_to_num(got, 7.0), torch.nan_to_num(want, 7.0)) and want[5] == 12 and want[4] == 0
+    x = torch.randn((64, 8), device="cuda")
+    x[3, 2] = float("nan")
+    gamma, beta = torch.ones(8, device="cuda"), torch.zeros(8, device="cuda")
+    y, mean, invstd = xb.bn_fwd(x, gamma, beta)
+    act = xb.bn_relu_fwd(x, gamma, beta)[0]
+    assert torch.equal(act, xb.relu_fwd(y)) and not act[:, 2].any()
+    dy = torch.randn((64, 8), device="cuda")
+    want = xb.bn_bwd(x, xb.relu_bwd(act, dy), gamma, mean, invstd)
+    got = xb.bn_bwd_sgd(x, dy, gamma, beta, mean, invstd, relu=True)
+    assert all(torch.equal(torch.nan_to_num(u, 7.0), torch.nan_to_num(v, 7.0)) for u, v in zip(got, want))
+
+
+@pytest.mark.parametrize("kind", ["basic", "bottleneck"])
+def test_network_step_joined_or_operation_by_operation(xb, kind):
+    """A training step with the joined passes leaves the same losses, weights and parameters as with every operation a call."""
+    import workloads
+    from paper_2002_11151_amd import resnet_cifar, resnet_imagenet
+
+    class Single:
+        def __getattr__(self, name):
+            return getattr(xb, name)
+
+    kw = workloads.config_kwargs("resnet20")
+    states = []
+    for ops in (xb, Single()):
+        if kind == "basic":
+            net = resnet_cifar.ResNetCifar(kw, batch=3, n_blocks=2, image=12, widths=(8, 16, 20), seed=3)
+        else:
+            net = resnet_imagenet.ResNetBottleneck(kw, batch=3, image=24, classes=10, blocks=(1, 2), widths=(4, 8), stem=8, seed=3)
+        gen = torch.Generator(device="cuda").manual_seed(1)
+        images = torch.randn((3, 12, 12, 3) if kind == "basic" else (3, 24, 24, 3), generator=gen, device="cuda")
+        labels = torch.tensor([1, 7, 4], dtype=torch.int32, device="cuda")
+        net.ops = ops
+        net.calibrate(images, labels)
+        losses = [net.train_step(images, labels, 0.05).clone() for _ in range(2)]
+        norms = [net.stem_bn] + [v for blk in net.blocks for k, v in sorted(blk.items()) if k.startswith("bn")]
+        states.append(losses + [layer.W for layer in net.layers] + [t for n in norms for t in (n.gamma, n.beta)])
+    assert all(torch.equal(a, b) for a, b in zip(*states))
+
+
+@pytest.mark.parametrize("B,H,W,C,k,stride,pad", [(2, 9, 8, 8, 3, 2, 1), (1, 7, 7, 4, 3, 1, 1), (2, 11, 6, 20, 2, 3, 1),
+                                                  (3, 5, 5, 16, 5, 1, 2)])
+def test_pooling_of_quads(xb, B, H, W, C, k, stride, pad):
+    """Four channels per thread; windows that overlap, leave gaps between them or hang over the edge."""
+    test_pooling(xb, B, H, W, C, k, stride, pad)
