@@ -302,6 +302,10 @@ __device__ __forceinline__ void vmm_contract_adc(const half8 (&ab)[PM][NK], cons
           float f = __builtin_fmaf(old[vp][r], gain_old, vmagic);
           f = __builtin_amdgcn_fmed3f(f, clamp_lo, clamp_hi);
           y[vp][r] = (__builtin_bit_cast(uint32_t, f) << sh_old) + y[vp][r];
+          // one shift-and-add per conversion: where the conversions of two slices stand in one block, the compiler
+          // makes two shifts and a three-way addition of them (tiles of up to 64 rows: 251 -> 219 instructions for 64 conversions;
+          // with pairs of staged slices below: ResNet-20 step at batch 128 3526 -> 3442 us)
+          asm("" : "+v"(y[vp][r]));
         }
       }
       if (kBarrierPerMfma) __builtin_amdgcn_sched_barrier(0);
@@ -523,7 +527,7 @@ __device__ __forceinline__ void vmm_tile(const VmmArgs& a, u32x4* lds, int p, in
     }
   constexpr int NF = TERMS * NK;
   const int sg_max = min(a.S_w, a.lds_kb / NF);      // slices per staged group
-  const int sg = WIDE == 2 ? sg_max & ~1 : sg_max;
+  const int sg = sg_max > 1 && sg_max < a.S_w ? sg_max & ~1 : sg_max;   // the pipelined path takes slices in pairs
   for (int sg0 = 0, ns; sg0 < a.S_w; sg0 += ns) {
     // sums of two halves: a staged group lies in one of them
     ns = min(sg, (WIDE == 2 && sg0 < a.split_sg ? a.split_sg : a.S_w) - sg0);

@@ -344,6 +344,20 @@ def test_eight_waves_of_the_small_pass(xb, R, ib, sb, wb, slb, M, K, N, flags):
     assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
 
 
+# fp16 planes whose staged slices would be an odd number: six k-steps (64 KiB hold five slices of them), the same on 256-row arrays
+# (eleven: two), slices that are an odd number themselves, one slice that no group of two holds
+@pytest.mark.parametrize("R,wb,slb,M,K,N", [(128, 16, 2, 3000, 90, 200), (128, 14, 2, 3000, 90, 200), (256, 16, 2, 3000, 170, 100),
+                                            (256, 16, 2, 3000, 250, 100), (256, 12, 1, 2500, 81, 100), (96, 10, 2, 2500, 250, 90)])
+def test_staged_slices_come_in_pairs(xb, R, wb, slb, M, K, N):
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=M + K)
+    fs = 1.037 * workloads.adc_full_scale(R, 4, slb)
+    cfg = xb.make_config(xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=slb, input_bits=8, stream_bits=4, adc_fs_fwd=fs, adc_fs_bwd=fs,
+                         flags=xb.NI_WIRE_AAM | xb.INPUT_SIGNED, seed=4)
+    w_max, xs, gs = float(np.abs(W).max()), float(np.abs(X).max()), float(np.abs(dY).max())
+    assert np.array_equal(gpu_fwd(xb, cfg, W, X, w_max, xs, codes=False), gpu_fwd(xb, cfg, W, X, w_max, xs)[0])
+    assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
+
+
 @pytest.mark.parametrize("cin,image", [(7, 31), (7, 25), (8, 31)])
 def test_gathered_inputs_of_the_small_pass(xb, cin, image):
     from oracle import conv
