@@ -417,7 +417,8 @@ constexpr int kFromDevices = 2;   // anything else: every device of the patch co
 // numbers and the wire model (one Philox block for the four devices of a slice pair); each weight is quantised once per slice
 // pair.  The terms of 32 values come out of the conversion instructions a record at a time, twice (either direction), which is
 // a tenth of the integer work of finding every value's term codes and picking the records' bits from them: 4096 x 4096 weights
-// with variation, 8 slices, 5 terms, 1485 -> 1197 us, and 1658 -> 1485 with the shorter normal numbers.
+// with variation, 8 slices, 5 terms, 1485 -> 1197 us, and 1658 -> 1485 with the shorter normal numbers; 1133 -> 1000 with the
+// constants of the normal numbers and the Philox keys in scalar registers.
 template <int SRC, int NPOL, int NTH>
 __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns) {
   constexpr int SL = NPOL == 2 ? 1 : 2;              // slices per turn: as many words in LDS either way
@@ -431,6 +432,7 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
   const uint32_t dmask = (1u << a.slice_bits) - 1;
   const int i0 = k0 % a.R, j = n0 % a.C + lane;      // place in the array: whole steps of 64 do not straddle arrays
   NormalStream rng(a.seed, kStreamVariation, effective_step(a.step, a.step_add));
+  const uint32_t key0 = rng.k0, key1 = rng.k1;
   int q[PER];
   if constexpr (SRC != kFromDevices) {
 #pragma unroll
@@ -451,6 +453,12 @@ __global__ __launch_bounds__(NTH, 4) void tile_f6_kernel(BothCopies b, int turns
         const int w = real ? quantized_weight(a.W[(size_t)k * a.N + n], (double)a.w_max, a.qw, a.q_per_w) : 0;
         const int sign = (w > 0) - (w < 0);
         const uint32_t mag = (uint32_t)::abs(w);
+        // the keys of the ten Philox rounds are made anew by scalar additions: kept across the loop they outgrow the scalar
+        // registers and come back from vector registers one by one
+        uint32_t first = __builtin_amdgcn_readfirstlane(key0), second = __builtin_amdgcn_readfirstlane(key1);
+        asm volatile("" : "+s"(first), "+s"(second));
+        rng.k0 = first;
+        rng.k1 = second;
 #pragma unroll
         for (int sl = 0; sl < SL; ++sl) {
           double u[NPOL];

@@ -230,6 +230,14 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
   out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
+// a b + a constant, which the instruction takes from scalar registers: left to itself the compiler copies it into the vector
+// registers of the sum first, a tenth of a normal number's instructions.
+__device__ __forceinline__ double fma_constant(double a, double b, double constant) {
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(constant));
+  return r;
+}
+
 // Standard normal number i of (seed, stream, step): four consecutive i share one Philox block,
 // words (0,1) -> numbers 0,1 (cosine, sine branch of Box-Muller), words (2,3) -> numbers 2,3.
 struct NormalStream {
@@ -289,12 +297,12 @@ struct NormalStream {
     // ln m = 2 artanh s = 2 s + s^3 q(s^2) = f - s (f - s^2 q): q of degree 6 fitted to 2^-51 on s^2 <= 0.0295
     const double z = s * s;
     double q = 0x1.2b5b5fb2eac92p-3;
-    q = __builtin_fma(q, z, 0x1.39fe208c33457p-3);
-    q = __builtin_fma(q, z, 0x1.7462b69705382p-3);
-    q = __builtin_fma(q, z, 0x1.c71c62debf86bp-3);
-    q = __builtin_fma(q, z, 0x1.2492492df6947p-2);
-    q = __builtin_fma(q, z, 0x1.99999999952b2p-2);
-    q = __builtin_fma(q, z, 0x1.5555555555558p-1);
+    q = fma_constant(q, z, 0x1.39fe208c33457p-3);
+    q = fma_constant(q, z, 0x1.7462b69705382p-3);
+    q = fma_constant(q, z, 0x1.c71c62debf86bp-3);
+    q = fma_constant(q, z, 0x1.2492492df6947p-2);
+    q = fma_constant(q, z, 0x1.99999999952b2p-2);
+    q = fma_constant(q, z, 0x1.5555555555558p-1);
     const double kd = (double)k, top = __builtin_fma(kd, 0x1.62e42fefa39efp-1, f);           // k ln 2, in two words, plus f
     const double rest = __builtin_fma(kd, 0x1.62e42fefa39efp-1, -top) + f;
     const double ln = top + __builtin_fma(-s, __builtin_fma(-z, q, f), __builtin_fma(kd, 0x1.abc9e3b39803fp-56, rest));
@@ -309,18 +317,18 @@ struct NormalStream {
     const uint32_t quarter = (b + 0x20000000u) >> 30;
     const double x = __builtin_fma((double)(int)(b - (quarter << 30)), 0x1p-29, 0x1p-30), xx = x * x;
     double sn = 0x1.e3f38399551bfp-38;
-    sn = __builtin_fma(sn, xx, -0x1.e30071afc3e59p-30);
-    sn = __builtin_fma(sn, xx, 0x1.50782fda12d96p-22);
-    sn = __builtin_fma(sn, xx, -0x1.32d2cce2e5b19p-15);
-    sn = __builtin_fma(sn, xx, 0x1.466bc677587f8p-9);
-    sn = __builtin_fma(sn, xx, -0x1.4abbce625be41p-4);
+    sn = fma_constant(sn, xx, -0x1.e30071afc3e59p-30);
+    sn = fma_constant(sn, xx, 0x1.50782fda12d96p-22);
+    sn = fma_constant(sn, xx, -0x1.32d2cce2e5b19p-15);
+    sn = fma_constant(sn, xx, 0x1.466bc677587f8p-9);
+    sn = fma_constant(sn, xx, -0x1.4abbce625be41p-4);
     sn = __builtin_fma(x, 0x1.921fb54442d18p-1, __builtin_fma(x * xx, sn, x * 0x1.1a62633145c07p-55));   // pi / 4 in two words
     double cs = -0x1.b264ba152378ap-42;
-    cs = __builtin_fma(cs, xx, 0x1.f9cc41140bb60p-34);
-    cs = __builtin_fma(cs, xx, -0x1.a6d1ec7906c20p-26);
-    cs = __builtin_fma(cs, xx, 0x1.e1f5068355e15p-19);
-    cs = __builtin_fma(cs, xx, -0x1.55d3c7e3c90f8p-12);
-    cs = __builtin_fma(cs, xx, 0x1.03c1f081b5aacp-6);
+    cs = fma_constant(cs, xx, 0x1.f9cc41140bb60p-34);
+    cs = fma_constant(cs, xx, -0x1.a6d1ec7906c20p-26);
+    cs = fma_constant(cs, xx, 0x1.e1f5068355e15p-19);
+    cs = fma_constant(cs, xx, -0x1.55d3c7e3c90f8p-12);
+    cs = fma_constant(cs, xx, 0x1.03c1f081b5aacp-6);
     // ... its first two terms, and the square of x, in two words
     const double big = __builtin_fma(xx, -0x1.3bd3cc9be45dep-2, 1.0), small = __builtin_fma(xx, -0x1.3bd3cc9be45dep-2, 1.0 - big);
     cs = big + __builtin_fma(cs * xx, xx, __builtin_fma(__builtin_fma(x, x, -xx), -0x1.3bd3cc9be45dep-2, small));
