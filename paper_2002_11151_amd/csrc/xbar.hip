@@ -1198,8 +1198,9 @@ __device__ __forceinline__ float written_weight(const WriteArgs& a, float w, dou
   if (a.flags & XBAR_NI_UPD_NL) {
     const double x = clampd(0.5 * (g + 1.0), 0.0, 1.0);
     const double change = -a.lr * delta;
-    if (change > 0.0) written = delta * ::exp(-a.v * x);
-    else if (change < 0.0) written = delta * ::exp(-a.v * (1.0 - x));
+    // one exponential for both directions: the lanes of a wave go either way, and with one in each branch it runs both
+    const double factor = ::exp(-a.v * (change > 0.0 ? x : 1.0 - x));
+    if (change > 0.0 || change < 0.0) written = delta * factor;
   }
   if (a.flags & XBAR_NI_UPD_NOISE) written += a.gamma * ::sqrt(::fabs(delta)) * z;
   return (float)(a.w_max * clampd(g - a.lr * written, -1.0, 1.0));
@@ -1219,9 +1220,8 @@ __device__ __forceinline__ float written_pair(const WriteArgs& a, float& gp, flo
     const double change = dir * a.lr * half;
     double written = half;
     if (a.flags & XBAR_NI_UPD_NL) {
-      const double x = clampd(state[pol], 0.0, 1.0);
-      if (change > 0.0) written = half * ::exp(-a.v * x);
-      else if (change < 0.0) written = half * ::exp(-a.v * (1.0 - x));
+      const double x = clampd(state[pol], 0.0, 1.0), factor = ::exp(-a.v * (change > 0.0 ? x : 1.0 - x));
+      if (change > 0.0 || change < 0.0) written = half * factor;
     }
     if (a.flags & XBAR_NI_UPD_NOISE) written += a.gamma * ::sqrt(::fabs(half)) * z[pol];
     state[pol] = clampd(state[pol] + dir * a.lr * written, 0.0, 1.0);
