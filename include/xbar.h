@@ -433,6 +433,12 @@ void xbar_trace_next_vmm(void* before, void* after);
 void xbar_withhold_next_small_vmm(int turns);
 
 /*
+ * Instrumentation for tests (no part of the method): driven rows of a crossbar that one block of xbar_fcm_profile solves, the first
+ * of them without what the others take over from it; 0 for arrays that are not 64 x 64 or 128 x 128, or what validation refuses.
+ */
+int xbar_fcm_rows_per_block(const xbar_config* cfg, int K, int N);
+
+/*
  * Instrumentation for the benchmark (no part of the method): enqueues a kernel that does nothing but
  * dependent-chain fp16 matrix instructions (the instruction the contraction uses, v_mfma_f32_32x32x16_f16)
  * on register-resident operands, 2 waves per SIMD on every CU, so that the caller can time the matrix

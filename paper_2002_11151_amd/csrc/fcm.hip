@@ -238,6 +238,11 @@ __global__ __launch_bounds__(256) void fcm_kernel(FcmArgs a) {
 // once at the end.  One that misses the tolerance is finished by conjugate gradients, and the next starts anew.  (On the CPU,
 // 128 x 128 devices at 1e-11: as many iterations as conjugate gradients of its own or one more, for Rmin of 1e3 .. 1e5 Ohm, 10 %
 // variation, ragged tiles.)
+// The polynomial is small on what the first solve drives and nowhere else.  Where the rows see little of each other (no column wires,
+// say) and the first one is all off, it multiplies the others' residuals by up to 1e20, and since the residual is the recurrence's own,
+// which does not see what was rounded on the way, a solve that went through such values must not be finished, whatever it ends at.  So
+// every solve watches how far its voltages swing (`swing`), and one beyond kMaxSwing is thrown away, as is one that hardly shrank its
+// residual: conjugate gradients of its own then give the next rows' coefficients.  After the second a block shares nothing any more.
 // What bounds it: the issue of vector instructions, 770 per thread and iteration of 32 devices (353 the recurrences at 11 per
 // device, the rest sums across lanes and waves), some 70 % of the time.  784 x 500 layer of the 784-500-10 perceptron (128 x 128
 // arrays, 4 slices): 5.1 -> 3.4 ms against scalar products in every iteration (1130 instructions, four barriers for two, 15 of
@@ -302,6 +307,11 @@ __device__ __forceinline__ double block_sum_n(double v, double* red) {
   for (int w = 0; w < NW; ++w) t += red[w];
   return t;
 }
+
+// The driven row is at 1 V, and wires take no more than that off it: solves that share well swing by 0.1 .. 30 V (128 x 128 and
+// 64 x 64 devices of 100 Ohm .. 100 kOhm, on the CPU), those that must not by 1e2 .. 1e20.  A thousand cost the result 1e-13 of the
+// conductances around the row.
+constexpr double kMaxSwing = 1e3;
 
 template <int SR, int SC, int NT>
 struct FcmShape {
@@ -378,10 +388,10 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
     }
   }
 
-  int steps = 0;                                     // coefficients known
+  int steps = 0, discarded = 0;                      // coefficients known; solves that they did not fit
   for (int rhs = rhs_begin; rhs < rhs_end; ++rhs) {
     double u[SR][SC], w[SR][SC], e = 0.0;            // e: solution summed over column tid % C
-    double beta = 0.0, alpha = 0.0, part = 0.0;
+    double beta = 0.0, alpha = 0.0, part = 0.0, swing = 0.0;
     // v^2 / g; a device that is not there has v = 0.  The instruction's reciprocal is good to 2^-26 or so: scalar products that
     // choose a step and a stop need no more
     auto over_g = [&](double v, double g) __attribute__((always_inline)) { return v * v * __builtin_amdgcn_rcp(::fmax(g, 1e-300)); };
@@ -502,6 +512,7 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
         part = 0.0;
       }
       // u <- u - alpha A w
+      double high = 0.0;
 #pragma unroll
       for (int bc = 0; bc < SC; ++bc) {
         double above, below1, all;
@@ -516,43 +527,60 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
           row0[ar] = __builtin_fma(-a.r_row, w[ar][bc], row0[ar]);
           lc += pre;
           pre = __builtin_fma(-a.r_col, w[ar][bc], pre);
-          const double q = __builtin_fma(g, row1[ar] + lc, w[ar][bc]);
+          const double drop = row1[ar] + lc, q = __builtin_fma(g, drop, w[ar][bc]);
           u[ar][bc] = __builtin_fma(-alpha, q, u[ar][bc]);
+          // What a solve amplifies is smooth along the wires, so one device of a patch per column is looked at, which are one
+          // or two per row.  All of them: 4 % of the instructions, not 1
+          if constexpr (!CG) {
+            if (bc * SR / SC == ar) high = ::fmax(high, ::fabs(drop));
+          }
           if constexpr (CG) part += over_g(u[ar][bc], g);
           pin(u[ar][bc], row0[ar], row1[ar]);
           if constexpr (CG) pin(part, lc, pre);
         }
       }
       e = __builtin_fma(alpha, total[tid & (C - 1)], e);   // column sum of x = sum alpha w
+      if constexpr (!CG) swing = ::fmax(swing, ::fabs(alpha) * high);
     };
 
-    double b2 = 0.0;                                 // square of the right-hand side S v
+    // The right-hand side S v, solved so far: nothing.  Returns this thread's share of its square.
+    auto begin = [&]() __attribute__((always_inline)) {
+      double b2 = 0.0;
 #pragma unroll
-    for (int ar = 0; ar < SR; ++ar)
+      for (int ar = 0; ar < SR; ++ar)
 #pragma unroll
-      for (int bc = 0; bc < SC; ++bc) {
-        u[ar][bc] = (i0 + ar == rhs) ? g_of(ar * SC + bc) : 0.0;
-        w[ar][bc] = 0.0;
-        b2 += u[ar][bc];
-      }
-    double rr = block_sum_n<NW>(b2, red + NW);
-    const double stop = a.tol2 * rr;
-    const bool known = steps > 0;
+        for (int bc = 0; bc < SC; ++bc) {
+          u[ar][bc] = (i0 + ar == rhs) ? g_of(ar * SC + bc) : 0.0;
+          w[ar][bc] = 0.0;
+          b2 += u[ar][bc];
+        }
+      beta = e = 0.0;
+      return b2;
+    };
+    double rr = block_sum_n<NW>(begin(), red + NW);
+    const double b2 = rr, stop = a.tol2 * rr;
+    bool known = steps > 0;
     if (known) {
       for (int it = 0; it < steps; ++it) {
         alpha = coef[it];
         beta = coef[kSteps + it];
         iterate(std::false_type{}, it == 0, 0.0);
       }
-      part = 0.0;
+      part = swing <= kMaxSwing ? 0.0 : INFINITY;    // (a NaN in the voltages is one in u)
 #pragma unroll
       for (int ar = 0; ar < SR; ++ar)
 #pragma unroll
         for (int bc = 0; bc < SC; ++bc) part += over_g(u[ar][bc], g_of(ar * SC + bc));
       rr = block_sum_n<NW>(part, red);
       beta = 0.0;
+      if (!(rr <= 1e-6 * b2)) {                      // also an infinity or a NaN
+        known = false;
+        ++discarded;
+        begin();
+        rr = b2;
+      }
     }
-    // conjugate gradients: all of the first solve, what a later one may have left
+    // conjugate gradients: all of a solve of its own, what the coefficients may have left of another
     const double goal = known ? stop : 0.25 * stop;
     int it = 0;
     for (; it < a.max_iter && rr > goal; ++it) {
@@ -566,7 +594,7 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
       rr = rr_new;
     }
     // a solve that missed the tolerance drives what the first one hardly did (a row of off-state devices, say): the next starts anew
-    steps = known ? (it > 0 ? 0 : steps) : it <= kSteps ? it : 0;
+    steps = known ? (it > 0 ? 0 : steps) : it <= kSteps && discarded < 2 ? it : 0;
     if (tid < C) sums[tid] = e;                      // the sums of the last iteration have been read: two barriers ago at least
     __syncthreads();
     if (rhs >= i0 && rhs < i0 + SR) {
@@ -583,21 +611,14 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
   }
 }
 
-// False: no such LDS size on this device.  PER_CU: blocks that a compute unit holds.  The driven rows of a crossbar are split over
-// several blocks, as many as fill the chip evenly: every block sets its devices up and has one solve without known coefficients,
-// together worth about kSetupRows rows.
+// The driven rows of a crossbar are split over several blocks, as many as fill the chip (`slots` blocks at a time) evenly: every block
+// sets its devices up and has one solve without known coefficients, together worth about kSetupRows rows.
 constexpr double kSetupRows = 1.2;
-template <int SR, int SC, int NT, int PER_CU>
-bool launch_onchip(FcmArgs a, hipStream_t st) {
-  constexpr int lds_bytes = (int)FcmShape<SR, SC, NT>::kLdsBytes, slots = 256 * PER_CU;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&fcm_onchip_kernel<SR, SC, NT>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          lds_bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
+int rows_per_block(const FcmArgs& a, int slots) {
   // Whole tiles' blocks come first and take so many rounds over the chip; the last tile row's rows fill the last round's gaps
   const int tiles_r = cdiv(a.K, a.R), sets = a.tiles_c * a.S_w * 2, last = a.K - (tiles_r - 1) * a.R;
   double best = 0.0;
+  int rows = 1;
   for (int g = 1; g <= a.R; ++g) {
     const int per = cdiv(a.R, g);
     const double whole = kSetupRows + per, part = kSetupRows + std::min(per, last);
@@ -607,11 +628,26 @@ bool launch_onchip(FcmArgs a, hipStream_t st) {
     const double cost = (rounds + (rest ? 1 : 0)) * whole + (double)((more + slots - 1) / slots) * part;
     if (g == 1 || cost < best) {
       best = cost;
-      a.rhs_per_group = per;
+      rows = per;
     }
   }
+  return rows;
+}
+constexpr int kSlots128 = 256, kSlots64 = 256 * 3;   // blocks that the chip holds
+
+// False: no such LDS size on this device.
+template <int SR, int SC, int NT>
+bool launch_onchip(FcmArgs a, int slots, hipStream_t st) {
+  constexpr int lds_bytes = (int)FcmShape<SR, SC, NT>::kLdsBytes;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&fcm_onchip_kernel<SR, SC, NT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          lds_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  a.rhs_per_group = rows_per_block(a, slots);
   a.groups = cdiv(a.R, a.rhs_per_group);
-  hipLaunchKernelGGL((fcm_onchip_kernel<SR, SC, NT>), dim3((unsigned)(tiles_r * sets * a.groups)), dim3(NT), lds_bytes, st, a);
+  const unsigned blocks = (unsigned)(cdiv(a.K, a.R) * a.tiles_c * a.S_w * 2 * a.groups);
+  hipLaunchKernelGGL((fcm_onchip_kernel<SR, SC, NT>), dim3(blocks), dim3(NT), lds_bytes, st, a);
   return true;
 }
 
@@ -670,11 +706,20 @@ int xbar_fcm_profile(const xbar_config* cfg, const float* W, int K, int N, float
   a.tol2 = 1e-22;                                   // relative residual 1e-11
   a.w_max = w_max; a.seed = cfg->seed; a.step = step; a.step_add = current_step_source();
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  if (p.onchip == 128 ? launch_onchip<4, 8, 512, 1>(a, st) : p.onchip == 64 && launch_onchip<4, 4, 256, 3>(a, st))
+  if (p.onchip == 128 ? launch_onchip<4, 8, 512>(a, kSlots128, st) : p.onchip == 64 && launch_onchip<4, 4, 256>(a, kSlots64, st))
     return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
   hipLaunchKernelGGL(fcm_kernel, dim3((unsigned)p.blocks), dim3(256), 0, st, a);
   if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
   return XBAR_OK;
+}
+
+int xbar_fcm_rows_per_block(const xbar_config* cfg, int K, int N) {
+  if (xbar_config_validate(cfg) || check_shape(1, K, N)) return 0;
+  const Derived d = derive(cfg);
+  const int onchip = plan_fcm(cfg, d, K, N).onchip;
+  FcmArgs a = {};
+  a.K = K; a.R = cfg->xbar_rows; a.S_w = d.S_w; a.tiles_c = cdiv(N, cfg->xbar_cols);
+  return onchip ? rows_per_block(a, onchip == 128 ? kSlots128 : kSlots64) : 0;
 }
 
 }  // extern "C"

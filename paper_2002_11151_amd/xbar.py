@@ -96,6 +96,7 @@ _SIGNATURES = {
     "xbar_pulse_slots": (C.c_int, [C.POINTER(Config), C.c_int]),
     "xbar_trace_next_vmm": (None, [C.c_void_p, C.c_void_p]),
     "xbar_withhold_next_small_vmm": (None, [C.c_int]),
+    "xbar_fcm_rows_per_block": (C.c_int, [C.POINTER(Config), C.c_int, C.c_int]),
     "xbar_set_step_source": (None, [C.c_void_p]),
     "xbar_step_advance": (C.c_int, [C.c_void_p, C.c_void_p]),
     "xbar_probe_mfma_rate": (C.c_int, [C.c_int, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]),

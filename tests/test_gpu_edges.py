@@ -294,6 +294,30 @@ def test_circuit_model_with_shared_coefficients(xo, xb, R, K, N, r_min, off):
     assert np.abs(Dg - fcm.fcm_profile(co, W, w_max, step=1)).max() <= 2e-7
 
 
+# ... and rows that see nothing of each other (no column wires), the first one of every block all off: its coefficients multiply the
+# others' residuals by up to 1e20.  Each row is a system of its own.  (A profile of 64-bit sums, stored in single precision)
+@pytest.mark.parametrize("R,r_min,r_row,r_source", [(128, 1e3, 4.6, 0.0), (128, 1e2, 1.0, 0.0), (64, 1e2, 4.6, 2.0), (64, 1e2, 10.0, 2.0),
+                                                    (64, 1e4, 4.6, 2.0)])
+def test_circuit_model_of_rows_apart(xo, xb, R, r_min, r_row, r_source):
+    co, cg = both_configs(xo, xb, xbar_rows=R, xbar_cols=R, weight_bits=16, slice_bits=2, flags=0, r_min=r_min, r_max=10 * r_min,
+                          r_row=r_row, r_col=0.0, r_source=r_source, r_sense=0.0)
+    K, N = R, 2 * R
+    W, _, _ = workloads.layer_tensors_np(workloads.Gemm("t", K, N, 1, True, 1), seed=R)
+    w_max = float(np.abs(W).max())
+    rows = xb.lib().xbar_fcm_rows_per_block(cg, K, N)
+    assert rows >= 2
+    W[::rows] = 0.0
+    Dg = xb.fcm_profile(cg, dev(W), w_max, step=1).cpu().numpy()
+    G = xo.device_conductances(co, W, w_max, 1)
+    wires = r_source + r_row * (np.minimum.outer(np.arange(R), np.arange(R)) + 1.0)
+    want = np.empty_like(G)
+    for n0 in (0, R):
+        g = G[..., n0:n0 + R]
+        x = np.linalg.solve(np.eye(R) / g[..., None] + wires, np.ones(g.shape + (1,)))[..., 0]
+        want[..., n0:n0 + R] = (g - x) / g
+    assert np.abs(Dg - want).max() <= 2e-7
+
+
 # One kernel for a whole pass (layers of few patches): its outputs are those of the chunked kernels, which the code tap
 # runs, bit for bit -- one row, patches plus and minus one, slices that do not fill a block's waves, arrays of 16 .. 256
 # rows, one and several blocks per patch, sums within and beyond 32 bits, every way of coding inputs and reading arrays
