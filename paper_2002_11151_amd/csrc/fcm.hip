@@ -235,7 +235,10 @@ __global__ __launch_bounds__(256) void fcm_kernel(FcmArgs a) {
 // The driven rows of a crossbar differ in the right-hand side alone and excite much the same part of the spectrum, so only a
 // block's first solve works out alpha and beta (conjugate gradients, stopped at half the tolerance); the others run the same
 // coefficients -- a fixed polynomial in the matrix -- without the scalar products and their barriers, and measure the residual
-// once at the end.  One that misses the tolerance is finished by conjugate gradients, and the next starts anew.  (On the CPU,
+// once at the end.  Conjugate gradients run on the voltages u / G and w / G, which makes w.w / G and u.u / G products of the two: full
+// precision and no reciprocal per device (with the instruction's 24 bits instead, on currents: 784 x 500 weights at 100 Ohm, where
+// no solve shares, 98.3 ms against 81.0).
+// One that misses the tolerance is finished by conjugate gradients, and the next starts anew.  (On the CPU,
 // 128 x 128 devices at 1e-11: as many iterations as conjugate gradients of its own or one more, for Rmin of 1e3 .. 1e5 Ohm, 10 %
 // variation, ragged tiles.)
 // The polynomial is small on what the first solve drives and nowhere else.  Where the rows see little of each other (no column wires,
@@ -392,12 +395,10 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
   for (int rhs = rhs_begin; rhs < rhs_end; ++rhs) {
     double u[SR][SC], w[SR][SC], e = 0.0;            // e: solution summed over column tid % C
     double beta = 0.0, alpha = 0.0, part = 0.0, swing = 0.0;
-    // v^2 / g; a device that is not there has v = 0.  The instruction's reciprocal is good to 2^-26 or so: scalar products that
-    // choose a step and a stop need no more
-    auto over_g = [&](double v, double g) __attribute__((always_inline)) { return v * v * __builtin_amdgcn_rcp(::fmax(g, 1e-300)); };
     // Computed here: left alone, the compiler moves the arithmetic behind the next branch and keeps all that it waits for
     auto pin = [](double& x, double& y, double& z) __attribute__((always_inline)) { asm volatile("" : "+v"(x), "+v"(y), "+v"(z)); };
-    // One iteration; CG: alpha from w.A w and, in `part`, the square of what is left.  `first`: w is 0 outside the driven row.
+    // One iteration; CG: on u / G and w / G, alpha from w.A w and, in `part`, the square of what is left.  `first`: w is 0 outside
+    // the driven row.
     auto iterate = [&](auto is_cg, bool first, double rr) __attribute__((always_inline)) {
       constexpr bool CG = decltype(is_cg)::value;
       // Column by column in both passes: two running sums per row, those of one column at a time.  (Row by row the running sums
@@ -413,12 +414,13 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
 #pragma unroll
           for (int ar = 0; ar < SR; ++ar) {
             w[ar][bc] = __builtin_fma(beta, w[ar][bc], u[ar][bc]);
-            row0[ar] = bc == SC - 1 ? w[ar][bc] : row0[ar] + w[ar][bc];   // no sums that begin with 0: they are not free
+            const double current = CG ? g_of(ar * SC + bc) * w[ar][bc] : w[ar][bc];
+            row0[ar] = bc == SC - 1 ? current : row0[ar] + current;       // no sums that begin with 0: they are not free
             row1[ar] = bc == SC - 1 ? row0[ar] : row1[ar] + row0[ar];
-            run = ar == 0 ? w[ar][bc] : run + w[ar][bc];
+            run = ar == 0 ? current : run + current;
             runs = ar == 0 ? run : runs + run;
             if constexpr (CG) {
-              pq += over_g(w[ar][bc], g_of(ar * SC + bc));
+              pq = __builtin_fma(current, w[ar][bc], pq);
               row_sq = __builtin_fma(row0[ar], row0[ar], row_sq);
               col_sq = __builtin_fma(run, run, col_sq);
               pin(pq, row_sq, col_sq);
@@ -522,19 +524,19 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
         double pre = a.r_col * last, lc = __builtin_fma(a.r_col, __builtin_fma((double)(R - SR - i0), last, below1), a.r_sense * all);
 #pragma unroll
         for (int ar = SR - 1; ar >= 0; --ar) {
-          const double g = g_of(ar * SC + bc);
+          const double g = g_of(ar * SC + bc), current = CG ? g * w[ar][bc] : w[ar][bc];
           row1[ar] += row0[ar];
-          row0[ar] = __builtin_fma(-a.r_row, w[ar][bc], row0[ar]);
+          row0[ar] = __builtin_fma(-a.r_row, current, row0[ar]);
           lc += pre;
-          pre = __builtin_fma(-a.r_col, w[ar][bc], pre);
-          const double drop = row1[ar] + lc, q = __builtin_fma(g, drop, w[ar][bc]);
+          pre = __builtin_fma(-a.r_col, current, pre);
+          const double drop = row1[ar] + lc, q = CG ? w[ar][bc] + drop : __builtin_fma(g, drop, w[ar][bc]);
           u[ar][bc] = __builtin_fma(-alpha, q, u[ar][bc]);
           // What a solve amplifies is smooth along the wires, so one device of a patch per column is looked at, which are one
           // or two per row.  All of them: 4 % of the instructions, not 1
           if constexpr (!CG) {
             if (bc * SR / SC == ar) high = ::fmax(high, ::fabs(drop));
           }
-          if constexpr (CG) part += over_g(u[ar][bc], g);
+          if constexpr (CG) part = __builtin_fma(g * u[ar][bc], u[ar][bc], part);
           pin(u[ar][bc], row0[ar], row1[ar]);
           if constexpr (CG) pin(part, lc, pre);
         }
@@ -543,22 +545,18 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
       if constexpr (!CG) swing = ::fmax(swing, ::fabs(alpha) * high);
     };
 
-    // The right-hand side S v, solved so far: nothing.  Returns this thread's share of its square.
-    auto begin = [&]() __attribute__((always_inline)) {
-      double b2 = 0.0;
+    double b2 = 0.0;                                 // square of the right-hand side S v
 #pragma unroll
-      for (int ar = 0; ar < SR; ++ar)
+    for (int ar = 0; ar < SR; ++ar)
 #pragma unroll
-        for (int bc = 0; bc < SC; ++bc) {
-          u[ar][bc] = (i0 + ar == rhs) ? g_of(ar * SC + bc) : 0.0;
-          w[ar][bc] = 0.0;
-          b2 += u[ar][bc];
-        }
-      beta = e = 0.0;
-      return b2;
-    };
-    double rr = block_sum_n<NW>(begin(), red + NW);
-    const double b2 = rr, stop = a.tol2 * rr;
+      for (int bc = 0; bc < SC; ++bc) {
+        u[ar][bc] = (i0 + ar == rhs) ? g_of(ar * SC + bc) : 0.0;
+        w[ar][bc] = 0.0;
+        b2 += u[ar][bc];
+      }
+    b2 = block_sum_n<NW>(b2, red + NW);
+    const double stop = a.tol2 * b2;
+    double rr = b2;
     bool known = steps > 0;
     if (known) {
       for (int it = 0; it < steps; ++it) {
@@ -566,19 +564,42 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
         beta = coef[kSteps + it];
         iterate(std::false_type{}, it == 0, 0.0);
       }
+      // An upper bound of the residual first: the instruction's reciprocal is good to 2^29 units in the last place by the documents of
+      // the instruction set, 2^-23 (2^-24.4 measured), and only what it clears is done.  (By division 4 % of a solve of eight iterations.)
       part = swing <= kMaxSwing ? 0.0 : INFINITY;    // (a NaN in the voltages is one in u)
 #pragma unroll
       for (int ar = 0; ar < SR; ++ar)
 #pragma unroll
-        for (int bc = 0; bc < SC; ++bc) part += over_g(u[ar][bc], g_of(ar * SC + bc));
-      rr = block_sum_n<NW>(part, red);
-      beta = 0.0;
+        for (int bc = 0; bc < SC; ++bc)              // a device that is not there has u = 0
+          part = __builtin_fma(u[ar][bc] * __builtin_amdgcn_rcp(::fmax(g_of(ar * SC + bc), 1e-300)), u[ar][bc], part);
+      rr = (1.0 + 0x1p-20) * block_sum_n<NW>(part, red);
       if (!(rr <= 1e-6 * b2)) {                      // also an infinity or a NaN
         known = false;
         ++discarded;
-        begin();
-        rr = b2;
+      } else if (rr > stop) {                        // conjugate gradients from here, on u / G (w counts for nothing: beta is 0)
+        part = 0.0;
+#pragma unroll
+        for (int ar = 0; ar < SR; ++ar)
+#pragma unroll
+          for (int bc = 0; bc < SC; ++bc) {
+            const double g = g_of(ar * SC + bc), left = g > 0.0 ? u[ar][bc] / g : 0.0;
+            part = __builtin_fma(left, u[ar][bc], part);
+            u[ar][bc] = left;
+          }
+        rr = block_sum_n<NW>(part, red + NW);
+        beta = 0.0;
       }
+    }
+    if (!known) {                                    // from the start: u / G is v
+#pragma unroll
+      for (int ar = 0; ar < SR; ++ar)
+#pragma unroll
+        for (int bc = 0; bc < SC; ++bc) {
+          u[ar][bc] = (i0 + ar == rhs) ? 1.0 : 0.0;
+          w[ar][bc] = 0.0;
+        }
+      beta = e = 0.0;
+      rr = b2;
     }
     // conjugate gradients: all of a solve of its own, what the coefficients may have left of another
     const double goal = known ? stop : 0.25 * stop;

@@ -275,21 +275,21 @@ def test_circuit_model_on_chip(xo, xb, R, K, N, r_min):
     assert np.abs(Dg.cpu().numpy() - fcm.fcm_profile(co, W, w_max, step=1)).max() <= 2e-7
 
 
-# ... solves that take over the coefficients of a block's first one: every fourth row or all but one device of the first off, so that
-# the first solve hardly sees what the others do; more iterations than coefficients are kept (64 x 64 arrays, 100 Ohm); several
-# blocks per array and several rounds of blocks
-@pytest.mark.parametrize("R,K,N,r_min,off", [(64, 70, 64, 1e2, "rows"), (64, 64, 40, 1e3, "device"), (128, 128, 128, 1e2, "rows"),
-                                             (128, 150, 128, 1e3, "device"), (128, 140, 30, 1e5, "rows"), (64, 300, 200, 1e4, "rows")])
-def test_circuit_model_with_shared_coefficients(xo, xb, R, K, N, r_min, off):
+# ... solves that take over the coefficients of a block's first one: the first row of every block, or all but one device of it, off, so
+# that the first solve hardly sees what the others do; two and many rows to a block; at 100 Ohm more iterations than coefficients are
+# kept, at 1 kOhm just about as many
+@pytest.mark.parametrize("R,K,N,wb,r_min,off", [(64, 64, 40, 16, 1e2, "rows"), (64, 64, 64, 16, 1e3, "device"), (64, 300, 200, 2, 1e4, "rows"),
+                                                (64, 128, 128, 16, 1e3, "rows"), (128, 150, 128, 2, 1e3, "device"), (128, 140, 30, 2, 1e5, "rows"),
+                                                (128, 128, 20, 8, 1e2, "rows"), (128, 128, 20, 16, 1e4, "device")])
+def test_circuit_model_with_shared_coefficients(xo, xb, R, K, N, wb, r_min, off):
     from oracle import fcm
     W, _, _ = workloads.layer_tensors_np(workloads.Gemm("t", K, N, 1, True, 1), seed=K + N)
     w_max = float(np.abs(W).max())
-    if off == "rows":
-        W[::4] = 0.0
-    else:
-        W[::R // 4, 1:] = 0.0
-    co, cg = both_configs(xo, xb, xbar_rows=R, xbar_cols=R, weight_bits=2, slice_bits=2, flags=0, r_min=r_min, r_max=10 * r_min,
+    co, cg = both_configs(xo, xb, xbar_rows=R, xbar_cols=R, weight_bits=wb, slice_bits=2, flags=0, r_min=r_min, r_max=10 * r_min,
                           r_source=2.0, r_sense=3.0)
+    rows = xb.lib().xbar_fcm_rows_per_block(cg, K, N)
+    assert rows >= 2
+    W[::rows, (0 if off == "rows" else 1):] = 0.0
     Dg = xb.fcm_profile(cg, dev(W), w_max, step=1).cpu().numpy()
     assert np.abs(Dg - fcm.fcm_profile(co, W, w_max, step=1)).max() <= 2e-7
 
