@@ -389,26 +389,43 @@ __global__ __launch_bounds__(256) void pulse_walk_kernel(PulseArgs a) {
 // The streamed walk: a block has one wave that walks and, for each of its devices, one that feeds it.  Only the moves of a
 // device are sequential; which samples it is pulsed in, the trains and the normal numbers of its pulses are not.  A feeding
 // wave lists its device's marked samples (ring in LDS), fetches the trains of 64 of them side by side, lists their pulses (a
-// second ring) and evaluates 64 normal numbers side by side; the walking wave, a lane per device, takes the 64 moves before
-// while the next ones are made.  One barrier per 64 pulses of every device hands them over.  Without marks (MARKED false: too
-// few samples for a marking pass to pay) a feeding wave takes the trains of 256 samples at a time, marked or not.
-// What bounds it: few devices, the walk's chain of dependent double-precision operations beside the latency of the lists;
-// many, the normal numbers (some 300 instructions per 64 pulses).  Whole update of 144 x 16 devices and 131072 samples, series
-// and noise: 1669 -> 894 us (300 of it trains, 96 marks) against 64 lanes per device that all ran through every move; 27 x 16 506 ->
-// 300, 576 x 64 and 8192 samples 1151 -> 765.
+// second ring) and makes a batch of moves of them; the walking wave, a lane per device, takes the batch before while the next
+// is made.  One barrier per batch of every device hands them over.  Without marks (MARKED false: too few samples for a marking pass
+// to pay) a feeding wave takes the trains of 256 samples at a time, marked or not.
+// What bounds it: few devices, the instructions of the walking wave, each of which takes it 8 to 10 cycles (so its moves are
+// read two groups at a time, without copies, in a scalar loop where all devices are full); many, with noise the normal numbers (some
+// 300 instructions per 64 pulses), without it the lists.  64 registers, for two blocks to a compute unit.
+// ms of a whole update, series, trains of 12 pulses a sample / of one in 30 samples, against one to four devices per wave that all its
+// lanes walk (or above 20480 devices, 40960 with noise, a lane per device that does everything by itself): 144 x 16 devices, 32768
+// samples 51.0 -> 20.4 / 2.97 -> 1.43, with noise 60.6 -> 30.8 / 3.46 -> 2.10; 27 x 16 x 32768 22.9 -> 18.0 / 1.49 -> 0.98; 128 x 128 x 4096 14.1 ->
+// 10.2 / 1.06 -> 0.88; 576 x 64 x 4096 24.3 -> 14.8 / 1.76 -> 1.37, with noise 45.7 -> 41.2 / 3.04 -> 2.65.  A pulse handed over as a double
+// and a noise also without noise, out of rings of 256: 576 x 64, linear 22.6 / 1.17, now 7.1 / 0.95.
 // NL: 0 linear device; 1 write non-linearity by its power series about mid-range (v <= 1/32: six powers leave less than 1e-18
 // of exp(-v y) on 0 <= y <= 1); 2 by exp().
 // With the series an upward pulse moves the state g by dw_min exp(-v (1 + g) / 2), a downward one back by dw_min exp(-v (1 - g) / 2),
 // that is by direction times the even powers of g plus the odd ones as they are.  A move is complete, noise included, before it
 // joins the state, which is rounded once per pulse: 2.4e-16 rms after 200 pulses against 113-bit arithmetic (noise joining the state
 // by itself: 3.5e-16; a state held on 0 .. 1, which the last operation could clamp by itself: 1.2e-15).
-constexpr int kStreamRing = 256;                     // entries of a ring: fewer than 64 waiting, plus what a fetch brings
-constexpr int kStreamMoves = 65;                     // moves of a device and batch, one more to spread the devices over the banks
 constexpr int kStreamMaxDevices = 15;                // per block: 16 waves
-
-constexpr size_t stream_lds_bytes(int devices) {
-  return (size_t)devices * (2 * kStreamMoves * sizeof(double2) + 2 * kStreamRing * sizeof(uint32_t)) + 2 * 16 * sizeof(int) + 2 * sizeof(int);
-}
+constexpr int kSampleRing = 256;                     // marked samples of a device: up to 127 wait, and a word of 64 fits beside them
+                                                     //   (what does not fit is fetched again)
+// What a feeding wave hands over.  With noise 64 moves, each a noise and a direction, out of a ring of pulses: up to 127 wait, and those
+// of 64 samples with 14 each fit beside them, so that the 31 turns of the list that makes them are shared by as many (the rest
+// is fetched again).  Without noise a pulse is its direction: 128 of them out of a ring of bits (1 downwards), which always has room
+// for 64 samples beside the 255 pulses that wait; a sample sets all of its bits at once, and its device's wave spreads them, so
+// that the walking wave has a load for two moves and nothing else but the moves.
+template <bool NOISE>
+struct Stream {
+  using Move = std::conditional_t<NOISE, double2, double>;       // noise and direction, or the direction
+  static constexpr int kBatch = NOISE ? 64 : 128;
+  static constexpr int kGroup = NOISE ? 4 : 8;                   // moves that the walking wave reads together
+  static constexpr int kStride = kBatch + (NOISE ? 1 : 2);       // spreads the devices over the banks
+  static constexpr int kRoom = NOISE ? 1024 : 4096;              // pulses that the ring holds
+  static constexpr int kRingWords = NOISE ? kRoom : kRoom / 32;
+  static constexpr size_t lds_bytes(int devices) {
+    return (size_t)devices * (2 * kStride * sizeof(Move) + (kSampleRing + kRingWords) * sizeof(uint32_t)) + 2 * 16 * sizeof(int) + 2 * sizeof(int);
+  }
+};
 
 // Inclusive sum over the lanes of a wave: DPP row shifts by 1, 2, 4 and 8, then the last lane of a row or half to the rows behind.
 __device__ __forceinline__ int wave_scan(int v) {
@@ -422,12 +439,15 @@ __device__ __forceinline__ int wave_scan(int v) {
 }
 
 template <int NL, bool NOISE, bool MARKED>
-__global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int devices) {
+__global__ __launch_bounds__(1024, 8) void pulse_stream_kernel(PulseArgs a, int devices) {
 #pragma clang fp contract(off)
   extern __shared__ __align__(16) char stream_lds[];
-  double2* moves = reinterpret_cast<double2*>(stream_lds);      // [2][devices][kStreamMoves]: noise, direction (half of it: linear, exp())
-  uint32_t* rings = reinterpret_cast<uint32_t*>(moves + 2 * devices * kStreamMoves);   // [devices][samples, pulses][kStreamRing]
-  int* runs = reinterpret_cast<int*>(rings + devices * 2 * kStreamRing);               // [2][16] moves of a device in a batch
+  using S = Stream<NOISE>;
+  // a direction: dw_min of a linear device, 1 with the series, a half with exp(), or less than 0 by as much
+  using Move = typename S::Move;
+  Move* moves = reinterpret_cast<Move*>(stream_lds);            // [2][devices][kStride]
+  uint32_t* rings = reinterpret_cast<uint32_t*>(moves + 2 * devices * S::kStride);     // [devices][samples, then pulses]
+  int* runs = reinterpret_cast<int*>(rings + devices * (kSampleRing + S::kRingWords)); // [2][16] moves of a device in a batch
   int* alive = runs + 2 * 16;                                   // [2] batch number + 1 where a device had moves in it
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const size_t kn = (size_t)a.K * a.N, dev0 = (size_t)blockIdx.x * devices;
@@ -438,54 +458,68 @@ __global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int dev
     __builtin_amdgcn_s_setprio(3);                   // the chain: what feeds it has time
     const bool valid = lane < devices && dev0 + lane < kn;
     const size_t dev = valid ? dev0 + lane : kn - 1;
-    const double2* mine = moves + min(lane, devices - 1) * kStreamMoves;
     auto begin = [&]() __attribute__((always_inline)) { return a.first ? (double)a.W[dev] / a.w_max : a.state[dev]; };
     double g = begin();
     double gx = clampd(g, -1.0, 1.0);                // where the non-linearity finds the state
     bool pulsed = false;
     const double up_down = 2.0 * a.dw_min;
-    auto move = [&](const double2 b) __attribute__((always_inline)) {
-      double next;
+    auto move = [&](const Move b) __attribute__((always_inline)) {      // the state after it
+      double next, direction, noise = 0.0;
+      if constexpr (NOISE) direction = b.y, noise = b.x;
+      else direction = b;
       if constexpr (NL == 1) {
         const double z = gx * gx, zz = z * z;
         const double odd = __builtin_fma(zz, a.series[5], __builtin_fma(z, a.series[3], a.series[1]));
         const double even = __builtin_fma(zz, __builtin_fma(z, a.series[6], a.series[4]), __builtin_fma(z, a.series[2], a.series[0]));
-        const double directed = NOISE ? __builtin_fma(b.y, even, b.x) : b.y * even;
+        const double directed = NOISE ? __builtin_fma(direction, even, noise) : direction * even;
         next = g + __builtin_fma(gx, odd, directed);
       } else {
-        const double step = b.y * up_down;
-        if constexpr (NL == 0) next = g + step;
-        else next = g + step * ::exp(-a.v * __builtin_fma(b.y, gx, 0.5));   // x upwards, 1 - x downwards
-        if constexpr (NOISE) next += b.x;
+        if constexpr (NL == 0) next = g + direction;
+        else next = g + direction * up_down * ::exp(-a.v * __builtin_fma(direction, gx, 0.5));   // x upwards, 1 - x downwards
+        if constexpr (NOISE) next += noise;
       }
       return ::fmin(::fmax(next, -1.0), 1.0);
     };
     for (int batch = 0;; ++batch) {
       if (batch > 0) {                               // the moves before, while the next ones are made
-        const double2* mv = mine + ((batch - 1) & 1) * devices * kStreamMoves;
         const int run = valid ? runs[((batch - 1) & 1) * 16 + lane] : 0;
         pulsed = pulsed || run > 0;
-        auto walk = [&](auto partial) __attribute__((always_inline)) {
-          double2 b[8], ahead[8];
+        const Move* mv = moves + (((batch - 1) & 1) * devices + min(lane, devices - 1)) * S::kStride;
+        // Two groups of moves in registers, one read under the moves of the other
+        constexpr int G = S::kGroup;
+        Move one[G], other[G];
+        auto load = [&](Move (&group)[G], int t) __attribute__((always_inline)) {
+          const int from = min(t, S::kBatch - G);
 #pragma unroll
-          for (int t = 0; t < 8; ++t) ahead[t] = mv[t];
-#pragma unroll 1
-          for (int t0 = 0; t0 < 64; t0 += 8) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) b[t] = ahead[t];
-            const int behind = min(t0 + 8, 56);      // read under this turn's moves
-#pragma unroll
-            for (int t = 0; t < 8; ++t) ahead[t] = mv[behind + t];
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-              const double next = move(b[t]);
-              if (decltype(partial)::value && t0 + t >= run) continue;   // a device without a pulse keeps its state, also beyond the range
-              g = gx = next;
-            }
-          }
+          for (int i = 0; i < G; ++i) group[i] = mv[from + i];
+          __builtin_amdgcn_sched_barrier(0);         // here, not where the first of them is needed
         };
-        if (__any(valid && run < 64)) walk(std::true_type{});
-        else walk(std::false_type{});
+        load(one, 0);
+        auto two_groups = [&](int t0) __attribute__((always_inline)) {
+          load(other, t0 + G);
+#pragma unroll
+          for (int t = 0; t < G; ++t) g = gx = move(one[t]);
+          load(one, t0 + 2 * G);
+#pragma unroll
+          for (int t = 0; t < G; ++t) g = gx = move(other[t]);
+        };
+        int t0 = 0;
+        if (__all(!valid || run == S::kBatch)) {     // a scalar loop: a move of 50 cycles is 5 shorter
+#pragma unroll 1
+          for (int t = 0; t < S::kBatch; t += 2 * G) two_groups(t);
+          t0 = S::kBatch;
+        } else {
+#pragma unroll 1
+          for (; t0 + 2 * G <= run; t0 += 2 * G) two_groups(t0);         // lanes that have run out wait
+        }
+        if (__any(t0 < run)) {                       // a device without a pulse keeps its state, also beyond the range
+          load(other, t0 + G);
+#pragma unroll
+          for (int t = 0; t < 2 * G - 1; ++t) {
+            const double next = move(t < G ? one[t] : other[t - G]);
+            if (t0 + t < run) g = gx = next;
+          }
+        }
       }
       __syncthreads();
       if (alive[batch & 1] != batch + 1) break;      // no device had moves in this batch: none has any left
@@ -507,13 +541,17 @@ __global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int dev
   const size_t dev = valid ? dev0 + slot : kn - 1;
   const int k = (int)(dev / a.N), n = (int)(dev % a.N);
   NormalStream rng(a.seed, kStreamPulseNoise, (effective_step(a.step, a.step_add) << 31) | dev);
-  uint32_t* sq = rings + slot * 2 * kStreamRing;     // marked samples
-  uint32_t* pq = sq + kStreamRing;                   // pulses: sample << 6 | ordinal << 1 | upwards
-  const double unit = NL == 1 ? 1.0 : 0.5;
+  uint32_t* sq = rings + slot * (kSampleRing + S::kRingWords);   // marked samples
+  uint32_t* pq = sq + kSampleRing;                   // pulses: sample << 6 | ordinal << 1 | upwards; without noise a bit each
+  if constexpr (!NOISE) {
+    for (int i = lane; i < S::kRingWords; i += 64) pq[i] = 0;
+    wave_exchange();
+  }
+  const double unit = NL == 0 ? a.dw_min : NL == 1 ? 1.0 : 0.5;
   int n_s = 0, s_head = 0, n_p = 0, p_head = 0, moved = 0;   // entries waiting, and where they begin
   // Marked: the next word of marks, this lane's word and its sample; else the next sample and four of this lane
   constexpr int U = MARKED ? 1 : 4;
-  const unsigned long long* marks = a.marks + dev * a.n_words;
+  const unsigned long long* marks = MARKED ? a.marks + dev * a.n_words : nullptr;
   const int n_next = !valid ? 0 : MARKED ? a.n_words : a.mc;
   int next = 0;
   uint32_t at[U], q[U], up[U];                       // number, shared slots, direction
@@ -532,7 +570,7 @@ __global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int dev
       q[u] = 0;
       if constexpr (MARKED) {
         if (lane < n_s) {
-          at[u] = sq[(s_head + lane) & (kStreamRing - 1)];
+          at[u] = sq[(s_head + lane) & (kSampleRing - 1)];
           trains(u);
         }
       } else {
@@ -545,14 +583,24 @@ __global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int dev
   // The pulses of 64 samples into their ring, as many samples as there is room for; returns how many.
   auto append_pulses = [&](int u, bool there) __attribute__((always_inline)) {
     const int c = __popc(q[u]), inc = wave_scan(c);
-    const bool fits = there && n_p + inc <= kStreamRing;
+    const bool fits = there && n_p + inc <= S::kRoom;
     const int taken = __popcll(__ballot(fits));      // the first lanes: inc does not fall with the lane
-    uint32_t bits = fits ? q[u] : 0u, pos = (uint32_t)(p_head + n_p + inc - c);
-    for (uint32_t ord = 0; __any(bits != 0); ++ord)
-      if (bits) {
-        pq[pos++ & (kStreamRing - 1)] = (at[u] << 6) | (ord << 1) | up[u];
-        bits &= bits - 1;
+    uint32_t pos = (uint32_t)(p_head + n_p + inc - c);
+    if constexpr (NOISE) {
+      uint32_t bits = fits ? q[u] : 0u;
+      for (uint32_t ord = 0; __any(bits != 0); ++ord)
+        if (bits) {
+          pq[pos++ & (S::kRoom - 1)] = (at[u] << 6) | (ord << 1) | up[u];
+          bits &= bits - 1;
+        }
+    } else if (fits) {
+      moved += up[u] ? c : -c;
+      if (c > 0 && !up[u]) {
+        const uint64_t ones = ((1ull << c) - 1) << (pos & 31);
+        atomicOr(&pq[(pos >> 5) & (S::kRingWords - 1)], (uint32_t)ones);
+        if (ones >> 32) atomicOr(&pq[((pos >> 5) + 1) & (S::kRingWords - 1)], (uint32_t)(ones >> 32));
       }
+    }
     if (taken > 0) n_p += __builtin_amdgcn_readlane(inc, taken - 1);
     return taken;
   };
@@ -566,14 +614,14 @@ __global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int dev
       }
       if (more_words) {
         const int c = __popcll(word), inc = wave_scan(c);
-        const bool fits = n_s + inc <= kStreamRing;
+        const bool fits = n_s + inc <= kSampleRing;
         const int taken = __popcll(__ballot(fits));
         unsigned long long bits = fits ? word : 0ull;
         uint32_t pos = (uint32_t)(s_head + n_s + inc - c);
         const uint32_t base = (uint32_t)(next + lane) * 64u;
         while (__any(bits != 0))
           if (bits) {
-            sq[pos++ & (kStreamRing - 1)] = base + (uint32_t)__builtin_ctzll(bits);
+            sq[pos++ & (kSampleRing - 1)] = base + (uint32_t)__builtin_ctzll(bits);
             bits &= bits - 1;
           }
         if (taken > 0) n_s += __builtin_amdgcn_readlane(inc, taken - 1);
@@ -590,10 +638,10 @@ __global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int dev
     }
     wave_exchange();
   };
-  // With fewer than 64 pulses waiting there is room for a sample's (at most 31); where no marked sample waits, for a word's:
-  // every turn of this loop takes one of them.
+  // With fewer pulses waiting than a batch has there is room for a sample's (at most 31); where no marked sample waits, for a
+  // word's: every turn of this loop takes one of them.
   auto fill = [&]() __attribute__((always_inline)) {
-    while (n_p < 64 && left()) {
+    while (n_p < S::kBatch && left()) {
       fetch();
       append();
     }
@@ -603,18 +651,26 @@ __global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int dev
     if (ahead) append();
     fill();
     // the loads of the batch after this one are on their way under the normal numbers
-    ahead = n_p < 128 && left();
+    ahead = n_p < 2 * S::kBatch && left();
     if (ahead) fetch();
-    const int run = min(n_p, 64);
-    double2 e = {0.0, 0.0};
-    if (lane < run) {
-      const uint32_t p = pq[(p_head + lane) & (kStreamRing - 1)];
-      const bool upwards = (p & 1u) != 0;
-      e.y = upwards ? unit : -unit;
-      moved += upwards ? 1 : -1;
-      if constexpr (NOISE) e.x = a.sigma * rng.get((uint64_t)(a.m0 + (int)(p >> 6)) * 32 + ((p >> 1) & 31u));
+    const int run = min(n_p, S::kBatch);
+    Move* mine = moves + ((batch & 1) * devices + slot) * S::kStride;
+    if constexpr (NOISE) {
+      double2 e = {0.0, 0.0};
+      if (lane < run) {
+        const uint32_t p = pq[(p_head + lane) & (S::kRoom - 1)];
+        const bool upwards = (p & 1u) != 0;
+        e.y = upwards ? unit : -unit;
+        moved += upwards ? 1 : -1;
+        e.x = a.sigma * rng.get((uint64_t)(a.m0 + (int)(p >> 6)) * 32 + ((p >> 1) & 31u));
+      }
+      mine[lane] = e;
+    } else {                                         // whole words of bits: only a device's last batch is not full
+      const uint32_t down = pq[((p_head >> 5) + (lane >> 4)) & (S::kRingWords - 1)] >> (2 * (lane & 15));
+      reinterpret_cast<double2*>(mine)[lane] = double2{down & 1u ? -unit : unit, down & 2u ? -unit : unit};
+      wave_exchange();
+      if (lane < S::kBatch / 32) pq[((p_head >> 5) + lane) & (S::kRingWords - 1)] = 0;
     }
-    moves[((batch & 1) * devices + slot) * kStreamMoves + lane] = e;
     if (lane == 0) {
       runs[(batch & 1) * 16 + slot] = run;
       if (run > 0) alive[batch & 1] = batch + 1;
@@ -632,7 +688,7 @@ __global__ __launch_bounds__(1024) void pulse_stream_kernel(PulseArgs a, int dev
 int move_mode(const PulseArgs& a, bool nl) { return !nl ? 0 : a.v <= 1.0 / 32.0 ? 1 : 2; }   // NL of pulse_stream_kernel
 
 template <bool MARKED>
-void launch_pulse_stream(const PulseArgs& a, bool nl, bool noise, hipStream_t st) {
+hipError_t launch_pulse_stream(const PulseArgs& a, bool nl, bool noise, hipStream_t st) {
   const int mode = move_mode(a, nl);
   void (*k)(PulseArgs, int);
   if (noise) k = mode == 0 ? pulse_stream_kernel<0, true, MARKED> : mode == 1 ? pulse_stream_kernel<1, true, MARKED> : pulse_stream_kernel<2, true, MARKED>;
@@ -640,7 +696,13 @@ void launch_pulse_stream(const PulseArgs& a, bool nl, bool noise, hipStream_t st
   // a block per compute unit at a time, the devices spread evenly over the rounds that takes
   const long long kn = (long long)a.K * a.N, per_round = 256 * kStreamMaxDevices, rounds = (kn + per_round - 1) / per_round;
   const int devices = (int)((kn + 256 * rounds - 1) / (256 * rounds));
-  hipLaunchKernelGGL(k, dim3((unsigned)((kn + devices - 1) / devices)), dim3(64 * (devices + 1)), stream_lds_bytes(devices), st, a, devices);
+  const size_t lds = noise ? Stream<true>::lds_bytes(devices) : Stream<false>::lds_bytes(devices);
+  if (lds > 48 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k, dim3((unsigned)((kn + devices - 1) / devices)), dim3(64 * (devices + 1)), lds, st, a, devices);
+  return hipGetLastError();
 }
 
 constexpr int kTwoPhaseBlocks = 4096;
@@ -757,11 +819,12 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
       const long long devices = (long long)K * N;
       // Up to where the streamed walk beats a lane per device that does everything by itself: the walk that others feed does
       // not take longer for more devices until the feeding waves fill the chip, from then on it does, and an exp() per move
-      // fills it sooner.  Streamed / not, us per update, around each line:
-      //   linear  576 x 96 devices, 8192 samples 597 / 686, 576 x 128 x 4096 499 / 476; series 576 x 128 x 4096 574 / 603, 576 x 256
-      //   961 / 711; exp() 288 x 96 x 8192 566 / 744, 576 x 64 944 / 879; with noise: linear 576 x 128 x 4096 740 / 799, 576 x 256
-      //   1330 / 986; series 576 x 96 x 8192 1078 / 1502, 576 x 128 x 4096 874 / 856; exp() 576 x 64 x 8192 1043 / 1284, 576 x 96 1478 / 1502
-      const int line[2][3] = {{65536, 77824, 32768}, {90112, 69632, 53248}};
+      // fills it sooner.  Streamed / not, around each line, trains of 12 pulses a sample | one per sample | one in 30 samples, whichever
+      // lets it lose first, 128 rows and 4096 samples:
+      //   linear  400 columns 0.55 | 0.72 | 0.94, 448 0.60 | 0.79 | 1.03; series 352 0.72 | 0.83 | 0.93, 384 0.81 | 0.90 | 1.01; exp() 192 0.94 |
+      //   0.98 | 1.00, 208 0.94 | 0.93 | 0.89; with noise: linear 576 0.93 | 0.91 | 1.00; series 544 0.96 | 0.93 | 0.97, 576 1.00 | 0.97 |
+      //   1.01; exp() 240 0.99 | 0.95 | 0.91, 256 1.12 | 1.09 | 1.03
+      const int line[2][3] = {{55296, 47104, 26624}, {73728, 69632, 30720}};
       const bool stream = devices < line[noise ? 1 : 0][move_mode(a, nl)];
       const unsigned tiles16 = (unsigned)(cdiv(K, 16) * cdiv(N, 16));
       // measured, ms per update, [n_words][K N] / [K N][n_words], walks of one lane per device: noise, 65536 devices x 12544
@@ -773,8 +836,9 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
       a.seg_words = !stream || tiles16 >= 256 ? 64 : tiles16 >= 64 ? 16 : 4;
       hipLaunchKernelGGL(pulse_mark_kernel, dim3(tiles16 * (unsigned)cdiv(a.n_words, a.seg_words)), dim3(256), 0, st, a);
       if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
-      if (stream) launch_pulse_stream<true>(a, nl, noise, st);
-      else if (noise) {
+      if (stream) {
+        if (launch_pulse_stream<true>(a, nl, noise, st) != hipSuccess) return XBAR_EHIP;
+      } else if (noise) {
         // lanes decoupled over the whole chunk: with a normal number per pulse every turn counts
         void (*walk)(PulseArgs) = nl ? pulse_walk_kernel<true, true> : pulse_walk_kernel<false, true>;
         hipLaunchKernelGGL(walk, dim3((unsigned)cdiv(K * N, 64)), dim3(64), 0, st, a);     // one wave per block: spread over the chip
@@ -791,8 +855,7 @@ int run_update_pulsed(const xbar_config* cfg, float* W, const float* X, const fl
     // samples 15 / 21 | 14 / 14, 2000 samples 40 / 232 | 37 / 138; 784 x 10, 32 samples 28 / 21 | 20 / 15, 64 29 / 32 | 21 / 21, 1024
     // 91 / 236 | 72 / 135; 400 x 40, 256 samples 61 / 60 | 47 / 35, 2000 253 / 328 | 248 / 192
     if ((long long)K * N <= 8192 && M >= 64) {
-      launch_pulse_stream<false>(a, nl, noise, st);
-      if (hipGetLastError() != hipSuccess) return XBAR_EHIP;
+      if (launch_pulse_stream<false>(a, nl, noise, st) != hipSuccess) return XBAR_EHIP;
       continue;
     }
     void (*k)(PulseArgs);

@@ -195,7 +195,10 @@ def test_lines_of_the_pulsed_walk(xo, xb, K, N, v, ni):
 
 
 # ... on both sides of the lines between the streamed walk and a lane per device
-@pytest.mark.parametrize("K,N,v,ni", [(128, 511, 0.0, ""), (128, 513, 0.0, ""), (128, 607, 0.01, "nl"), (128, 609, 0.01, "nl"), (128, 703, 0.0, "noise"),
+@pytest.mark.parametrize("K,N,v,ni", [(128, 431, 0.0, ""), (128, 433, 0.0, ""), (128, 367, 0.01, "nl"), (128, 369, 0.01, "nl"), (128, 207, 0.04, "nl"),
+                                      (128, 209, 0.04, "nl"), (128, 575, 0.0, "noise"), (128, 577, 0.0, "noise"), (128, 239, 0.04, "nl+noise"),
+                                      (128, 241, 0.04, "nl+noise"),
+                                      (128, 511, 0.0, ""), (128, 513, 0.0, ""), (128, 607, 0.01, "nl"), (128, 609, 0.01, "nl"), (128, 703, 0.0, "noise"),
                                       (128, 705, 0.0, "noise"), (128, 543, 0.01, "nl+noise"), (128, 545, 0.01, "nl+noise"),
                                       (128, 415, 0.04, "nl+noise"), (128, 417, 0.04, "nl+noise")])
 def test_lines_of_the_streamed_walk(xo, xb, K, N, v, ni):
@@ -210,6 +213,25 @@ def test_lines_of_the_streamed_walk(xo, xb, K, N, v, ni):
     (2047, 128, 64, 0.05, 0.04, "nl"), (300, 128, 65, 0.3, 0.01, "nl+noise")])
 def test_streamed_walk_without_marks(xo, xb, M, K, N, density, v, ni):
     test_pulsed_walk(xo, xb, M, K, N, density, v, ni)
+
+
+# ... and trains so dense that the rings run full in the middle of 64 samples: pulses in every slot, in most, and devices that run out
+# of pulses at different times
+@pytest.mark.parametrize("M,K,N", [(2048, 20, 40), (2100, 90, 64), (2048, 3, 5), (300, 20, 40)])
+@pytest.mark.parametrize("v,ni", [(0.01, "nl"), (0.0, ""), (0.04, "nl"), (0.01, "nl+noise"), (0.0, "noise"), (0.04, "nl+noise")])
+def test_streamed_walk_of_dense_trains(xo, xb, M, K, N, v, ni):
+    W, X, dY = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=M + K + N)
+    X, dY = X / np.abs(X).max(), dY / np.abs(dY).max()
+    X[:, ::2] = np.sign(X[:, ::2])
+    dY[:, ::3] = np.sign(dY[:, ::3])
+    X[: M // 2, 1::4] = 0.0
+    w_max = float(np.abs(W).max())
+    flags = (xo.UPD_NL if "nl" in ni else 0) | (xo.UPD_NOISE if "noise" in ni else 0)
+    co, cg = both_configs(xo, xb, flags=flags, upd_nl_v=v, upd_noise_gamma=0.4, seed=3)
+    Wo, pulses_o = xo.update_pulsed(co, W, X, dY, w_max, 1.0, 1.0, 31, 2.0 ** -10, step=6, want_pulses=True)
+    Wg, pulses_g = xb.update_pulsed(cg, dev(W.copy()), dev(X), dev(dY), w_max, 1.0, 1.0, 31, 2.0 ** -10, step=6, want_pulses=True)
+    assert np.array_equal(pulses_g.cpu().numpy(), pulses_o)
+    assert np.abs(Wg.cpu().numpy() - Wo).max() <= 2e-7 * w_max     # one rounding to single precision
 
 
 # Weights that are no numbers or lie at or beyond the range, in devices with pulses in every batch, in some and in none (rows
