@@ -251,17 +251,26 @@ __global__ __launch_bounds__(256) void bn_finalize_bwd_kernel(double* part, int 
   }
 }
 
-// Which elements a thread of the normalisation's last kernels has: VEC channels of ROWS rows; `lanes` (a power of two) threads
-// side by side along the channels.
+// Which elements a thread of the normalisation's last kernels has: VEC channels of ROWS rows.  Rows of quads: `lanes` (a power of two)
+// threads side by side along the channels.  Other rows: threads side by side through the rows as they lie in memory, a fixed
+// number of whole rows apart from one of a thread's elements to the next (lanes of powers of two leave half of the threads of 257
+// channels without one: 50176 x 257, forward and backward 42.1 -> 37.1, 58.6 -> 51.4 us).
 template <int VEC, int ROWS>
 struct RowSpan {
   int c;
   size_t r0, step;
-  __device__ __forceinline__ RowSpan(int lanes_log2) {
-    const int lanes = 1 << lanes_log2;
-    step = 256 >> lanes_log2;
-    c = VEC * ((int)blockIdx.y * lanes + ((int)threadIdx.x & (lanes - 1)));
-    r0 = (size_t)blockIdx.x * ROWS * step + (threadIdx.x >> lanes_log2);
+  __device__ __forceinline__ RowSpan(int lanes_log2, size_t rows, int C) {
+    if constexpr (VEC == 1) {
+      const uint32_t t = blockIdx.x * 256u + threadIdx.x, row = t / (uint32_t)C;
+      step = (rows + ROWS - 1) / ROWS;
+      r0 = row;
+      c = row < step ? (int)(t - row * (uint32_t)C) : C;         // C: none
+    } else {
+      const int lanes = 1 << lanes_log2;
+      step = 256 >> lanes_log2;
+      c = VEC * ((int)blockIdx.y * lanes + ((int)threadIdx.x & (lanes - 1)));
+      r0 = (size_t)blockIdx.x * ROWS * step + (threadIdx.x >> lanes_log2);
+    }
   }
 };
 
@@ -272,7 +281,7 @@ template <bool RELU, int VEC, int ROWS>
 __global__ __launch_bounds__(256) void bn_apply_fwd_kernel(const float* x, const float* skip, const float* gamma, const float* beta,
                                                            const float* mean, const float* invstd, float* y, size_t rows, int C,
                                                            int lanes_log2) {
-  const RowSpan<VEC, ROWS> at(lanes_log2);
+  const RowSpan<VEC, ROWS> at(lanes_log2, rows, C);
   if (at.c >= C) return;
   float v[ROWS][VEC], s[ROWS][VEC];
 #pragma unroll
@@ -307,7 +316,7 @@ __global__ __launch_bounds__(256) void bn_apply_bwd_kernel(const float* x, const
                                                            int stride, const float* mean, const float* invstd, const float* dgamma,
                                                            const float* dbeta, float* dx, size_t rows, int C, int lanes_log2,
                                                            double inv_rows) {
-  const RowSpan<VEC, ROWS> at(lanes_log2);
+  const RowSpan<VEC, ROWS> at(lanes_log2, rows, C);
   if (at.c >= C) return;
   float v[ROWS][VEC], d[ROWS][VEC];
 #pragma unroll
@@ -341,11 +350,16 @@ __global__ __launch_bounds__(256) void bn_apply_bwd_kernel(const float* x, const
 
 // The launch of either: one row per thread, or four where that leaves eight blocks per compute unit.
 struct ApplyGrid {
-  int lanes_log2, four_rows;
+  int lanes_log2 = 0, four_rows;
   dim3 grid;
   ApplyGrid(size_t rows, int C, int vec) {
-    const int across = (C + vec - 1) / vec;
-    for (lanes_log2 = 0; lanes_log2 < 8 && (1 << lanes_log2) < across;) ++lanes_log2;
+    if (vec == 1) {
+      four_rows = rows * (size_t)C / 256 >= 4 * 2048;
+      grid = dim3((unsigned)(((four_rows ? (rows + 3) / 4 : rows) * (size_t)C + 255) / 256));
+      return;
+    }
+    const int across = C / vec;
+    while (lanes_log2 < 8 && (1 << lanes_log2) < across) ++lanes_log2;
     const size_t step = 256 >> lanes_log2, strips = (size_t)(across + (1 << lanes_log2) - 1) >> lanes_log2;
     const size_t blocks = (rows + step - 1) / step;
     four_rows = blocks * strips >= 4 * 2048;
@@ -538,12 +552,15 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float* x, size_t n, u
   }
 }
 
-// Strips of 64 channels (whole 256-byte pieces of a row) where they make a block for every compute unit twice over, else of 16.
+// Strips of 64 channels (whole 256-byte pieces of a row) where they make 160 blocks or more, else of 16: blocks enough outweigh that
+// another block takes the other half of a 128-byte line.  us, whole calls, strips of 16 / of 64, forward, backward: 12544 x 256 (100
+// blocks of 64) 14.4 / 14.3, 20.0 / 25.1, 2000 x 2048 (128) 17.3 / 15.9, 25.0 / 27.5; 12544 x 512 (200) 22.6 / 20.0, 35.3 / 33.3, 50000 x 130
+// (294) 27.2 / 29.3, 42.5 / 34.9, 12544 x 1024 (400) 36.6 / 30.0, 58.8 / 44.9, 50176 x 257 (490) 51.7 / 42.1, 82.4 / 58.6.
 template <bool BWD, bool RELU>
 void launch_bn_partial(const float* x, const float* dy, const float* gamma, const float* beta, const float* mean, const float* invstd,
                        double* part, size_t rows, int channels, int chunks, hipStream_t st) {
   const int wide = (channels + 63) / 64;
-  const bool narrow = channels <= 32 || (long long)chunks * wide < 512;
+  const bool narrow = channels <= 32 || (long long)chunks * wide < 160;
   const dim3 grid((unsigned)chunks, (unsigned)(narrow ? (channels + 15) / 16 : wide));
   void (*k)(const float*, const float*, const float*, const float*, const float*, const float*, double*, size_t, int);
   if ((channels & 3) == 0) k = narrow ? bn_partial_kernel<BWD, RELU, 4, 4> : bn_partial_kernel<BWD, RELU, 4, 16>;

@@ -54,6 +54,32 @@ def test_batchnorm_relu_add(xb, B, H, W, C):
     close(p, x.astype(np.float64) - np.float32(0.1).astype(np.float64) * dy, 1e-6)
 
 
+# Rows that are no quads, one or four of them to a thread: one element, more channels than a block has threads, rows that four do not
+# divide; both sides of the line between strips of 16 and of 64 channels
+@pytest.mark.parametrize("rows,C", [(1, 1), (2, 257), (7, 259), (1025, 513), (8191, 257), (9001, 257), (53 * 512, 130), (53 * 512 + 1, 130), (53 * 512, 132),
+                                    (53 * 512 + 1, 132), (5, 1030)])
+def test_normalisation_of_ragged_rows(xb, rows, C):
+    from oracle import periph
+    rng = np.random.default_rng(rows + C)
+    x = (rng.normal(size=(rows, C)) * 2 + 0.5).astype(np.float32)
+    dy = rng.normal(size=(rows, C)).astype(np.float32)
+    gamma, beta = rng.uniform(0.5, 1.5, size=C).astype(np.float32), rng.normal(size=C).astype(np.float32)
+    y, mean, invstd = xb.bn_fwd(dev(x), dev(gamma), dev(beta), 1e-5)
+    yo, mo, io = periph.bn_fwd(x, gamma, beta, 1e-5)
+    close(mean, mo)
+    assert (np.abs(invstd.cpu().numpy() - io) <= 2.0 ** -23 * io).all()
+    # mean and 1 / std are stored in single precision, which two rows that lie close to each other multiply by 1 / std
+    bound = 2.0 ** -22 * (np.abs(gamma) * io * (np.abs(x) + np.abs(mo)) + np.abs(beta) + np.abs(yo))
+    assert (np.abs(y.cpu().numpy() - yo) <= bound).all()
+    dx, dgamma, dbeta = xb.bn_bwd(dev(x), dev(dy), dev(gamma), mean, invstd)
+    m64, i64 = mean.cpu().numpy().astype(np.float64), invstd.cpu().numpy().astype(np.float64)
+    dxo, dgo, dbo = periph.bn_bwd(x, dy, gamma, m64, i64)
+    close(dgamma, dgo, 1e-5)
+    close(dbeta, dbo, 1e-5)
+    bound = 2.0 ** -22 * np.abs(gamma) * i64 * (np.abs(dy) + (np.abs(dbo) + np.abs((x - m64) * i64 * dgo)) / rows)
+    assert (np.abs(dx.cpu().numpy() - dxo) <= bound + 1e-30).all()
+
+
 @pytest.mark.parametrize("B,H,W,C,k,stride,pad", [(2, 9, 8, 5, 3, 2, 1), (3, 8, 8, 64, 2, 2, 0), (1, 7, 7, 3, 3, 1, 1)])
 def test_pooling(xb, B, H, W, C, k, stride, pad):
     from oracle import periph
