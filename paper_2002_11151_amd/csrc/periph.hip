@@ -367,29 +367,44 @@ struct ApplyGrid {
   }
 };
 
-// A block takes 16 channels of a sample, 16 threads a channel: one thread's chain of loads per channel took 19 us for 64 positions.
+// GROUPS threads share the positions of an output, 256 / GROUPS outputs side by side, AHEAD loads of a thread in flight.  us, 1 / 4 /
+// 16 threads an output: 8192 outputs of 64 positions 4.6 / 3.2 / 3.0, of 784 28 / 9.1 / 9.7; 32768 of 49 4.3 / 3.3 / 4.1; 65536 of 49
+// 4.3 / 3.7 / 5.5, of 9 3.0 / 3.2 / 4.5; 131072 of 49 4.5 / 4.6 / 12, of 16 3.3 / 3.9 / 6.7; 524288 of 49 17 / 17 / 39; any of up to four
+// positions 1.  (A thread each for 16 channels of a sample, 16 threads a channel, whatever the sizes: the 64 x 49 x 2048 of a ResNet-50 at
+// batch 64 12.1, with a thread an output and one load at a time 8.2, now 4.5; 2097152 of one position 61, 6.0, 7.3.)
 constexpr size_t kPoolBlocks = 1 << 20;     // of one launch; beyond that a block takes several
 
-__global__ __launch_bounds__(256) void avgpool_fwd_kernel(const float* x, float* y, size_t work, int positions, int C, size_t strips) {
-  __shared__ double red[16][16];
-  const int lane = threadIdx.x & 15, grp = threadIdx.x >> 4;
-  for (size_t i = blockIdx.x; i < work; i += gridDim.x) {
-    const size_t b = i / strips, c = 16 * (i - b * strips) + lane;
+template <int GROUPS, int AHEAD>
+__global__ __launch_bounds__(256) void avgpool_fwd_kernel(const float* x, float* y, size_t outputs, int positions, int C) {
+  constexpr int LANES = 256 / GROUPS;
+  __shared__ double red[GROUPS][LANES];
+  const int lane = threadIdx.x % LANES, grp = threadIdx.x / LANES;
+  for (size_t o0 = (size_t)blockIdx.x * LANES; o0 < outputs; o0 += (size_t)gridDim.x * LANES) {
+    const size_t o = o0 + lane;
     double s = 0.0;
-    if (c < (size_t)C) {
-#pragma unroll 4
-      for (int p = grp; p < positions; p += 16) s += (double)x[(b * positions + p) * C + c];
+    if (o < outputs) {
+      const size_t b = outputs >> 32 ? o / (size_t)C : (uint32_t)o / (uint32_t)C, c = o - b * C;
+      const float* from = x + b * positions * C + c;
+#pragma unroll AHEAD
+      for (int p = grp; p < positions; p += GROUPS) s += (double)from[(size_t)p * C];
     }
-    red[grp][lane] = s;
-    __syncthreads();
-    if (grp == 0 && c < (size_t)C) {
+    if constexpr (GROUPS > 1) {
+      red[grp][lane] = s;
+      __syncthreads();
       s = 0.0;
 #pragma unroll
-      for (int g = 0; g < 16; ++g) s += red[g][lane];        // fixed order
-      y[b * C + c] = (float)(s / (double)positions);
+      for (int g = 0; g < GROUPS; ++g) s += red[g][lane];        // fixed order
     }
-    __syncthreads();
+    if (grp == 0 && o < outputs) y[o] = (float)(s / (double)positions);
+    if constexpr (GROUPS > 1) __syncthreads();
   }
+}
+
+template <int GROUPS, int AHEAD>
+void launch_avgpool(const float* x, float* y, size_t outputs, int positions, int C, hipStream_t st) {
+  const size_t blocks = (outputs + 256 / GROUPS - 1) / (256 / GROUPS);
+  hipLaunchKernelGGL((avgpool_fwd_kernel<GROUPS, AHEAD>), dim3((unsigned)(blocks < kPoolBlocks ? blocks : kPoolBlocks)), dim3(256), 0, st, x, y,
+                     outputs, positions, C);
 }
 
 __global__ __launch_bounds__(256) void avgpool_bwd_kernel(const float* dy, float* dx, int batch, int positions, int C) {
@@ -721,9 +736,10 @@ int xbar_bn_bwd_sgd(const float* x, const float* dy, float* gamma, float* beta, 
 int xbar_avgpool_fwd(const float* x, float* y, int batch, int positions, int channels, void* hip_stream) {
   if (batch <= 0 || positions <= 0 || channels <= 0) return XBAR_ESHAPE;
   if (!aligned16(x) || !aligned16(y)) return XBAR_EALIGN;
-  const size_t strips = ((size_t)channels + 15) / 16, work = (size_t)batch * strips;
-  hipLaunchKernelGGL(avgpool_fwd_kernel, dim3((unsigned)(work < kPoolBlocks ? work : kPoolBlocks)), dim3(256), 0,
-                     reinterpret_cast<hipStream_t>(hip_stream), x, y, work, positions, channels, strips);
+  const size_t outputs = (size_t)batch * channels;
+  void (*launch)(const float*, float*, size_t, int, int, hipStream_t) =
+      positions < 4 ? launch_avgpool<1, 1> : positions < 8 || outputs >= 131072 ? launch_avgpool<1, 4> : outputs > 16384 ? launch_avgpool<4, 4> : launch_avgpool<16, 4>;
+  launch(x, y, outputs, positions, channels, reinterpret_cast<hipStream_t>(hip_stream));
   return launched();
 }
 

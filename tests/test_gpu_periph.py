@@ -98,6 +98,15 @@ def test_pooling(xb, B, H, W, C, k, stride, pad):
     close(xb.avgpool_bwd(dev(dg), x.shape), periph.avgpool_bwd(dg, x.shape))
 
 
+# One, four or sixteen threads to an output: positions and outputs on both sides of the lines, outputs that fill no block
+@pytest.mark.parametrize("B,positions,C", [(1, 1, 1), (3, 3, 5), (3, 4, 5), (3, 7, 67), (3, 8, 67), (128, 17, 128), (127, 8, 129), (5, 9, 3277), (131, 16, 1000), (131, 9, 1001),
+                                           (70000, 2, 3)])
+def test_average_pool(xb, B, positions, C):
+    from oracle import periph
+    x = np.random.default_rng(B + C).normal(size=(B, positions, 1, C)).astype(np.float32)
+    close(xb.avgpool_fwd(dev(x)), periph.avgpool_fwd(x))
+
+
 @pytest.mark.parametrize("B,classes", [(5, 10), (64, 1000), (3, 1)])
 def test_softmax_cross_entropy(xb, B, classes):
     from oracle import periph
