@@ -231,11 +231,11 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 }
 
 // a b + a constant, which the instruction takes from scalar registers: left to itself the compiler copies it into the vector
-// registers of the sum first, a tenth of a normal number's instructions.
+// registers of the sum first, a tenth of a normal number's instructions.  The addition itself is left to the compiler, which puts the
+// waits that this unit wants between a scalar register's reload and its use (it does not look into inline assembly for them).
 __device__ __forceinline__ double fma_constant(double a, double b, double constant) {
-  double r;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(constant));
-  return r;
+  asm("" : "+s"(constant));
+  return __builtin_fma(a, b, constant);
 }
 
 // Standard normal number i of (seed, stream, step): four consecutive i share one Philox block,
