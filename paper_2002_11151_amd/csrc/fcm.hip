@@ -23,9 +23,9 @@ namespace {
 struct FcmArgs {
   const float* W;
   float* profile;        // [S_w][2][K][N]
-  double* scratch;       // per resident block: s, y, r, p, q of R C doubles each
+  double* scratch;       // per resident block: s, y, r, p, q of R C doubles each; state on chip: `far` pairs of coefficients
   int K, N, R, C, S_w, slice_bits, weight_bits, tiles_c;
-  int groups, rhs_per_group, n_items, max_iter;
+  int groups, rhs_per_group, n_items, max_iter, far;
   uint32_t flags;
   double g_min, dg, var_sigma, r_row, r_col, r_source, r_sense, tol2;
   float w_max;
@@ -236,8 +236,8 @@ __global__ __launch_bounds__(256) void fcm_kernel(FcmArgs a) {
 // block's first solve works out alpha and beta (conjugate gradients, stopped at half the tolerance); the others run the same
 // coefficients -- a fixed polynomial in the matrix -- without the scalar products and their barriers, and measure the residual
 // once at the end.  Conjugate gradients run on the voltages u / G and w / G, which makes w.w / G and u.u / G products of the two: full
-// precision and no reciprocal per device (with the instruction's 24 bits instead, on currents: 784 x 500 weights at 100 Ohm, where
-// no solve shares, 98.3 ms against 81.0).
+// precision and no reciprocal per device (with the instruction's 24 bits instead, on currents: 784 x 500 weights at 100 Ohm, when
+// no solve of so many iterations shared, 98.3 ms against 81.0).
 // One that misses the tolerance is finished by conjugate gradients, and the next starts anew.  (On the CPU,
 // 128 x 128 devices at 1e-11: as many iterations as conjugate gradients of its own or one more, for Rmin of 1e3 .. 1e5 Ohm, 10 %
 // variation, ragged tiles.)
@@ -324,7 +324,7 @@ struct FcmShape {
   // G, a wave's column sums, what lies before / behind a wave; the last wave has nothing behind it: that line holds the slots
   // of the block sums and the coefficients
   static constexpr size_t kLdsBytes = (size_t)(R * C + 2 * kSums) * sizeof(double);
-  static constexpr int kSteps = (C - 2 * NW) / 2;    // coefficients kept
+  static constexpr int kSteps = (C - 2 * NW) / 2;    // pairs of coefficients kept there; those of later steps in the workspace
 };
 
 template <int SR, int SC, int NT>
@@ -392,6 +392,7 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
   }
 
   int steps = 0, discarded = 0;                      // coefficients known; solves that they did not fit
+  double2* far = reinterpret_cast<double2*>(a.scratch) + (size_t)blockIdx.x * a.far - kSteps;
   for (int rhs = rhs_begin; rhs < rhs_end; ++rhs) {
     double u[SR][SC], w[SR][SC], e = 0.0;            // e: solution summed over column tid % C
     double beta = 0.0, alpha = 0.0, part = 0.0, swing = 0.0;
@@ -560,8 +561,14 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
     bool known = steps > 0;
     if (known) {
       for (int it = 0; it < steps; ++it) {
-        alpha = coef[it];
-        beta = coef[kSteps + it];
+        if (it < kSteps) {
+          alpha = coef[it];
+          beta = coef[kSteps + it];
+        } else {
+          const double2 both = far[it];
+          alpha = both.x;
+          beta = both.y;
+        }
         iterate(std::false_type{}, it == 0, 0.0);
       }
       // An upper bound of the residual first: the instruction's reciprocal is good to 2^29 units in the last place by the documents of
@@ -606,16 +613,20 @@ __global__ __launch_bounds__(NT, 2) void fcm_onchip_kernel(FcmArgs a) {
     int it = 0;
     for (; it < a.max_iter && rr > goal; ++it) {
       iterate(std::true_type{}, false, rr);
-      if (!known && tid == 0 && it < kSteps) {
-        coef[it] = alpha;
-        coef[kSteps + it] = beta;
+      if (!known && tid == 0) {                      // the solves after this one read them behind a barrier
+        if (it < kSteps) {
+          coef[it] = alpha;
+          coef[kSteps + it] = beta;
+        } else if (it < kSteps + a.far) {
+          far[it] = double2{alpha, beta};
+        }
       }
       const double rr_new = block_sum_n<NW>(part, red);
       beta = rr_new / rr;
       rr = rr_new;
     }
     // a solve that missed the tolerance drives what the first one hardly did (a row of off-state devices, say): the next starts anew
-    steps = known ? (it > 0 ? 0 : steps) : it <= kSteps && discarded < 2 ? it : 0;
+    steps = known ? (it > 0 ? 0 : steps) : it <= kSteps + a.far && discarded < 2 ? it : 0;
     if (tid < C) sums[tid] = e;                      // the sums of the last iteration have been read: two barriers ago at least
     __syncthreads();
     if (rhs >= i0 && rhs < i0 + SR) {
@@ -658,7 +669,7 @@ constexpr int kSlots128 = 256, kSlots64 = 256 * 3;   // blocks that the chip hol
 
 // False: no such LDS size on this device.
 template <int SR, int SC, int NT>
-bool launch_onchip(FcmArgs a, int slots, hipStream_t st) {
+bool launch_onchip(FcmArgs a, int slots, size_t ws_bytes, hipStream_t st) {
   constexpr int lds_bytes = (int)FcmShape<SR, SC, NT>::kLdsBytes;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(&fcm_onchip_kernel<SR, SC, NT>), hipFuncAttributeMaxDynamicSharedMemorySize,
                           lds_bytes) != hipSuccess) {
@@ -668,6 +679,10 @@ bool launch_onchip(FcmArgs a, int slots, hipStream_t st) {
   a.rhs_per_group = rows_per_block(a, slots);
   a.groups = cdiv(a.R, a.rhs_per_group);
   const unsigned blocks = (unsigned)(cdiv(a.K, a.R) * a.tiles_c * a.S_w * 2 * a.groups);
+  // The workspace, which the general kernel needs, has room for 256 pairs per block but for the very largest layers.  784 x 500
+  // weights, 128 x 128 arrays, ms with the pairs in LDS alone and with these, against scalar products in every iteration: 100
+  // Ohm (some 130 iterations) 81.0, 63.2, 74.6, 300 Ohm 48.3, 35.3, 44.9; 256 x 256 on 64 x 64 arrays, 100 Ohm 3.73, 3.01, 3.20
+  a.far = (int)std::min<size_t>(256, ws_bytes / sizeof(double2) / blocks);
   hipLaunchKernelGGL((fcm_onchip_kernel<SR, SC, NT>), dim3(blocks), dim3(NT), lds_bytes, st, a);
   return true;
 }
@@ -727,7 +742,7 @@ int xbar_fcm_profile(const xbar_config* cfg, const float* W, int K, int N, float
   a.tol2 = 1e-22;                                   // relative residual 1e-11
   a.w_max = w_max; a.seed = cfg->seed; a.step = step; a.step_add = current_step_source();
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  if (p.onchip == 128 ? launch_onchip<4, 8, 512>(a, kSlots128, st) : p.onchip == 64 && launch_onchip<4, 4, 256>(a, kSlots64, st))
+  if (p.onchip == 128 ? launch_onchip<4, 8, 512>(a, kSlots128, ws_bytes, st) : p.onchip == 64 && launch_onchip<4, 4, 256>(a, kSlots64, ws_bytes, st))
     return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
   hipLaunchKernelGGL(fcm_kernel, dim3((unsigned)p.blocks), dim3(256), 0, st, a);
   if (hipGetLastError() != hipSuccess) return XBAR_EHIP;

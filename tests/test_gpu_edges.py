@@ -299,7 +299,7 @@ def test_circuit_model_on_chip(xo, xb, R, K, N, r_min):
 
 # ... solves that take over the coefficients of a block's first one: the first row of every block, or all but one device of it, off, so
 # that the first solve hardly sees what the others do; two and many rows to a block; at 100 Ohm more iterations than coefficients are
-# kept, at 1 kOhm just about as many
+# of, at 1 kOhm just about as many
 @pytest.mark.parametrize("R,K,N,wb,r_min,off", [(64, 64, 40, 16, 1e2, "rows"), (64, 64, 64, 16, 1e3, "device"), (64, 300, 200, 2, 1e4, "rows"),
                                                 (64, 128, 128, 16, 1e3, "rows"), (128, 150, 128, 2, 1e3, "device"), (128, 140, 30, 2, 1e5, "rows"),
                                                 (128, 128, 20, 8, 1e2, "rows"), (128, 128, 20, 16, 1e4, "device")])
