@@ -24,13 +24,15 @@ namespace {
 // and meet all the same, four on more compute units are faster: up to one block of four per compute unit.  us, four / eight waves:
 // one block a patch, 73 x 14, 31 rows 12.8 / 10.8, 42 x 32, 1280 rows 9.5 / 8.0; several, 131 x 111, 20 rows backward 11.1 / 12.3,
 // 188 x 225, 49 rows 14.1 / 14.9; beyond the line 144 x 82, 646 rows 13.7 / 12.6, 113 x 1396, 736 rows 50.4 / 30.3, 212 x 1116, 200
-// rows 50.0 / 37.5; but with few rows of inputs to share and a little more than one block of eight per compute unit, 25 x 416, 363
-// rows backward, 312 blocks 14.2 / 15.5.  (Same results.)
+// rows 50.0 / 37.5; but with few rows of inputs to share, up to four terms and a little more than one block of eight per compute
+// unit: signed inputs, 4 terms, 25 x 416, 363 rows, 312 blocks 12.9 / 14.0, 16 x 1056, 150 rows, 330 blocks 12.4 / 13.8, 64 x 192, 900 rows, 348 blocks
+// 13.4 / 14.2, 1 term 11.0 / 11.7, 10.8 / 11.6, 11.9 / 12.0, fp16 planes of 2 terms 13.5 / 14.1, 13.1 / 13.3, 15.0 / 15.3 (with 5 terms 19.1 / 15.5,
+// 18.5 / 14.6, 18.9 / 15.1).  (Same results.)
 int waves_of(const VmmPlan& p, const Derived& d) {
   if (d.S_w <= 4 || (d.fmt == kFmtF16 && d.terms * p.g.ks > 16)) return 4;
   const long long tiles = (long long)p.MP * p.g.OP * p.VT, eights = tiles * cdiv(d.S_w, 8);
   if (p.VT * cdiv(d.S_w, 8) == 1) return 8;
-  if (std::min(p.Lin, p.g.tile) <= 64 && eights > 256 && eights <= 384) return 4;
+  if (d.terms < 5 && std::min(p.Lin, p.g.tile) <= 64 && eights > 256 && eights <= 384) return 4;
   return tiles * cdiv(d.S_w, 4) > 256 ? 8 : 4;
 }
 

@@ -390,6 +390,20 @@ def test_eight_waves_of_the_small_pass(xb, R, ib, sb, wb, slb, M, K, N, flags):
     assert np.array_equal(gpu_bwd(xb, cfg, W, dY, w_max, gs, codes=False), gpu_bwd(xb, cfg, W, dY, w_max, gs)[0])
 
 
+# ... and both sides of the lines between which few inputs and up to four terms take blocks of four again (256, 272, 384, 400 blocks of eight)
+@pytest.mark.parametrize("M", [512, 513, 768, 769])
+@pytest.mark.parametrize("flags", ["aam+signed", "var+signed"])
+def test_four_waves_of_few_inputs(xb, M, flags):
+    K, N = 40, 256
+    W, X, _ = workloads.layer_tensors_np(workloads.Gemm("t", K, N, M, True, 1), seed=M)
+    fs = 1.037 * workloads.adc_full_scale(128, 1, 2)
+    cfg = xb.make_config(xbar_rows=128, xbar_cols=128, weight_bits=16, slice_bits=2, stream_bits=1, var_sigma=0.1, adc_fs_fwd=fs, adc_fs_bwd=fs, seed=4,
+                         flags=xb.INPUT_SIGNED | (xb.NI_VARIATION if "var" in flags else xb.NI_WIRE_AAM))
+    assert xb.plane_format(cfg) == (1, 5 if "var" in flags else 4)
+    w_max, xs = float(np.abs(W).max()), float(np.abs(X).max())
+    assert np.array_equal(gpu_fwd(xb, cfg, W, X, w_max, xs, codes=False), gpu_fwd(xb, cfg, W, X, w_max, xs)[0])
+
+
 # fp16 planes whose staged slices would be an odd number: six k-steps (64 KiB hold five slices of them), the same on 256-row arrays
 # (eleven: two), slices that are an odd number themselves, one slice that no group of two holds
 @pytest.mark.parametrize("R,wb,slb,M,K,N", [(128, 16, 2, 3000, 90, 200), (128, 14, 2, 3000, 90, 200), (256, 16, 2, 3000, 170, 100),
