@@ -124,10 +124,11 @@ def test_softmax_cross_entropy(xb, B, classes):
 
 
 @pytest.mark.parametrize("rows,C", [(3, 4), (513, 7), (700, 16), (1100, 36), (2000, 64), (65, 1028), (7, 257), (40000, 64),
-                                    (524289, 16), (140001, 61)])
+                                    (524289, 16), (140001, 61), (131072, 16), (32768, 32), (8192, 64), (12544, 1024), (3136, 2048)])
 def test_joined_normalisation_passes(xb, rows, C):
     """Sums and passes at the edges of their strips (16 and 64 channels, quads or not), of 512 rows and of one or four rows per
-    thread, against 64 bits; normalisation, addition, ReLU and parameter step in one against the single operations, bit for bit."""
+    thread, and at layers of the networks, against 64 bits; normalisation, addition, ReLU and parameter step in one against the
+    single operations, bit for bit."""
     g = torch.Generator(device="cuda").manual_seed(rows + C)
     x, dy, skip = (torch.randn((rows, C), generator=g, device="cuda") for _ in range(3))
     gamma, beta = torch.rand(C, generator=g, device="cuda") + 0.5, torch.randn(C, generator=g, device="cuda")
