@@ -2020,6 +2020,10 @@ int run_update(const xbar_config* cfg, float* W, const float* X, const float* dY
     return hipGetLastError() == hipSuccess ? XBAR_OK : XBAR_EHIP;
   }
   if (N % 4 == 0 && (conv ? conv->C : K) % 4 == 0) {
+    // Tiles of 128 columns also where one or two waves have rows of W to contract: us of a whole update, tiles of 128 / of 64 columns / the
+    // kernel below, which shares the batch rows among the waves: 8 x 128 weights, 200704 rows 30.7 / 35.2 / 37.6, 32 x 128 33.7 / 38.0 / 39.3,
+    // 16 x 256 x 12544 13.1 / 14.4 / 14.2, 64 x 256 x 200704 63 / 73 / 70, 64 x 4096 x 4096 29.9 / 33.7 / 32.5; the other way about 32 x 512 x 4096
+    // 18.2 / 18.5 / 17.3, 32 x 1024 x 2048 18.6 / 19.0 / 17.8, 64 x 512 x 4096 23.8 / 24.3 / 22.8 (of 35 layers of up to 64 rows five, by 5 % at most)
     const bool wide = N > 64;
     const int tile_cols = wide ? 128 : 64;
     g.KB = cdiv(K, wide ? 128 : kQuadRows);
